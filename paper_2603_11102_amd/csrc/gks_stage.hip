@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
             gp[v][1][4] = vp * ih2;
         }
 
-        // ---- flux at this thread's two Gauss points, quadrature weight 1/4 each
+        // ---- flux at this thread's two Gauss points (their quadrature weight 1/4 is part of the divergence)
         real fa0[4] = {0, 0, 0, 0}, fa1[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
                 g[1][v] = gp[v][n][3];
                 g[2][v] = gp[v][n][4];
             }
-            gp_flux<real, NEED_F0, SHIFT>(qL, qR, g, a.fc, real(0.25), fa0, fa1, cm);
+            gp_flux<real, NEED_F0, SHIFT>(qL, qR, g, a.fc, fa0, fa1, cm);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
             // between compile-time indices: indexing the argument or register arrays with the
             // lane-dependent index would fetch pointers from memory and move the arrays to scratch.
             real2 d1, d0;
-            const real ihc = STR ? a.ihc[cell] : a.inv_hn;
+            const real ihc = real(0.25) * (STR ? a.ihc[cell] : a.inv_hn);  // 1/4: weight of a Gauss point
             const real2 prev1 = PAIR_PREV ? pprev1 : lane_pair(fprev1);
             d1.x = -(fcur1.x - prev1.x) * ihc;
             d1.y = -(fcur1.y - prev1.y) * ihc;

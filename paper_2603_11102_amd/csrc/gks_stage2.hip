@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(T2O_THREADS) face2_kernel(const FaceArgs<real>
                 g[1][v] = (s_face[buf][v][3][ck][cj + 1] - s_face[buf][v][3][ck][cj - 1]) * (real(0.5) * ih1);
                 g[2][v] = (s_face[buf][v][3][ck + 1][cj] - s_face[buf][v][3][ck - 1][cj]) * (real(0.5) * ih2);
             }
-            gp_flux<real, NEED_F0, SHIFT>(qL, qR, g, a.fc, real(1), fa0, fa1, cm);
+            gp_flux<real, NEED_F0, SHIFT>(qL, qR, g, a.fc, fa0, fa1, cm);
         }
         if (f + 1 <= f1) column_step(f + 1, buf ^ 1);
         if (f > f0 && face_ok) {
