@@ -24,6 +24,11 @@
 
 namespace gks {
 
+// Tile of the recompute pass: 16 x 8 faces, 256 threads (one per column and per face line), one wave per SIMD.
+struct AdjTile {
+    static constexpr int T2 = 8, THREADS = 256;
+};
+
 struct AdjFaceArgs {
     const double* q[4];     // field in LOCAL variable order (padded)
     const double* mu0[4];   // seed of L (interior, local order), stage 1 only

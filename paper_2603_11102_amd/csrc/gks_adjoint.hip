@@ -54,15 +54,15 @@ __device__ __forceinline__ double wcoef(int side, const double* c, int r) {
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
-// pass A: recompute the face pipeline of one direction (the forward's 16 x 8 face tiles of 256 threads,
+// pass A: recompute the face pipeline of one direction (16 x 8 face tiles of 256 threads,
 // one wave per SIMD so that the FP64 state fits the unified register file), store the inputs of the
 // tangential WENO evaluations (normal face values, t1 line values) and, per face and Gauss point, the
 // adjoints of the Gauss-point inputs from the reverse of the flux (seeds Fbar(f) = (mu(f) - mu(f-1)) / h)
 // ------------------------------------------------------------------------------------------------
 template <int STAGE>
-__global__ void __launch_bounds__(FaceTile<double>::THREADS) adj_face_kernel(const AdjFaceArgs a) {
+__global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFaceArgs a) {
     constexpr bool NEED_F0 = (STAGE == 1);
-    constexpr int T2 = FaceTile<double>::T2, X2 = T2 + 4, NTH = FaceTile<double>::THREADS;
+    constexpr int T2 = AdjTile::T2, X2 = T2 + 4, NTH = AdjTile::THREADS;
     static_assert(EXT1 * X2 <= NTH && 2 * TILE1 * T2 == NTH && TILE1 * X2 <= NTH, "thread roles");
     __shared__ double s_nrm[4][X2][EXT1];
     __shared__ double s_t1[5][X2][TILE1][2];
@@ -581,7 +581,7 @@ hipError_t launch_adj_passes(const AdjFaceArgs& a, int stage, hipStream_t s) {
     const int nchunks = (a.n_n + a.chunk - 1) / a.chunk;
     const long long blocks = ((long long)a.tiles_t1 * a.tiles_t2 * nchunks + 7) / 8 * 8;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 fgrid((unsigned)blocks), fblock(FaceTile<double>::THREADS);
+    const dim3 fgrid((unsigned)blocks), fblock(AdjTile::THREADS);
     if (stage == 1) hipLaunchKernelGGL((adj_face_kernel<1>), fgrid, fblock, 0, s, a);
     else hipLaunchKernelGGL((adj_face_kernel<2>), fgrid, fblock, 0, s, a);
     const BcSplit bc = bc_split(a.n_t1);

@@ -69,7 +69,9 @@ struct gks_ctx {
     int stretched;
     std::vector<double> faces[3];  // host copy of the faces of each stretched axis (empty when uniform)
     double lam, c, hmin, eps;
+    int t2[3];         // t2 rows of a face tile, per direction
     int chunk[3];      // faces per workgroup of the face kernels, per direction
+    int adj_chunk[3];  // faces per workgroup of the adjoint's recompute pass
     int seg_len[3], n_wg[3];  // work split of the order-5 face launches (FaceArgs)
     int flags;
     // actuator line model
@@ -141,12 +143,6 @@ int fail(gks_ctx* c, int code, const std::string& msg) {
     } while (0)
 
 size_t elem_size(const gks_config* c) { return c->precision == GKS_FP32 ? 4 : 8; }
-
-// t2 extent of the face tile: the high-order kernel's per-precision tile, 16 for the second-order one
-template <typename real>
-int face_tile_t2(int order) {
-    return order == 2 ? TILE2 : FaceTile<real>::T2;
-}
 
 // workspace layout; base == nullptr only measures
 struct Layout {
@@ -398,7 +394,8 @@ FaceArgs<real> face_args_buf(gks_ctx* c, int d, int stage, void* const src[4], v
     a.n_n = c->g.n[ax[0]];
     a.n_t1 = c->g.n[ax[1]];
     a.n_t2 = c->g.n[ax[2]];
-    const int t2 = face_tile_t2<real>(c->cfg.order);
+    const int t2 = c->t2[d];
+    a.t2 = t2;
     a.tiles_t1 = (a.n_t1 + TILE1 - 1) / TILE1;
     a.tiles_t2 = (a.n_t2 + t2 - 1) / t2;
     a.chunk = c->chunk[d];
@@ -472,10 +469,9 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, void* const src[4],
     a.n_n = c->g.n[ax[0]];
     a.n_t1 = c->g.n[ax[1]];
     a.n_t2 = c->g.n[ax[2]];
-    // the forward FP64 face tiles (16 x 8 faces, 256 threads) and march chunks
     a.tiles_t1 = (a.n_t1 + TILE1 - 1) / TILE1;
-    a.tiles_t2 = (a.n_t2 + FaceTile<double>::T2 - 1) / FaceTile<double>::T2;
-    a.chunk = c->chunk[d];
+    a.tiles_t2 = (a.n_t2 + AdjTile::T2 - 1) / AdjTile::T2;
+    a.chunk = c->adj_chunk[d];
     a.st_n = c->g.st[ax[0]];
     a.st_t1 = c->g.st[ax[1]];
     a.st_t2 = c->g.st[ax[2]];
@@ -730,15 +726,36 @@ int gks_init(const gks_config* cfg, gks_field q, gks_field q_stage, gks_field q_
     c->eps = c->cfg.weno_eps;
     c->diag_nblk = diag_blocks(c->g);
     c->flags = cfg->ma > 0.3 ? GKS_WARN_MACH : 0;
-    const int slots = cfg->order == 2 ? (cfg->precision == GKS_FP32 ? face2_slots<float>() : face2_slots<double>())
-                                      : (cfg->precision == GKS_FP32 ? face_slots<float>() : face_slots<double>());
-    const int t2 = cfg->precision == GKS_FP32 ? face_tile_t2<float>(cfg->order) : face_tile_t2<double>(cfg->order);
+    // tile heights a face launch can take: per direction the one whose plan costs least wins (FACE64_ROWS)
+    const bool f64 = cfg->precision == GKS_FP64;
+    const int nopt = cfg->order != 2 && f64 ? 2 : 1;
+    int rows[2] = {TILE2, TILE2}, slots[2];
+    for (int o = 0; o < nopt; ++o) {
+        if (nopt > 1) rows[o] = FACE64_ROWS[o];
+        slots[o] = cfg->order == 2 ? (f64 ? face2_slots<double>() : face2_slots<float>())
+                                   : (f64 ? face_slots<double>(rows[o]) : face_slots<float>(rows[o]));
+    }
     for (int d = 0; d < 3; ++d) {
         const int* ax = kAxes[d];
-        const int tiles = ((n[ax[1]] + TILE1 - 1) / TILE1) * ((n[ax[2]] + t2 - 1) / t2);
-        c->chunk[d] = cfg->precision == GKS_FP32 ? face_chunk<float>(n[ax[0]], tiles, slots)
-                                                 : face_chunk<double>(n[ax[0]], tiles, slots);
-        face_plan(n[ax[0]], tiles, slots, c->chunk[d], &c->seg_len[d], &c->n_wg[d]);
+        const int t1_tiles = (n[ax[1]] + TILE1 - 1) / TILE1;
+        long long best = -1;
+        for (int o = 0; o < nopt; ++o) {
+            const int tiles = t1_tiles * ((n[ax[2]] + rows[o] - 1) / rows[o]);
+            const int chunk = face_chunk(n[ax[0]], tiles, slots[o]);
+            int seg, wgs;
+            const long long cost =
+                face_plan(n[ax[0]], tiles, slots[o], chunk, &seg, &wgs) * (nopt > 1 ? FACE64_STEP[o] : 1);
+            if (best < 0 || cost < best) {
+                best = cost;
+                c->t2[d] = rows[o];
+                c->chunk[d] = chunk;
+                c->seg_len[d] = seg;
+                c->n_wg[d] = wgs;
+            }
+        }
+        // the adjoint's recompute pass: its own tiles, one workgroup per CU (its LDS), as the 8-row forward tile
+        const int adj_tiles = ((n[ax[1]] + TILE1 - 1) / TILE1) * ((n[ax[2]] + AdjTile::T2 - 1) / AdjTile::T2);
+        c->adj_chunk[d] = nopt > 1 ? face_chunk(n[ax[0]], adj_tiles, slots[1]) : 0;
     }
     hipError_t e = cfg->precision == GKS_FP32 ? upload_metrics<float>(c, cfg) : upload_metrics<double>(c, cfg);
     if (e == hipSuccess) e = hipMemsetAsync(c->st, 0, sizeof(DevState), c->stream);

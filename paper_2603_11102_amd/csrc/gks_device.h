@@ -35,15 +35,24 @@ template <> struct Rc<double> {
 
 #define GKS_SQRT3 1.7320508075688772935274463415059
 
-// Reciprocal: FP32 uses the hardware v_rcp_f32 (about 1 ulp); FP64 refines v_rcp_f64 by two Newton
-// steps (about 1 ulp). Arguments are positive normal numbers here (densities, WENO denominators).
+// Reciprocal: FP32 uses the hardware v_rcp_f32 (about 1 ulp); FP64 refines v_rcp_f64 (relative error e up
+// to 2^-24.4, measured over 2^20 arguments) by the three terms 1 + e + e^2 of its series: error e^3 and about
+// 1 ulp of rounding, with one multiply-add less than two Newton steps. Arguments are positive normal numbers here (densities, WENO denominators).
 template <typename real> __device__ __forceinline__ real rcp(real x);
 template <> __device__ __forceinline__ float rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
 template <> __device__ __forceinline__ double rcp<double>(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = fma(fma(-x, y, 1.0), y, y);
-    y = fma(fma(-x, y, 1.0), y, y);
-    return y;
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(fma(e, e, e), y, y);
+}
+
+// a b + c with a wave-uniform c. FP64: v_fma_f64 with c in scalar registers (the compiler's own choice, the
+// two-operand v_fmac_f64, first copies c to vector registers: an instruction more).
+__device__ __forceinline__ float fma_uniform(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_uniform(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -54,25 +63,28 @@ template <> __device__ __forceinline__ double rcp<double>(double x) {
 // so that its smoothness indicator is 4 beta_k = (13/3) a_k^2 + b_k^2, its values at the faces
 // xi = +-1/2 are q0 + (a_k +- 3 b_k)/12 and at the Gauss points xi = s sqrt3/6 q0 + s (sqrt3/12) b_k
 // (the two-point Gauss rule integrates the quadratic exactly, so its even part there is q0).
+// The second differences are carried as sa_k = sqrt(13/3) a_k, which makes 4 beta_k two multiply-adds.
 // P_k = prod_{j != k} (4 eps + 4 beta_j)^2: the nonlinear weights gamma_k / (eps + beta_k)^2,
 // normalised, equal gamma_k P_k / sum_j gamma_j P_j (the common factor 4^4 cancels), so one reciprocal
 // per evaluation point suffices.
 // ---------------------------------------------------------------------------------------------
+#define GKS_SA 2.0816659994661327  // sqrt(13/3)
 template <typename real>
 __device__ __forceinline__ void js_parts(real qm2, real qm1, real q0, real qp1, real qp2, real eps,
-                                         real a[3], real b[3], real P[3]) {
+                                         real sa[3], real b[3], real P[3]) {
     const real d1 = qm1 - qm2, d2 = q0 - qm1, d3 = qp1 - q0, d4 = qp2 - qp1;
-    a[0] = d2 - d1;
+    const real s = real(GKS_SA), e4 = real(4) * eps;
+    const real s2 = s * d2, s3 = s * d3;
+    sa[0] = s2 - s * d1;
     b[0] = real(3) * d2 - d1;
-    a[1] = d3 - d2;
+    sa[1] = s3 - s2;
     b[1] = d2 + d3;
-    a[2] = d4 - d3;
+    sa[2] = s * d4 - s3;
     b[2] = real(3) * d3 - d4;
-    const real c133 = real(13.0 / 3.0), e4 = real(4) * eps;
     real e[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        e[k] = e4 + c133 * a[k] * a[k] + b[k] * b[k];
+        e[k] = fma_uniform(sa[k], sa[k], e4) + b[k] * b[k];
         e[k] *= e[k];
     }
     P[0] = e[1] * e[2];
@@ -82,23 +94,24 @@ __device__ __forceinline__ void js_parts(real qm2, real qm1, real q0, real qp1, 
 
 // Face values of cell 0: right face (xi = +1/2, linear weights 1/10, 3/5, 3/10) and left face
 // (xi = -1/2, weights 3/10, 3/5, 1/10). Both share the cell's smoothness indicators. The weights are
-// divided by 3/5, and the 1/12 of the sub-stencil values goes into the denominator.
+// divided by 3/5, and the 1/12 of the sub-stencil values and the scale of sa go into the denominator.
 template <typename real>
 __device__ __forceinline__ void weno_faces(real qm2, real qm1, real q0, real qp1, real qp2, real eps,
                                            real& right, real& left) {
-    real a[3], b[3], P[3];
-    js_parts(qm2, qm1, q0, qp1, qp2, eps, a, b, P);
-    const real P1x = real(12) * P[1];
-    real X0 = P[0] * (a[0] + real(3) * b[0]);
-    real X1 = P[1] * (a[1] + real(3) * b[1]);
-    real X2 = P[2] * (a[2] + real(3) * b[2]);
+    real sa[3], b[3], P[3];
+    js_parts(qm2, qm1, q0, qp1, qp2, eps, sa, b, P);
+    const real s3 = real(3 * GKS_SA);
+    const real P1x = real(12 * GKS_SA) * P[1];
+    real X0 = P[0] * (sa[0] + s3 * b[0]);
+    real X1 = P[1] * (sa[1] + s3 * b[1]);
+    real X2 = P[2] * (sa[2] + s3 * b[2]);
     right = q0 + (real(1.0 / 6.0) * X0 + (real(0.5) * X2 + X1)) *
-                     rcp<real>(real(2) * P[0] + (real(6) * P[2] + P1x));
-    X0 = P[0] * (a[0] - real(3) * b[0]);
-    X1 = P[1] * (a[1] - real(3) * b[1]);
-    X2 = P[2] * (a[2] - real(3) * b[2]);
+                     rcp<real>(real(2 * GKS_SA) * P[0] + (real(6 * GKS_SA) * P[2] + P1x));
+    X0 = P[0] * (sa[0] - s3 * b[0]);
+    X1 = P[1] * (sa[1] - s3 * b[1]);
+    X2 = P[2] * (sa[2] - s3 * b[2]);
     left = q0 + (real(0.5) * X0 + (real(1.0 / 6.0) * X2 + X1)) *
-                    rcp<real>(real(6) * P[0] + (real(2) * P[2] + P1x));
+                    rcp<real>(real(6 * GKS_SA) * P[0] + (real(2 * GKS_SA) * P[2] + P1x));
 }
 
 // Linear weights at the Gauss points s = +-1 that reproduce the quartic: (7/36 - s sqrt3/1080, 11/18,
@@ -180,13 +193,34 @@ __device__ __forceinline__ void horner_pair(const double (&c)[10], real A, real 
 #pragma unroll
     for (int k = N - 1; k >= 0; --k) {
         rk[k] = r;  // coefficient k of the quotient
-        r = fma(A, r, real(c[k]));
+        r = fma_uniform(A, r, real(c[k]));
     }
     PA = r;
     q = rk[N - 1];
 #pragma unroll
     for (int k = N - 2; k >= 0; --k) q = fma(B, q, rk[k]);
     Q = q;
+}
+
+// Library form of kin_trans below. In FP64 it is a call on purpose: flows inside the series' range never reach
+// it, and its code inlined in the face kernels cost 60 registers and spills in their march.
+template <typename real>
+struct KinTrans {
+    real hL, hR, hd, eR, dE;
+};
+template <typename real>
+__device__ __forceinline__ KinTrans<real> kin_library_code(real aL, real aR) {
+    KinTrans<real> k;
+    k.hL = real(0.5) * (real(1) + Rc<real>::erf_(aL));
+    k.hR = real(0.5) * (real(1) - Rc<real>::erf_(aR));
+    k.hd = real(0.5) * erf_diff<real>(aL, aR);
+    k.eR = Rc<real>::exp_(-aR * aR);
+    k.dE = k.eR * Rc<real>::expm1_((aR - aL) * (aL + aR));
+    return k;
+}
+__device__ __forceinline__ KinTrans<float> kin_library(float aL, float aR) { return kin_library_code(aL, aR); }
+__device__ __attribute__((noinline)) KinTrans<double> kin_library(double aL, double aR) {
+    return kin_library_code(aL, aR);
 }
 
 // Transcendentals of the kinetic average at aL, aR: the half-space weights hL = (1 + erf aL) / 2 and
@@ -206,7 +240,7 @@ __device__ __forceinline__ void kin_trans(real aL, real aR, real& hL, real& hR, 
                                           real& dE) {
     constexpr bool F32 = sizeof(real) == 4;
     const real dif = aL - aR, sum = aL + aR;
-    if (fmax(fabs(aL), fabs(aR)) <= real(0.25)) {
+    if (__builtin_expect(fmax(fabs(aL), fabs(aR)) <= real(0.25), 1)) {
         constexpr int NP = F32 ? 4 : 9, NE = F32 ? 5 : 9;
         const real k1 = real(0.56418958354775628695);  // 1/sqrt(pi)
         const real A = aL * aL, B = aR * aR, AB = dif * sum;
@@ -219,11 +253,12 @@ __device__ __forceinline__ void kin_trans(real aL, real aR, real& hL, real& hR, 
         dE = AB * QE;
         eR = eL - dE;
     } else {
-        hL = real(0.5) * (real(1) + Rc<real>::erf_(aL));
-        hR = real(0.5) * (real(1) - Rc<real>::erf_(aR));
-        hd = real(0.5) * erf_diff<real>(aL, aR);
-        eR = Rc<real>::exp_(-aR * aR);
-        dE = eR * Rc<real>::expm1_(-dif * sum);
+        const KinTrans<real> k = kin_library(aL, aR);
+        hL = k.hL;
+        hR = k.hR;
+        hd = k.hd;
+        eR = k.eR;
+        dE = k.dE;
         eL = eR + dE;
     }
 }
@@ -296,8 +331,9 @@ __device__ __forceinline__ void gp_flux(const real qL[4], const real qR[4], cons
 template <typename real>
 __device__ __forceinline__ void weno_faces_w(real qm2, real qm1, real q0, real qp1, real qp2, real eps,
                                              real& right, real& left, real wr[3], real wl[3]) {
-    real a[3], b[3], P[3];
+    real a[3], b[3], P[3];  // a: scaled by GKS_SA
     js_parts(qm2, qm1, q0, qp1, qp2, eps, a, b, P);
+    const real s3 = real(3 * GKS_SA), ia = real(1.0 / GKS_SA);
     // weights divided by 3/5 and multiplied by 12 in the denominator, as in weno_faces
     const real P1x = real(12) * P[1];
     real c0 = real(2) * P[0], c2 = real(6) * P[2];
@@ -305,16 +341,16 @@ __device__ __forceinline__ void weno_faces_w(real qm2, real qm1, real q0, real q
     wr[0] = c0 * is;
     wr[1] = P1x * is;
     wr[2] = c2 * is;
-    right = q0 + (real(1.0 / 6.0) * P[0] * (a[0] + real(3) * b[0]) +
-                  (real(0.5) * P[2] * (a[2] + real(3) * b[2]) + P[1] * (a[1] + real(3) * b[1]))) * is;
+    right = q0 + (real(1.0 / 6.0) * P[0] * (a[0] + s3 * b[0]) +
+                  (real(0.5) * P[2] * (a[2] + s3 * b[2]) + P[1] * (a[1] + s3 * b[1]))) * (ia * is);
     c0 = real(6) * P[0];
     c2 = real(2) * P[2];
     is = rcp<real>(c0 + (c2 + P1x));
     wl[0] = c0 * is;
     wl[1] = P1x * is;
     wl[2] = c2 * is;
-    left = q0 + (real(0.5) * P[0] * (a[0] - real(3) * b[0]) +
-                 (real(1.0 / 6.0) * P[2] * (a[2] - real(3) * b[2]) + P[1] * (a[1] - real(3) * b[1]))) * is;
+    left = q0 + (real(0.5) * P[0] * (a[0] - s3 * b[0]) +
+                 (real(1.0 / 6.0) * P[2] * (a[2] - s3 * b[2]) + P[1] * (a[1] - s3 * b[1]))) * (ia * is);
 }
 
 template <typename real>

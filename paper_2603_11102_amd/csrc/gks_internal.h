@@ -13,18 +13,30 @@ constexpr int TILE1 = 16, TILE2 = 16;    // tangential faces per workgroup (t1 x
 constexpr int EXT1 = TILE1 + 4, EXT2 = TILE2 + 4;
 constexpr int FACE_THREADS = 512;        // 8 wave64 per workgroup
 
-// Tile of the high-order face kernel per precision. FP32: 16 x 16 faces, 512 threads (two waves per
-// SIMD, up to 256 registers each). FP64: 16 x 8 faces, 256 threads: one workgroup per CU (its LDS), one
-// wave per SIMD, so that a wave can use the 512 registers of the unified VGPR/AGPR file its doubled live
-// state needs instead of spilling to scratch. Both map one thread per tile column (20 x 20 and 20 x 12)
-// and one thread per face and Gauss line.
-template <typename real>
-struct FaceTile {
-    static constexpr int T2 = 16, THREADS = 512;
+// Tiles of the order-5 face kernels, TILE1 x T2 faces. FP32: 16 x 16 faces, 512 threads (two waves per
+// SIMD, up to 256 registers each), two lanes per face. FP64: four lanes per face, 16 x 12 faces on 768
+// threads or 16 x 8 on 512. A step of the 12-row tile takes 1.41 times a step of the 8-row one (6.25 against
+// 4.44 us, 192 x 96 x 96 channel) for 1.5 times the faces, so it wins where both fill the chip (channel step
+// 1.56 against 1.64 ms) and loses on small or badly divided planes (32^3: 119 against 98 us); face_plan's cost
+// decides per direction. 16 rows do not fit: 128 registers a thread spill (1.96 ms).
+constexpr int FACE64_ROWS[2] = {12, 8};
+constexpr int FACE64_STEP[2] = {141, 100};  // relative time of a face step
+
+// Local index (the pass's variable order: density, normal momentum, t1, t2 momenta) of each global
+// variable (density, x, y, z momenta) for the x (MODE 3), y (MODE 0) and z (MODE 4) passes.
+template <int MODE>
+struct LocalOrder;
+template <>
+struct LocalOrder<3> {
+    static constexpr int v[4] = {0, 1, 2, 3};
 };
 template <>
-struct FaceTile<double> {
-    static constexpr int T2 = 8, THREADS = 256;
+struct LocalOrder<0> {
+    static constexpr int v[4] = {0, 2, 1, 3};
+};
+template <>
+struct LocalOrder<4> {
+    static constexpr int v[4] = {0, 2, 3, 1};
 };
 
 // Arguments of the per-direction face kernel. Arrays are in the face's LOCAL variable order
@@ -50,6 +62,7 @@ struct FaceArgs {
     real* lo_b;
     int n_n, n_t1, n_t2;     // interior cells along normal, t1, t2
     int chunk, tiles_t1, tiles_t2;
+    int t2;                  // t2 rows of a tile
     // work split of the order-5 face kernel over its n_wg logical workgroups: seg_len == 0, workgroup b
     // marches chunk b / (tiles) of tile b % (tiles); seg_len > 0, it marches cells
     // [b seg_len, (b + 1) seg_len) of the tile-major (tile, cell) order, one segment per tile it meets
@@ -115,12 +128,21 @@ struct Field4 {
 // host launchers (gks_stage.hip)
 template <typename real>
 hipError_t launch_face(const FaceArgs<real>& a, int stage, hipStream_t s);
-template <typename real>
 int face_chunk(int n_n, int tiles, int slots);
-// order-5 face launches: the work split (FaceArgs seg_len, n_wg) for chunks of `chunk` cells
-void face_plan(int n_n, int tiles, int slots, int chunk, int* seg_len, int* n_wg);
+// order-5 face launches: the work split (FaceArgs seg_len, n_wg) for chunks of `chunk` cells; returns its cost
+// in face steps
+long long face_plan(int n_n, int tiles, int slots, int chunk, int* seg_len, int* n_wg);
+// resident workgroups of the order-5 face kernel with tiles of t2 rows
 template <typename real>
-int face_slots();
+int face_slots(int t2);
+template <>
+hipError_t launch_face<float>(const FaceArgs<float>& a, int stage, hipStream_t s);  // gks_stage.hip
+template <>
+hipError_t launch_face<double>(const FaceArgs<double>& a, int stage, hipStream_t s);  // gks_stage64.hip
+template <>
+int face_slots<float>(int t2);
+template <>
+int face_slots<double>(int t2);
 // second-order variant (gks_stage2.hip)
 template <typename real>
 hipError_t launch_face2(const FaceArgs<real>& a, int stage, hipStream_t s);

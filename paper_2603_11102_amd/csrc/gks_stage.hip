@@ -1,25 +1,26 @@
-// gks_stage.hip -- the S2O4 stage kernels: reconstruction, gas-kinetic flux, flux divergence and the
-// stage combination, one launch per face direction (Section 2, Eqs. (semi), (finite), (x_example),
-// (flux); the two-stage fourth-order combinations).
+// gks_stage.hip -- the FP32 S2O4 stage kernels (the FP64 ones are in gks_stage64.hip): reconstruction,
+// gas-kinetic flux, flux divergence and the stage combination, one launch per face direction (Section 2,
+// Eqs. (semi), (finite), (x_example), (flux); the two-stage fourth-order combinations). Also the work split
+// of both precisions.
 //
-// One workgroup owns a tile of faces in the tangential plane (FP32: 16 x 16 faces, 512 threads = 8 wave64;
-// FP64: 16 x 8 faces, 256 threads) and marches along the face normal through a chunk of faces (or
-// through an equal share of the tile-major (tile, cell) order, one march per tile the share meets, when
-// the tiles do not divide the resident workgroup slots: see face_plan):
-//   * column phase: each of the 20 x 20 (FP64 20 x 12) tangential columns (tile + 2-cell halo per side) keeps a
+// One workgroup owns a tile of 16 x 16 faces in the tangential plane (512 threads = 8 wave64) and marches
+// along the face normal through a chunk of faces (or through an equal share of the tile-major (tile, cell)
+// order, one march per tile the share meets, when the tiles do not divide the resident workgroup slots: see
+// face_plan):
+//   * column phase: each of the 20 x 20 tangential columns (tile + 2-cell halo per side) keeps a
 //     5-cell window of the field in registers; per cell it evaluates the WENO-JS values at both of its
 //     faces with one set of smoothness indicators, the normal derivative D (cubic through four cells)
 //     and C = (q^L + q^R)/2 for all four variables -> LDS;
 //   * t1 phase: WENO-JS at the two Gauss points of q^L, q^R, quartic Gauss values of D and C and the
-//     quartic Gauss derivative of C along t1, the 4 x 320 (FP64 4 x 192) (variable, position) items spread
-//     over all threads -> LDS;
+//     quartic Gauss derivative of C along t1, the 4 x 320 (variable, position) items spread over all
+//     threads -> LDS;
 //   * t2 phase: the same along t2 for each Gauss line, giving per Gauss point q^L, q^R, dQ/dn, dQ/dt1,
 //     dQ/dt2 in registers (one thread per face and Gauss line);
 //   * flux phase: closed-form flux per Gauss point, quadrature over the face, divergence against the
 //     previous face of the column, and the accumulation (or the S2O4 epilogue in the last direction).
-// No face flux is written to memory. FP32 runs the phases as a software pipeline over two LDS buffers
+// No face flux is written to memory. The phases run as a software pipeline over two LDS buffers
 // (the face step of f, the t1 phase of f + 1 and the column phase of f + 2 between two barriers; 155 KB of
-// the 160 KB per CU); FP64 runs them in turn with two barriers per face step (93 KB).
+// the 160 KB per CU).
 #include <algorithm>
 
 #include "gks_internal.h"
@@ -37,11 +38,6 @@ template <>
 struct Vec2<float> {
     using type = float2;
 };
-template <>
-struct Vec2<double> {
-    using type = double2;
-};
-
 // The pair of variables (2m, 2m + 1) of cell i in an array that holds four variables per cell.
 template <typename real>
 __device__ __forceinline__ typename Vec2<real>::type ld2(const real* p, long long i, int m) {
@@ -52,34 +48,9 @@ __device__ __forceinline__ void st2(real* p, long long i, int m, typename Vec2<r
     *reinterpret_cast<typename Vec2<real>::type*>(p + 4 * i + 2 * m) = v;
 }
 
-// Local index (the pass's variable order: density, normal momentum, t1, t2 momenta) of each global
-// variable (density, x, y, z momenta) for the x (MODE 3), y (MODE 0) and z (MODE 4) passes.
-template <int MODE>
-struct LocalOrder;
-template <>
-struct LocalOrder<3> {
-    static constexpr int v[4] = {0, 1, 2, 3};
-};
-template <>
-struct LocalOrder<0> {
-    static constexpr int v[4] = {0, 2, 1, 3};
-};
-template <>
-struct LocalOrder<4> {
-    static constexpr int v[4] = {0, 2, 3, 1};
-};
-
-// The value of the partner lane (lane ^ 1; all lanes are active where it is used). FP32, bound by VALU
-// issue, moves it through the LDS crossbar (ds_bpermute), off the VALU; FP64, bound by latency at one
-// wave per SIMD, takes it with a DPP quad permutation [1, 0, 3, 2] on the VALU, without the LDS round trip
-// (with the crossbar the compiler waited for each value in turn).
+// The value of the partner lane (lane ^ 1; all lanes are active where it is used), moved through the LDS
+// crossbar (ds_bpermute), off the VALU that bounds the kernel.
 __device__ __forceinline__ float pair_swap(float x) { return __shfl_xor(x, 1); }
-__device__ __forceinline__ double pair_swap(double x) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffu), 0xB1, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0xB1, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
 
 // Error-free sum (Knuth): s + e == a + b exactly, s = fl(a + b).
 __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
@@ -93,42 +64,35 @@ __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
 // STR: the mesh is stretched and the spacings come from the per-axis arrays; otherwise the uniform
 // inverse spacings are kernel arguments (no memory access for them inside the march).
 template <typename real, int STAGE, int MODE, bool STR>
-__global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const FaceArgs<real> a) {
+__global__ void __launch_bounds__(FACE_THREADS) face_kernel(const FaceArgs<real> a) {
     static_assert(MODE == 0 || MODE == 3 || MODE == 4, "face pass mode");
-    // tile of this precision: TILE1 x T2 faces, EXT1 x X2 columns, NTH threads
-    constexpr int T2 = FaceTile<real>::T2, X2 = T2 + 4, NTH = FaceTile<real>::THREADS;
+    // TILE1 x T2 faces, EXT1 x X2 columns, NTH threads
+    constexpr int T2 = TILE2, X2 = EXT2, NTH = FACE_THREADS;
     static_assert(EXT1 * X2 <= NTH && 2 * TILE1 * T2 == NTH, "one thread per column and per face line");
     constexpr bool NEED_F0 = (STAGE == 1);
-    // the z pass loads its epilogue operands at the top of the step, so that their latency overlaps the
-    // step's arithmetic; FP32 also updates the compensated state (high part in the field, low part in
-    // lo_in / lo_a / lo_b)
-    constexpr bool EPI_PREFETCH = true;
-    constexpr bool COMPENSATED = sizeof(real) == 4;
     using real2 = typename Vec2<real>::type;
     constexpr int LOC[4] = {LocalOrder<MODE>::v[0], LocalOrder<MODE>::v[1], LocalOrder<MODE>::v[2],
                             LocalOrder<MODE>::v[3]};
     // LDS: per variable, the column values [q^L, q^R, D, C][t2 row][t1 column] and the t1-phase results
     // [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. A wave of the t1 phase takes
     // one row of all four variables, 16 consecutive positions each; the variable blocks are padded to
-    // start 16 words apart modulo 64 (FP32; 32 in FP64, whose elements take two banks), so its reads
-    // meet no bank twice, and the t1-phase results of the four variables start 32 words apart modulo 64
-    // (FP32), the least the wave's 64-bit stores can share banks.
-    // PAIR_PREV: the FP32 stage-1 z pass, which sits at the register limit, keeps only its lane's two
+    // start 16 words apart modulo 64, so its reads
+    // meet no bank twice, and the t1-phase results of the four variables start 32 words apart modulo 64,
+    // the least the wave's 64-bit stores can share banks.
+    // PAIR_PREV: the stage-1 z pass, which sits at the register limit, keeps only its lane's two
     // variables of the previous face's fluxes (the other passes keep all four: fewer selects per step).
-    constexpr bool PAIR_PREV = (MODE == 4 && STAGE == 1 && sizeof(real) == 4);
+    constexpr bool PAIR_PREV = (MODE == 4 && STAGE == 1);
     struct NrmV {
         real a[4][X2][EXT1];
         real pad[16];
     };
     struct T1V {
         real a[5][X2][TILE1][2];
-        real pad[sizeof(real) == 4 ? 32 : 2];
+        real pad[32];
     };
-    // DB (FP32): two LDS buffers, so that the phases of consecutive faces overlap (FP64 has no room)
-    constexpr bool DB = sizeof(real) == 4;
-    constexpr int NB = DB ? 2 : 1;
-    __shared__ NrmV s_nrm[NB][4];
-    __shared__ T1V s_t1[NB][4];
+    // two LDS buffers, so that the phases of consecutive faces overlap
+    __shared__ NrmV s_nrm[2][4];
+    __shared__ T1V s_t1[2][4];
 
     const int tid = threadIdx.x;
     // consecutive logical workgroups run on the same XCD (the hardware deals workgroups round-robin to
@@ -174,13 +138,12 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
     const int fj = (tid >> 1) % TILE1, fk = (tid >> 1) / TILE1;
     const bool face_ok = (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
 
-    // FP32: inside the kernel the normal momentum is carried as its deviation from a workgroup constant
+    // Inside the kernel the normal momentum is carried as its deviation from a workgroup constant
     // cm (the midrange of its values in the first window of the tile), so that the O(1) part of the
     // mass flux cancels exactly between the two faces of a cell and FP32 rounding acts on the deviation
     // only. The WENO and linear stencils commute with the shift (their weights sum to one and the
     // smoothness indicators use differences); the derivatives are unchanged.
-    constexpr bool SHIFT = sizeof(real) == 4;
-    real cm = real(0);
+    real cm;
     real ring[4][5];
     real carry[4];
 #pragma unroll
@@ -198,7 +161,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
             for (int v = 0; v < 4; ++v) ring[v][r] = a.q[v][idx];
         }
     }
-    if constexpr (SHIFT) {
+    {
         __shared__ float s_range[2][NTH / 64];
         float lo = col_ld ? float(ring[1][0]) : 3.0e38f, up = col_ld ? float(ring[1][0]) : -3.0e38f;
 #pragma unroll
@@ -259,7 +222,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
         real q[2];
     };
     auto epi_load = [&](int f, Epi& ep) {
-        if constexpr (EPI_PREFETCH && MODE == 4) {
+        if constexpr (MODE == 4) {
             // loaded on every path (for the same reason as the column prefetch): at f = f0, one face past
             // the march and for faces outside the domain a clamped cell is read and its values are not used
             const int cell = min(max(f - 1, 0), a.n_n - 1), je = min(j0 + fj, a.n_t1 - 1), ke = min(k0 + fk, a.n_t2 - 1);
@@ -268,7 +231,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
             const long long xidx = rx_block_index(je, ke, cell, a.rx_nx, a.rx_nyb);
             ep.r1 = ld2(a.r1, ridx, m);
             ep.x1 = ld2(a.rx1, xidx, m);
-            if (COMPENSATED) ep.lo = ld2(a.lo_in, ridx, m);
+            ep.lo = ld2(a.lo_in, ridx, m);
             if (NEED_F0) {
                 ep.r0 = ld2(a.r0, ridx, m);
                 ep.x0 = ld2(a.rx0, xidx, m);
@@ -291,7 +254,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
 #pragma unroll
                 for (int r = 0; r < 4; ++r) ring[v][r] = ring[v][r + 1];
                 // the shift is applied here, a step after the load, so that the prefetch stays in flight
-                ring[v][4] = (SHIFT && v == 1) ? nxt[v] - cm : nxt[v];
+                ring[v][4] = v == 1 ? nxt[v] - cm : nxt[v];
             }
         }
         {
@@ -396,7 +359,7 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
                 g[1][v] = gp[v][n][3];
                 g[2][v] = gp[v][n][4];
             }
-            gp_flux<real, NEED_F0, SHIFT>(qL, qR, g, a.fc, fa0, fa1, cm);
+            gp_flux<real, NEED_F0, true>(qL, qR, g, a.fc, fa0, fa1, cm);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -445,68 +408,36 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
                 st2(a.r1, ridx, m, d1);
                 if (NEED_F0) st2(a.r0, ridx, m, d0);
             } else {
-                real2 r1v, x1v, r0v = {0, 0}, x0v = {0, 0};
-                if constexpr (EPI_PREFETCH) {
-                    r1v = ep.r1;
-                    x1v = ep.x1;
-                    r0v = ep.r0;
-                    x0v = ep.x0;
-                } else {
-                    const long long xidx = rx_block_index(j0 + fj, k0 + fk, cell, a.rx_nx, a.rx_nyb);
-                    r1v = ld2(a.r1, ridx, m);
-                    x1v = ld2(a.rx1, xidx, m);
-                    if (NEED_F0) {
-                        r0v = ld2(a.r0, ridx, m);
-                        x0v = ld2(a.rx0, xidx, m);
-                    }
-                }
+                const real2 r1v = ep.r1, x1v = ep.x1, r0v = ep.r0, x0v = ep.x0;
                 const real L1[2] = {r1v.x + (d1.x + x1v.x), r1v.y + (d1.y + x1v.y)};
                 const real L0[2] = {r0v.x + (d0.x + x0v.x), r0v.y + (d0.y + x0v.y)};
-                if constexpr (COMPENSATED) {
-                    // FP32: the state is carried as hi + lo; each update is an error-free sum of the
-                    // stored high part and (low part + increment)
-                    const real lo[2] = {ep.lo.x, ep.lo.y};
-                    real2 la = {0, 0}, lb = {0, 0};
+                // the state is carried as hi + lo; each update is an error-free sum of the
+                // stored high part and (low part + increment)
+                const real lo[2] = {ep.lo.x, ep.lo.y};
+                real2 la = {0, 0}, lb = {0, 0};
 #pragma unroll
-                    for (int vv = 0; vv < 2; ++vv) {
-                        real* const outa = pick(hi, a.out_a[LOC[2 + vv]], a.out_a[LOC[vv]]);
-                        float sh, sl;
-                        if (NEED_F0) {
-                            real* const outb = pick(hi, a.out_b[LOC[2 + vv]], a.out_b[LOC[vv]]);
-                            two_sum(ep.q[vv], lo[vv] + (real(0.5) * dt * L0[vv] + real(0.125) * dt * dt * L1[vv]), sh, sl);
-                            outa[pidx] = sh;
-                            if (vv == 0) la.x = sl; else la.y = sl;
-                            two_sum(ep.q[vv], lo[vv] + (dt * L0[vv] + (dt * dt * real(1.0 / 6.0)) * L1[vv]), sh, sl);
-                            outb[pidx] = sh;
-                            if (vv == 0) lb.x = sl; else lb.y = sl;
-                        } else {
-                            // body force G on the momenta (global variables 1..3)
-                            const real gv = pick(hi, a.g_global[1 + vv], vv == 1 ? a.g_global[0] : real(0));
-                            const real add = (dt * dt * real(1.0 / 3.0)) * L1[vv] + dt * gv;
-                            two_sum(ep.q[vv], lo[vv] + add, sh, sl);
-                            outa[pidx] = sh;
-                            if (vv == 0) la.x = sl; else la.y = sl;
-                        }
-                    }
-                    st2(a.lo_a, ridx, m, la);
-                    if (NEED_F0) st2(a.lo_b, ridx, m, lb);
-                } else {
-                    // FP64: the plain stage update from the prefetched Q^n (stage 1) or S (stage 2)
-#pragma unroll
-                    for (int vv = 0; vv < 2; ++vv) {
-                        real* const outa = pick(hi, a.out_a[LOC[2 + vv]], a.out_a[LOC[vv]]);
-                        if (NEED_F0) {
-                            const real Q = ep.q[vv];
-                            real* const outb = pick(hi, a.out_b[LOC[2 + vv]], a.out_b[LOC[vv]]);
-                            outa[pidx] = Q + real(0.5) * dt * L0[vv] + real(0.125) * dt * dt * L1[vv];
-                            outb[pidx] = Q + dt * L0[vv] + (dt * dt * real(1.0 / 6.0)) * L1[vv];
-                        } else {
-                            const real gv = pick(hi, a.g_global[1 + vv], vv == 1 ? a.g_global[0] : real(0));
-                            const real add = (dt * dt * real(1.0 / 3.0)) * L1[vv] + dt * gv;
-                            outa[pidx] = ep.q[vv] + add;
-                        }
+                for (int vv = 0; vv < 2; ++vv) {
+                    real* const outa = pick(hi, a.out_a[LOC[2 + vv]], a.out_a[LOC[vv]]);
+                    float sh, sl;
+                    if (NEED_F0) {
+                        real* const outb = pick(hi, a.out_b[LOC[2 + vv]], a.out_b[LOC[vv]]);
+                        two_sum(ep.q[vv], lo[vv] + (real(0.5) * dt * L0[vv] + real(0.125) * dt * dt * L1[vv]), sh, sl);
+                        outa[pidx] = sh;
+                        if (vv == 0) la.x = sl; else la.y = sl;
+                        two_sum(ep.q[vv], lo[vv] + (dt * L0[vv] + (dt * dt * real(1.0 / 6.0)) * L1[vv]), sh, sl);
+                        outb[pidx] = sh;
+                        if (vv == 0) lb.x = sl; else lb.y = sl;
+                    } else {
+                        // body force G on the momenta (global variables 1..3)
+                        const real gv = pick(hi, a.g_global[1 + vv], vv == 1 ? a.g_global[0] : real(0));
+                        const real add = (dt * dt * real(1.0 / 3.0)) * L1[vv] + dt * gv;
+                        two_sum(ep.q[vv], lo[vv] + add, sh, sl);
+                        outa[pidx] = sh;
+                        if (vv == 0) la.x = sl; else la.y = sl;
                     }
                 }
+                st2(a.lo_a, ridx, m, la);
+                if (NEED_F0) st2(a.lo_b, ridx, m, lb);
             }
         }
         if constexpr (PAIR_PREV) {
@@ -520,54 +451,41 @@ __global__ void __launch_bounds__(FaceTile<real>::THREADS) face_kernel(const Fac
             }
         }
     };
-    if constexpr (DB) {
-        // software pipeline over two LDS buffers with one barrier per face: the face step of f reads
-        // s_t1[buf], the t1 phase of f + 1 reads s_nrm[buf ^ 1] and writes s_t1[buf ^ 1], the column
-        // phase of f + 2 writes s_nrm[buf]; each buffer was last read or written before the previous
-        // barrier. The epilogue operands of the next face step are loaded one step ahead. Waves whose
-        // column phase is light (400 columns on 512 threads) go on to the next face's work.
-        Epi ep = {};
-        epi_load(f0, ep);
-        column_step(f0, 0);
+    // software pipeline over two LDS buffers with one barrier per face: the face step of f reads
+    // s_t1[buf], the t1 phase of f + 1 reads s_nrm[buf ^ 1] and writes s_t1[buf ^ 1], the column
+    // phase of f + 2 writes s_nrm[buf]; each buffer was last read or written before the previous
+    // barrier. The epilogue operands of the next face step are loaded one step ahead. Waves whose
+    // column phase is light (400 columns on 512 threads) go on to the next face's work.
+    Epi ep = {};
+    epi_load(f0, ep);
+    column_step(f0, 0);
+    __syncthreads();
+    t1_step(0);
+    column_step(f0 + 1, 1);
+    __syncthreads();
+    for (int f = f0; f <= f1; ++f) {
+        const int buf = (f - f0) & 1;
+        face_step(f, buf, ep);
+        epi_load(f + 1, ep);
+        if (f + 1 <= f1) t1_step(buf ^ 1);
+        if (f + 2 <= f1) column_step(f + 2, buf);
         __syncthreads();
-        t1_step(0);
-        column_step(f0 + 1, 1);
-        __syncthreads();
-        for (int f = f0; f <= f1; ++f) {
-            const int buf = (f - f0) & 1;
-            face_step(f, buf, ep);
-            epi_load(f + 1, ep);
-            if (f + 1 <= f1) t1_step(buf ^ 1);
-            if (f + 2 <= f1) column_step(f + 2, buf);
-            __syncthreads();
-        }
-    } else {
-        for (int f = f0; f <= f1; ++f) {
-            Epi ep = {};
-            epi_load(f, ep);
-            column_step(f, 0);
-            __syncthreads();
-            t1_step(0);
-            __syncthreads();
-            face_step(f, 0, ep);
-        }
     }
     }  // segments
 }
 
-template <typename real>
-int face_slots() {
+template <>
+int face_slots<float>(int) {
     // workgroups of the face kernel that the device holds at once
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, face_kernel<real, 1, 4, false>, FaceTile<real>::THREADS,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, face_kernel<float, 1, 4, false>, FACE_THREADS,
                                                      0) != hipSuccess)
         return 0;
     return cus * per_cu;
 }
 
-template <typename real>
 int face_chunk(int n_n, int tiles, int slots) {
     // Workgroups of one launch run in rounds of `slots`; a workgroup costs about (chunk + 2) face steps
     // (chunk + 1 faces, and the column phase primes five planes before the first one). Pick the chunk
@@ -587,7 +505,7 @@ int face_chunk(int n_n, int tiles, int slots) {
     return best_chunk;
 }
 
-void face_plan(int n_n, int tiles, int slots, int chunk, int* seg_len, int* n_wg) {
+long long face_plan(int n_n, int tiles, int slots, int chunk, int* seg_len, int* n_wg) {
     // Worst workgroup of each split, in face steps (a march over L cells costs about L + 2), times the
     // rounds of `slots` workgroups: aligned chunks of `chunk` cells, or equal runs of the tile-major
     // (tile, cell) order, whose workgroups fill the slots when the tiles do not divide them but pay a
@@ -616,17 +534,18 @@ void face_plan(int n_n, int tiles, int slots, int chunk, int* seg_len, int* n_wg
         }
         if (len == 1) break;
     }
+    return best;
 }
 
-template <typename real>
-hipError_t launch_face(const FaceArgs<real>& a, int stage, hipStream_t s) {
+template <>
+hipError_t launch_face<float>(const FaceArgs<float>& a, int stage, hipStream_t s) {
     const long long blocks = ((long long)a.n_wg + 7) / 8 * 8;
     if (a.n_wg <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(FaceTile<real>::THREADS);
+    const dim3 grid((unsigned)blocks), block(FACE_THREADS);
 #define GKS_FACE_LAUNCH(ST, MD)                                                                     \
     do {                                                                                            \
-        if (a.stretched) hipLaunchKernelGGL((face_kernel<real, ST, MD, true>), grid, block, 0, s, a);  \
-        else hipLaunchKernelGGL((face_kernel<real, ST, MD, false>), grid, block, 0, s, a);             \
+        if (a.stretched) hipLaunchKernelGGL((face_kernel<float, ST, MD, true>), grid, block, 0, s, a);  \
+        else hipLaunchKernelGGL((face_kernel<float, ST, MD, false>), grid, block, 0, s, a);             \
     } while (0)
     if (stage == 1) {
         if (a.mode == 0) GKS_FACE_LAUNCH(1, 0);
@@ -642,12 +561,5 @@ hipError_t launch_face(const FaceArgs<real>& a, int stage, hipStream_t s) {
 #undef GKS_FACE_LAUNCH
     return hipGetLastError();
 }
-
-template hipError_t launch_face<float>(const FaceArgs<float>&, int, hipStream_t);
-template hipError_t launch_face<double>(const FaceArgs<double>&, int, hipStream_t);
-template int face_chunk<float>(int, int, int);
-template int face_chunk<double>(int, int, int);
-template int face_slots<float>();
-template int face_slots<double>();
 
 }  // namespace gks

@@ -23,3 +23,17 @@ def test_kinetic_average_on_both_sides_of_its_series_range(ma, order):
         err = rel_errors(s.interior(), ref)
         assert max(err) < bar, (precision, err)
         assert bool(torch.isfinite(s.interior()).all())
+
+
+@pytest.mark.parametrize("case,grid", [
+    ("tgv", (160, 78, 12)),      # x and y passes: the 12-row FP64 tile, z pass the 8-row one
+    ("channel", (150, 70, 23)),  # z pass: the 12-row tile, t2 = 70 leaves ten rows of its last tile
+])
+def test_fp64_tile_heights_vs_oracle(case, grid):
+    # the launch rule mixes the two FP64 tile heights over the directions at these sizes
+    cfg = make_case(case, grid=grid)
+    print_case("fp64-tiles", case=case, grid=grid)
+    s, _ = run_gpu(cfg, "fp64", 1)
+    o, _ = run_oracle(cfg, 1)
+    err = rel_errors(s.interior(), oracle_dev(o.Q, cfg.rho_ref))
+    assert max(err) < 1e-12, err
