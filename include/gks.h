@@ -272,9 +272,10 @@ int gks_read_statistics(gks_ctx* ctx, double u_inf, double* mean, double* rms, d
 int gks_set_history(gks_ctx* ctx, double* buffer, int32_t capacity);
 int gks_history_count(gks_ctx* ctx, int64_t* count);
 
-/* Per-launch timing with HIP events recorded on the context's stream around each launch group.
- * Categories (index into the arrays of gks_read_timing): */
-#define GKS_TIMER_GHOST 0      /* ghost-cell fills (3 launches per stage) */
+/* Per-launch timing with HIP events recorded on the context's stream around each launch group. The face
+ * passes of two or three directions may share one launch: it then counts once in each of their categories,
+ * with an equal share of its time. Categories (index into the arrays of gks_read_timing): */
+#define GKS_TIMER_GHOST 0      /* ghost-cell fills */
 #define GKS_TIMER_DT 1         /* |U|max reduction and the dt update */
 #define GKS_TIMER_S1X 2        /* stage-1 face kernel, x faces */
 #define GKS_TIMER_S1Y 3

@@ -73,6 +73,7 @@ struct gks_ctx {
     int chunk[3];      // faces per workgroup of the face kernels, per direction
     int adj_chunk[3];  // faces per workgroup of the adjoint's recompute pass
     int seg_len[3], n_wg[3];  // work split of the order-5 face launches (FaceArgs)
+    int side_by_side;  // order 5: the three directions of a stage run in one launch (face_layout)
     int flags;
     // actuator line model
     int has_rotor;
@@ -99,7 +100,7 @@ struct gks_ctx {
     // event timing
     int timing;
     std::vector<hipEvent_t> ev_pool;
-    std::vector<int> ev_cat;   // category of each recorded pair
+    std::vector<unsigned> ev_cat;  // categories of each recorded pair (bit mask)
     size_t ev_used;            // events in use (2 per pair)
     double t_ms[GKS_TIMER_COUNT];
     long long t_cnt[GKS_TIMER_COUNT];
@@ -503,16 +504,23 @@ int timing_flush(gks_ctx* c) {
     for (size_t p = 0; p < c->ev_cat.size(); ++p) {
         float ms = 0.f;
         HIPCHK(c, hipEventElapsedTime(&ms, c->ev_pool[2 * p], c->ev_pool[2 * p + 1]));
-        c->t_ms[c->ev_cat[p]] += ms;
-        c->t_cnt[c->ev_cat[p]] += 1;
+        // a launch group that serves several categories counts once in each, with an equal share of its time
+        const unsigned cats = c->ev_cat[p];
+        const int n = __builtin_popcount(cats);
+        for (int k = 0; k < GKS_TIMER_COUNT; ++k)
+            if (cats >> k & 1u) {
+                c->t_ms[k] += ms / n;
+                c->t_cnt[k] += 1;
+            }
     }
     c->ev_cat.clear();
     c->ev_used = 0;
     return GKS_OK;
 }
 
-// open a timed launch group; returns the pair index or -1 when timing is off
-int tbeg(gks_ctx* c, int cat) {
+// open a timed launch group that serves category cat (and cat2, cat3 unless negative); returns the pair index
+// or -1 when timing is off
+int tbeg(gks_ctx* c, int cat, int cat2 = -1, int cat3 = -1) {
     if (!c->timing) return -1;
     if (c->ev_used + 2 > 4096 && timing_flush(c) != GKS_OK) return -1;
     while (c->ev_pool.size() < c->ev_used + 2) {
@@ -523,12 +531,67 @@ int tbeg(gks_ctx* c, int cat) {
     const size_t i = c->ev_used;
     if (hipEventRecord(c->ev_pool[i], c->stream) != hipSuccess) return -1;
     c->ev_used += 2;
-    c->ev_cat.push_back(cat);
+    c->ev_cat.push_back(1u << cat | (cat2 < 0 ? 0u : 1u << cat2) | (cat3 < 0 ? 0u : 1u << cat3));
     return (int)(i / 2);
 }
 
 void tend(gks_ctx* c, int pair) {
     if (pair >= 0) (void)hipEventRecord(c->ev_pool[2 * pair + 1], c->stream);
+}
+
+// Tiles, work split and launches of the face passes.
+void face_layout(gks_ctx* c) {
+    const gks_config* cfg = &c->cfg;
+    const bool f64 = cfg->precision == GKS_FP64;
+    const int n[3] = {cfg->nx, cfg->ny, cfg->nz};
+    auto tiles = [&](int d, int rows) {
+        const int* ax = kAxes[d];
+        return ((n[ax[1]] + TILE1 - 1) / TILE1) * ((n[ax[2]] + rows - 1) / rows);
+    };
+    c->side_by_side = 0;
+    if (cfg->order == 2) {
+        const int slots = f64 ? face2_slots<double>() : face2_slots<float>();
+        for (int d = 0; d < 3; ++d) {
+            c->t2[d] = TILE2;
+            c->chunk[d] = face_chunk(n[kAxes[d][0]], tiles(d, TILE2), slots);
+            c->seg_len[d] = c->n_wg[d] = c->adj_chunk[d] = 0;
+        }
+        return;
+    }
+    // Each tile height (FP64: two, see FACE64_ROWS) in both launch schemes, by estimated time in ns: face steps
+    // of the longest workgroup times the step, and per launch its start and end.
+    const double cells = (double)n[0] * n[1] * n[2];
+    double best = -1.0;
+    for (int o = 0; o < (f64 ? 2 : 1); ++o) {
+        const int rows = f64 ? FACE64_ROWS[o] : TILE2;
+        const int slots = f64 ? face_slots<double>(rows) : face_slots<float>(rows);
+        const double step = f64 ? FACE64_STEP[o] : FACE32_STEP;
+        FaceDir dir[3];
+        for (int d = 0; d < 3; ++d) dir[d] = FaceDir{n[kAxes[d][0]], tiles(d, rows)};
+        for (int scheme = 0; scheme < 2; ++scheme) {
+            FaceSplit sp[3];
+            double t;
+            if (scheme == 0) {
+                t = step * (face_split(dir, 2, slots, sp) + face_split(dir + 2, 1, slots, sp + 2)) + 2 * FACE_LAUNCH;
+            } else {
+                t = step * face_split(dir, 3, slots, sp) + FACE_LAUNCH + COMBINE_LAUNCH +
+                    (f64 ? COMBINE_CELL64 : COMBINE_CELL32) * cells;
+            }
+            if (best < 0.0 || t < best) {
+                best = t;
+                c->side_by_side = scheme;
+                for (int d = 0; d < 3; ++d) {
+                    c->t2[d] = rows;
+                    c->chunk[d] = sp[d].chunk;
+                    c->seg_len[d] = sp[d].seg_len;
+                    c->n_wg[d] = (int)sp[d].n_wg;
+                }
+            }
+        }
+        // the adjoint's recompute pass: its own tiles, one workgroup per CU (its LDS), as the 8-row forward tile
+        if (f64 && rows == AdjTile::T2)
+            for (int d = 0; d < 3; ++d) c->adj_chunk[d] = face_chunk(n[kAxes[d][0]], tiles(d, AdjTile::T2), slots);
+    }
 }
 
 // FP32: zero the low-order parts of the compensated state (the state is then the field itself).
@@ -541,6 +604,33 @@ hipError_t clear_low_parts(gks_ctx* c) {
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// The face passes and the stage update of one stage.
+template <typename real>
+int stage_faces(gks_ctx* c, int stage, void* const src[4], const int cat[3]) {
+    FaceArgs<real> a[3];
+    for (int d = 0; d < 3; ++d) a[d] = face_args<real>(c, d, stage, src);
+    if (c->cfg.order == 2) {
+        for (int d = 0; d < 3; ++d) {
+            const int tp = tbeg(c, cat[d]);
+            HIPCHK(c, launch_face2<real>(a[d], stage, c->stream));
+            tend(c, tp);
+        }
+    } else if (c->side_by_side) {
+        const int tp = tbeg(c, cat[0], cat[1], cat[2]);
+        HIPCHK(c, launch_face_xyz<real>(a[0], a[1], a[2], stage, c->stream));
+        HIPCHK(c, launch_combine<real>(a[2], c->g, stage, c->stream));
+        tend(c, tp);
+    } else {
+        int tp = tbeg(c, cat[0], cat[1]);
+        HIPCHK(c, launch_face_xy<real>(a[0], a[1], stage, c->stream));
+        tend(c, tp);
+        tp = tbeg(c, cat[2]);
+        HIPCHK(c, launch_face_z<real>(a[2], stage, c->stream));
+        tend(c, tp);
+    }
+    return GKS_OK;
 }
 
 template <typename real>
@@ -571,12 +661,8 @@ int steps(gks_ctx* c, int nsteps) {
         HIPCHK(c, launch_dt(c->st, c->umax_part, umax_blocks(c->g), c->cfg.cfl, c->hmin, c->c, c->cfg.dt_fixed,
                             c->stream));
         tend(c, tp);
-        for (int d = 0; d < 3; ++d) {
-            tp = tbeg(c, cat1[d]);
-            HIPCHK(c, c->cfg.order == 2 ? launch_face2<real>(face_args<real>(c, d, 1, c->q), 1, c->stream)
-                                        : launch_face<real>(face_args<real>(c, d, 1, c->q), 1, c->stream));
-            tend(c, tp);
-        }
+        int rc = stage_faces<real>(c, 1, c->q, cat1);
+        if (rc) return rc;
         if (ck) {
             tp = tbeg(c, GKS_TIMER_OTHER);
             for (int v = 0; v < 4; ++v) HIPCHK(c, launch_copy_field(c->qs[v], ck + (4 + v) * fb, field_bytes, c->stream));
@@ -586,12 +672,8 @@ int steps(gks_ctx* c, int nsteps) {
         HIPCHK(c, launch_ghost_transpose<real>(field<real>(c->qs), field<real>(c->qt), c->g, c->cfg.bc, c->cfg.u_in,
                                                c->c, c->cfg.rho_ref, c->stream));
         tend(c, tp);
-        for (int d = 0; d < 3; ++d) {
-            tp = tbeg(c, cat2[d]);
-            HIPCHK(c, c->cfg.order == 2 ? launch_face2<real>(face_args<real>(c, d, 2, c->qs), 2, c->stream)
-                                        : launch_face<real>(face_args<real>(c, d, 2, c->qs), 2, c->stream));
-            tend(c, tp);
-        }
+        rc = stage_faces<real>(c, 2, c->qs, cat2);
+        if (rc) return rc;
         if (ck) {
             tp = tbeg(c, GKS_TIMER_OTHER);
             for (int v = 0; v < 4; ++v) HIPCHK(c, launch_copy_field(c->q[v], ck + (8 + v) * fb, field_bytes, c->stream));
@@ -726,37 +808,7 @@ int gks_init(const gks_config* cfg, gks_field q, gks_field q_stage, gks_field q_
     c->eps = c->cfg.weno_eps;
     c->diag_nblk = diag_blocks(c->g);
     c->flags = cfg->ma > 0.3 ? GKS_WARN_MACH : 0;
-    // tile heights a face launch can take: per direction the one whose plan costs least wins (FACE64_ROWS)
-    const bool f64 = cfg->precision == GKS_FP64;
-    const int nopt = cfg->order != 2 && f64 ? 2 : 1;
-    int rows[2] = {TILE2, TILE2}, slots[2];
-    for (int o = 0; o < nopt; ++o) {
-        if (nopt > 1) rows[o] = FACE64_ROWS[o];
-        slots[o] = cfg->order == 2 ? (f64 ? face2_slots<double>() : face2_slots<float>())
-                                   : (f64 ? face_slots<double>(rows[o]) : face_slots<float>(rows[o]));
-    }
-    for (int d = 0; d < 3; ++d) {
-        const int* ax = kAxes[d];
-        const int t1_tiles = (n[ax[1]] + TILE1 - 1) / TILE1;
-        long long best = -1;
-        for (int o = 0; o < nopt; ++o) {
-            const int tiles = t1_tiles * ((n[ax[2]] + rows[o] - 1) / rows[o]);
-            const int chunk = face_chunk(n[ax[0]], tiles, slots[o]);
-            int seg, wgs;
-            const long long cost =
-                face_plan(n[ax[0]], tiles, slots[o], chunk, &seg, &wgs) * (nopt > 1 ? FACE64_STEP[o] : 1);
-            if (best < 0 || cost < best) {
-                best = cost;
-                c->t2[d] = rows[o];
-                c->chunk[d] = chunk;
-                c->seg_len[d] = seg;
-                c->n_wg[d] = wgs;
-            }
-        }
-        // the adjoint's recompute pass: its own tiles, one workgroup per CU (its LDS), as the 8-row forward tile
-        const int adj_tiles = ((n[ax[1]] + TILE1 - 1) / TILE1) * ((n[ax[2]] + AdjTile::T2 - 1) / AdjTile::T2);
-        c->adj_chunk[d] = nopt > 1 ? face_chunk(n[ax[0]], adj_tiles, slots[1]) : 0;
-    }
+    face_layout(c);
     hipError_t e = cfg->precision == GKS_FP32 ? upload_metrics<float>(c, cfg) : upload_metrics<double>(c, cfg);
     if (e == hipSuccess) e = hipMemsetAsync(c->st, 0, sizeof(DevState), c->stream);
     if (e == hipSuccess) e = clear_low_parts(c);

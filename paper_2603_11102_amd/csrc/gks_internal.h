@@ -15,12 +15,17 @@ constexpr int FACE_THREADS = 512;        // 8 wave64 per workgroup
 
 // Tiles of the order-5 face kernels, TILE1 x T2 faces. FP32: 16 x 16 faces, 512 threads (two waves per
 // SIMD, up to 256 registers each), two lanes per face. FP64: four lanes per face, 16 x 12 faces on 768
-// threads or 16 x 8 on 512. A step of the 12-row tile takes 1.41 times a step of the 8-row one (6.25 against
-// 4.44 us, 192 x 96 x 96 channel) for 1.5 times the faces, so it wins where both fill the chip (channel step
-// 1.56 against 1.64 ms) and loses on small or badly divided planes (32^3: 119 against 98 us); face_plan's cost
-// decides per direction. 16 rows do not fit: 128 registers a thread spill (1.96 ms).
+// threads or 16 x 8 on 512. A step of the 12-row tile takes 1.30 times a step of the 8-row one for 1.5 times
+// the faces, so it wins where both fill the chip and loses on small or badly divided planes (us a step,
+// 12 rows / 8 rows: 192 x 96 x 96 channel 1496 / 1685, periodic cubes 128^3 1802 / 1921, 56^3 245 / 256,
+// 32^3 101 / 88). 16 rows do not fit: 128 registers a thread spill (192 x 96 x 96: 1690 to 1960).
 constexpr int FACE64_ROWS[2] = {12, 8};
-constexpr int FACE64_STEP[2] = {141, 100};  // relative time of a face step
+constexpr double FACE64_STEP[2] = {6000.0, 4600.0};  // ns a face step
+constexpr double FACE32_STEP = 4300.0;
+// ns: what a face launch costs beyond its face steps, a combine launch, and the latter's time per cell.
+// Measured on periodic cubes, us a step, two launches a stage against one and the combine: FP32 16^3 71 / 52,
+// 40^3 104 / 95, 56^3 161 / 161, 128^3 950 / 1121; FP64 16^3 71 / 53, 40^3 136 / 127, 128^3 1802 / 2029.
+constexpr double FACE_LAUNCH = 1000.0, COMBINE_LAUNCH = 3000.0, COMBINE_CELL32 = 0.039, COMBINE_CELL64 = 0.052;
 
 // Local index (the pass's variable order: density, normal momentum, t1, t2 momenta) of each global
 // variable (density, x, y, z momenta) for the x (MODE 3), y (MODE 0) and z (MODE 4) passes.
@@ -38,6 +43,10 @@ template <>
 struct LocalOrder<4> {
     static constexpr int v[4] = {0, 2, 3, 1};
 };
+template <>
+struct LocalOrder<5> : LocalOrder<4> {};  // the z pass that leaves its residual to combine_kernel
+
+__host__ __device__ inline int pad8(int n) { return (n + 7) / 8 * 8; }
 
 // Arguments of the per-direction face kernel. Arrays are in the face's LOCAL variable order
 // (rho', m_normal, m_t1, m_t2); the caller permutes the global pointers.
@@ -125,24 +134,42 @@ struct Field4 {
     real* v[4];
 };
 
-// host launchers (gks_stage.hip)
+// host launchers (gks_stage.hip: FP32 and the work split; gks_stage64.hip: FP64)
 template <typename real>
-hipError_t launch_face(const FaceArgs<real>& a, int stage, hipStream_t s);
-int face_chunk(int n_n, int tiles, int slots);
-// order-5 face launches: the work split (FaceArgs seg_len, n_wg) for chunks of `chunk` cells; returns its cost
-// in face steps
-long long face_plan(int n_n, int tiles, int slots, int chunk, int* seg_len, int* n_wg);
-// resident workgroups of the order-5 face kernel with tiles of t2 rows
+hipError_t launch_face_xy(const FaceArgs<real>& ax, const FaceArgs<real>& ay, int stage, hipStream_t s);
+template <typename real>
+hipError_t launch_face_z(const FaceArgs<real>& a, int stage, hipStream_t s);
+template <typename real>
+hipError_t launch_face_xyz(const FaceArgs<real>& ax, const FaceArgs<real>& ay, const FaceArgs<real>& az, int stage,
+                           hipStream_t s);
+// resident workgroups of the order-5 face kernels with tiles of t2 rows
 template <typename real>
 int face_slots(int t2);
-template <>
-hipError_t launch_face<float>(const FaceArgs<float>& a, int stage, hipStream_t s);  // gks_stage.hip
-template <>
-hipError_t launch_face<double>(const FaceArgs<double>& a, int stage, hipStream_t s);  // gks_stage64.hip
-template <>
-int face_slots<float>(int t2);
-template <>
-int face_slots<double>(int t2);
+#define GKS_FACE_DECL(real)                                                                                     \
+    template <>                                                                                                 \
+    hipError_t launch_face_xy<real>(const FaceArgs<real>& ax, const FaceArgs<real>& ay, int stage, hipStream_t s); \
+    template <>                                                                                                 \
+    hipError_t launch_face_z<real>(const FaceArgs<real>& a, int stage, hipStream_t s);                          \
+    template <>                                                                                                 \
+    hipError_t launch_face_xyz<real>(const FaceArgs<real>& ax, const FaceArgs<real>& ay, const FaceArgs<real>& az, \
+                                     int stage, hipStream_t s);                                                 \
+    template <>                                                                                                 \
+    int face_slots<real>(int t2);
+GKS_FACE_DECL(float)
+GKS_FACE_DECL(double)
+#undef GKS_FACE_DECL
+// chunk of the launches whose workgroups march aligned chunks (second-order pass, adjoint recompute)
+int face_chunk(int n_n, int tiles, int slots);
+// Work split of one order-5 launch over the directions that share it: n cells along the normal and tiles per
+// direction in, FaceArgs chunk, seg_len, n_wg out; returns the longest workgroup's face steps.
+struct FaceDir {
+    int n, tiles;
+};
+struct FaceSplit {
+    int chunk, seg_len;
+    long long n_wg;
+};
+int face_split(const FaceDir* dirs, int ndirs, int slots, FaceSplit* out);
 // second-order variant (gks_stage2.hip)
 template <typename real>
 hipError_t launch_face2(const FaceArgs<real>& a, int stage, hipStream_t s);
@@ -153,6 +180,10 @@ int face2_slots();
 template <typename real>
 hipError_t launch_ghost(Field4<real> f, const GridDesc& g, int axis, int bc_lo, int bc_hi, const double u_in[3],
                         double c, double rho_ref, hipStream_t s);
+// stage update of an order-5 stage whose z pass left its residual in the output fields (launch_face_xyz):
+// az: the z pass's arguments
+template <typename real>
+hipError_t launch_combine(const FaceArgs<real>& az, const GridDesc& g, int stage, hipStream_t s);
 template <typename real>
 hipError_t launch_umax(Field4<real> f, const GridDesc& g, double rho_ref, double* part, hipStream_t s);
 int umax_blocks(const GridDesc& g);

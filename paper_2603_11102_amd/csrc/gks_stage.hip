@@ -6,7 +6,7 @@
 // One workgroup owns a tile of 16 x 16 faces in the tangential plane (512 threads = 8 wave64) and marches
 // along the face normal through a chunk of faces (or through an equal share of the tile-major (tile, cell)
 // order, one march per tile the share meets, when the tiles do not divide the resident workgroup slots: see
-// face_plan):
+// face_split):
 //   * column phase: each of the 20 x 20 tangential columns (tile + 2-cell halo per side) keeps a
 //     5-cell window of the field in registers; per cell it evaluates the WENO-JS values at both of its
 //     faces with one set of smoothness indicators, the normal derivative D (cubic through four cells)
@@ -59,13 +59,33 @@ __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
     e = (a - (s - bb)) + (b - bb);
 }
 
+// LDS: two buffers, so that the phases of consecutive faces overlap; per variable the column values
+// [q^L, q^R, D, C][t2 row][t1 column] and the t1-phase results
+// [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. A wave of the t1 phase takes
+// one row of all four variables, 16 consecutive positions each; the variable blocks are padded to
+// start 16 words apart modulo 64, so its reads meet no bank twice, and the t1-phase results of the four
+// variables start 32 words apart modulo 64, the least the wave's 64-bit stores can share banks.
+struct FaceLds {
+    struct {
+        float a[4][EXT2][EXT1];
+        float pad[16];
+    } nrm[2][4];
+    struct {
+        float a[5][EXT2][TILE1][2];
+        float pad[32];
+    } t1[2][4];
+    float range[2][FACE_THREADS / 64];
+};
+
+// The marches of workgroup blk of the nblk (a multiple of 8) that take this direction.
 // MODE (the direction's role): 3 = x pass, writes its residual to the blocked arrays; 0 = y pass,
-// writes the main residual arrays; 4 = z pass, adds both and applies the S2O4 stage update.
+// writes the main residual arrays; 4 = z pass, adds both and applies the S2O4 stage update; 5 = z pass
+// beside the other two, leaves its residual where the stage update will stand (combine_kernel does it).
 // STR: the mesh is stretched and the spacings come from the per-axis arrays; otherwise the uniform
 // inverse spacings are kernel arguments (no memory access for them inside the march).
 template <typename real, int STAGE, int MODE, bool STR>
-__global__ void __launch_bounds__(FACE_THREADS) face_kernel(const FaceArgs<real> a) {
-    static_assert(MODE == 0 || MODE == 3 || MODE == 4, "face pass mode");
+__device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int blk, const int nblk, FaceLds& lds) {
+    static_assert(MODE == 0 || MODE == 3 || MODE == 4 || MODE == 5, "face pass mode");
     // TILE1 x T2 faces, EXT1 x X2 columns, NTH threads
     constexpr int T2 = TILE2, X2 = EXT2, NTH = FACE_THREADS;
     static_assert(EXT1 * X2 <= NTH && 2 * TILE1 * T2 == NTH, "one thread per column and per face line");
@@ -73,32 +93,17 @@ __global__ void __launch_bounds__(FACE_THREADS) face_kernel(const FaceArgs<real>
     using real2 = typename Vec2<real>::type;
     constexpr int LOC[4] = {LocalOrder<MODE>::v[0], LocalOrder<MODE>::v[1], LocalOrder<MODE>::v[2],
                             LocalOrder<MODE>::v[3]};
-    // LDS: per variable, the column values [q^L, q^R, D, C][t2 row][t1 column] and the t1-phase results
-    // [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. A wave of the t1 phase takes
-    // one row of all four variables, 16 consecutive positions each; the variable blocks are padded to
-    // start 16 words apart modulo 64, so its reads
-    // meet no bank twice, and the t1-phase results of the four variables start 32 words apart modulo 64,
-    // the least the wave's 64-bit stores can share banks.
     // PAIR_PREV: the stage-1 z pass, which sits at the register limit, keeps only its lane's two
     // variables of the previous face's fluxes (the other passes keep all four: fewer selects per step).
     constexpr bool PAIR_PREV = (MODE == 4 && STAGE == 1);
-    struct NrmV {
-        real a[4][X2][EXT1];
-        real pad[16];
-    };
-    struct T1V {
-        real a[5][X2][TILE1][2];
-        real pad[32];
-    };
-    // two LDS buffers, so that the phases of consecutive faces overlap
-    __shared__ NrmV s_nrm[2][4];
-    __shared__ T1V s_t1[2][4];
+    auto& s_nrm = lds.nrm;
+    auto& s_t1 = lds.t1;
 
     const int tid = threadIdx.x;
     // consecutive logical workgroups run on the same XCD (the hardware deals workgroups round-robin to
     // the 8 XCDs; the grid is padded to a multiple of 8), so neighbouring tiles share that XCD's L2 for
     // their halo columns
-    const int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+    const int b = (blk % 8) * (nblk / 8) + blk / 8;
     if (b >= a.n_wg) return;
     // this workgroup's cells as a range [lin, lin_end) of the tile-major (tile, cell) order
     const int tiles = a.tiles_t1 * a.tiles_t2;
@@ -162,7 +167,7 @@ __global__ void __launch_bounds__(FACE_THREADS) face_kernel(const FaceArgs<real>
         }
     }
     {
-        __shared__ float s_range[2][NTH / 64];
+        auto& s_range = lds.range;
         float lo = col_ld ? float(ring[1][0]) : 3.0e38f, up = col_ld ? float(ring[1][0]) : -3.0e38f;
 #pragma unroll
         for (int r = 1; r < 5; ++r) {
@@ -407,6 +412,13 @@ __global__ void __launch_bounds__(FACE_THREADS) face_kernel(const FaceArgs<real>
             } else if constexpr (MODE == 0) {
                 st2(a.r1, ridx, m, d1);
                 if (NEED_F0) st2(a.r0, ridx, m, d0);
+            } else if constexpr (MODE == 5) {
+                pick(hi, a.out_a[LOC[2]], a.out_a[LOC[0]])[pidx] = d1.x;
+                pick(hi, a.out_a[LOC[3]], a.out_a[LOC[1]])[pidx] = d1.y;
+                if (NEED_F0) {
+                    pick(hi, a.out_b[LOC[2]], a.out_b[LOC[0]])[pidx] = d0.x;
+                    pick(hi, a.out_b[LOC[3]], a.out_b[LOC[1]])[pidx] = d0.y;
+                }
             } else {
                 const real2 r1v = ep.r1, x1v = ep.x1, r0v = ep.r0, x0v = ep.x0;
                 const real L1[2] = {r1v.x + (d1.x + x1v.x), r1v.y + (d1.y + x1v.y)};
@@ -474,14 +486,43 @@ __global__ void __launch_bounds__(FACE_THREADS) face_kernel(const FaceArgs<real>
     }  // segments
 }
 
+// x and y passes in one launch: the workgroups of both directions share the chip, so a workgroup marches twice
+// as far as in a launch of its own and the start of a march (about 1.5 face steps) and the launch's end
+// are paid once.
+template <typename real, int STAGE, bool STR>
+__global__ void __launch_bounds__(FACE_THREADS) face_xy_kernel(const FaceArgs<real> ax, const FaceArgs<real> ay) {
+    __shared__ FaceLds lds;
+    const int nx = pad8(ax.n_wg), blk = blockIdx.x;
+    if (blk < nx) face_march<real, STAGE, 3, STR>(ax, blk, nx, lds);
+    else face_march<real, STAGE, 0, STR>(ay, blk - nx, pad8(ay.n_wg), lds);
+}
+
+// the z pass with the stage update
+template <typename real, int STAGE, bool STR>
+__global__ void __launch_bounds__(FACE_THREADS) face_z_kernel(const FaceArgs<real> a) {
+    __shared__ FaceLds lds;
+    face_march<real, STAGE, 4, STR>(a, blockIdx.x, pad8(a.n_wg), lds);
+}
+
+// all three directions in one launch, for grids that leave much of the chip idle in each (combine_kernel follows)
+template <typename real, int STAGE, bool STR>
+__global__ void __launch_bounds__(FACE_THREADS) face_xyz_kernel(const FaceArgs<real> ax, const FaceArgs<real> ay,
+                                                                const FaceArgs<real> az) {
+    __shared__ FaceLds lds;
+    const int nx = pad8(ax.n_wg), ny = pad8(ay.n_wg), blk = blockIdx.x;
+    if (blk < nx) face_march<real, STAGE, 3, STR>(ax, blk, nx, lds);
+    else if (blk < nx + ny) face_march<real, STAGE, 0, STR>(ay, blk - nx, ny, lds);
+    else face_march<real, STAGE, 5, STR>(az, blk - nx - ny, pad8(az.n_wg), lds);
+}
+
 template <>
 int face_slots<float>(int) {
-    // workgroups of the face kernel that the device holds at once
+    // workgroups of the face kernels that the device holds at once
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, face_kernel<float, 1, 4, false>, FACE_THREADS,
-                                                     0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, face_z_kernel<float, 1, false>, FACE_THREADS, 0) !=
+        hipSuccess)
         return 0;
     return cus * per_cu;
 }
@@ -505,61 +546,87 @@ int face_chunk(int n_n, int tiles, int slots) {
     return best_chunk;
 }
 
-long long face_plan(int n_n, int tiles, int slots, int chunk, int* seg_len, int* n_wg) {
-    // Worst workgroup of each split, in face steps (a march over L cells costs about L + 2), times the
-    // rounds of `slots` workgroups: aligned chunks of `chunk` cells, or equal runs of the tile-major
-    // (tile, cell) order, whose workgroups fill the slots when the tiles do not divide them but pay a
-    // second march where a run crosses into the next tile. The cheaper wins; ties go to the chunks.
+int face_split(const FaceDir* dirs, int ndirs, int slots, FaceSplit* out) {
+    // The least T, in face steps, at which the directions' workgroups of at most T steps each fit the `slots`
+    // that run at once (a march over L cells costs about L + 2). Per direction either aligned chunks of T - 2
+    // cells, or equal runs of the tile-major (tile, cell) order, which fill the slots when the tiles do not
+    // divide them but pay two steps more where a run crosses into the next tile; the fewer workgroups win.
+    // Counts are rounded up to a multiple of 8 per direction: workgroups go round-robin to the 8 XCDs, and a
+    // rest that piles up on the first ones gives those a second round (the 192 x 96 x 96 channel in one
+    // launch took 1.9 times as long).
     if (slots <= 0) slots = 512;
-    const long long nch = (n_n + chunk - 1) / chunk;
-    const long long wg_c = (long long)tiles * nch;
-    long long best = ((wg_c + slots - 1) / slots) * (chunk + 2);
-    *seg_len = 0;
-    *n_wg = (int)wg_c;
-    const long long total = (long long)tiles * n_n;
-    for (long long rounds = 1; rounds <= 8; ++rounds) {
-        const long long len = (total + rounds * slots - 1) / (rounds * slots);
-        const long long wgs = (total + len - 1) / len;
-        long long worst = 0;
-        for (long long w = 0; w < wgs; ++w) {
-            const long long c0 = w * len, c1 = std::min(c0 + len, total);
-            const long long segs = (c1 - 1) / n_n - c0 / n_n + 1;
-            worst = std::max(worst, (c1 - c0) + 2 * segs);
+    auto fewest = [&](const FaceDir& d, int T, FaceSplit* o) {
+        const long long total = (long long)d.tiles * d.n;
+        const int chunk = std::min(T - 2, d.n);
+        long long best = (long long)d.tiles * ((d.n + chunk - 1) / chunk);
+        o->seg_len = 0;
+        o->chunk = chunk;
+        for (int segs = 1; segs <= (T - 2) / d.n + 2; ++segs) {
+            const long long len = std::min((long long)T - 2 * segs, total);
+            if (len < 1) break;
+            const long long wgs = (total + len - 1) / len;
+            if (wgs >= best || wgs > slots) continue;
+            long long worst = 0;
+            for (long long w = 0; w < wgs; ++w) {
+                const long long c0 = w * len, c1 = std::min(c0 + len, total);
+                worst = std::max(worst, (c1 - c0) + 2 * ((c1 - 1) / d.n - c0 / d.n + 1));
+            }
+            if (worst > T) continue;
+            best = wgs;
+            o->seg_len = (int)len;
         }
-        const long long cost = ((wgs + slots - 1) / slots) * worst;
-        if (cost < best && wgs <= 0x7ffffff8LL) {
-            best = cost;
-            *seg_len = (int)len;
-            *n_wg = (int)wgs;
-        }
-        if (len == 1) break;
+        o->n_wg = best;
+        return best;
+    };
+    auto total_wgs = [&](int T, FaceSplit* o) {
+        long long n = 0;
+        for (int d = 0; d < ndirs; ++d) n += (fewest(dirs[d], T, o + d) + 7) / 8 * 8;
+        return n;
+    };
+    int lo = 3, hi = 3;
+    while (total_wgs(hi, out) > slots && hi < (1 << 29)) {
+        lo = hi + 1;
+        hi *= 2;
     }
-    return best;
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (total_wgs(mid, out) <= slots) hi = mid;
+        else lo = mid + 1;
+    }
+    total_wgs(hi, out);
+    return hi;
+}
+
+#define GKS_LAUNCH_STR(KERNEL, ST, BLOCKS, ...)                                                               \
+    do {                                                                                                      \
+        const dim3 grid((unsigned)(BLOCKS)), block(FACE_THREADS);                                             \
+        if (str) hipLaunchKernelGGL((KERNEL<float, ST, true>), grid, block, 0, s, __VA_ARGS__);               \
+        else hipLaunchKernelGGL((KERNEL<float, ST, false>), grid, block, 0, s, __VA_ARGS__);                  \
+        return hipGetLastError();                                                                             \
+    } while (0)
+
+template <>
+hipError_t launch_face_xy<float>(const FaceArgs<float>& ax, const FaceArgs<float>& ay, int stage, hipStream_t s) {
+    const bool str = ax.stretched != 0;
+    const long long blocks = (long long)pad8(ax.n_wg) + pad8(ay.n_wg);
+    if (stage == 1) GKS_LAUNCH_STR(face_xy_kernel, 1, blocks, ax, ay);
+    else GKS_LAUNCH_STR(face_xy_kernel, 2, blocks, ax, ay);
 }
 
 template <>
-hipError_t launch_face<float>(const FaceArgs<float>& a, int stage, hipStream_t s) {
-    const long long blocks = ((long long)a.n_wg + 7) / 8 * 8;
-    if (a.n_wg <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(FACE_THREADS);
-#define GKS_FACE_LAUNCH(ST, MD)                                                                     \
-    do {                                                                                            \
-        if (a.stretched) hipLaunchKernelGGL((face_kernel<float, ST, MD, true>), grid, block, 0, s, a);  \
-        else hipLaunchKernelGGL((face_kernel<float, ST, MD, false>), grid, block, 0, s, a);             \
-    } while (0)
-    if (stage == 1) {
-        if (a.mode == 0) GKS_FACE_LAUNCH(1, 0);
-        else if (a.mode == 3) GKS_FACE_LAUNCH(1, 3);
-        else if (a.mode == 4) GKS_FACE_LAUNCH(1, 4);
-        else return hipErrorInvalidValue;
-    } else {
-        if (a.mode == 0) GKS_FACE_LAUNCH(2, 0);
-        else if (a.mode == 3) GKS_FACE_LAUNCH(2, 3);
-        else if (a.mode == 4) GKS_FACE_LAUNCH(2, 4);
-        else return hipErrorInvalidValue;
-    }
-#undef GKS_FACE_LAUNCH
-    return hipGetLastError();
+hipError_t launch_face_z<float>(const FaceArgs<float>& a, int stage, hipStream_t s) {
+    const bool str = a.stretched != 0;
+    if (stage == 1) GKS_LAUNCH_STR(face_z_kernel, 1, pad8(a.n_wg), a);
+    else GKS_LAUNCH_STR(face_z_kernel, 2, pad8(a.n_wg), a);
+}
+
+template <>
+hipError_t launch_face_xyz<float>(const FaceArgs<float>& ax, const FaceArgs<float>& ay, const FaceArgs<float>& az,
+                                  int stage, hipStream_t s) {
+    const bool str = ax.stretched != 0;
+    const long long blocks = (long long)pad8(ax.n_wg) + pad8(ay.n_wg) + pad8(az.n_wg);
+    if (stage == 1) GKS_LAUNCH_STR(face_xyz_kernel, 1, blocks, ax, ay, az);
+    else GKS_LAUNCH_STR(face_xyz_kernel, 2, blocks, ax, ay, az);
 }
 
 }  // namespace gks

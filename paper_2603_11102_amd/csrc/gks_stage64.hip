@@ -3,7 +3,7 @@
 // (Section 2, Eqs. (semi), (finite), (x_example), (flux); the two-stage fourth-order combinations).
 //
 // One workgroup owns a tile of 16 x T2 faces in the tangential plane and marches along the normal over its
-// share of the tile-major (tile, cell) order (face_plan). FOUR lanes work on a face: lane bits 2 (h) and 3
+// share of the tile-major (tile, cell) order (face_split). FOUR lanes work on a face: lane bits 2 (h) and 3
 // (m). What bounds the kernel is FP64 vector issue and the dependent-instruction latency behind it, so it
 // needs several waves per SIMD, and the state of a whole face line (40 doubles of Gauss-point values, a
 // 28-double column window) does not fit their registers: with two lanes per face, one wave per SIMD, 28 % of
@@ -49,40 +49,46 @@ __device__ __forceinline__ T sel(bool c, T x, T y) {
 
 }  // namespace
 
+// LDS, per variable: column values [q^L, q^R, D, C][t2 row][t1 column] and t1-phase results
+// [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. Blocks are padded so that a
+// half wave's 64-bit reads meet no bank twice: the t1 phase reads 16 positions of two consecutive
+// variables (32 words apart modulo 64), the t2 phase 16 values of variables v and v + 2 (2 x 16 words).
+template <int X2>
+struct Face64Lds {
+    struct {
+        double a[4][X2][EXT1];
+        double pad[(16 - (4 * X2 * EXT1) % 32 + 32) % 32];
+    } nrm[4];
+    struct {
+        double a[5][X2][TILE1][2];
+        double pad[(8 - (5 * X2 * TILE1 * 2) % 32 + 32) % 32];
+    } t1[4];
+};
+
+// The marches of workgroup blk of the nblk (a multiple of 8) that take this direction.
 // MODE (the direction's role): 3 = x pass, writes its residual to the blocked arrays; 0 = y pass,
-// writes the main residual arrays; 4 = z pass, adds both and applies the S2O4 stage update.
+// writes the main residual arrays; 4 = z pass, adds both and applies the S2O4 stage update; 5 = z pass
+// beside the other two, leaves its residual where the stage update will stand (combine_kernel does it).
 // STR: the mesh is stretched and the spacings come from the per-axis arrays; otherwise the uniform
-// inverse spacings are kernel arguments.
-// T2: rows of the tile; a wave per row.
+// inverse spacings are kernel arguments. T2: rows of the tile; a wave per row.
 template <int T2, int STAGE, int MODE, bool STR>
-__global__ void __launch_bounds__(64 * T2) face64_kernel(const FaceArgs<double> a) {
-    static_assert(MODE == 0 || MODE == 3 || MODE == 4, "face pass mode");
+__device__ __forceinline__ void face64_march(const FaceArgs<double>& a, const int blk, const int nblk,
+                                             Face64Lds<T2 + 4>& lds) {
+    static_assert(MODE == 0 || MODE == 3 || MODE == 4 || MODE == 5, "face pass mode");
     constexpr int X2 = T2 + 4, NTH = 64 * T2;
     static_assert(TILE1 == 16 && NTH == 4 * TILE1 * T2 && 2 * EXT1 * X2 <= NTH,
                   "four lanes per face, a wave per t2 row, two threads per column");
     constexpr bool NEED_F0 = (STAGE == 1);
     constexpr int LOC[4] = {LocalOrder<MODE>::v[0], LocalOrder<MODE>::v[1], LocalOrder<MODE>::v[2],
                             LocalOrder<MODE>::v[3]};
-    // LDS, per variable: column values [q^L, q^R, D, C][t2 row][t1 column] and t1-phase results
-    // [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. Blocks are padded so that a
-    // half wave's 64-bit reads meet no bank twice: the t1 phase reads 16 positions of two consecutive
-    // variables (32 words apart modulo 64), the t2 phase 16 values of variables v and v + 2 (2 x 16 words).
-    struct NrmV {
-        double a[4][X2][EXT1];
-        double pad[(16 - (4 * X2 * EXT1) % 32 + 32) % 32];
-    };
-    struct T1V {
-        double a[5][X2][TILE1][2];
-        double pad[(8 - (5 * X2 * TILE1 * 2) % 32 + 32) % 32];
-    };
-    __shared__ NrmV s_nrm[4];
-    __shared__ T1V s_t1[4];
+    auto& s_nrm = lds.nrm;
+    auto& s_t1 = lds.t1;
 
     const int tid = threadIdx.x;
     // consecutive logical workgroups run on the same XCD (the hardware deals workgroups round-robin to
     // the 8 XCDs; the grid is padded to a multiple of 8), so neighbouring tiles share that XCD's L2 for
     // their halo columns
-    const int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+    const int b = (blk % 8) * (nblk / 8) + blk / 8;
     if (b >= a.n_wg) return;
     // this workgroup's cells as a range [lin, lin_end) of the tile-major (tile, cell) order
     const int tiles = a.tiles_t1 * a.tiles_t2;
@@ -225,7 +231,7 @@ __global__ void __launch_bounds__(64 * T2) face64_kernel(const FaceArgs<double> 
             double gp[2][2][5];  // [variable][Gauss n][q^L, q^R, d/dn, d/dt1, d/dt2]
 #pragma unroll
             for (int v = 0; v < 2; ++v) {
-                const T1V& t = s_t1[2 * hi + v];
+                const auto& t = s_t1[2 * hi + v];
 #pragma unroll
                 for (int q = 0; q < 5; ++q) {
                     double y[5];
@@ -285,6 +291,9 @@ __global__ void __launch_bounds__(64 * T2) face64_kernel(const FaceArgs<double> 
                 } else if constexpr (MODE == 0) {
                     a.r1[ridx] = d1;
                     if (NEED_F0) a.r0[ridx] = d0;
+                } else if constexpr (MODE == 5) {
+                    out_a[pidx] = d1;
+                    if (NEED_F0) out_b[pidx] = d0;
                 } else {
                     const double L1 = r1v + (d1 + x1v), L0 = r0v + (d0 + x0v);
                     if (NEED_F0) {
@@ -303,13 +312,38 @@ __global__ void __launch_bounds__(64 * T2) face64_kernel(const FaceArgs<double> 
     }
 }
 
+// the launches: see the FP32 kernels of the same names
+template <int T2, int STAGE, bool STR>
+__global__ void __launch_bounds__(64 * T2) face64_xy_kernel(const FaceArgs<double> ax, const FaceArgs<double> ay) {
+    __shared__ Face64Lds<T2 + 4> lds;
+    const int nx = pad8(ax.n_wg), blk = blockIdx.x;
+    if (blk < nx) face64_march<T2, STAGE, 3, STR>(ax, blk, nx, lds);
+    else face64_march<T2, STAGE, 0, STR>(ay, blk - nx, pad8(ay.n_wg), lds);
+}
+
+template <int T2, int STAGE, bool STR>
+__global__ void __launch_bounds__(64 * T2) face64_z_kernel(const FaceArgs<double> a) {
+    __shared__ Face64Lds<T2 + 4> lds;
+    face64_march<T2, STAGE, 4, STR>(a, blockIdx.x, pad8(a.n_wg), lds);
+}
+
+template <int T2, int STAGE, bool STR>
+__global__ void __launch_bounds__(64 * T2) face64_xyz_kernel(const FaceArgs<double> ax, const FaceArgs<double> ay,
+                                                             const FaceArgs<double> az) {
+    __shared__ Face64Lds<T2 + 4> lds;
+    const int nx = pad8(ax.n_wg), ny = pad8(ay.n_wg), blk = blockIdx.x;
+    if (blk < nx) face64_march<T2, STAGE, 3, STR>(ax, blk, nx, lds);
+    else if (blk < nx + ny) face64_march<T2, STAGE, 0, STR>(ay, blk - nx, ny, lds);
+    else face64_march<T2, STAGE, 5, STR>(az, blk - nx - ny, pad8(az.n_wg), lds);
+}
+
 template <int T2>
 int slots64() {
-    // workgroups of the face kernel that the device holds at once
+    // workgroups of the face kernels that the device holds at once
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, face64_kernel<T2, 1, 4, false>, 64 * T2, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, face64_z_kernel<T2, 1, false>, 64 * T2, 0) != hipSuccess)
         return 0;
     return cus * per_cu;
 }
@@ -319,36 +353,41 @@ int face_slots<double>(int t2) {
     return t2 == 12 ? slots64<12>() : slots64<8>();
 }
 
-template <int T2>
-hipError_t launch64(const FaceArgs<double>& a, int stage, hipStream_t s) {
-    const long long blocks = ((long long)a.n_wg + 7) / 8 * 8;
-    if (a.n_wg <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(64 * T2);
-#define GKS_FACE_LAUNCH(ST, MD)                                                                     \
-    do {                                                                                            \
-        if (a.stretched) hipLaunchKernelGGL((face64_kernel<T2, ST, MD, true>), grid, block, 0, s, a);  \
-        else hipLaunchKernelGGL((face64_kernel<T2, ST, MD, false>), grid, block, 0, s, a);             \
+#define GKS_LAUNCH_STR(KERNEL, T2, ST, BLOCKS, ...)                                                           \
+    do {                                                                                                      \
+        const dim3 grid((unsigned)(BLOCKS)), block(64 * T2);                                                  \
+        if (str) hipLaunchKernelGGL((KERNEL<T2, ST, true>), grid, block, 0, s, __VA_ARGS__);                  \
+        else hipLaunchKernelGGL((KERNEL<T2, ST, false>), grid, block, 0, s, __VA_ARGS__);                     \
+        return hipGetLastError();                                                                             \
     } while (0)
-    if (stage == 1) {
-        if (a.mode == 0) GKS_FACE_LAUNCH(1, 0);
-        else if (a.mode == 3) GKS_FACE_LAUNCH(1, 3);
-        else if (a.mode == 4) GKS_FACE_LAUNCH(1, 4);
-        else return hipErrorInvalidValue;
-    } else {
-        if (a.mode == 0) GKS_FACE_LAUNCH(2, 0);
-        else if (a.mode == 3) GKS_FACE_LAUNCH(2, 3);
-        else if (a.mode == 4) GKS_FACE_LAUNCH(2, 4);
-        else return hipErrorInvalidValue;
-    }
-#undef GKS_FACE_LAUNCH
-    return hipGetLastError();
+#define GKS_LAUNCH64(KERNEL, ROWS, BLOCKS, ...)                                                               \
+    do {                                                                                                      \
+        if (ROWS == 12 && stage == 1) GKS_LAUNCH_STR(KERNEL, 12, 1, BLOCKS, __VA_ARGS__);                     \
+        if (ROWS == 12) GKS_LAUNCH_STR(KERNEL, 12, 2, BLOCKS, __VA_ARGS__);                                   \
+        if (ROWS == 8 && stage == 1) GKS_LAUNCH_STR(KERNEL, 8, 1, BLOCKS, __VA_ARGS__);                       \
+        if (ROWS == 8) GKS_LAUNCH_STR(KERNEL, 8, 2, BLOCKS, __VA_ARGS__);                                     \
+        return hipErrorInvalidValue;                                                                          \
+    } while (0)
+
+template <>
+hipError_t launch_face_xy<double>(const FaceArgs<double>& ax, const FaceArgs<double>& ay, int stage, hipStream_t s) {
+    const bool str = ax.stretched != 0;
+    const long long blocks = (long long)pad8(ax.n_wg) + pad8(ay.n_wg);
+    GKS_LAUNCH64(face64_xy_kernel, ax.t2, blocks, ax, ay);
 }
 
 template <>
-hipError_t launch_face<double>(const FaceArgs<double>& a, int stage, hipStream_t s) {
-    if (a.t2 == 12) return launch64<12>(a, stage, s);
-    if (a.t2 == 8) return launch64<8>(a, stage, s);
-    return hipErrorInvalidValue;
+hipError_t launch_face_z<double>(const FaceArgs<double>& a, int stage, hipStream_t s) {
+    const bool str = a.stretched != 0;
+    GKS_LAUNCH64(face64_z_kernel, a.t2, pad8(a.n_wg), a);
+}
+
+template <>
+hipError_t launch_face_xyz<double>(const FaceArgs<double>& ax, const FaceArgs<double>& ay, const FaceArgs<double>& az,
+                                   int stage, hipStream_t s) {
+    const bool str = ax.stretched != 0;
+    const long long blocks = (long long)pad8(ax.n_wg) + pad8(ay.n_wg) + pad8(az.n_wg);
+    GKS_LAUNCH64(face64_xyz_kernel, ax.t2, blocks, ax, ay, az);
 }
 
 }  // namespace gks

@@ -37,3 +37,18 @@ def test_fp64_tile_heights_vs_oracle(case, grid):
     o, _ = run_oracle(cfg, 1)
     err = rel_errors(s.interior(), oracle_dev(o.Q, cfg.rho_ref))
     assert max(err) < 1e-12, err
+
+
+@pytest.mark.parametrize("precision,bar", [("fp64", 1e-12), ("fp32", 1e-5)])
+@pytest.mark.parametrize("grid", [
+    (3, 3, 3),      # one workgroup per direction, every cell within a stencil of two sides
+    (24, 20, 18),   # the three directions in one launch
+    (70, 66, 50),   # x and y passes in one launch, marches that cross tiles
+])
+def test_launch_schemes_vs_oracle(grid, precision, bar):
+    cfg = make_case("channel", grid=grid)
+    print_case("launch-scheme", grid=grid, precision=precision)
+    s, _ = run_gpu(cfg, precision, 2)
+    o, _ = run_oracle(cfg, 2)
+    err = rel_errors(s.interior(), oracle_dev(o.Q, cfg.rho_ref))
+    assert max(err) < bar, err
