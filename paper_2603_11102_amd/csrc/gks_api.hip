@@ -361,6 +361,18 @@ int ghost_all(gks_ctx* c, void* const p[4]) {
     return GKS_OK;
 }
 
+template <typename real>
+FluxConst<real> flux_const(const gks_ctx* c) {
+    FluxConst<real> k;
+    k.lam = real(c->lam);
+    k.sl = real(std::sqrt(c->lam));
+    k.kk = real(1.0 / (2.0 * std::sqrt(M_PI * c->lam)));
+    k.c2 = real(1.0 / (2.0 * c->lam));
+    k.mu = real(c->cfg.mu);
+    k.rho_ref = real(c->cfg.rho_ref);
+    return k;
+}
+
 // Face-kernel arguments for direction d. stage 1: reads src, writes out_a = Q*, out_b = S and reads
 // q_c = Q^n in the epilogue; stage 2: reads src = Q*, writes out_a = Q^{n+1} from s_in = S.
 template <typename real>
@@ -427,12 +439,7 @@ FaceArgs<real> face_args_buf(gks_ctx* c, int d, int stage, void* const src[4], v
     a.ih1 = static_cast<const real*>(c->ihc[ax[1]]);
     a.ih2 = static_cast<const real*>(c->ihc[ax[2]]);
     a.eps = real(c->eps);
-    a.fc.lam = real(c->lam);
-    a.fc.sl = real(std::sqrt(c->lam));
-    a.fc.kk = real(1.0 / (2.0 * std::sqrt(M_PI * c->lam)));
-    a.fc.c2 = real(1.0 / (2.0 * c->lam));
-    a.fc.mu = real(c->cfg.mu);
-    a.fc.rho_ref = real(c->cfg.rho_ref);
+    a.fc = flux_const<real>(c);
     for (int j = 0; j < 3; ++j) a.g_global[j] = real(c->cfg.body_force[j]);
     a.dt_ptr = &c->st->dt;
     // x faces write their own arrays in the blocked layout [z][y/16][x][y%16] so that the x pass
@@ -488,12 +495,7 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, void* const src[4],
     a.ih1 = static_cast<const double*>(c->ihc[ax[1]]);
     a.ih2 = static_cast<const double*>(c->ihc[ax[2]]);
     a.eps = c->eps;
-    a.fc.lam = c->lam;
-    a.fc.sl = std::sqrt(c->lam);
-    a.fc.kk = 1.0 / (2.0 * std::sqrt(M_PI * c->lam));
-    a.fc.c2 = 1.0 / (2.0 * c->lam);
-    a.fc.mu = c->cfg.mu;
-    a.fc.rho_ref = c->cfg.rho_ref;
+    a.fc = flux_const<double>(c);
     a.exact = exact;
     return a;
 }
@@ -550,12 +552,8 @@ void face_layout(gks_ctx* c) {
     };
     c->side_by_side = 0;
     if (cfg->order == 2) {
-        const int slots = f64 ? face2_slots<double>() : face2_slots<float>();
-        for (int d = 0; d < 3; ++d) {
-            c->t2[d] = TILE2;
-            c->chunk[d] = face_chunk(n[kAxes[d][0]], tiles(d, TILE2), slots);
-            c->seg_len[d] = c->n_wg[d] = c->adj_chunk[d] = 0;
-        }
+        for (int d = 0; d < 3; ++d) c->t2[d] = c->chunk[d] = c->seg_len[d] = c->n_wg[d] = c->adj_chunk[d] = 0;
+        c->chunk[2] = stage2_chunk(n, f64);
         return;
     }
     // Each tile height (FP64: two, see FACE64_ROWS) in both launch schemes, by estimated time in ns: face steps
@@ -606,18 +604,58 @@ hipError_t clear_low_parts(gks_ctx* c) {
     return hipSuccess;
 }
 
+// Arguments of the second-order variant's stage.
+template <typename real>
+Face2Args<real> face2_args(gks_ctx* c, int stage, void* const src[4]) {
+    Face2Args<real> a;
+    std::memset(&a, 0, sizeof(a));
+    for (int v = 0; v < 4; ++v) {
+        a.q[v] = static_cast<const real*>(src[v]);
+        a.q_c[v] = static_cast<const real*>(c->q[v]);
+        a.s_in[v] = static_cast<const real*>(c->qa[v]);
+        a.out_a[v] = static_cast<real*>(stage == 1 ? c->qs[v] : c->q[v]);
+        a.out_b[v] = static_cast<real*>(c->qa[v]);
+    }
+    a.lo_in = static_cast<const real*>(stage == 1 ? c->lo_q : c->lo_qa);
+    a.lo_a = static_cast<real*>(stage == 1 ? c->lo_qs : c->lo_q);
+    a.lo_b = static_cast<real*>(c->lo_qa);
+    for (int d = 0; d < 3; ++d) {
+        a.n[d] = c->g.n[d];
+        a.st[d] = c->g.st[d];
+        a.inv_h[d] = real(1.0 / c->g.h[d]);
+        a.ihf[d] = static_cast<const real*>(c->ihf[d]);
+        a.ihc[d] = static_cast<const real*>(c->ihc[d]);
+        a.g_global[d] = real(c->cfg.body_force[d]);
+    }
+    a.pad0 = c->g.pad0;
+    a.chunk = c->chunk[2];
+    a.stretched = c->stretched;
+    a.fc = flux_const<real>(c);
+    a.dt_ptr = &c->st->dt;
+    return a;
+}
+
+// Ghost cells of a stage input and, for the high-order x pass, its [x][z][y] copy.
+template <typename real>
+hipError_t stage_ghosts(gks_ctx* c, void* const p[4]) {
+    if (c->cfg.order == 2)
+        return launch_ghost_shell<real>(field<real>(p), c->g, c->cfg.bc, c->cfg.u_in, c->c, c->cfg.rho_ref, c->stream);
+    return launch_ghost_transpose<real>(field<real>(p), field<real>(c->qt), c->g, c->cfg.bc, c->cfg.u_in, c->c,
+                                        c->cfg.rho_ref, c->stream);
+}
+
 // The face passes and the stage update of one stage.
 template <typename real>
 int stage_faces(gks_ctx* c, int stage, void* const src[4], const int cat[3]) {
+    if (c->cfg.order == 2) {
+        const int tp = tbeg(c, cat[0], cat[1], cat[2]);
+        HIPCHK(c, launch_stage2<real>(face2_args<real>(c, stage, src), stage, c->stream));
+        tend(c, tp);
+        return GKS_OK;
+    }
     FaceArgs<real> a[3];
     for (int d = 0; d < 3; ++d) a[d] = face_args<real>(c, d, stage, src);
-    if (c->cfg.order == 2) {
-        for (int d = 0; d < 3; ++d) {
-            const int tp = tbeg(c, cat[d]);
-            HIPCHK(c, launch_face2<real>(a[d], stage, c->stream));
-            tend(c, tp);
-        }
-    } else if (c->side_by_side) {
+    if (c->side_by_side) {
         const int tp = tbeg(c, cat[0], cat[1], cat[2]);
         HIPCHK(c, launch_face_xyz<real>(a[0], a[1], a[2], stage, c->stream));
         HIPCHK(c, launch_combine<real>(a[2], c->g, stage, c->stream));
@@ -653,8 +691,7 @@ int steps(gks_ctx* c, int nsteps) {
             c->ckpt_n++;
         }
         tp = tbeg(c, GKS_TIMER_GHOST);
-        HIPCHK(c, launch_ghost_transpose<real>(field<real>(c->q), field<real>(c->qt), c->g, c->cfg.bc, c->cfg.u_in,
-                                               c->c, c->cfg.rho_ref, c->stream));
+        HIPCHK(c, stage_ghosts<real>(c, c->q));
         tend(c, tp);
         tp = tbeg(c, GKS_TIMER_DT);
         if (c->cfg.cfl > 0) HIPCHK(c, launch_umax<real>(field<real>(c->q), c->g, c->cfg.rho_ref, c->umax_part, c->stream));
@@ -669,8 +706,7 @@ int steps(gks_ctx* c, int nsteps) {
             tend(c, tp);
         }
         tp = tbeg(c, GKS_TIMER_GHOST);
-        HIPCHK(c, launch_ghost_transpose<real>(field<real>(c->qs), field<real>(c->qt), c->g, c->cfg.bc, c->cfg.u_in,
-                                               c->c, c->cfg.rho_ref, c->stream));
+        HIPCHK(c, stage_ghosts<real>(c, c->qs));
         tend(c, tp);
         rc = stage_faces<real>(c, 2, c->qs, cat2);
         if (rc) return rc;

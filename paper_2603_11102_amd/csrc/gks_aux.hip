@@ -207,9 +207,7 @@ __global__ void __launch_bounds__(256) ghost_transpose_kernel(Field4<real> q, Fi
         }
 }
 
-template <typename real>
-hipError_t launch_ghost_transpose(Field4<real> q, Field4<real> qt, const GridDesc& gd, const int bc[6],
-                                  const double u_in[3], double c, double rho_ref, hipStream_t s) {
+GhostAll ghost_args(const GridDesc& gd, const int bc[6], const double u_in[3], double c, double rho_ref) {
     GhostAll G;
     for (int a = 0; a < 3; ++a) {
         G.n[a] = gd.n[a];
@@ -219,42 +217,65 @@ hipError_t launch_ghost_transpose(Field4<real> q, Field4<real> qt, const GridDes
     }
     G.c = c;
     G.rho_ref = rho_ref;
-    const int X = gd.n[0] + 6, Y = gd.n[1] + 6, Z = gd.n[2] + 6;
-    hipLaunchKernelGGL((ghost_transpose_kernel<real>), dim3(Z, (X + 31) / 32, (Y + 31) / 32), dim3(256), 0, s, q,
-                       qt, G);
+    return G;
+}
+
+// The ghost cells alone, one thread each, for passes that need no copy of the field: the six z planes, then
+// the y rows of the interior planes, then the x ends of the interior rows.
+template <typename real>
+__global__ void __launch_bounds__(256) ghost_shell_kernel(Field4<real> q, GhostAll G) {
+    const int X = G.n[0] + 6, Y = G.n[1] + 6;
+    const long long nz = 6LL * X * Y, ny = 6LL * X * G.n[2], nx = 6LL * G.n[1] * G.n[2];
+    long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    int x, y, z;  // cell, 0 .. n - 1 inside the domain
+    auto ghost = [](int s, int n) { return s < 3 ? s - 3 : n + s - 3; };
+    if (t < nz) {
+        x = (int)(t % X) - 3;
+        y = (int)(t / X % Y) - 3;
+        z = ghost((int)(t / ((long long)X * Y)), G.n[2]);
+    } else if ((t -= nz) < ny) {
+        x = (int)(t % X) - 3;
+        y = ghost((int)(t / X % 6), G.n[1]);
+        z = (int)(t / (6LL * X));
+    } else if ((t -= ny) < nx) {
+        x = ghost((int)(t % 6), G.n[0]);
+        y = (int)(t / 6 % G.n[1]);
+        z = (int)(t / (6LL * G.n[1]));
+    } else {
+        return;
+    }
+    int sd[3];
+    const int si = ghost_source(x, G.n[0], G.bc_lo[0], G.bc_hi[0], sd[0]);
+    const int sj = ghost_source(y, G.n[1], G.bc_lo[1], G.bc_hi[1], sd[1]);
+    const int sk = ghost_source(z, G.n[2], G.bc_lo[2], G.bc_hi[2], sd[2]);
+    const long long src = ((long long)(sk + 3) * Y + (sj + 3)) * X + (si + 3);
+    real v[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v[w] = q.v[w][src];
+    for (int a = 0; a < 3; ++a)
+        if (sd[a] >= 0) ghost_transform(v, a, sd[a], sd[a] == 0 ? G.bc_lo[a] : G.bc_hi[a], G);
+    const long long dst = ((long long)(z + 3) * Y + (y + 3)) * X + (x + 3);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) q.v[w][dst] = v[w];
+}
+
+template <typename real>
+hipError_t launch_ghost_shell(Field4<real> q, const GridDesc& gd, const int bc[6], const double u_in[3], double c,
+                              double rho_ref, hipStream_t s) {
+    const GhostAll G = ghost_args(gd, bc, u_in, c, rho_ref);
+    const long long X = gd.n[0] + 6, Y = gd.n[1] + 6;
+    const long long total = 6 * (X * Y + X * gd.n[2] + (long long)gd.n[1] * gd.n[2]);
+    hipLaunchKernelGGL((ghost_shell_kernel<real>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, q, G);
     return hipGetLastError();
 }
 
-// Copy of a padded field in the layout [x][z][y] (y fastest), read by the x-direction face pass so that
-// its column loads are contiguous along y. One 32 x 32 (x, y) tile of one z-plane per workgroup.
 template <typename real>
-__global__ void __launch_bounds__(256) transpose_xy_kernel(Field4<real> in, Field4<real> out, int X, int Y, int Z) {
-    __shared__ real t[4][32][33];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int x0 = blockIdx.x * 32, y0 = blockIdx.y * 32, z = blockIdx.z;
-    // all 16 loads of a thread are issued before the single barrier
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int r = ty; r < 32; r += 8) {
-            const int x = x0 + tx, y = y0 + r;
-            if (x < X && y < Y) t[v][r][tx] = in.v[v][((long long)z * Y + y) * X + x];
-        }
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int r = ty; r < 32; r += 8) {
-            const int y = y0 + tx, x = x0 + r;
-            if (x < X && y < Y) out.v[v][((long long)x * Z + z) * Y + y] = t[v][tx][r];
-        }
-}
-
-template <typename real>
-hipError_t launch_transpose_xy(Field4<real> in, Field4<real> out, const GridDesc& g, hipStream_t s) {
-    const int X = g.n[0] + 6, Y = g.n[1] + 6, Z = g.n[2] + 6;
-    hipLaunchKernelGGL((transpose_xy_kernel<real>), dim3((X + 31) / 32, (Y + 31) / 32, Z), dim3(256), 0, s, in, out,
-                       X, Y, Z);
+hipError_t launch_ghost_transpose(Field4<real> q, Field4<real> qt, const GridDesc& gd, const int bc[6],
+                                  const double u_in[3], double c, double rho_ref, hipStream_t s) {
+    const GhostAll G = ghost_args(gd, bc, u_in, c, rho_ref);
+    const int X = gd.n[0] + 6, Y = gd.n[1] + 6, Z = gd.n[2] + 6;
+    hipLaunchKernelGGL((ghost_transpose_kernel<real>), dim3(Z, (X + 31) / 32, (Y + 31) / 32), dim3(256), 0, s, q,
+                       qt, G);
     return hipGetLastError();
 }
 
@@ -549,8 +570,8 @@ template hipError_t launch_ghost<float>(Field4<float>, const GridDesc&, int, int
 template hipError_t launch_ghost<double>(Field4<double>, const GridDesc&, int, int, int, const double*, double, double, hipStream_t);
 template hipError_t launch_ghost_transpose<float>(Field4<float>, Field4<float>, const GridDesc&, const int[6], const double[3], double, double, hipStream_t);
 template hipError_t launch_ghost_transpose<double>(Field4<double>, Field4<double>, const GridDesc&, const int[6], const double[3], double, double, hipStream_t);
-template hipError_t launch_transpose_xy<float>(Field4<float>, Field4<float>, const GridDesc&, hipStream_t);
-template hipError_t launch_transpose_xy<double>(Field4<double>, Field4<double>, const GridDesc&, hipStream_t);
+template hipError_t launch_ghost_shell<float>(Field4<float>, const GridDesc&, const int[6], const double[3], double, double, hipStream_t);
+template hipError_t launch_ghost_shell<double>(Field4<double>, const GridDesc&, const int[6], const double[3], double, double, hipStream_t);
 template hipError_t launch_combine<float>(const FaceArgs<float>&, const GridDesc&, int, hipStream_t);
 template hipError_t launch_combine<double>(const FaceArgs<double>&, const GridDesc&, int, hipStream_t);
 template hipError_t launch_umax<float>(Field4<float>, const GridDesc&, double, double*, hipStream_t);

@@ -95,6 +95,29 @@ struct FaceArgs {
                // 4: z pass (add both, S2O4 stage update)
 };
 
+// Arguments of the second-order stage kernel; arrays in the global variable order.
+template <typename real>
+struct Face2Args {
+    const real* q[4];     // stage input (padded)
+    const real* q_c[4];   // stage 1: Q^n at the cell
+    const real* s_in[4];  // stage 2: S
+    real* out_a[4];       // stage 1 -> Q*, stage 2 -> Q^{n+1} (padded)
+    real* out_b[4];       // stage 1 -> S
+    const real* lo_in;    // FP32 compensated state, as in FaceArgs
+    real* lo_a;
+    real* lo_b;
+    int n[3];
+    int chunk, tiles_x, tiles_y;
+    long long st[3], pad0;
+    real inv_h[3];
+    int stretched;        // inverse spacings per axis (faces, widths) of a stretched mesh
+    const real* ihf[3];
+    const real* ihc[3];
+    FluxConst<real> fc;
+    real g_global[3];
+    const double* dt_ptr;
+};
+
 // Index of cell (x, y, z) in the blocked layout [z][y/16][x][y%16]: the x pass stores 16 consecutive y
 // per row (its lanes run along y), the z pass reads a 16 x 16 (x, y) tile as one contiguous block.
 __host__ __device__ inline long long rx_block_index(int x, int y, int z, int nx, int nyb) {
@@ -170,11 +193,10 @@ struct FaceSplit {
     long long n_wg;
 };
 int face_split(const FaceDir* dirs, int ndirs, int slots, FaceSplit* out);
-// second-order variant (gks_stage2.hip)
+// second-order variant (gks_stage2.hip): one launch per stage; stage2_chunk: planes per workgroup
 template <typename real>
-hipError_t launch_face2(const FaceArgs<real>& a, int stage, hipStream_t s);
-template <typename real>
-int face2_slots();
+hipError_t launch_stage2(Face2Args<real> a, int stage, hipStream_t s);
+int stage2_chunk(const int n[3], int f64);
 
 // host launchers (gks_aux.hip)
 template <typename real>
@@ -189,7 +211,8 @@ hipError_t launch_umax(Field4<real> f, const GridDesc& g, double rho_ref, double
 int umax_blocks(const GridDesc& g);
 hipError_t launch_zero_words(void* p, size_t bytes, hipStream_t s);
 template <typename real>
-hipError_t launch_transpose_xy(Field4<real> in, Field4<real> out, const GridDesc& g, hipStream_t s);
+hipError_t launch_ghost_shell(Field4<real> q, const GridDesc& gd, const int bc[6], const double u_in[3], double c,
+                              double rho_ref, hipStream_t s);
 template <typename real>
 hipError_t launch_ghost_transpose(Field4<real> q, Field4<real> qt, const GridDesc& gd, const int bc[6],
                                   const double u_in[3], double c, double rho_ref, hipStream_t s);

@@ -1,46 +1,33 @@
-// gks_stage2.hip -- face pass of the second-order GKS variant (the comparison scheme of the paper's
-// accuracy study, Section 4.3.3; its construction is defined by reference only): the gas-kinetic flux
-// and the S2O4 stages of the high-order scheme, with van Leer-limited linear face states, central-
-// difference gradients of the equilibrium state and one flux evaluation at the face centre.
+// gks_stage2.hip -- stages of the second-order GKS variant (the comparison scheme of the paper's accuracy
+// study, Section 4.3.3; its construction is defined by reference only): the gas-kinetic flux and the S2O4
+// stages of the high-order scheme, with van Leer-limited linear face states, central-difference gradients
+// of the equilibrium state and one flux evaluation at the face centre.
 //
-// Layout of one workgroup (384 threads): a 16 x 16 tile of faces marching along the normal. Threads
-// 0..323 own the 18 x 18 columns of the tile and its one-cell tangential halo: they keep the cells
-// f-2 .. f+1 of their column in registers (next cell prefetched one step ahead) and publish the face
-// states, the normal derivative and the face average C to LDS. Threads 0..255 own one face each: they
-// read their column's states and the four neighbouring face averages, evaluate the flux and the
-// divergence against the previous face of the column, and run the same epilogue roles as the
-// high-order face pass (x: blocked residual, y: main residual, z: S2O4 stage update). Two LDS buffers of
-// face states let the face phase of one face and the column phase of the next run between one pair of
-// barriers (one barrier per face).
+// One launch does a whole stage: a workgroup of 512 threads owns 32 x 16 cells of the (x, y) plane and
+// marches along z; each thread evaluates the three lower (x, y) and upper (z) faces of its cell. The scheme
+// reads 13 cells per face and does a few hundred operations on them, so it is bound by the passes over memory:
+// one pass per direction (with residual arrays between them and a transposed copy of the field for the x
+// pass) moved 590 MB per stage 1 of the 192 x 96 x 96 channel in FP32, where reading the state and writing
+// the stage's results is 200 MB. Four planes of the tile and its two-cell halo live in LDS (46 KB FP32, two
+// workgroups per CU), the next plane is loaded a step ahead, the x and y fluxes of a plane are exchanged through
+// LDS and the z flux is kept from one plane to the next. The faces at the tile's upper x and y ends are extra
+// evaluations of two waves.
+#include <type_traits>
+
 #include "gks_internal.h"
 
 namespace gks {
 
 namespace {
 
-constexpr int T2O_THREADS = 384;
-constexpr int T2O_EXT = TILE1 + 2;  // 18 columns per tangential direction
+constexpr int O2X = 32, O2Y = 16, O2_THREADS = O2X * O2Y;
+constexpr int O2H1 = O2X + 4, O2H2 = O2Y + 4;  // tile plus two cells per side
 
 template <typename real>
 __device__ __forceinline__ real van_leer(real dm, real dp) {
     const real prod = dm * dp;
-    return prod > real(0) ? real(2) * prod / (dm + dp) : real(0);
+    return prod > real(0) ? real(2) * prod * rcp<real>(dm + dp) : real(0);
 }
-
-template <int MODE>
-struct LocalOrder2;
-template <>
-struct LocalOrder2<3> {
-    static constexpr int v[4] = {0, 1, 2, 3};
-};
-template <>
-struct LocalOrder2<0> {
-    static constexpr int v[4] = {0, 2, 1, 3};
-};
-template <>
-struct LocalOrder2<4> {
-    static constexpr int v[4] = {0, 2, 3, 1};
-};
 
 template <typename real>
 struct Vec4;
@@ -53,301 +40,297 @@ struct Vec4<double> {
     using type = double4;
 };
 
-// the four variables of cell i in an array that holds them together
-template <typename real>
-__device__ __forceinline__ void ld4(const real* p, long long i, real out[4]) {
-    const typename Vec4<real>::type v = *reinterpret_cast<const typename Vec4<real>::type*>(p + 4 * i);
-    out[0] = v.x;
-    out[1] = v.y;
-    out[2] = v.z;
-    out[3] = v.w;
-}
-template <typename real>
-__device__ __forceinline__ void st4(real* p, long long i, const real in[4]) {
-    typename Vec4<real>::type v;
-    v.x = in[0];
-    v.y = in[1];
-    v.z = in[2];
-    v.w = in[3];
-    *reinterpret_cast<typename Vec4<real>::type*>(p + 4 * i) = v;
-}
-
 __device__ __forceinline__ void two_sum2(float a, float b, float& s, float& e) {
     s = a + b;
     const float bb = s - a;
     e = (a - (s - bb)) + (b - bb);
 }
 
+// global variable of each local one (density, normal, t1, t2 momenta) of the x, y, z faces
+constexpr int kLocal[3][4] = {{0, 1, 2, 3}, {0, 2, 1, 3}, {0, 3, 1, 2}};
+
 }  // namespace
 
-template <typename real, int STAGE, int MODE, bool STR>
-__global__ void __launch_bounds__(T2O_THREADS) face2_kernel(const FaceArgs<real> a) {
-    static_assert(MODE == 0 || MODE == 3 || MODE == 4, "face pass mode");
+template <typename real, int STAGE, bool STR>
+__global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_kernel(const Face2Args<real> a) {
+    using V4 = typename Vec4<real>::type;
     constexpr bool NEED_F0 = (STAGE == 1);
-    constexpr bool COMP = sizeof(real) == 4;  // FP32: compensated state in the z-pass stage update
-    constexpr int LOC[4] = {LocalOrder2<MODE>::v[0], LocalOrder2<MODE>::v[1], LocalOrder2<MODE>::v[2],
-                            LocalOrder2<MODE>::v[3]};
-    __shared__ real s_face[2][4][4][T2O_EXT][T2O_EXT];  // [buffer][variable][q^L, q^R, D, C][t2][t1]
+    constexpr bool COMP = sizeof(real) == 4;   // FP32: compensated state in the stage update
+    constexpr bool SHIFT = sizeof(real) == 4;  // FP32: momenta carried as deviations from workgroup constants
+    constexpr int NF = NEED_F0 ? 2 : 1;
+    __shared__ V4 s_q[4][O2H2][O2H1];       // planes, plane k in slot k mod 4
+    __shared__ V4 s_fx[NF][O2Y][O2X + 1];   // fluxes of the lower x faces (F1, then F0)
+    __shared__ V4 s_fy[NF][O2Y + 1][O2X];
 
     const int tid = threadIdx.x;
-    // consecutive logical workgroups run on the same XCD (the hardware deals workgroups round-robin to
-    // the 8 XCDs; the grid is padded to a multiple of 8), so neighbouring tiles share that XCD's L2 for
-    // their halo columns
+    // consecutive logical workgroups on the same XCD (grid padded to a multiple of 8)
     int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
-    if (b >= a.tiles_t1 * a.tiles_t2 * ((a.n_n + a.chunk - 1) / a.chunk)) return;
-    const int tile1 = b % a.tiles_t1;
-    b /= a.tiles_t1;
-    const int tile2 = b % a.tiles_t2;
-    b /= a.tiles_t2;
-    const int f0 = b * a.chunk;
-    const int f1 = min(f0 + a.chunk, a.n_n);  // residuals of cells [f0, f1); faces f0..f1
-    const int j0 = tile1 * TILE1, k0 = tile2 * TILE2;
+    const int nch = (a.n[2] + a.chunk - 1) / a.chunk;
+    if (b >= a.tiles_x * a.tiles_y * nch) return;
+    const int i0 = (b % a.tiles_x) * O2X;
+    b /= a.tiles_x;
+    const int j0 = (b % a.tiles_y) * O2Y;
+    const int k0 = (b / a.tiles_y) * a.chunk;
+    const int k1 = min(k0 + a.chunk, a.n[2]);
 
-    // column role: column (c1, c2) of the 18 x 18 grid, cells (j0 - 1 + c1, k0 - 1 + c2)
-    const bool col = tid < T2O_EXT * T2O_EXT;
-    const int c1 = tid % T2O_EXT, c2 = tid / T2O_EXT;
-    const int jc = j0 - 1 + c1, kc = k0 - 1 + c2;
-    const bool col_ld = col && (jc <= a.n_t1) && (kc <= a.n_t2);
-    const long long cbase = a.pad0 + (long long)jc * a.st_t1 + (long long)kc * a.st_t2;
-    // the in-loop column prefetch is done by every thread (threads without a column read a clamped one
-    // whose values are not used): a load on every path keeps the compiler from waiting for it, and for
-    // the step's stores, before the next step
-    const long long cbase_ld = a.pad0 + (long long)min(jc, a.n_t1 + NG - 1) * a.st_t1 +
-                               (long long)min(kc, a.n_t2 + NG - 1) * a.st_t2;
-    // face role
-    const bool face = tid < TILE1 * TILE2;
-    const int fj = tid % TILE1, fk = tid / TILE1;
-    const bool face_ok = face && (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
-
-    // FP32: the normal momentum is carried as its deviation from a workgroup constant (the midrange of
-    // its values in the tile's first window) and the mass flux is formed in deviation form, as in the
-    // high-order pass; the limiter and the differences commute with the shift
-    constexpr bool SHIFT = sizeof(real) == 4;
-    real cm = real(0);
-    real ring[4][4];  // cells f-2, f-1, f, f+1
-    real nxt[4];
+    const int ti = tid % O2X, tj = tid / O2X;
+    const int i = i0 + ti, j = j0 + tj;
+    const bool in = i < a.n[0] && j < a.n[1];
+    // cells of a plane that this thread stages: positions tid and tid + 512 of the 36 x 20 ones, clamped to the
+    // padded domain (what lies beyond reaches no cell of it)
+    const int pos[2] = {tid, min(tid + O2_THREADS, O2H1 * O2H2 - 1)};
+    long long src[2];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        nxt[v] = real(0);
+    for (int s = 0; s < 2; ++s)
+        src[s] = a.pad0 + min(i0 - 2 + pos[s] % O2H1, a.n[0] + 2) +
+                 (long long)min(j0 - 2 + pos[s] / O2H1, a.n[1] + 2) * a.st[1];
+    auto load_plane = [&](int k, real (&x)[2][4]) {
+        const long long off = (long long)min(k, a.n[2] + 2) * a.st[2];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ring[v][r] = real(0);
-    }
-    if (col_ld) {
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int r = 1; r < 4; ++r) {  // cells f0-2 .. f0; the step shifts in f0+1
-            const long long idx = cbase + (long long)(f0 - 3 + r) * a.st_n;
+            for (int v = 0; v < 4; ++v) x[s][v] = a.q[v][src[s] + off];
+    };
+    real cm[3] = {0, 0, 0};
+    auto store_plane = [&](int k, const real (&x)[2][4]) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) ring[v][r] = a.q[v][idx];
-        }
-        const long long idx = cbase + (long long)(f0 + 1) * a.st_n;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) nxt[v] = a.q[v][idx];
-    }
-    if constexpr (SHIFT) {
-        __shared__ float s_range[2][T2O_THREADS / 64];
-        float lo = col_ld ? float(ring[1][1]) : 3.0e38f, up = col_ld ? float(ring[1][1]) : -3.0e38f;
-#pragma unroll
-        for (int r = 2; r < 4; ++r) {
-            lo = col_ld ? fminf(lo, float(ring[1][r])) : lo;
-            up = col_ld ? fmaxf(up, float(ring[1][r])) : up;
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = fminf(lo, __shfl_xor(lo, o));
-            up = fmaxf(up, __shfl_xor(up, o));
-        }
-        if ((tid & 63) == 0) {
-            s_range[0][tid >> 6] = lo;
-            s_range[1][tid >> 6] = up;
-        }
-        __syncthreads();
-        lo = s_range[0][0];
-        up = s_range[1][0];
-#pragma unroll
-        for (int w = 1; w < T2O_THREADS / 64; ++w) {
-            lo = fminf(lo, s_range[0][w]);
-            up = fmaxf(up, s_range[1][w]);
-        }
-        cm = lo <= up ? real(0.5f * (lo + up)) : real(0);
-#pragma unroll
-        for (int r = 1; r < 4; ++r) ring[1][r] -= cm;
-    }
-    const real dt = real(*a.dt_ptr);
-    real fprev0[4] = {0, 0, 0, 0}, fprev1[4] = {0, 0, 0, 0};
-    // tangential inverse widths of this thread's face line
-    const real ih1 = STR ? a.ih1[min(j0 + fj, a.n_t1 - 1)] : a.inv_h1;
-    const real ih2 = STR ? a.ih2[min(k0 + fk, a.n_t2 - 1)] : a.inv_h2;
-
-    // column phase of face f into LDS buffer buf
-    auto column_step = [&](int f, int buf) {
-        const real ihf_f = STR ? a.ihf[f] : a.inv_hn;  // inverse spacing at face f (normal derivative)
-        // ---- column phase: window cells f-2 .. f+1 (prefetch f+2)
-        if (col) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-#pragma unroll
-                for (int r = 0; r < 3; ++r) ring[v][r] = ring[v][r + 1];
-                // the shift is applied here, a step after the load, so that the prefetch stays in flight
-                ring[v][3] = (SHIFT && v == 1) ? nxt[v] - cm : nxt[v];
-            }
-        }
-        {
-            const long long idx = cbase_ld + (long long)min(f + 2, a.n_n + 2) * a.st_n;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) nxt[v] = a.q[v][idx];
-        }
-        if (col) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const real qm2 = ring[v][0], qm1 = ring[v][1], q0 = ring[v][2], qp1 = ring[v][3];
-                s_face[buf][v][0][c2][c1] = qm1 + real(0.5) * van_leer(qm1 - qm2, q0 - qm1);
-                s_face[buf][v][1][c2][c1] = q0 - real(0.5) * van_leer(q0 - qm1, qp1 - q0);
-                s_face[buf][v][2][c2][c1] = (q0 - qm1) * ihf_f;
-                s_face[buf][v][3][c2][c1] = real(0.5) * (qm1 + q0);
-            }
+        for (int s = 0; s < 2; ++s) {
+            V4 y;
+            y.x = x[s][0];
+            y.y = SHIFT ? x[s][1] - cm[0] : x[s][1];
+            y.z = SHIFT ? x[s][2] - cm[1] : x[s][2];
+            y.w = SHIFT ? x[s][3] - cm[2] : x[s][3];
+            (&s_q[k & 3][0][0])[pos[s]] = y;
         }
     };
-    // two LDS buffers, one barrier per face: the face phase of f reads buffer f mod 2 while the column
-    // phase of f + 1 fills the other
-    column_step(f0, 0);
+    // planes k0 - 2 .. k0 + 1 to LDS and k0 + 2 in registers, all loads issued together
+    real nxt[2][4], pre[4][2][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) load_plane(k0 - 2 + r, pre[r]);
+    load_plane(k0 + 2, nxt);
+    if constexpr (SHIFT) {
+        // the midrange of each momentum over the chunk's first plane of the tile: the constant part of a mass
+        // flux then cancels exactly between the two faces of a cell and FP32 rounding acts on the deviation only
+        __shared__ float s_range[6][O2_THREADS / 64];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            float lo = fminf(pre[2][0][1 + d], pre[2][1][1 + d]), up = fmaxf(pre[2][0][1 + d], pre[2][1][1 + d]);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                lo = fminf(lo, __shfl_xor(lo, o));
+                up = fmaxf(up, __shfl_xor(up, o));
+            }
+            if ((tid & 63) == 0) {
+                s_range[2 * d][tid >> 6] = lo;
+                s_range[2 * d + 1][tid >> 6] = up;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            float lo = s_range[2 * d][0], up = s_range[2 * d + 1][0];
+            for (int w = 1; w < O2_THREADS / 64; ++w) {
+                lo = fminf(lo, s_range[2 * d][w]);
+                up = fmaxf(up, s_range[2 * d + 1][w]);
+            }
+            cm[d] = 0.5f * (lo + up);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) store_plane(k0 - 2 + r, pre[r]);
+
+    // Flux of the face between cells -1 and 0 along axis D: at(n, t1, t2) is the cell at these offsets.
+    auto face_flux = [&](auto dir, auto at, real ihf, real ih1, real ih2, V4& F1, V4& F0) {
+        constexpr int D = decltype(dir)::value;
+        const V4 cm2 = at(-2, 0, 0), cm1 = at(-1, 0, 0), c0 = at(0, 0, 0), cp1 = at(1, 0, 0);
+        const V4 p1a = at(-1, 1, 0), p1b = at(0, 1, 0), m1a = at(-1, -1, 0), m1b = at(0, -1, 0);
+        const V4 p2a = at(-1, 0, 1), p2b = at(0, 0, 1), m2a = at(-1, 0, -1), m2b = at(0, 0, -1);
+        auto get = [](const V4& x, int v) { return v == 0 ? x.x : v == 1 ? x.y : v == 2 ? x.z : x.w; };
+        real qL[4], qR[4], g[3][4], f0[4] = {0, 0, 0, 0}, f1[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            const int v = kLocal[D][l];
+            const real qm2 = get(cm2, v), qm1 = get(cm1, v), q0 = get(c0, v), qp1 = get(cp1, v);
+            const real dm = q0 - qm1;
+            qL[l] = qm1 + real(0.5) * van_leer(qm1 - qm2, dm);
+            qR[l] = q0 - real(0.5) * van_leer(dm, qp1 - q0);
+            if (SHIFT && l > 1) {  // tangential momenta enter the flux whole
+                qL[l] += cm[v - 1];
+                qR[l] += cm[v - 1];
+            }
+            g[0][l] = dm * ihf;
+            g[1][l] = ((get(p1a, v) + get(p1b, v)) - (get(m1a, v) + get(m1b, v))) * (real(0.25) * ih1);
+            g[2][l] = ((get(p2a, v) + get(p2b, v)) - (get(m2a, v) + get(m2b, v))) * (real(0.25) * ih2);
+        }
+        gp_flux<real, NEED_F0, SHIFT>(qL, qR, g, a.fc, f0, f1, SHIFT ? cm[D] : real(0));
+        auto put = [](V4& x, int v, real y) {
+            if (v == 0) x.x = y;
+            else if (v == 1) x.y = y;
+            else if (v == 2) x.z = y;
+            else x.w = y;
+        };
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            put(F1, kLocal[D][l], f1[l]);
+            if (NEED_F0) put(F0, kLocal[D][l], f0[l]);
+        }
+    };
+
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ic = min(i, a.n[0] - 1), jc = min(j, a.n[1] - 1);
+    // inverse widths of this thread's cell and face spacings of its lower faces
+    const real ihcx = STR ? a.ihc[0][ic] : a.inv_h[0], ihcy = STR ? a.ihc[1][jc] : a.inv_h[1];
+    const real ihfx = STR ? a.ihf[0][min(i, a.n[0])] : a.inv_h[0], ihfy = STR ? a.ihf[1][min(j, a.n[1])] : a.inv_h[1];
+    // the same at the tile's upper faces: x of row tid (wave 1), y of column tid (wave 0)
+    const real ihfx_e = STR ? a.ihf[0][min(i0 + O2X, a.n[0])] : a.inv_h[0];
+    const real ihfy_e = STR ? a.ihf[1][min(j0 + O2Y, a.n[1])] : a.inv_h[1];
+    const int re = tid & 63;
+    const real ihcy_e = STR ? a.ihc[1][min(j0 + min(re, O2Y - 1), a.n[1] - 1)] : a.inv_h[1];
+    const real ihcx_e = STR ? a.ihc[0][min(i0 + min(re, O2X - 1), a.n[0] - 1)] : a.inv_h[0];
+    const real dt = real(*a.dt_ptr);
+    const long long pbase = a.pad0 + ic + (long long)jc * a.st[1];
+    const long long cbase = ic + (long long)a.n[0] * jc;
+    V4 zp1, zp0 = {};  // z fluxes of the face below
     __syncthreads();
-    for (int f = f0; f <= f1; ++f) {
-        const int buf = (f - f0) & 1;
-        // ---- face phase: flux at the face centre (weight 1)
-        real fa0[4] = {0, 0, 0, 0}, fa1[4] = {0, 0, 0, 0};
-        if (face) {
-            const int cj = fj + 1, ck = fk + 1;
-            real qL[4], qR[4], g[3][4];
+    // step k evaluates the x and y faces of plane k and the z face above it; the step before the chunk only
+    // the z face below its first plane
+#pragma unroll 1
+    for (int k = k0 - 1; k < k1; ++k) {
+        const bool first = k < k0;
+        const int sl[4] = {(k - 1) & 3, k & 3, (k + 1) & 3, (k + 2) & 3};
+        const real ihcz = STR ? a.ihc[2][max(k, 0)] : a.inv_h[2];
+        V4 X1, X0 = {}, Y1, Y0 = {};
+        // epilogue operands of cell (i, j, k), loaded ahead of the plane's arithmetic
+        const long long p = pbase + (long long)max(k, 0) * a.st[2];
+        const long long c = cbase + (long long)a.n[0] * a.n[1] * max(k, 0);
+        real qe[4];
+        V4 lo = {};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) qe[v] = NEED_F0 ? a.q_c[v][p] : a.s_in[v][p];
+        if (COMP) lo = *reinterpret_cast<const V4*>(a.lo_in + 4 * c);
+        if (!first) {
+            // x faces: every thread's lower one; wave 1 then the 16 faces at the tile's upper end
+#pragma unroll 1
+            for (int rep = 0; rep < (wave == 1 ? 2 : 1); ++rep) {
+                const int fi = rep ? O2X : ti, fj = rep ? min(re, O2Y - 1) : tj;
+                V4 F1, F0 = {};
+                face_flux(std::integral_constant<int, 0>{},
+                          [&](int n, int y, int z) { return s_q[sl[1 + z]][fj + 2 + y][fi + 2 + n]; },
+                          rep ? ihfx_e : ihfx, rep ? ihcy_e : ihcy, ihcz, F1, F0);
+                if (rep == 0) {
+                    X1 = F1;
+                    X0 = F0;
+                }
+                if (rep == 0 || re < O2Y) {
+                    s_fx[0][fj][fi] = F1;
+                    if (NEED_F0) s_fx[NF - 1][fj][fi] = F0;
+                }
+            }
+            // y faces: wave 0 then the 32 faces at the tile's upper end
+#pragma unroll 1
+            for (int rep = 0; rep < (wave == 0 ? 2 : 1); ++rep) {
+                const int fi = rep ? min(re, O2X - 1) : ti, fj = rep ? O2Y : tj;
+                V4 F1, F0 = {};
+                face_flux(std::integral_constant<int, 1>{},
+                          [&](int n, int x, int z) { return s_q[sl[1 + z]][fj + 2 + n][fi + 2 + x]; },
+                          rep ? ihfy_e : ihfy, rep ? ihcx_e : ihcx, ihcz, F1, F0);
+                if (rep == 0) {
+                    Y1 = F1;
+                    Y0 = F0;
+                }
+                if (rep == 0 || re < O2X) {
+                    s_fy[0][fj][fi] = F1;
+                    if (NEED_F0) s_fy[NF - 1][fj][fi] = F0;
+                }
+            }
+        }
+        V4 Z1, Z0 = {};
+        face_flux(std::integral_constant<int, 2>{},
+                  [&](int n, int x, int y) { return s_q[sl[2 + n]][tj + 2 + y][ti + 2 + x]; },
+                  STR ? a.ihf[2][k + 1] : a.inv_h[2], ihcx, ihcy, Z1, Z0);
+        __syncthreads();
+        // plane k - 1 was last read before the barrier: plane k + 3 takes its slot
+        store_plane(k + 3, nxt);
+        load_plane(k + 4, nxt);
+        if (!first && in) {
+            const V4 xr1 = s_fx[0][tj][ti + 1], yr1 = s_fy[0][tj + 1][ti];
+            V4 xr0 = {}, yr0 = {};
+            if (NEED_F0) {
+                xr0 = s_fx[NF - 1][tj][ti + 1];
+                yr0 = s_fy[NF - 1][tj + 1][ti];
+            }
+            auto res = [&](real xl, real xr, real yl, real yr, real zl, real zr) {
+                return (yl - yr) * ihcy + ((zl - zr) * ihcz + (xl - xr) * ihcx);
+            };
+            const real L1[4] = {res(X1.x, xr1.x, Y1.x, yr1.x, zp1.x, Z1.x), res(X1.y, xr1.y, Y1.y, yr1.y, zp1.y, Z1.y),
+                                res(X1.z, xr1.z, Y1.z, yr1.z, zp1.z, Z1.z), res(X1.w, xr1.w, Y1.w, yr1.w, zp1.w, Z1.w)};
+            const real L0[4] = {res(X0.x, xr0.x, Y0.x, yr0.x, zp0.x, Z0.x), res(X0.y, xr0.y, Y0.y, yr0.y, zp0.y, Z0.y),
+                                res(X0.z, xr0.z, Y0.z, yr0.z, zp0.z, Z0.z), res(X0.w, xr0.w, Y0.w, yr0.w, zp0.w, Z0.w)};
+            const real lov[4] = {lo.x, lo.y, lo.z, lo.w};
+            real la[4], lb[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                qL[v] = s_face[buf][v][0][ck][cj];
-                qR[v] = s_face[buf][v][1][ck][cj];
-                g[0][v] = s_face[buf][v][2][ck][cj];
-                g[1][v] = (s_face[buf][v][3][ck][cj + 1] - s_face[buf][v][3][ck][cj - 1]) * (real(0.5) * ih1);
-                g[2][v] = (s_face[buf][v][3][ck + 1][cj] - s_face[buf][v][3][ck - 1][cj]) * (real(0.5) * ih2);
-            }
-            gp_flux<real, NEED_F0, SHIFT>(qL, qR, g, a.fc, fa0, fa1, cm);
-        }
-        if (f + 1 <= f1) column_step(f + 1, buf ^ 1);
-        if (f > f0 && face_ok) {
-            const int cell = f - 1;
-            const long long ridx = (long long)cell * a.ist_n + (long long)(j0 + fj) * a.ist_t1 +
-                                   (long long)(k0 + fk) * a.ist_t2;
-            const long long pidx = a.pad0 + (long long)cell * a.st_n + (long long)(j0 + fj) * a.st_t1 +
-                                   (long long)(k0 + fk) * a.st_t2;
-            real d1[4], d0[4];  // global variable order
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const real ihc = STR ? a.ihc[cell] : a.inv_hn;
-                d1[g] = -(fa1[LOC[g]] - fprev1[LOC[g]]) * ihc;
-                d0[g] = NEED_F0 ? -(fa0[LOC[g]] - fprev0[LOC[g]]) * ihc : real(0);
-            }
-            if constexpr (MODE == 3) {
-                const long long xidx = rx_block_index(cell, j0 + fj, k0 + fk, a.rx_nx, a.rx_nyb);
-                st4(a.rx1, xidx, d1);
-                if (NEED_F0) st4(a.rx0, xidx, d0);
-            } else if constexpr (MODE == 0) {
-                st4(a.r1, ridx, d1);
-                if (NEED_F0) st4(a.r0, ridx, d0);
-            } else {
-                const long long xidx = rx_block_index(j0 + fj, k0 + fk, cell, a.rx_nx, a.rx_nyb);
-                real r1v[4], x1v[4], r0v[4] = {0, 0, 0, 0}, x0v[4] = {0, 0, 0, 0}, lov[4] = {0, 0, 0, 0};
-                real loa[4], lob[4];
-                ld4(a.r1, ridx, r1v);
-                ld4(a.rx1, xidx, x1v);
-                if (NEED_F0) {
-                    ld4(a.r0, ridx, r0v);
-                    ld4(a.rx0, xidx, x0v);
-                }
-                if (COMP) ld4(a.lo_in, ridx, lov);
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int lv = LOC[g];
-                    const real L1 = r1v[g] + (d1[g] + x1v[g]);
-                    const real L0 = NEED_F0 ? r0v[g] + (d0[g] + x0v[g]) : real(0);
-                    if constexpr (COMP) {
-                        const real lo = lov[g];
-                        float sh, sl;
-                        if (NEED_F0) {
-                            const real Q = a.q_c[lv][pidx];
-                            two_sum2(Q, lo + (real(0.5) * dt * L0 + real(0.125) * dt * dt * L1), sh, sl);
-                            a.out_a[lv][pidx] = sh;
-                            loa[g] = sl;
-                            two_sum2(Q, lo + (dt * L0 + (dt * dt * real(1.0 / 6.0)) * L1), sh, sl);
-                            a.out_b[lv][pidx] = sh;
-                            lob[g] = sl;
-                        } else {
-                            const real add = (dt * dt * real(1.0 / 3.0)) * L1 + (g > 0 ? dt * a.g_global[g - 1] : real(0));
-                            two_sum2(a.s_in[lv][pidx], lo + add, sh, sl);
-                            a.out_a[lv][pidx] = sh;
-                            loa[g] = sl;
-                        }
-                    } else {
-                        if (NEED_F0) {
-                            const real Q = a.q_c[lv][pidx];
-                            a.out_a[lv][pidx] = Q + real(0.5) * dt * L0 + real(0.125) * dt * dt * L1;
-                            a.out_b[lv][pidx] = Q + dt * L0 + (dt * dt * real(1.0 / 6.0)) * L1;
-                        } else {
-                            const real add = (dt * dt * real(1.0 / 3.0)) * L1 + (g > 0 ? dt * a.g_global[g - 1] : real(0));
-                            a.out_a[lv][pidx] = a.s_in[lv][pidx] + add;
-                        }
-                    }
-                }
+                const real add = NEED_F0 ? real(0.5) * dt * L0[v] + real(0.125) * dt * dt * L1[v]
+                                         : (dt * dt * real(1.0 / 3.0)) * L1[v] + (v > 0 ? dt * a.g_global[v > 0 ? v - 1 : 0] : real(0));
+                const real add2 = NEED_F0 ? dt * L0[v] + (dt * dt * real(1.0 / 6.0)) * L1[v] : real(0);
                 if constexpr (COMP) {
-                    st4(a.lo_a, ridx, loa);
-                    if (NEED_F0) st4(a.lo_b, ridx, lob);
+                    float sh, sl_;
+                    two_sum2(qe[v], lov[v] + add, sh, sl_);
+                    a.out_a[v][p] = sh;
+                    la[v] = sl_;
+                    if (NEED_F0) {
+                        two_sum2(qe[v], lov[v] + add2, sh, sl_);
+                        a.out_b[v][p] = sh;
+                        lb[v] = sl_;
+                    }
+                } else {
+                    a.out_a[v][p] = qe[v] + add;
+                    if (NEED_F0) a.out_b[v][p] = qe[v] + add2;
                 }
             }
+            if constexpr (COMP) {
+                *reinterpret_cast<V4*>(a.lo_a + 4 * c) = V4{la[0], la[1], la[2], la[3]};
+                if (NEED_F0) *reinterpret_cast<V4*>(a.lo_b + 4 * c) = V4{lb[0], lb[1], lb[2], lb[3]};
+            }
         }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            fprev1[v] = fa1[v];
-            if (NEED_F0) fprev0[v] = fa0[v];
-        }
+        zp1 = Z1;
+        zp0 = Z0;
         __syncthreads();
     }
 }
 
-template <typename real>
-int face2_slots() {
+int stage2_chunk(const int n[3], int f64) {
+    // planes per workgroup: rounds of the resident workgroups times (planes + the start of a march)
     int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, face2_kernel<real, 1, 4, false>, T2O_THREADS, 0) !=
-        hipSuccess)
-        return 0;
-    return cus * per_cu;
+    int slots = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) {
+        const hipError_t e =
+            f64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage2_kernel<double, 1, false>, O2_THREADS, 0)
+                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage2_kernel<float, 1, false>, O2_THREADS, 0);
+        if (e == hipSuccess) slots = cus * per_cu;
+    }
+    return face_chunk(n[2], ((n[0] + O2X - 1) / O2X) * ((n[1] + O2Y - 1) / O2Y), slots);
 }
 
 template <typename real>
-hipError_t launch_face2(const FaceArgs<real>& a, int stage, hipStream_t s) {
-    const int nchunks = (a.n_n + a.chunk - 1) / a.chunk;
-    const long long blocks = ((long long)a.tiles_t1 * a.tiles_t2 * nchunks + 7) / 8 * 8;
+hipError_t launch_stage2(Face2Args<real> a, int stage, hipStream_t s) {
+    a.tiles_x = (a.n[0] + O2X - 1) / O2X;
+    a.tiles_y = (a.n[1] + O2Y - 1) / O2Y;
+    const long long blocks = ((long long)a.tiles_x * a.tiles_y * ((a.n[2] + a.chunk - 1) / a.chunk) + 7) / 8 * 8;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(T2O_THREADS);
-#define GKS_FACE2_LAUNCH(ST, MD)                                                                     \
-    do {                                                                                             \
-        if (a.stretched) hipLaunchKernelGGL((face2_kernel<real, ST, MD, true>), grid, block, 0, s, a);  \
-        else hipLaunchKernelGGL((face2_kernel<real, ST, MD, false>), grid, block, 0, s, a);             \
-    } while (0)
+    const dim3 grid((unsigned)blocks), block(O2_THREADS);
     if (stage == 1) {
-        if (a.mode == 0) GKS_FACE2_LAUNCH(1, 0);
-        else if (a.mode == 3) GKS_FACE2_LAUNCH(1, 3);
-        else if (a.mode == 4) GKS_FACE2_LAUNCH(1, 4);
-        else return hipErrorInvalidValue;
+        if (a.stretched) hipLaunchKernelGGL((stage2_kernel<real, 1, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((stage2_kernel<real, 1, false>), grid, block, 0, s, a);
     } else {
-        if (a.mode == 0) GKS_FACE2_LAUNCH(2, 0);
-        else if (a.mode == 3) GKS_FACE2_LAUNCH(2, 3);
-        else if (a.mode == 4) GKS_FACE2_LAUNCH(2, 4);
-        else return hipErrorInvalidValue;
+        if (a.stretched) hipLaunchKernelGGL((stage2_kernel<real, 2, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((stage2_kernel<real, 2, false>), grid, block, 0, s, a);
     }
-#undef GKS_FACE2_LAUNCH
     return hipGetLastError();
 }
 
-template hipError_t launch_face2<float>(const FaceArgs<float>&, int, hipStream_t);
-template hipError_t launch_face2<double>(const FaceArgs<double>&, int, hipStream_t);
-template int face2_slots<float>();
-template int face2_slots<double>();
+template hipError_t launch_stage2<float>(Face2Args<float>, int, hipStream_t);
+template hipError_t launch_stage2<double>(Face2Args<double>, int, hipStream_t);
 
 }  // namespace gks

@@ -52,3 +52,19 @@ def test_launch_schemes_vs_oracle(grid, precision, bar):
     o, _ = run_oracle(cfg, 2)
     err = rel_errors(s.interior(), oracle_dev(o.Q, cfg.rho_ref))
     assert max(err) < bar, err
+
+
+@pytest.mark.parametrize("precision,bar", [("fp64", 1e-12), ("fp32", 1e-5)])
+@pytest.mark.parametrize("case,grid", [
+    ("channel", (3, 3, 3)),       # fewer cells than the stencil reaches
+    ("tgv", (33, 17, 9)),         # one cell past the 32 x 16 tile in x and y
+    ("channel", (64, 32, 21)),    # whole tiles, walls at tile ends, several marches along z
+    ("alm", (36, 18, 18)),        # inflow, outflow and slip ghost cells
+])
+def test_order2_stage_vs_oracle(case, grid, precision, bar):
+    cfg = make_case(case, grid=grid).with_(order=2, rotor=None)
+    print_case("order2-stage", case=case, grid=grid, precision=precision)
+    s, _ = run_gpu(cfg, precision, 2)
+    o, _ = run_oracle(cfg, 2)
+    err = rel_errors(s.interior(), oracle_dev(o.Q, cfg.rho_ref))
+    assert max(err) < bar, err
