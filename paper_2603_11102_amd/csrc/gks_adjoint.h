@@ -2,19 +2,15 @@
 //
 // The reverse sweep linearises the step exactly; the WENO nonlinear weights are either held at their
 // forward values (frozen, the default) or differentiated too (exact). Per face direction and stage
-// operator the transpose is computed in gather form, without atomics, in four passes over buffers in
-// the adjoint workspace:
-//   A  recompute the forward face pipeline, store the inputs of the tangential WENO evaluations (the
-//      normal face values q^L, q^R and the t1 line values q^L_m, q^R_m) and the adjoints of the
-//      Gauss-point inputs (q^L, q^R, dQ/dn, dQ/dt1, dQ/dt2) from the flux seeds;
-//   B  transpose of the t2 sweep (gather over the five faces whose stencils hold a t1 line value),
-//   C  then, row by row in the same kernel with the t1 line adjoints in LDS, transpose of the t1 sweep
-//      (gather over five positions) and of C = (q^L + q^R)/2;
-//   D  transpose of the normal reconstruction into the padded cell adjoint;
-// B, C and D rebuild the coefficients of the WENO evaluations they transpose (frozen: the weights;
-// exact: the Jacobian row) from those stored inputs, or from the field for the normal evaluations, with
-// the recompute's own routine on the same values, so the coefficients are bitwise the recompute's;
-// then the transpose of the ghost-cell fill folds ghost adjoints into interior cells.
+// operator the transpose is computed without atomics, every sum in a fixed order, in two passes:
+//   A  tile by tile: the forward face pipeline, the reverse of the flux at the Gauss points from the flux
+//      seeds, the transposes of the t2 and t1 sweeps and of C = (q^L + q^R)/2, down to the adjoints of the
+//      normal face values (q^L, q^R, D) at the tile's columns;
+//   D  transpose of the normal reconstruction into the padded cell adjoint, adding the tiles' shares of a
+//      column.
+// Both rebuild the coefficients of the WENO evaluations they transpose (frozen: the weights; exact: the
+// Jacobian row) from the values the evaluations read; then the transpose of the ghost-cell fill folds ghost
+// adjoints into interior cells.
 #pragma once
 
 #include <stddef.h>
@@ -24,26 +20,23 @@
 
 namespace gks {
 
-// Tile of the recompute pass: 16 x 8 faces, 256 threads (one per column and per face line), one wave per SIMD.
+// Tile of pass A: 16 x 8 faces, four lanes per face, one workgroup per CU (its LDS: 162 KB), two waves per SIMD.
 struct AdjTile {
-    static constexpr int T2 = 8, THREADS = 256;
+    static constexpr int T2 = 8, THREADS = 64 * T2;
 };
 
 struct AdjFaceArgs {
     const double* q[4];     // field in LOCAL variable order (padded)
     const double* mu0[4];   // seed of L (interior, local order), stage 1 only
     const double* mu1[4];   // seed of L_t
-    double* gpbar;          // [80][nface]
-    double* t1v;            // [16][nt1pos]: t1 line values q^L_m, q^R_m, index (v * 2 + side) * 2 + m
-    double* fv;             // [8][nnpos]: normal face values q^L, q^R, index v * 2 + side
-    double* fabar;          // [12][nnpos]
+    double* fabar;          // [tile][face][12][12 t2 rows][20 t1 columns]: adjoints of q^L, q^R, D per variable
     double* acc[4];         // padded cell adjoint accumulator (LOCAL order)
     int n_n, n_t1, n_t2;
-    int chunk, tiles_t1, tiles_t2;
+    int tiles_t1, tiles_t2;
+    int chunk, seg_len, n_wg;  // work split over the n_n + 1 faces of each tile, as in FaceArgs
     long long st_n, st_t1, st_t2;
     long long ist_n, ist_t1, ist_t2;
     long long pad0;
-    long long nface, nt1pos, nnpos;
     // inverse spacings (device, the forward's arrays; 1/h on a uniform axis): normal face spacings
     // [n_n + 1], normal widths [n_n], t1 widths [n_t1], t2 widths [n_t2]
     const double* ihf;
@@ -66,9 +59,6 @@ struct AdjBuffers {
     double* qpre[4];     // padded: Q^{n+1,pre}
     double* mu0[4];      // interior seeds
     double* mu1[4];
-    double* gpbar;
-    double* t1v;
-    double* fv;
     double* fabar;
     double* pt;          // per-point scratch of the ALM adjoint: [16][n_act]
 };

@@ -16,16 +16,6 @@ namespace gks {
 
 namespace {
 
-__device__ __forceinline__ long long face_ix(const AdjFaceArgs& a, int f, int j, int k) {
-    return ((long long)f * a.n_t2 + k) * a.n_t1 + j;
-}
-__device__ __forceinline__ long long t1_ix(const AdjFaceArgs& a, int f, int j, int kx) {
-    return ((long long)f * (a.n_t2 + 4) + (kx + 2)) * a.n_t1 + j;
-}
-__device__ __forceinline__ long long n_ix(const AdjFaceArgs& a, int f, int jx, int kx) {
-    return ((long long)f * (a.n_t2 + 4) + (kx + 2)) * (a.n_t1 + 4) + (jx + 2);
-}
-
 // Coefficients of one WENO evaluation on `side` (stencil q, nonlinear weights w, value v): the frozen
 // weights w0 and w2 (w1 = 1 - w0 - w2 is rebuilt where they are used) or (EXACT) the Jacobian row.
 template <bool EXACT>
@@ -51,428 +41,374 @@ __device__ __forceinline__ double wcoef(int side, const double* c, int r) {
     }
 }
 
+// DPP moves inside a row of 16 lanes. dpp_sel: lanes of the four-lane banks in BANK take the value of lane + 4
+// (ROW_SHL4), lane - 4 (ROW_SHR4) or lane ^ 8 (ROW_ROR8), the others keep `old`. dpp_shift: the value of lane +
+// k (shl) or lane - k (shr), zero where that lies outside the row.
+constexpr int ROW_SHL4 = 0x104, ROW_SHR4 = 0x114, ROW_ROR8 = 0x128;
+constexpr int BANK_H0 = 0x5, BANK_H1 = 0xA, BANK_M0 = 0x3, BANK_M1 = 0xC;
+
+template <int CTRL, int BANK, bool ZERO>
+__device__ __forceinline__ double dpp_move(double old, double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned long long o = (unsigned long long)__double_as_longlong(old);
+    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)(o & 0xffffffffu), (int)(unsigned)(b & 0xffffffffu), CTRL,
+                                               0xF, BANK, ZERO);
+    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(o >> 32), (int)(unsigned)(b >> 32), CTRL, 0xF, BANK, ZERO);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+template <int CTRL, int BANK>
+__device__ __forceinline__ double dpp_sel(double old, double x) {
+    return dpp_move<CTRL, BANK, false>(old, x);
+}
+template <int K>
+__device__ __forceinline__ double dpp_shl(double x) {
+    return dpp_move<0x100 + K, 0xF, true>(0.0, x);
+}
+template <int K>
+__device__ __forceinline__ double dpp_shr(double x) {
+    return dpp_move<0x110 + K, 0xF, true>(0.0, x);
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
-// pass A: recompute the face pipeline of one direction (16 x 8 face tiles of 256 threads,
-// one wave per SIMD so that the FP64 state fits the unified register file), store the inputs of the
-// tangential WENO evaluations (normal face values, t1 line values) and, per face and Gauss point, the
-// adjoints of the Gauss-point inputs from the reverse of the flux (seeds Fbar(f) = (mu(f) - mu(f-1)) / h)
+// pass A: the tile's forward face pipeline and its transpose back to the normal face values.
+//
+// The kernel marches 16 x 8 face tiles with the lane layout of the forward FP64 kernel (four lanes per face:
+// lane bit 2 is h, bit 3 m; a wave per t2 row) and, per face, runs the reverse of the flux at each Gauss point,
+// undoes the exchange of the lane pair, and transposes the t2 sweep, the t1 sweep and C = (q^L + q^R)/2 inside the
+// tile. Only the adjoints of (q^L, q^R, D) at the tile's 20 x 12 columns leave it; columns of a tile's two-cell
+// halo are partial sums, which pass D adds over the (at most four) tiles that hold a column, in a fixed order.
+// Before, the Gauss-point adjoints (640 B a face) and the inputs of the tangential WENO evaluations (192 B) went
+// through memory between separate kernels, which ran at 2.6 to 3.7 TB/s and one wave per SIMD; this one writes
+// 180 B a face and is bound by FP64 issue and its barriers.
+//
+// t2 transpose: each lane forms, for its two variables, the WENO terms of its face for the five rows it reaches
+// (10 values) and keeps the linear terms' six inputs; these 16 values go to LDS (over the t1 results, then dead), and
+// a thread per (variable, position, line) and run of three rows gathers the seven faces that reach them.
+// t1 transpose: a lane per (variable, row, position) forms its terms for five columns; neighbouring positions are
+// neighbouring lanes, so the sums over positions are DPP shifts inside the row of 16, the four columns beyond its ends
+// landing in lanes 14, 15, 0 and 1.
 // ------------------------------------------------------------------------------------------------
-template <int STAGE>
+template <int STAGE, bool EXACT>
 __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFaceArgs a) {
     constexpr bool NEED_F0 = (STAGE == 1);
-    constexpr int T2 = AdjTile::T2, X2 = T2 + 4, NTH = AdjTile::THREADS;
-    static_assert(EXT1 * X2 <= NTH && 2 * TILE1 * T2 == NTH && TILE1 * X2 <= NTH, "thread roles");
-    __shared__ double s_nrm[4][X2][EXT1];
-    __shared__ double s_t1[5][X2][TILE1][2];
-    // Gauss-point states of each thread's face line: [(variable * 2 + Gauss point) * 5 + quantity][thread]
-    __shared__ double s_gp[40][NTH];
+    constexpr int T2 = AdjTile::T2, X2 = T2 + 4, NTH = AdjTile::THREADS, NW = EXACT ? 5 : 2;
+    static_assert(T2 == 8 && NTH == 64 * T2 && 2 * EXT1 * X2 <= NTH, "thread roles");
+    // padded as in the forward kernel: reads of a half wave meet no bank twice
+    __shared__ struct {
+        double a[4][X2][EXT1];
+        double pad[16];
+    } s_nrm[4];
+    // t1 results, then the faces' terms of the t2 transpose, then the t1-line adjoints
+    __shared__ double s_w[32 * NTH];
+    constexpr int T1S = 5 * X2 * 32 + 8;  // doubles per variable
+    auto t1_at = [&](int v, int q, int row, int c) -> double& { return s_w[v * T1S + (q * X2 + row) * 32 + c]; };
 
     const int tid = threadIdx.x;
-    // consecutive logical workgroups on the same XCD (grid padded to a multiple of 8), as in the forward
-    int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
-    if (b >= a.tiles_t1 * a.tiles_t2 * ((a.n_n + a.chunk - 1) / a.chunk)) return;
-    const int tile1 = b % a.tiles_t1;
-    b /= a.tiles_t1;
-    const int tile2 = b % a.tiles_t2;
-    b /= a.tiles_t2;
-    const int f0 = b * a.chunk;
-    const int f1 = min(f0 + a.chunk, a.n_n);
-    const int j0 = tile1 * TILE1, k0 = tile2 * T2;
+    const int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+    if (b >= a.n_wg) return;
+    const int nf = a.n_n + 1;
+    const int tiles = a.tiles_t1 * a.tiles_t2;
+    long long lin, lin_end;  // this workgroup's faces in the tile-major (tile, face) order
+    if (a.seg_len > 0) {
+        lin = (long long)b * a.seg_len;
+        lin_end = min(lin + a.seg_len, (long long)tiles * nf);
+    } else {
+        const int c0 = (b / tiles) * a.chunk;
+        lin = (long long)(b % tiles) * nf + c0;
+        lin_end = lin + min(a.chunk, nf - c0);
+    }
     const double eps = a.eps;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // column role: variables cv, cv + 1 of column (c1, c2)
+    const int half = __builtin_amdgcn_readfirstlane(tid / (NTH / 2));
+    const int cv = 2 * half, ct = tid % (NTH / 2);
+    const bool col = ct < EXT1 * X2;
+    const int c1 = ct % EXT1, c2 = ct / EXT1;
+    const double* const qcol[2] = {half ? a.q[2] : a.q[0], half ? a.q[3] : a.q[1]};
+    // face role
+    const int hi = (tid >> 2) & 1, m = (tid >> 3) & 1;
+    const int fj = (tid & 3) + 4 * ((tid >> 4) & 3), fk = wv;
+    const int own = 2 * hi + m;  // the variable whose seeds this lane loads
+    auto lane_field = [&](const double* const(&p)[4]) {
+        return hi ? (m ? p[3] : p[2]) : (m ? p[1] : p[0]);
+    };
+    const double* const mu1 = lane_field(a.mu1);
+    const double* const mu0 = lane_field(a.mu0);
+    // t1 role: position tj of variable tv
+    const int tj = tid & 15, tv = (tid >> 4) & 3;
 
-    const bool col = tid < EXT1 * X2;
-    const int c1 = tid % EXT1, c2 = tid / EXT1;
-    const int jc = j0 - 2 + c1, kc = k0 - 2 + c2;
-    const bool col_ld = col && (jc < a.n_t1 + NG) && (kc < a.n_t2 + NG);
-    const bool col_st = col && (jc < a.n_t1 + 2) && (kc < a.n_t2 + 2);
-    const long long cbase = a.pad0 + (long long)jc * a.st_t1 + (long long)kc * a.st_t2;
-    const bool t1r = tid < TILE1 * X2;
-    const int tj = tid % TILE1, tk = tid / TILE1;
-    const bool t1_st = t1r && (j0 + tj < a.n_t1) && (k0 - 2 + tk < a.n_t2 + 2);
-    const int m = tid & 1;
-    const int fj = (tid >> 1) % TILE1, fk = (tid >> 1) / TILE1;
-    const bool face_ok = (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
-
-    double ring[4][5];
-    double carry[4];
-    for (int v = 0; v < 4; ++v) {
-        carry[v] = 0.0;
-        for (int r = 0; r < 5; ++r) ring[v][r] = 0.0;
-    }
-    if (col_ld) {
-        for (int r = 0; r < 5; ++r) {
-            const long long idx = cbase + (long long)(f0 - 3 + r) * a.st_n;
-            for (int v = 0; v < 4; ++v) ring[v][r] = a.q[v][idx];
+    while (lin < lin_end) {
+        const int tile = (int)(lin / nf);
+        const int f0 = (int)(lin - (long long)tile * nf);
+        const int f1 = (int)min((long long)nf, f0 + (lin_end - lin));  // faces [f0, f1)
+        lin += f1 - f0;
+        const int j0 = (tile % a.tiles_t1) * TILE1, k0 = (tile / a.tiles_t1) * T2;
+        // columns outside the padded domain read a clamped column; their faces have zero seeds
+        const int jc = min(j0 - 2 + c1, a.n_t1 + NG - 1), kc = min(k0 - 2 + c2, a.n_t2 + NG - 1);
+        const long long cbase = a.pad0 + (long long)jc * a.st_t1 + (long long)kc * a.st_t2;
+        const bool face_ok = (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
+        const int je = min(j0 + fj, a.n_t1 - 1), ke = min(k0 + fk, a.n_t2 - 1);
+        const long long mbase = (long long)je * a.ist_t1 + (long long)ke * a.ist_t2;
+        const double ih2 = a.ih2[ke], ih1 = a.ih1[min(j0 + tj, a.n_t1 - 1)];
+        double ring[2][5], carry[2], nxt[2];
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+#pragma unroll
+            for (int r = 0; r < 5; ++r) ring[v][r] = qcol[v][cbase + (long long)(f0 - 3 + r) * a.st_n];
+            nxt[v] = qcol[v][cbase + (long long)min(f0 + 2, a.n_n + 2) * a.st_n];
+            double left;
+            weno_faces<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, carry[v], left);
         }
-        for (int v = 0; v < 4; ++v) {
-            double right, left, wr[3], wl[3];
-            weno_faces_w<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, right, left, wr, wl);
-            carry[v] = right;
+        // seeds Fbar(f) = mu(f) / w_f - mu(f-1) / w_{f-1} (cell widths w; no cell beyond the ends) of this
+        // lane's variable; the lower cell's term is kept from face to face
+        double lo0 = 0.0, lo1 = 0.0;
+        if (f0 >= 1) {
+            const double w = a.ihc[f0 - 1];
+            lo1 = mu1[mbase + (long long)(f0 - 1) * a.ist_n] * w;
+            if (NEED_F0) lo0 = mu0[mbase + (long long)(f0 - 1) * a.ist_n] * w;
         }
-    }
-
-    // the next cell of the column is loaded one step ahead, by every thread (columns outside the padded
-    // domain and threads without a column read a clamped column whose values only reach faces outside
-    // the domain): a load on every path needs no merge that would wait for it within the step
-    const long long cbase_ld = a.pad0 + (long long)min(jc, a.n_t1 + NG - 1) * a.st_t1 +
-                               (long long)min(kc, a.n_t2 + NG - 1) * a.st_t2;
-    double nxt[4];
-    for (int v = 0; v < 4; ++v) nxt[v] = a.q[v][cbase_ld + (long long)min(f0 + 2, a.n_n + 2) * a.st_n];
-    // inverse spacings: t1 width of this thread's tangential-line cell, t2 width of its face cell, and
-    // (per face, fetched one face ahead) the normal face spacing and the widths of the two cells
-    // sharing the face (clamped at the ends, where the terms they scale vanish)
-    const double ih1 = a.ih1[min(j0 + tj, a.n_t1 - 1)], ih2 = a.ih2[min(k0 + fk, a.n_t2 - 1)];
-    double ihf_nxt = a.ihf[f0], ihc_nxt = a.ihc[min(f0, a.n_n - 1)], ihc_lo = a.ihc[max(f0 - 1, 0)];
-    for (int f = f0; f <= f1; ++f) {
-        for (int v = 0; v < 4; ++v) {
-            for (int r = 0; r < 4; ++r) ring[v][r] = ring[v][r + 1];
-            ring[v][4] = nxt[v];
-        }
-        const double ihf = ihf_nxt, ihc_hi = ihc_nxt;
-        ihf_nxt = a.ihf[min(f + 1, a.n_n)];
-        ihc_nxt = a.ihc[min(f + 1, a.n_n - 1)];
-        {
-            const long long idx = cbase_ld + (long long)min(f + 3, a.n_n + 2) * a.st_n;
-            for (int v = 0; v < 4; ++v) nxt[v] = a.q[v][idx];
-        }
-        // column phase of one variable; v is a compile-time constant so that ring stays in registers
-        auto column = [&](auto vc) {
-            constexpr int v = decltype(vc)::value;
-            if (col) {
-                double right, left, wr[3], wl[3];
-                weno_faces_w<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, right, left,
-                                     wr, wl);
-                const double qL = carry[v];
-                const double D = (ring[v][0] - 15.0 * ring[v][1] + 15.0 * ring[v][2] - ring[v][3]) * (ihf / 12.0);
-                s_nrm[0][c2][c1] = qL;
-                s_nrm[1][c2][c1] = left;
-                s_nrm[2][c2][c1] = D;
-                s_nrm[3][c2][c1] = 0.5 * (qL + left);
-                carry[v] = right;
-                if (col_st) {
-                    // the inputs of the t1 WENO evaluations (pass C rebuilds their coefficients)
-                    const long long p = n_ix(a, f, jc, kc);
-                    a.fv[(v * 2 + 0) * a.nnpos + p] = qL;
-                    a.fv[(v * 2 + 1) * a.nnpos + p] = left;
-                }
+        for (int f = f0; f < f1; ++f) {
+            double up0 = 0.0, up1;
+            {
+                const int c = min(f, a.n_n - 1);
+                const double w = f < a.n_n ? a.ihc[c] : 0.0;
+                up1 = mu1[mbase + (long long)c * a.ist_n] * w;
+                if (NEED_F0) up0 = mu0[mbase + (long long)c * a.ist_n] * w;
             }
-        };
-
-        auto put = [&](int v, int n, int q, double val) { s_gp[(v * 2 + n) * 5 + q][tid] = val; };
-        column(std::integral_constant<int, 0>{});
-        __syncthreads();
-        for (int v = 0; v < 4; ++v) {
-            if (t1r) {
-                double x[4][5];
-                for (int q = 0; q < 4; ++q)
-                    for (int r = 0; r < 5; ++r) x[q][r] = s_nrm[q][tk][tj + r];
-                double vm, vp, wm[3], wp[3];
-                const long long p = t1_st ? t1_ix(a, f, j0 + tj, k0 - 2 + tk) : 0;
-                for (int side = 0; side < 2; ++side) {
-                    weno_gauss_w<double>(x[side][0], x[side][1], x[side][2], x[side][3], x[side][4], eps, vm, vp, wm, wp);
-                    s_t1[side][tk][tj][0] = vm;
-                    s_t1[side][tk][tj][1] = vp;
-                    if (t1_st) {
-                        // the inputs of the t2 WENO evaluations (pass B rebuilds their coefficients)
-                        a.t1v[((v * 2 + side) * 2 + 0) * a.nt1pos + p] = vm;
-                        a.t1v[((v * 2 + side) * 2 + 1) * a.nt1pos + p] = vp;
+            // ---- column phase
+            {
+                const double ihf = a.ihf[f];
+                const long long idx = cbase + (long long)min(f + 3, a.n_n + 2) * a.st_n;
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) ring[v][r] = ring[v][r + 1];
+                    ring[v][4] = nxt[v];
+                    nxt[v] = qcol[v][idx];
+                }
+                if (col) {
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) {
+                        double right, left;
+                        weno_faces<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, right, left);
+                        const double qL = carry[v];
+                        s_nrm[cv + v].a[0][c2][c1] = qL;
+                        s_nrm[cv + v].a[1][c2][c1] = left;
+                        s_nrm[cv + v].a[2][c2][c1] = (ring[v][0] - 15.0 * ring[v][1] + 15.0 * ring[v][2] - ring[v][3]) *
+                                                     ((1.0 / 12.0) * ihf);
+                        s_nrm[cv + v].a[3][c2][c1] = 0.5 * (qL + left);
+                        carry[v] = right;
                     }
                 }
-                quartic_gauss_value<double>(x[2][0], x[2][1], x[2][2], x[2][3], x[2][4], vm, vp);
-                s_t1[2][tk][tj][0] = vm;
-                s_t1[2][tk][tj][1] = vp;
-                quartic_gauss_deriv<double>(x[3][0], x[3][1], x[3][2], x[3][3], x[3][4], vm, vp);
-                s_t1[3][tk][tj][0] = vm * ih1;
-                s_t1[3][tk][tj][1] = vp * ih1;
-                quartic_gauss_value<double>(x[3][0], x[3][1], x[3][2], x[3][3], x[3][4], vm, vp);
-                s_t1[4][tk][tj][0] = vm;
-                s_t1[4][tk][tj][1] = vp;
             }
             __syncthreads();
+            // ---- t1 phase
+#pragma unroll
+            for (int kk = 0; kk < (X2 + T2 - 1) / T2; ++kk) {
+                const int tk = wv + kk * T2;
+                if (tk < X2) {
+                    double x[5], vm, vp;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                        for (int r = 0; r < 5; ++r) x[r] = s_nrm[tv].a[q][tk][tj + r];
+                        if (q < 2) weno_gauss<double>(x[0], x[1], x[2], x[3], x[4], eps, vm, vp);
+                        else quartic_gauss_value<double>(x[0], x[1], x[2], x[3], x[4], vm, vp);
+                        t1_at(tv, q == 3 ? 4 : q, tk, 2 * tj) = vm;
+                        t1_at(tv, q == 3 ? 4 : q, tk, 2 * tj + 1) = vp;
+                        if (q == 3) {
+                            quartic_gauss_deriv<double>(x[0], x[1], x[2], x[3], x[4], vm, vp);
+                            t1_at(tv, 3, tk, 2 * tj) = vm * ih1;
+                            t1_at(tv, 3, tk, 2 * tj + 1) = vp * ih1;
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+            // ---- t2 phase: variables 2h, 2h + 1 of line m at both Gauss points, exchanged so that lane h holds
+            // all four variables at point n = h
+            double w[4][5];
             {
-                double y[5][5];
-                for (int q = 0; q < 5; ++q)
-                    for (int r = 0; r < 5; ++r) y[q][r] = s_t1[q][fk + r][fj][m];
-                double vm, vp, wm[3], wp[3];
-                for (int side = 0; side < 2; ++side) {
-                    weno_gauss_w<double>(y[side][0], y[side][1], y[side][2], y[side][3], y[side][4], eps, vm, vp, wm, wp);
-                    put(v, 0, side, vm);
-                    put(v, 1, side, vp);
-                }
-                quartic_gauss_value<double>(y[2][0], y[2][1], y[2][2], y[2][3], y[2][4], vm, vp);
-                put(v, 0, 2, vm);
-                put(v, 1, 2, vp);
-                quartic_gauss_value<double>(y[3][0], y[3][1], y[3][2], y[3][3], y[3][4], vm, vp);
-                put(v, 0, 3, vm);
-                put(v, 1, 3, vp);
-                quartic_gauss_deriv<double>(y[4][0], y[4][1], y[4][2], y[4][3], y[4][4], vm, vp);
-                put(v, 0, 4, vm * ih2);
-                put(v, 1, 4, vp * ih2);
+                double gp[2][2][5];
+#pragma unroll
+                for (int v = 0; v < 2; ++v)
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) {
+                        double y[5], vm, vp;
+#pragma unroll
+                        for (int r = 0; r < 5; ++r) y[r] = t1_at(2 * hi + v, q, fk + r, 2 * fj + m);
+                        if (q < 2) weno_gauss<double>(y[0], y[1], y[2], y[3], y[4], eps, vm, vp);
+                        else if (q < 4) quartic_gauss_value<double>(y[0], y[1], y[2], y[3], y[4], vm, vp);
+                        else {
+                            quartic_gauss_deriv<double>(y[0], y[1], y[2], y[3], y[4], vm, vp);
+                            vm *= ih2;
+                            vp *= ih2;
+                        }
+                        gp[v][0][q] = vm;
+                        gp[v][1][q] = vp;
+                    }
+#pragma unroll
+                for (int v = 0; v < 2; ++v)
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) {
+                        w[v][q] = dpp_sel<ROW_SHR4, BANK_H1>(gp[v][0][q], gp[v][1][q]);
+                        w[2 + v][q] = dpp_sel<ROW_SHL4, BANK_H0>(gp[v][1][q], gp[v][0][q]);
+                    }
             }
-            switch (v) {
-                case 0: column(std::integral_constant<int, 1>{}); break;
-                case 1: column(std::integral_constant<int, 2>{}); break;
-                case 2: column(std::integral_constant<int, 3>{}); break;
-                default: break;
-            }
-            __syncthreads();
-        }
-
-        // reverse of the flux at this thread's two Gauss points: the adjoints of their inputs go to the
-        // gpbar slots of this face
-        if (face_ok) {
-            const long long fi = face_ix(a, f, j0 + fj, k0 + fk);
-            const long long jk = (long long)(j0 + fj) * a.ist_t1 + (long long)(k0 + fk) * a.ist_t2;
-            double b0[4], b1[4];
-            for (int v = 0; v < 4; ++v) {
-                const double hi1 = f < a.n_n ? a.mu1[v][(long long)f * a.ist_n + jk] : 0.0;
-                const double lo1 = f >= 1 ? a.mu1[v][(long long)(f - 1) * a.ist_n + jk] : 0.0;
-                // Fbar(f) = mu(f) / w_f - mu(f-1) / w_{f-1} (cell widths w)
-                b1[v] = hi1 * ihc_hi - lo1 * ihc_lo;
-                if (NEED_F0) {
-                    const double hi0 = f < a.n_n ? a.mu0[v][(long long)f * a.ist_n + jk] : 0.0;
-                    const double lo0 = f >= 1 ? a.mu0[v][(long long)(f - 1) * a.ist_n + jk] : 0.0;
-                    b0[v] = hi0 * ihc_hi - lo0 * ihc_lo;
-                } else {
-                    b0[v] = 0.0;
-                }
-            }
-            for (int n = 0; n < 2; ++n) {
+            // ---- reverse of the flux at this lane's Gauss point
+            {
+                // the four lanes of a face hold one seed each: all four to every lane
+                auto all_lanes = [&](double x, double (&y)[4]) {
+                    const double e = dpp_sel<ROW_ROR8, BANK_M1>(x, x), o = dpp_sel<ROW_ROR8, BANK_M0>(x, x);
+                    y[0] = dpp_sel<ROW_SHR4, BANK_H1>(e, e);
+                    y[1] = dpp_sel<ROW_SHR4, BANK_H1>(o, o);
+                    y[2] = dpp_sel<ROW_SHL4, BANK_H0>(e, e);
+                    y[3] = dpp_sel<ROW_SHL4, BANK_H0>(o, o);
+                };
+                double b0[4] = {0, 0, 0, 0}, b1[4];
+                all_lanes(face_ok ? up1 - lo1 : 0.0, b1);
+                if (NEED_F0) all_lanes(face_ok ? up0 - lo0 : 0.0, b0);
+                lo1 = up1;
+                lo0 = up0;
                 double qL[4], qR[4], g[3][4], qLb[4] = {0, 0, 0, 0}, qRb[4] = {0, 0, 0, 0};
                 double gb[3][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int q0 = (v * 2 + n) * 5;
-                    qL[v] = s_gp[q0][tid];
-                    qR[v] = s_gp[q0 + 1][tid];
-                    g[0][v] = s_gp[q0 + 2][tid];
-                    g[1][v] = s_gp[q0 + 3][tid];
-                    g[2][v] = s_gp[q0 + 4][tid];
+                    qL[v] = w[v][0];
+                    qR[v] = w[v][1];
+                    g[0][v] = w[v][2];
+                    g[1][v] = w[v][3];
+                    g[2][v] = w[v][4];
                 }
                 gp_flux_adj<NEED_F0>(qL, qR, g, a.fc, 0.25, b0, b1, qLb, qRb, gb);
+#pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const long long base = (long long)(((v * 2 + m) * 2 + n) * 5) * a.nface + fi;
-                    a.gpbar[base] = qLb[v];
-                    a.gpbar[base + a.nface] = qRb[v];
-                    a.gpbar[base + 2 * a.nface] = gb[0][v];
-                    a.gpbar[base + 3 * a.nface] = gb[1][v];
-                    a.gpbar[base + 4 * a.nface] = gb[2][v];
+                    w[v][0] = qLb[v];
+                    w[v][1] = qRb[v];
+                    w[v][2] = gb[0][v];
+                    w[v][3] = gb[1][v];
+                    w[v][4] = gb[2][v];
                 }
             }
-        }
-        ihc_lo = ihc_hi;
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// passes B and C fused: the transpose of the t2 sweep produces one row (fixed t2 position) of t1 line
-// adjoints at a time into LDS, and the transpose of the t1 sweep and of C = (q^L + q^R)/2 consumes it
-// there, so the t1 line adjoints never reach HBM
-// ------------------------------------------------------------------------------------------------
-constexpr int BC_ROWS = 64;  // t2 rows (outputs kx) per workgroup
-
-// Work split of the fused pass along t1 for n_t1 cells: outputs jx per segment, t1 positions per
-// segment at most (the threads are two per position: Gauss lines m = 0, 1), segments per row.
-struct BcSplit {
-    int seg, npt, nseg;
-};
-inline BcSplit bc_split(int n_t1) {
-    BcSplit b;
-    // at most 128 positions (LDS of the exact mode: 33 KB)
-    if (n_t1 <= 128) {  // one segment: all outputs -2 .. n_t1 + 1 from all positions 0 .. n_t1 - 1
-        b.seg = n_t1 + 4;
-        b.npt = (n_t1 + 31) / 32 * 32;
-    } else {  // segments of 124 outputs read 128 positions
-        b.seg = 124;
-        b.npt = 128;
-    }
-    b.nseg = (n_t1 + 4 + b.seg - 1) / b.seg;
-    return b;
-}
-
-template <bool EXACT>
-__global__ void __launch_bounds__(256) adj_t21_kernel(const AdjFaceArgs a, int seg_len, int npt) {
-    constexpr int NW = EXACT ? 5 : 2;
-    // one workgroup per (row chunk of BC_ROWS t2 positions incl. halo, t1 segment, variable, face) of
-    // 2 npt threads. Thread (jl, m), jl = tid % npt, m = tid / npt, runs the t2 transpose of t1 position
-    // j = jlo + jl, Gauss line m: it walks the faces of the chunk in ascending t2 order, each face adding
-    // its terms to the five rows kx = k-2 .. k+2 it reaches (a ring), the face's two t2 WENO
-    // coefficients rebuilt from the t1 line values of its stencil (a second ring). When row kx = k-2 is
-    // complete it goes to LDS, and the workgroup transposes the t1 sweep of that row: the coefficients
-    // of every position's t1 WENO evaluations are rebuilt from the normal face values of its stencil,
-    // and every output jx gathers its five positions (ascending t1, Gauss line m inner). Sums are in
-    // the same fixed orders as the separate passes.
-    extern __shared__ double lds[];
-    double* const s_tb = lds;                        // [10][npt]: t1 line adjoints [m * 5 + q][position]
-    double* const s_w = s_tb + 10 * npt;             // [4 NW][npt]: coefficients [(side * 2 + m) * NW + kk]
-    double* const s_f = s_w + 4 * NW * npt;          // [2][npt + 4]: normal face values q^L, q^R
-    double* const s_h1 = s_f + 2 * (npt + 4);        // [npt]: inverse t1 widths of the positions
-    const int tid = threadIdx.x;
-    const int nrc = (a.n_t2 + 4 + BC_ROWS - 1) / BC_ROWS;
-    const int nseg = (a.n_t1 + 4 + seg_len - 1) / seg_len;
-    long long r_ = blockIdx.x;
-    const int rc = (int)(r_ % nrc);
-    r_ /= nrc;
-    const int seg = (int)(r_ % nseg);
-    r_ /= nseg;
-    const int v = (int)(r_ % 4);
-    const int f = (int)(r_ / 4);
-    const int kx_lo = -2 + rc * BC_ROWS, kx_hi = min(kx_lo + BC_ROWS, a.n_t2 + 2);
-    const int seg0 = -2 + seg * seg_len, seg1 = min(seg0 + seg_len, a.n_t1 + 2);  // outputs jx
-    const int jlo = max(0, seg0 - 2), jhi = min(a.n_t1, seg1 + 2);                 // positions j
-    const int npos = jhi - jlo;
-    const int jl = tid % npt, m = tid / npt;
-    const bool tb = jl < npos;
-    const int j = jlo + jl;
-    const int vm = v * 2 + m;
-    if (tid < npos) s_h1[tid] = a.ih1[jlo + tid];  // read after the first row's barrier
-    auto t1val = [&](int side, int kx) -> double {
-        return (tb && kx >= -2 && kx < a.n_t2 + 2) ? a.t1v[((v * 2 + side) * 2 + m) * a.nt1pos + t1_ix(a, f, j, kx)]
-                                                   : 0.0;
-    };
-    // the adjoints of face k's Gauss-point inputs, [Gauss point n][quantity]
-    auto gp_in = [&](int k, double g[2][5]) {
-        const bool ok = tb && k >= 0 && k < a.n_t2;
-        const long long fi = ok ? face_ix(a, f, j, k) : 0;
+            // ---- terms of the t2 transpose, variable by variable
+            double term[2][16];
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
+            for (int v = 0; v < 2; ++v) {
+                double gn[2][5];  // the exchange undone: both Gauss points of variable 2h + v
 #pragma unroll
-            for (int q = 0; q < 5; ++q) g[n][q] = ok ? a.gpbar[(long long)((vm * 2 + n) * 5 + q) * a.nface + fi] : 0.0;
-    };
-    // software pipelining: the next face's inputs and the t1 line value two positions ahead are loaded
-    // one step before they are used
-    double y[2][5], ynext[2], gnext[2][5];
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-        y[side][0] = 0.0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) y[side][r + 1] = t1val(side, kx_lo - 4 + r);
-        ynext[side] = t1val(side, kx_lo);
-    }
-    gp_in(kx_lo - 2, gnext);
-    // inverse t2 width of face k's cell, fetched one face ahead (clamped outside the cells, where unused)
-    double ih2_nxt = a.ih2[min(max(kx_lo - 2, 0), a.n_t2 - 1)];
-    double acc[5][5];
-#pragma unroll
-    for (int r = 0; r < 5; ++r)
-#pragma unroll
-        for (int q = 0; q < 5; ++q) acc[r][q] = 0.0;
-    for (int k = kx_lo - 2; k < kx_hi + 2; ++k) {
-        // ---- t2 transpose: face k of this thread's position
-        double gcur[2][5];
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int q = 0; q < 5; ++q) gcur[n][q] = gnext[n][q];
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) y[side][r] = y[side][r + 1];
-            y[side][4] = ynext[side];
-            ynext[side] = t1val(side, k + 3);
-        }
-        gp_in(k + 1, gnext);
-        const double ih2 = ih2_nxt;
-        ih2_nxt = a.ih2[min(max(k + 1, 0), a.n_t2 - 1)];
-        if (tb && k >= 0 && k < a.n_t2) {
-            double cw[2][2][NW];
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                double gm, gp, wm[3], wp[3];
-                weno_gauss_w<double>(y[side][0], y[side][1], y[side][2], y[side][3], y[side][4], a.eps, gm, gp, wm, wp);
-                weno_coefs<EXACT>(2, y[side], a.eps, wm, gm, cw[side][0]);
-                weno_coefs<EXACT>(3, y[side], a.eps, wp, gp, cw[side][1]);
-            }
-#pragma unroll
-            for (int n = 0; n < 2; ++n) {
-                const int side = n == 0 ? 2 : 3;
-                const int sg = n == 0 ? -1 : 1;
-                const double* const gv = gcur[n];
-#pragma unroll
-                for (int r = 0; r < 5; ++r) {
-                    const double cv = quartic_coef(0, sg, r), cd = quartic_coef(1, sg, r) * ih2;
-                    acc[r][0] += wcoef<EXACT>(side, cw[0][n], r) * gv[0];
-                    acc[r][1] += wcoef<EXACT>(side, cw[1][n], r) * gv[1];
-                    acc[r][2] += cv * gv[2];
-                    acc[r][3] += cv * gv[3];
-                    acc[r][4] += cd * gv[4];
+                for (int q = 0; q < 5; ++q) {
+                    gn[0][q] = dpp_sel<ROW_SHR4, BANK_H1>(w[v][q], w[2 + v][q]);
+                    gn[1][q] = dpp_sel<ROW_SHL4, BANK_H0>(w[2 + v][q], w[v][q]);
                 }
-            }
-        }
-        const int kx = k - 2;  // row kx has all its faces now
-        if (kx >= kx_lo && kx < kx_hi) {
-            // ---- t1 transpose of row kx
-            if (tb)
 #pragma unroll
-                for (int q = 0; q < 5; ++q) s_tb[(m * 5 + q) * npt + jl] = acc[0][q];
-            for (int l = tid; l < npos + 4; l += 2 * npt) {
-                const int jx = jlo - 2 + l;
-                const bool in = jx >= -2 && jx < a.n_t1 + 2;
-                const long long p = in ? n_ix(a, f, jx, kx) : 0;
-                s_f[l] = in ? a.fv[(v * 2 + 0) * a.nnpos + p] : 0.0;
-                s_f[(npt + 4) + l] = in ? a.fv[(v * 2 + 1) * a.nnpos + p] : 0.0;
+                for (int side = 0; side < 2; ++side) {
+                    double y[5], vm, vp, wm[3], wp[3], cm[NW], cp[NW];
+#pragma unroll
+                    for (int r = 0; r < 5; ++r) y[r] = t1_at(2 * hi + v, side, fk + r, 2 * fj + m);
+                    weno_gauss_w<double>(y[0], y[1], y[2], y[3], y[4], eps, vm, vp, wm, wp);
+                    weno_coefs<EXACT>(2, y, eps, wm, vm, cm);
+                    weno_coefs<EXACT>(3, y, eps, wp, vp, cp);
+#pragma unroll
+                    for (int r = 0; r < 5; ++r)
+                        term[v][5 * side + r] = wcoef<EXACT>(2, cm, r) * gn[0][side] + wcoef<EXACT>(3, cp, r) * gn[1][side];
+                }
+#pragma unroll
+                for (int q = 2; q < 5; ++q)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) term[v][10 + 2 * (q - 2) + n] = q == 4 ? gn[n][q] * ih2 : gn[n][q];
             }
             __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) s_w[(16 * v + k) * NTH + tid] = term[v][k];
+            __syncthreads();
+            // ---- t2 transpose: rows 3 run .. 3 run + 2 of variable 2h + (wave & 1), ascending faces
+            double tb[3][5];
             {
-                // coefficients of position jl (side = the thread's m slot): stencil at t1 cells j-2 .. j+2
-                const int side = m;
-                if (tb) {
-                    double x[5];
+                const int i = wv & 1, run = wv >> 1;
 #pragma unroll
-                    for (int r = 0; r < 5; ++r) x[r] = s_f[side * (npt + 4) + jl + r];
-                    double gm, gp, wm[3], wp[3], cm[NW], cp[NW];
-                    weno_gauss_w<double>(x[0], x[1], x[2], x[3], x[4], a.eps, gm, gp, wm, wp);
-                    weno_coefs<EXACT>(2, x, a.eps, wm, gm, cm);
-                    weno_coefs<EXACT>(3, x, a.eps, wp, gp, cp);
+                for (int p = 0; p < 3; ++p)
 #pragma unroll
-                    for (int kk = 0; kk < NW; ++kk) {
-                        s_w[((side * 2 + 0) * NW + kk) * npt + jl] = cm[kk];
-                        s_w[((side * 2 + 1) * NW + kk) * npt + jl] = cp[kk];
-                    }
-                }
-            }
-            __syncthreads();
-            for (int o = tid; o < seg1 - seg0; o += 2 * npt) {
-                const int jx = seg0 + o;
-                double bar[3] = {0.0, 0.0, 0.0}, Cb = 0.0;
-                // positions jx - 2 .. jx + 2 in ascending order (stencil slot r = jx - jj + 2 descending)
+                    for (int q = 0; q < 5; ++q) tb[p][q] = 0.0;
 #pragma unroll
-                for (int r = 4; r >= 0; --r) {
-                    const int jj = jx - r + 2;
-                    if (jj < 0 || jj >= a.n_t1) continue;
-                    const int l = jj - jlo;
+                for (int jf = 0; jf < 7; ++jf) {
+                    const int k = 3 * run - 4 + jf;  // face row
+                    if (k >= 0 && k < T2) {
+                        const double* const t = s_w + (16 * i) * NTH + k * 64 + (tid & 63);
+                        double g[6];
 #pragma unroll
-                    for (int mm = 0; mm < 2; ++mm) {
-                        const int side = mm == 0 ? 2 : 3;
-                        const int sg = mm == 0 ? -1 : 1;
-                        const double cv = quartic_coef(0, sg, r), cd = quartic_coef(1, sg, r) * s_h1[l];
-                        double wL[NW], wR[NW];
+                        for (int n = 0; n < 6; ++n) g[n] = t[(10 + n) * NTH];
 #pragma unroll
-                        for (int kk = 0; kk < NW; ++kk) {
-                            wL[kk] = s_w[((0 * 2 + mm) * NW + kk) * npt + l];
-                            wR[kk] = s_w[((1 * 2 + mm) * NW + kk) * npt + l];
+                        for (int p = 0; p < 3; ++p) {
+                            const int r = p + 4 - jf;
+                            if (r < 0 || r > 4) continue;
+                            tb[p][0] += t[r * NTH];
+                            tb[p][1] += t[(5 + r) * NTH];
+                            tb[p][2] += quartic_coef(0, -1, r) * g[0] + quartic_coef(0, 1, r) * g[1];
+                            tb[p][3] += quartic_coef(0, -1, r) * g[2] + quartic_coef(0, 1, r) * g[3];
+                            tb[p][4] += quartic_coef(1, -1, r) * g[4] + quartic_coef(1, 1, r) * g[5];
                         }
-                        bar[0] += wcoef<EXACT>(side, wL, r) * s_tb[(mm * 5 + 0) * npt + l];
-                        bar[1] += wcoef<EXACT>(side, wR, r) * s_tb[(mm * 5 + 1) * npt + l];
-                        bar[2] += cv * s_tb[(mm * 5 + 2) * npt + l];
-                        Cb += cd * s_tb[(mm * 5 + 3) * npt + l];
-                        Cb += cv * s_tb[(mm * 5 + 4) * npt + l];
                     }
                 }
-                const long long p = n_ix(a, f, jx, kx);
-                a.fabar[(long long)(v * 3 + 0) * a.nnpos + p] = bar[0] + 0.5 * Cb;
-                a.fabar[(long long)(v * 3 + 1) * a.nnpos + p] = bar[1] + 0.5 * Cb;
-                a.fabar[(long long)(v * 3 + 2) * a.nnpos + p] = bar[2];
             }
             __syncthreads();
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int q = 0; q < 5; ++q) t1_at(2 * hi + (wv & 1), q, 3 * (wv >> 1) + p, 2 * fj + m) = tb[p][q];
+            __syncthreads();
+            // ---- t1 transpose and C = (q^L + q^R)/2
+            double* const out = a.fabar + ((long long)tile * nf + f) * (12 * X2 * EXT1) + 3 * tv * (X2 * EXT1);
+#pragma unroll
+            for (int kk = 0; kk < (X2 + T2 - 1) / T2; ++kk) {
+                const int tk = wv + kk * T2;
+                if (tk < X2) {
+                    double P[3][5];
+                    {
+                        const double d0 = t1_at(tv, 3, tk, 2 * tj) * ih1, d1 = t1_at(tv, 3, tk, 2 * tj + 1) * ih1;
+                        const double c0 = t1_at(tv, 4, tk, 2 * tj), c1_ = t1_at(tv, 4, tk, 2 * tj + 1);
+                        const double n0 = t1_at(tv, 2, tk, 2 * tj), n1 = t1_at(tv, 2, tk, 2 * tj + 1);
+#pragma unroll
+                        for (int r = 0; r < 5; ++r) {
+                            const double cm = quartic_coef(0, -1, r), cp = quartic_coef(0, 1, r);
+                            const double Cb = 0.5 * ((quartic_coef(1, -1, r) * d0 + quartic_coef(1, 1, r) * d1) + (cm * c0 + cp * c1_));
+                            P[0][r] = Cb;
+                            P[1][r] = Cb;
+                            P[2][r] = cm * n0 + cp * n1;
+                        }
+                    }
+#pragma unroll
+                    for (int side = 0; side < 2; ++side) {
+                        double x[5], vm, vp, wm[3], wp[3], cm[NW], cp[NW];
+#pragma unroll
+                        for (int r = 0; r < 5; ++r) x[r] = s_nrm[tv].a[side][tk][tj + r];
+                        weno_gauss_w<double>(x[0], x[1], x[2], x[3], x[4], eps, vm, vp, wm, wp);
+                        weno_coefs<EXACT>(2, x, eps, wm, vm, cm);
+                        weno_coefs<EXACT>(3, x, eps, wp, vp, cp);
+                        const double t0 = t1_at(tv, side, tk, 2 * tj), t1 = t1_at(tv, side, tk, 2 * tj + 1);
+#pragma unroll
+                        for (int r = 0; r < 5; ++r) P[side][r] += wcoef<EXACT>(2, cm, r) * t0 + wcoef<EXACT>(3, cp, r) * t1;
+                    }
+                    // column tj + r: stencil slot r of position tj. Lane l sums column l + 2; lanes 14, 15, 0, 1
+                    // also hold columns 0, 1, 18, 19
+                    const int edge = tj >= 14 ? tj - 14 : tj + 18;
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        const double mid = ((dpp_shr<2>(P[q][4]) + dpp_shr<1>(P[q][3])) + P[q][2]) +
+                                           (dpp_shl<1>(P[q][1]) + dpp_shl<2>(P[q][0]));
+                        const double end = (dpp_shr<14>(P[q][0]) + dpp_shr<15>(P[q][1])) +
+                                           (dpp_shl<15>(P[q][3]) + dpp_shl<14>(P[q][4]));
+                        double* const o = out + q * (X2 * EXT1) + tk * EXT1;
+                        o[tj + 2] = mid;
+                        if (tj < 2 || tj >= 14) o[edge] = end;
+                    }
+                }
+            }
+            __syncthreads();  // s_nrm and s_w are rewritten by the next face
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int q = 0; q < 5; ++q) acc[r][q] = acc[r + 1][q];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) acc[4][q] = 0.0;
     }
 }
 
@@ -503,6 +439,22 @@ __global__ void __launch_bounds__(256) adj_normal_kernel(const AdjFaceArgs a) {
     const int kx = (int)(r_ % (a.n_t2 + 4)) - 2;
     const int c = (int)(r_ / (a.n_t2 + 4));
     const int i_lo = -3 + c * N_CHUNK, i_hi = min(i_lo + N_CHUNK, a.n_n + 3);
+    // the tiles whose columns (with their two-cell halo) hold this one, ascending: partial sums of pass A
+    constexpr int X2 = AdjTile::T2 + 4, SLAB = 12 * X2 * EXT1;
+    const double* part[4];
+    bool has[4];
+    {
+        const int T1 = (jx + 2) / TILE1, c1 = (jx + 2) % TILE1, T2 = (kx + 2) / AdjTile::T2, c2 = (kx + 2) % AdjTile::T2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int d1 = 1 - (e & 1), d2 = 1 - (e >> 1);  // the tile before, then the column's own
+            const int t1 = T1 - d1, t2 = T2 - d2, x1 = c1 + TILE1 * d1, x2 = c2 + AdjTile::T2 * d2;
+            has[e] = t1 >= 0 && t1 < a.tiles_t1 && x1 < EXT1 && t2 >= 0 && t2 < a.tiles_t2 && x2 < X2;
+            part[e] = a.fabar + (has[e] ? (long long)(t2 * a.tiles_t1 + t1) * (a.n_n + 1) * SLAB +
+                                              3 * v * (X2 * EXT1) + x2 * EXT1 + x1
+                                        : 0);
+        }
+    }
     const long long colq = a.pad0 + (long long)jx * a.st_t1 + (long long)kx * a.st_t2;
     auto cell = [&](int i) -> double { return (i >= -3 && i < a.n_n + 3) ? a.q[v][colq + (long long)i * a.st_n] : 0.0; };
     double wl[6][NW], wr[6][NW], fb[6][3];
@@ -529,9 +481,15 @@ __global__ void __launch_bounds__(256) adj_normal_kernel(const AdjFaceArgs a) {
         for (int kk = 0; kk < NW; ++kk) wl[s][kk] = carryL[kk];
         weno_coefs<EXACT>(1, win, a.eps, w_l, left, wr[s]);
         weno_coefs<EXACT>(0, win, a.eps, w_r, right, carryL);
-        const long long p = ok[s] ? n_ix(a, fn, jx, kx) : 0;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) fb[s][q] = ok[s] ? a.fabar[(long long)(v * 3 + q) * a.nnpos + p] : 0.0;
+        for (int q = 0; q < 3; ++q) fb[s][q] = 0.0;
+        if (ok[s]) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (has[e])
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) fb[s][q] += part[e][(long long)fn * SLAB + q * (X2 * EXT1)];
+        }
         fb[s][2] *= a.ihf[min(max(fn, 0), a.n_n)];  // D's 1/h at face fn
 #pragma unroll
         for (int r = 0; r < 4; ++r) win[r] = win[r + 1];
@@ -578,17 +536,10 @@ __global__ void __launch_bounds__(256) adj_normal_kernel(const AdjFaceArgs a) {
 
 template <bool EXACT>
 hipError_t launch_adj_passes(const AdjFaceArgs& a, int stage, hipStream_t s) {
-    const int nchunks = (a.n_n + a.chunk - 1) / a.chunk;
-    const long long blocks = ((long long)a.tiles_t1 * a.tiles_t2 * nchunks + 7) / 8 * 8;
-    if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 fgrid((unsigned)blocks), fblock(AdjTile::THREADS);
-    if (stage == 1) hipLaunchKernelGGL((adj_face_kernel<1>), fgrid, fblock, 0, s, a);
-    else hipLaunchKernelGGL((adj_face_kernel<2>), fgrid, fblock, 0, s, a);
-    const BcSplit bc = bc_split(a.n_t1);
-    const long long nBC = (long long)(a.n_n + 1) * 4 * bc.nseg * ((a.n_t2 + 4 + BC_ROWS - 1) / BC_ROWS);
-    const size_t lds = ((size_t)(11 + 4 * (EXACT ? 5 : 2)) * bc.npt + 2 * (size_t)(bc.npt + 4)) * sizeof(double);
-    if (nBC > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((adj_t21_kernel<EXACT>), dim3((unsigned)nBC), dim3(2 * bc.npt), lds, s, a, bc.seg, bc.npt);
+    if (a.n_wg <= 0) return hipErrorInvalidValue;
+    const dim3 fgrid((unsigned)pad8(a.n_wg)), fblock(AdjTile::THREADS);
+    if (stage == 1) hipLaunchKernelGGL((adj_face_kernel<1, EXACT>), fgrid, fblock, 0, s, a);
+    else hipLaunchKernelGGL((adj_face_kernel<2, EXACT>), fgrid, fblock, 0, s, a);
     const long long nD = (long long)((a.n_n + 6 + N_CHUNK - 1) / N_CHUNK) * 4 * (a.n_t1 + 4) * (a.n_t2 + 4);
     hipLaunchKernelGGL((adj_normal_kernel<EXACT>), dim3((unsigned)((nD + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -971,17 +922,12 @@ void adjoint_carve(char* base, int nx, int ny, int nz, int n_act, AdjBuffers* b,
     for (int v = 0; v < 4; ++v) b->mu1[v] = reinterpret_cast<double*>(take(N * 8));
     const int n[3] = {nx, ny, nz};
     const int ax[3][3] = {{0, 1, 2}, {1, 0, 2}, {2, 0, 1}};
-    size_t nface = 0, nt1 = 0, nn = 0;
+    size_t slabs = 0;  // (tile, face) pairs of pass A
     for (int d = 0; d < 3; ++d) {
-        const size_t a0 = n[ax[d][0]] + 1, a1 = n[ax[d][1]], a2 = n[ax[d][2]];
-        nface = std::max(nface, a0 * a1 * a2);
-        nt1 = std::max(nt1, a0 * a1 * (a2 + 4));
-        nn = std::max(nn, a0 * (a1 + 4) * (a2 + 4));
+        const size_t t1 = (n[ax[d][1]] + TILE1 - 1) / TILE1, t2 = (n[ax[d][2]] + AdjTile::T2 - 1) / AdjTile::T2;
+        slabs = std::max(slabs, t1 * t2 * (n[ax[d][0]] + 1));
     }
-    b->gpbar = reinterpret_cast<double*>(take(80 * nface * 8));
-    b->t1v = reinterpret_cast<double*>(take(16 * nt1 * 8));
-    b->fv = reinterpret_cast<double*>(take(8 * nn * 8));
-    b->fabar = reinterpret_cast<double*>(take(12 * nn * 8));
+    b->fabar = reinterpret_cast<double*>(take(slabs * 12 * (AdjTile::T2 + 4) * EXT1 * 8));
     b->pt = reinterpret_cast<double*>(take(16 * (size_t)std::max(n_act, 1) * 8));
     *total = off;
 }

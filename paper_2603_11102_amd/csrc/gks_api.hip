@@ -71,7 +71,7 @@ struct gks_ctx {
     double lam, c, hmin, eps;
     int t2[3];         // t2 rows of a face tile, per direction
     int chunk[3];      // faces per workgroup of the face kernels, per direction
-    int adj_chunk[3];  // faces per workgroup of the adjoint's recompute pass
+    FaceSplit adj_split[3];  // work split of the adjoint's pass A
     int seg_len[3], n_wg[3];  // work split of the order-5 face launches (FaceArgs)
     int side_by_side;  // order 5: the three directions of a stage run in one launch (face_layout)
     int flags;
@@ -470,16 +470,15 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, void* const src[4],
         a.mu1[v] = B.mu1[gv];
         a.acc[v] = B.acc[gv];
     }
-    a.gpbar = B.gpbar;
-    a.t1v = B.t1v;
-    a.fv = B.fv;
     a.fabar = B.fabar;
     a.n_n = c->g.n[ax[0]];
     a.n_t1 = c->g.n[ax[1]];
     a.n_t2 = c->g.n[ax[2]];
     a.tiles_t1 = (a.n_t1 + TILE1 - 1) / TILE1;
     a.tiles_t2 = (a.n_t2 + AdjTile::T2 - 1) / AdjTile::T2;
-    a.chunk = c->adj_chunk[d];
+    a.chunk = c->adj_split[d].chunk;
+    a.seg_len = c->adj_split[d].seg_len;
+    a.n_wg = (int)c->adj_split[d].n_wg;
     a.st_n = c->g.st[ax[0]];
     a.st_t1 = c->g.st[ax[1]];
     a.st_t2 = c->g.st[ax[2]];
@@ -487,9 +486,6 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, void* const src[4],
     a.ist_t1 = ist[ax[1]];
     a.ist_t2 = ist[ax[2]];
     a.pad0 = c->g.pad0;
-    a.nface = (long long)(a.n_n + 1) * a.n_t1 * a.n_t2;
-    a.nt1pos = (long long)(a.n_n + 1) * a.n_t1 * (a.n_t2 + 4);
-    a.nnpos = (long long)(a.n_n + 1) * (a.n_t1 + 4) * (a.n_t2 + 4);
     a.ihf = static_cast<const double*>(c->ihf[ax[0]]);
     a.ihc = static_cast<const double*>(c->ihc[ax[0]]);
     a.ih1 = static_cast<const double*>(c->ihc[ax[1]]);
@@ -552,7 +548,7 @@ void face_layout(gks_ctx* c) {
     };
     c->side_by_side = 0;
     if (cfg->order == 2) {
-        for (int d = 0; d < 3; ++d) c->t2[d] = c->chunk[d] = c->seg_len[d] = c->n_wg[d] = c->adj_chunk[d] = 0;
+        for (int d = 0; d < 3; ++d) c->t2[d] = c->chunk[d] = c->seg_len[d] = c->n_wg[d] = 0;
         c->chunk[2] = stage2_chunk(n, f64);
         return;
     }
@@ -586,9 +582,12 @@ void face_layout(gks_ctx* c) {
                 }
             }
         }
-        // the adjoint's recompute pass: its own tiles, one workgroup per CU (its LDS), as the 8-row forward tile
+        // the adjoint's pass A: the 8-row tiles, one workgroup per CU as well, n + 1 faces per tile
         if (f64 && rows == AdjTile::T2)
-            for (int d = 0; d < 3; ++d) c->adj_chunk[d] = face_chunk(n[kAxes[d][0]], tiles(d, AdjTile::T2), slots);
+            for (int d = 0; d < 3; ++d) {
+                const FaceDir fd = {n[kAxes[d][0]] + 1, tiles(d, AdjTile::T2)};
+                face_split(&fd, 1, slots, &c->adj_split[d]);
+            }
     }
 }
 
