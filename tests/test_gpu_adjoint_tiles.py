@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 W = (1.0, 0.5)
 
 
-@pytest.mark.parametrize("n", [15, 17, 26])  # 16 x 8 tiles: n - 1, one past both extents, 16 + 10 and 3 x 8 + 2
+@pytest.mark.parametrize("n", [18, 23, 33])  # 16 x 8 tiles: 16 + 2 and 2 x 8 + 2, 16 + 7 and 2 x 8 + 7, one past both
 @pytest.mark.parametrize("exact", [False, True])
 def test_adjoint_tiles_match_oracle_reference(n, exact):
     from paper_2603_11102_amd import GksSolver
