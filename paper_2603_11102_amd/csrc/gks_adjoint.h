@@ -2,14 +2,11 @@
 //
 // The reverse sweep linearises the step exactly; the WENO nonlinear weights are either held at their
 // forward values (frozen, the default) or differentiated too (exact). Per face direction and stage
-// operator the transpose is computed without atomics, every sum in a fixed order, in two passes:
-//   A  tile by tile: the forward face pipeline, the reverse of the flux at the Gauss points from the flux
-//      seeds, the transposes of the t2 and t1 sweeps and of C = (q^L + q^R)/2, down to the adjoints of the
-//      normal face values (q^L, q^R, D) at the tile's columns;
-//   D  transpose of the normal reconstruction into the padded cell adjoint, adding the tiles' shares of a
-//      column.
-// Both rebuild the coefficients of the WENO evaluations they transpose (frozen: the weights; exact: the
-// Jacobian row) from the values the evaluations read; then the transpose of the ghost-cell fill folds ghost
+// operator the transpose is computed without atomics, every sum in a fixed order: tile by tile the forward
+// face pipeline, the reverse of the flux at the Gauss points from the flux seeds and the transposes of the
+// t2, t1 and normal reconstructions, down to the adjoints of the cells of the tile's columns; then the sum of
+// the tiles' shares. The coefficients of the WENO evaluations (frozen: the weights; exact: the Jacobian row)
+// are rebuilt from the values the evaluations read; then the transpose of the ghost-cell fill folds ghost
 // adjoints into interior cells.
 #pragma once
 
@@ -20,20 +17,28 @@
 
 namespace gks {
 
-// Tile of pass A: 16 x 8 faces, four lanes per face, one workgroup per CU (its LDS: 162 KB), two waves per SIMD.
+// Tile: 16 x 8 faces, four lanes per face, one workgroup per CU (its LDS: 162 KB), two waves per SIMD.
 struct AdjTile {
     static constexpr int T2 = 8, THREADS = 64 * T2;
 };
+constexpr int ADJ_CELL = 4 * (AdjTile::T2 + 4) * EXT1;  // doubles per cell layer of a tile's columns
+constexpr int ADJ_SLOTS = 256;  // workgroups at once (256 CUs); fixed, since the workspace's size depends on the split
+
+// Work split of one direction: marches of `chunk` faces, nch per tile.
+struct AdjSplit {
+    int tiles_t1, tiles_t2, chunk, nch;
+};
+AdjSplit adj_split(int n_n, int n_t1, int n_t2);
 
 struct AdjFaceArgs {
     const double* q[4];     // field in LOCAL variable order (padded)
     const double* mu0[4];   // seed of L (interior, local order), stage 1 only
     const double* mu1[4];   // seed of L_t
-    double* fabar;          // [tile][face][12][12 t2 rows][20 t1 columns]: adjoints of q^L, q^R, D per variable
+    double* slab;           // [tile][march][cell, chunk + 5][variable][12 t2 rows][20 t1 columns]: cell adjoints
     double* acc[4];         // padded cell adjoint accumulator (LOCAL order)
     int n_n, n_t1, n_t2;
     int tiles_t1, tiles_t2;
-    int chunk, seg_len, n_wg;  // work split over the n_n + 1 faces of each tile, as in FaceArgs
+    int chunk, nch, n_wg;  // marches of chunk of the n_n + 1 faces, nch per tile, one per workgroup
     long long st_n, st_t1, st_t2;
     long long ist_n, ist_t1, ist_t2;
     long long pad0;
@@ -59,7 +64,7 @@ struct AdjBuffers {
     double* qpre[4];     // padded: Q^{n+1,pre}
     double* mu0[4];      // interior seeds
     double* mu1[4];
-    double* fabar;
+    double* slab;
     double* pt;          // per-point scratch of the ALM adjoint: [16][n_act]
 };
 

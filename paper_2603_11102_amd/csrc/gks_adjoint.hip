@@ -72,16 +72,17 @@ __device__ __forceinline__ double dpp_shr(double x) {
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
-// pass A: the tile's forward face pipeline and its transpose back to the normal face values.
+// The tile's forward face pipeline and its transpose, down to the cells of the tile's columns.
 //
 // The kernel marches 16 x 8 face tiles with the lane layout of the forward FP64 kernel (four lanes per face:
 // lane bit 2 is h, bit 3 m; a wave per t2 row) and, per face, runs the reverse of the flux at each Gauss point,
-// undoes the exchange of the lane pair, and transposes the t2 sweep, the t1 sweep and C = (q^L + q^R)/2 inside the
-// tile. Only the adjoints of (q^L, q^R, D) at the tile's 20 x 12 columns leave it; columns of a tile's two-cell
-// halo are partial sums, which pass D adds over the (at most four) tiles that hold a column, in a fixed order.
-// Before, the Gauss-point adjoints (640 B a face) and the inputs of the tangential WENO evaluations (192 B) went
-// through memory between separate kernels, which ran at 2.6 to 3.7 TB/s and one wave per SIMD; this one writes
-// 180 B a face and is bound by FP64 issue and its barriers.
+// undoes the exchange of the lane pair, and transposes the t2 sweep, the t1 sweep, C = (q^L + q^R)/2 and the
+// normal reconstruction inside the tile. Only the adjoints of the cells of the tile's 20 x 12 columns leave it,
+// partial sums in the two-cell halo and at the ends of a march, which adj_sum_kernel adds in a fixed order.
+// With separate kernels the Gauss-point adjoints (640 B a face) and the inputs of the tangential WENO evaluations
+// (192 B) went through memory, at 2.6 to 3.7 TB/s and one wave per SIMD: 1.95 ms per direction and stage of the
+// 128^3 rotor box, against 0.98 ms and 0.10 ms of adj_sum_kernel. This one writes 60 B a face and is bound by FP64
+// issue and its barriers.
 //
 // t2 transpose: each lane forms, for its two variables, the WENO terms of its face for the five rows it reaches
 // (10 values) and keeps the linear terms' six inputs; these 16 values go to LDS (over the t1 results, then dead), and
@@ -103,22 +104,17 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
     // t1 results, then the faces' terms of the t2 transpose, then the t1-line adjoints
     __shared__ double s_w[32 * NTH];
     constexpr int T1S = 5 * X2 * 32 + 8;  // doubles per variable
+    // adjoints of the normal face values [variable][q^L, q^R, D][t2 row][t1 column], beside the t1-line adjoints
+    double* const s_fb = s_w + 4 * T1S;
+    static_assert(4 * T1S + 12 * X2 * EXT1 <= 32 * NTH && X2 * EXT1 * 4 == ADJ_CELL, "LDS regions");
     auto t1_at = [&](int v, int q, int row, int c) -> double& { return s_w[v * T1S + (q * X2 + row) * 32 + c]; };
 
     const int tid = threadIdx.x;
     const int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
     if (b >= a.n_wg) return;
+    // faces [f0, f1) of one tile
     const int nf = a.n_n + 1;
     const int tiles = a.tiles_t1 * a.tiles_t2;
-    long long lin, lin_end;  // this workgroup's faces in the tile-major (tile, face) order
-    if (a.seg_len > 0) {
-        lin = (long long)b * a.seg_len;
-        lin_end = min(lin + a.seg_len, (long long)tiles * nf);
-    } else {
-        const int c0 = (b / tiles) * a.chunk;
-        lin = (long long)(b % tiles) * nf + c0;
-        lin_end = lin + min(a.chunk, nf - c0);
-    }
     const double eps = a.eps;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     // column role: variables cv, cv + 1 of column (c1, c2)
@@ -139,11 +135,8 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
     // t1 role: position tj of variable tv
     const int tj = tid & 15, tv = (tid >> 4) & 3;
 
-    while (lin < lin_end) {
-        const int tile = (int)(lin / nf);
-        const int f0 = (int)(lin - (long long)tile * nf);
-        const int f1 = (int)min((long long)nf, f0 + (lin_end - lin));  // faces [f0, f1)
-        lin += f1 - f0;
+    {
+        const int tile = b % tiles, f0 = (b / tiles) * a.chunk, f1 = min(f0 + a.chunk, nf);
         const int j0 = (tile % a.tiles_t1) * TILE1, k0 = (tile / a.tiles_t1) * T2;
         // columns outside the padded domain read a clamped column; their faces have zero seeds
         const int jc = min(j0 - 2 + c1, a.n_t1 + NG - 1), kc = min(k0 - 2 + c2, a.n_t2 + NG - 1);
@@ -152,15 +145,22 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
         const int je = min(j0 + fj, a.n_t1 - 1), ke = min(k0 + fk, a.n_t2 - 1);
         const long long mbase = (long long)je * a.ist_t1 + (long long)ke * a.ist_t2;
         const double ih2 = a.ih2[ke], ih1 = a.ih1[min(j0 + tj, a.n_t1 - 1)];
-        double ring[2][5], carry[2], nxt[2];
+        // cells f0-3 .. f0+1 and the next; of the evaluation on cell f0-1 its right value (q^L of face f0) and
+        // that value's coefficients; the adjoints of cells f-3 .. f+2 that the faces so far reach
+        double ring[2][5], carry[2], nxt[2], coefL[2][NW], cell[2][6];
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
 #pragma unroll
             for (int r = 0; r < 5; ++r) ring[v][r] = qcol[v][cbase + (long long)(f0 - 3 + r) * a.st_n];
             nxt[v] = qcol[v][cbase + (long long)min(f0 + 2, a.n_n + 2) * a.st_n];
-            double left;
-            weno_faces<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, carry[v], left);
+            double left, wr[3], wl[3];
+            weno_faces_w<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, carry[v], left, wr, wl);
+            weno_coefs<EXACT>(0, ring[v], eps, wr, carry[v], coefL[v]);
+#pragma unroll
+            for (int r = 0; r < 6; ++r) cell[v][r] = 0.0;
         }
+        // this march's cells f0-3 .. f1+1 of its columns, [cell][variable][column]
+        double* const slab = a.slab + ((long long)tile * a.nch + f0 / a.chunk) * (a.chunk + 5) * ADJ_CELL;
         // seeds Fbar(f) = mu(f) / w_f - mu(f-1) / w_{f-1} (cell widths w; no cell beyond the ends) of this
         // lane's variable; the lower cell's term is kept from face to face
         double lo0 = 0.0, lo1 = 0.0;
@@ -361,7 +361,6 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
                 for (int q = 0; q < 5; ++q) t1_at(2 * hi + (wv & 1), q, 3 * (wv >> 1) + p, 2 * fj + m) = tb[p][q];
             __syncthreads();
             // ---- t1 transpose and C = (q^L + q^R)/2
-            double* const out = a.fabar + ((long long)tile * nf + f) * (12 * X2 * EXT1) + 3 * tv * (X2 * EXT1);
 #pragma unroll
             for (int kk = 0; kk < (X2 + T2 - 1) / T2; ++kk) {
                 const int tk = wv + kk * T2;
@@ -401,136 +400,103 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
                                            (dpp_shl<1>(P[q][1]) + dpp_shl<2>(P[q][0]));
                         const double end = (dpp_shr<14>(P[q][0]) + dpp_shr<15>(P[q][1])) +
                                            (dpp_shl<15>(P[q][3]) + dpp_shl<14>(P[q][4]));
-                        double* const o = out + q * (X2 * EXT1) + tk * EXT1;
+                        double* const o = s_fb + ((3 * tv + q) * X2 + tk) * EXT1;
                         o[tj + 2] = mid;
                         if (tj < 2 || tj >= 14) o[edge] = end;
                     }
                 }
             }
-            __syncthreads();  // s_nrm and s_w are rewritten by the next face
+            __syncthreads();
+            // ---- transpose of the normal reconstruction: this thread's column and variables. Face f reaches cells
+            // f-3 .. f+1 through q^L, f-2 .. f+2 through q^R and f-2 .. f+1 through D; cell f-3 is then complete
+            if (col) {
+                const double ihf = a.ihf[f] * (1.0 / 12.0);
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {
+                    const double* const fb = s_fb + ((3 * (cv + v)) * X2) * EXT1 + ct;
+                    const double bL = fb[0], bR = fb[X2 * EXT1], bD = fb[2 * X2 * EXT1] * ihf;
+                    double right, left, wr[3], wl[3], cR[NW];
+                    weno_faces_w<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, right, left, wr, wl);
+                    weno_coefs<EXACT>(1, ring[v], eps, wl, left, cR);
+#pragma unroll
+                    for (int r = 0; r < 5; ++r) {
+                        cell[v][r] += wcoef<EXACT>(0, coefL[v], r) * bL;
+                        cell[v][1 + r] += wcoef<EXACT>(1, cR, r) * bR;
+                    }
+                    cell[v][1] += bD;
+                    cell[v][2] -= 15.0 * bD;
+                    cell[v][3] += 15.0 * bD;
+                    cell[v][4] -= bD;
+                    weno_coefs<EXACT>(0, ring[v], eps, wr, right, coefL[v]);
+                    slab[(long long)(f - f0) * ADJ_CELL + (cv + v) * (X2 * EXT1) + ct] = cell[v][0];
+#pragma unroll
+                    for (int r = 0; r < 5; ++r) cell[v][r] = cell[v][r + 1];
+                    cell[v][5] = 0.0;
+                }
+            }
+            // the next face rewrites s_nrm at once (last read before the barrier) and s_fb after two barriers
         }
+        if (col)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int r = 0; r < 5; ++r)
+                    slab[(long long)(f1 - f0 + r) * ADJ_CELL + (cv + v) * (X2 * EXT1) + ct] = cell[v][r];
     }
 }
 
 // ------------------------------------------------------------------------------------------------
-// pass D: transpose of the normal reconstruction -> padded cell adjoint (accumulated)
+// Sum of the tiles' and marches' shares into the padded cell adjoint (accumulated). A workgroup takes 32 t1
+// positions x 32 cells of the normal for one t2 position and variable: read along t1 (the slabs' fastest index),
+// written along the axis of unit stride (the normal in the x direction) through LDS.
 // ------------------------------------------------------------------------------------------------
-constexpr int N_CHUNK = 32;  // consecutive cells along the normal per thread in pass D
-
-template <bool EXACT>
-__global__ void __launch_bounds__(256) adj_normal_kernel(const AdjFaceArgs a) {
-    constexpr int NW = EXACT ? 5 : 2;
-    // one thread per (tangential position incl. halo, variable, chunk of N_CHUNK cells along the
-    // normal); the t1 position is the fastest index. The thread walks its cells in order with the six
-    // faces f = i-2 .. i+3 that reach cell i in registers (slot s holds face i-2+s), loading each face
-    // once, and sums per cell the q^L terms, then the q^R terms, then the D terms, each in ascending f.
-    // The coefficients of the normal WENO evaluations are rebuilt from the field as the recompute's
-    // column march formed them: the evaluation on cell c (stencil c-2 .. c+2) gives q^R of face c and
-    // q^L of face c+1, so a five-cell window and the carried q^L coefficients suffice.
-    const int ncell = a.n_n + 6;  // padded cells i = -3 .. n_n + 2
-    const int nchunk = (ncell + N_CHUNK - 1) / N_CHUNK;
-    const long long total = (long long)nchunk * 4 * (a.n_t2 + 4) * (a.n_t1 + 4);
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    const int jx = (int)(t % (a.n_t1 + 4)) - 2;
-    long long r_ = t / (a.n_t1 + 4);
-    const int v = (int)(r_ % 4);
-    r_ /= 4;
-    const int kx = (int)(r_ % (a.n_t2 + 4)) - 2;
-    const int c = (int)(r_ / (a.n_t2 + 4));
-    const int i_lo = -3 + c * N_CHUNK, i_hi = min(i_lo + N_CHUNK, a.n_n + 3);
-    // the tiles whose columns (with their two-cell halo) hold this one, ascending: partial sums of pass A
-    constexpr int X2 = AdjTile::T2 + 4, SLAB = 12 * X2 * EXT1;
-    const double* part[4];
-    bool has[4];
+__global__ void __launch_bounds__(256) adj_sum_kernel(const AdjFaceArgs a) {
+    constexpr int X2 = AdjTile::T2 + 4;
+    __shared__ double s_t[32][33];
+    const int nt1 = (a.n_t1 + 4 + 31) / 32, nn = (a.n_n + 6 + 31) / 32;
+    int b = blockIdx.x;
+    const int jx0 = (b % nt1) * 32 - 2;
+    b /= nt1;
+    const int i0 = (b % nn) * 32 - 3;
+    b /= nn;
+    const int v = b % 4, kx = b / 4 - 2;
+    const int lane = threadIdx.x & 31, row = threadIdx.x >> 5;
+    const int nf = a.n_n + 1;
     {
+        const int jx = jx0 + lane;
+        // the tiles whose columns hold (jx, kx), ascending
         const int T1 = (jx + 2) / TILE1, c1 = (jx + 2) % TILE1, T2 = (kx + 2) / AdjTile::T2, c2 = (kx + 2) % AdjTile::T2;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int d1 = 1 - (e & 1), d2 = 1 - (e >> 1);  // the tile before, then the column's own
-            const int t1 = T1 - d1, t2 = T2 - d2, x1 = c1 + TILE1 * d1, x2 = c2 + AdjTile::T2 * d2;
-            has[e] = t1 >= 0 && t1 < a.tiles_t1 && x1 < EXT1 && t2 >= 0 && t2 < a.tiles_t2 && x2 < X2;
-            part[e] = a.fabar + (has[e] ? (long long)(t2 * a.tiles_t1 + t1) * (a.n_n + 1) * SLAB +
-                                              3 * v * (X2 * EXT1) + x2 * EXT1 + x1
-                                        : 0);
-        }
-    }
-    const long long colq = a.pad0 + (long long)jx * a.st_t1 + (long long)kx * a.st_t2;
-    auto cell = [&](int i) -> double { return (i >= -3 && i < a.n_n + 3) ? a.q[v][colq + (long long)i * a.st_n] : 0.0; };
-    double wl[6][NW], wr[6][NW], fb[6][3];
-    bool ok[6];
-    // the next face to enter the window, the field cells fn-2 .. fn+2 and the q^L coefficients of face fn
-    int fn = i_lo - 2;
-    double win[5], carryL[NW];
-    {
-        double s5[5];
-#pragma unroll
-        for (int r = 0; r < 5; ++r) s5[r] = cell(fn - 3 + r);
-        double right, left, w_r[3], w_l[3];
-        weno_faces_w<double>(s5[0], s5[1], s5[2], s5[3], s5[4], a.eps, right, left, w_r, w_l);
-        weno_coefs<EXACT>(0, s5, a.eps, w_r, right, carryL);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) win[r] = s5[r + 1];
-        win[4] = cell(fn + 2);
-    }
-    auto enter = [&](int s) {
-        ok[s] = fn >= 0 && fn <= a.n_n;
-        double right, left, w_r[3], w_l[3];
-        weno_faces_w<double>(win[0], win[1], win[2], win[3], win[4], a.eps, right, left, w_r, w_l);
-#pragma unroll
-        for (int kk = 0; kk < NW; ++kk) wl[s][kk] = carryL[kk];
-        weno_coefs<EXACT>(1, win, a.eps, w_l, left, wr[s]);
-        weno_coefs<EXACT>(0, win, a.eps, w_r, right, carryL);
-#pragma unroll
-        for (int q = 0; q < 3; ++q) fb[s][q] = 0.0;
-        if (ok[s]) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (has[e])
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) fb[s][q] += part[e][(long long)fn * SLAB + q * (X2 * EXT1)];
-        }
-        fb[s][2] *= a.ihf[min(max(fn, 0), a.n_n)];  // D's 1/h at face fn
-#pragma unroll
-        for (int r = 0; r < 4; ++r) win[r] = win[r + 1];
-        win[4] = cell(fn + 3);
-        ++fn;
-    };
-#pragma unroll
-    for (int s = 0; s < 6; ++s) enter(s);
-    const double cD[4] = {1.0 / 12.0, -15.0 / 12.0, 15.0 / 12.0, -1.0 / 12.0};
-    for (int i = i_lo; i < i_hi; ++i) {
-        double bar = 0.0;
-        // q^L(f) = sum_r W^L_f[r] Q(f-3+r): faces i-1 .. i+3 (slots 1..5), r = 5 - s
-#pragma unroll
-        for (int s = 1; s <= 5; ++s)
-            if (ok[s]) bar += wcoef<EXACT>(0, wl[s], 5 - s) * fb[s][0];
-        // q^R(f) = sum_r W^R_f[r] Q(f-2+r): faces i-2 .. i+2 (slots 0..4), r = 4 - s
-#pragma unroll
-        for (int s = 0; s <= 4; ++s)
-            if (ok[s]) bar += wcoef<EXACT>(1, wr[s], 4 - s) * fb[s][1];
-        // D(f) = (Q(f-2) - 15 Q(f-1) + 15 Q(f) - Q(f+1)) / (12 h_f): faces i-1 .. i+2 (slots 1..4), the
-        // 1/h_f already in fb
-#pragma unroll
-        for (int s = 1; s <= 4; ++s)
-            if (ok[s]) bar += cD[4 - s] * fb[s][2];
-        const long long q = a.pad0 + (long long)i * a.st_n + (long long)jx * a.st_t1 + (long long)kx * a.st_t2;
-        a.acc[v][q] += bar;
-        // slide the window: face i + 4 enters
-        if (i + 1 < i_hi) {
-#pragma unroll
-            for (int s = 0; s < 5; ++s) {
-                ok[s] = ok[s + 1];
-#pragma unroll
-                for (int kk = 0; kk < NW; ++kk) {
-                    wl[s][kk] = wl[s + 1][kk];
-                    wr[s][kk] = wr[s + 1][kk];
+        for (int s = 0; s < 4; ++s) {
+            const int i = i0 + row + 8 * s;
+            double sum = 0.0;
+            if (jx < a.n_t1 + 2 && i < a.n_n + 3) {
+                // marches whose faces reach cell i: faces i - 2 .. i + 3
+                const int m0 = max(i - 2, 0) / a.chunk, m1 = min(i + 3, a.n_n) / a.chunk;
+                for (int e = 0; e < 4; ++e) {
+                    const int d1 = 1 - (e & 1), d2 = 1 - (e >> 1);
+                    const int t1 = T1 - d1, t2 = T2 - d2, x1 = c1 + TILE1 * d1, x2 = c2 + AdjTile::T2 * d2;
+                    if (t1 < 0 || t1 >= a.tiles_t1 || x1 >= EXT1 || t2 < 0 || t2 >= a.tiles_t2 || x2 >= X2) continue;
+                    const long long tile = (long long)t2 * a.tiles_t1 + t1;
+                    for (int m = m0; m <= m1; ++m) {
+                        const int f0 = m * a.chunk, len = min(a.chunk, nf - f0), slot = i - (f0 - 3);
+                        if (slot < 0 || slot >= len + 5) continue;
+                        sum += a.slab[((tile * a.nch + m) * (a.chunk + 5) + slot) * ADJ_CELL + v * (X2 * EXT1) + x2 * EXT1 + x1];
+                    }
                 }
-#pragma unroll
-                for (int qq = 0; qq < 3; ++qq) fb[s][qq] = fb[s + 1][qq];
             }
-            enter(5);
+            s_t[row + 8 * s][lane] = sum;
         }
+    }
+    __syncthreads();
+    const bool along_n = a.st_n == 1;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int r = row + 8 * s;
+        const int i = i0 + (along_n ? lane : r), jx = jx0 + (along_n ? r : lane);
+        if (jx < a.n_t1 + 2 && i < a.n_n + 3)
+            a.acc[v][a.pad0 + (long long)i * a.st_n + (long long)jx * a.st_t1 + (long long)kx * a.st_t2] +=
+                s_t[i - i0][jx - jx0];
     }
 }
 
@@ -540,8 +506,9 @@ hipError_t launch_adj_passes(const AdjFaceArgs& a, int stage, hipStream_t s) {
     const dim3 fgrid((unsigned)pad8(a.n_wg)), fblock(AdjTile::THREADS);
     if (stage == 1) hipLaunchKernelGGL((adj_face_kernel<1, EXACT>), fgrid, fblock, 0, s, a);
     else hipLaunchKernelGGL((adj_face_kernel<2, EXACT>), fgrid, fblock, 0, s, a);
-    const long long nD = (long long)((a.n_n + 6 + N_CHUNK - 1) / N_CHUNK) * 4 * (a.n_t1 + 4) * (a.n_t2 + 4);
-    hipLaunchKernelGGL((adj_normal_kernel<EXACT>), dim3((unsigned)((nD + 255) / 256)), dim3(256), 0, s, a);
+    const long long blocks = (long long)((a.n_t1 + 4 + 31) / 32) * ((a.n_n + 6 + 31) / 32) * 4 * (a.n_t2 + 4);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(adj_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -906,6 +873,15 @@ hipError_t launch_alm_adjoint(const AlmAdjArgs& A, hipStream_t s) {
 // ------------------------------------------------------------------------------------------------
 // workspace
 // ------------------------------------------------------------------------------------------------
+AdjSplit adj_split(int n_n, int n_t1, int n_t2) {
+    AdjSplit s;
+    s.tiles_t1 = (n_t1 + TILE1 - 1) / TILE1;
+    s.tiles_t2 = (n_t2 + AdjTile::T2 - 1) / AdjTile::T2;
+    s.chunk = face_chunk(n_n + 1, s.tiles_t1 * s.tiles_t2, ADJ_SLOTS);
+    s.nch = (n_n + 1 + s.chunk - 1) / s.chunk;
+    return s;
+}
+
 void adjoint_carve(char* base, int nx, int ny, int nz, int n_act, AdjBuffers* b, size_t* total) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> char* {
@@ -922,12 +898,12 @@ void adjoint_carve(char* base, int nx, int ny, int nz, int n_act, AdjBuffers* b,
     for (int v = 0; v < 4; ++v) b->mu1[v] = reinterpret_cast<double*>(take(N * 8));
     const int n[3] = {nx, ny, nz};
     const int ax[3][3] = {{0, 1, 2}, {1, 0, 2}, {2, 0, 1}};
-    size_t slabs = 0;  // (tile, face) pairs of pass A
+    size_t cells = 0;  // (tile, march, cell) of the tile kernel's output
     for (int d = 0; d < 3; ++d) {
-        const size_t t1 = (n[ax[d][1]] + TILE1 - 1) / TILE1, t2 = (n[ax[d][2]] + AdjTile::T2 - 1) / AdjTile::T2;
-        slabs = std::max(slabs, t1 * t2 * (n[ax[d][0]] + 1));
+        const AdjSplit sp = adj_split(n[ax[d][0]], n[ax[d][1]], n[ax[d][2]]);
+        cells = std::max(cells, (size_t)sp.tiles_t1 * sp.tiles_t2 * sp.nch * (sp.chunk + 5));
     }
-    b->fabar = reinterpret_cast<double*>(take(slabs * 12 * (AdjTile::T2 + 4) * EXT1 * 8));
+    b->slab = reinterpret_cast<double*>(take(cells * ADJ_CELL * 8));
     b->pt = reinterpret_cast<double*>(take(16 * (size_t)std::max(n_act, 1) * 8));
     *total = off;
 }

@@ -71,7 +71,6 @@ struct gks_ctx {
     double lam, c, hmin, eps;
     int t2[3];         // t2 rows of a face tile, per direction
     int chunk[3];      // faces per workgroup of the face kernels, per direction
-    FaceSplit adj_split[3];  // work split of the adjoint's pass A
     int seg_len[3], n_wg[3];  // work split of the order-5 face launches (FaceArgs)
     int side_by_side;  // order 5: the three directions of a stage run in one launch (face_layout)
     int flags;
@@ -470,15 +469,16 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, void* const src[4],
         a.mu1[v] = B.mu1[gv];
         a.acc[v] = B.acc[gv];
     }
-    a.fabar = B.fabar;
+    a.slab = B.slab;
     a.n_n = c->g.n[ax[0]];
     a.n_t1 = c->g.n[ax[1]];
     a.n_t2 = c->g.n[ax[2]];
-    a.tiles_t1 = (a.n_t1 + TILE1 - 1) / TILE1;
-    a.tiles_t2 = (a.n_t2 + AdjTile::T2 - 1) / AdjTile::T2;
-    a.chunk = c->adj_split[d].chunk;
-    a.seg_len = c->adj_split[d].seg_len;
-    a.n_wg = (int)c->adj_split[d].n_wg;
+    const AdjSplit sp = adj_split(a.n_n, a.n_t1, a.n_t2);
+    a.tiles_t1 = sp.tiles_t1;
+    a.tiles_t2 = sp.tiles_t2;
+    a.chunk = sp.chunk;
+    a.nch = sp.nch;
+    a.n_wg = sp.tiles_t1 * sp.tiles_t2 * sp.nch;
     a.st_n = c->g.st[ax[0]];
     a.st_t1 = c->g.st[ax[1]];
     a.st_t2 = c->g.st[ax[2]];
@@ -582,12 +582,6 @@ void face_layout(gks_ctx* c) {
                 }
             }
         }
-        // the adjoint's pass A: the 8-row tiles, one workgroup per CU as well, n + 1 faces per tile
-        if (f64 && rows == AdjTile::T2)
-            for (int d = 0; d < 3; ++d) {
-                const FaceDir fd = {n[kAxes[d][0]] + 1, tiles(d, AdjTile::T2)};
-                face_split(&fd, 1, slots, &c->adj_split[d]);
-            }
     }
 }
 
