@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
         const int tile = b % tiles, f0 = (b / tiles) * a.chunk, f1 = min(f0 + a.chunk, nf);
         const int j0 = (tile % a.tiles_t1) * TILE1, k0 = (tile / a.tiles_t1) * T2;
         // columns outside the padded domain read a clamped column; their faces have zero seeds
-        const int jc = min(j0 - 2 + c1, a.n_t1 + NG - 1), kc = min(k0 - 2 + c2, a.n_t2 + NG - 1);
+        const int jc = min(j0 - 2 + c1, a.n_t1 + NG - 1), kc = min(k0 - 2 + min(c2, X2 - 1), a.n_t2 + NG - 1);
         const long long cbase = a.pad0 + (long long)jc * a.st_t1 + (long long)kc * a.st_t2;
         const bool face_ok = (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
         const int je = min(j0 + fj, a.n_t1 - 1), ke = min(k0 + fk, a.n_t2 - 1);

@@ -137,7 +137,7 @@ __device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int bl
     // path leaves the compiler no merge of a loaded and a kept value, which would make it wait for the
     // load within the same step, and for the step's stores at the next one
     const long long cbase_ld = a.pad0 + (long long)min(jc, a.n_t1 + NG - 1) * a.st_t1 +
-                               (long long)min(kc, a.n_t2 + NG - 1) * a.st_t2;
+                               (long long)min(k0 - 2 + min(c2, X2 - 1), a.n_t2 + NG - 1) * a.st_t2;
     // face role: face (fj, fk) of the tile, Gauss line m (partner lane tid ^ 1 holds the other line)
     const int m = tid & 1;
     const int fj = (tid >> 1) % TILE1, fk = (tid >> 1) / TILE1;

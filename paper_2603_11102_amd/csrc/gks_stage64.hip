@@ -134,7 +134,7 @@ __device__ __forceinline__ void face64_march(const FaceArgs<double>& a, const in
         const int j0 = tile1 * TILE1, k0 = tile2 * T2;
         // columns outside the padded domain and threads without a column read a clamped column, whose
         // values reach no face of the domain
-        const int jc = min(j0 - 2 + c1, a.n_t1 + NG - 1), kc = min(k0 - 2 + c2, a.n_t2 + NG - 1);
+        const int jc = min(j0 - 2 + c1, a.n_t1 + NG - 1), kc = min(k0 - 2 + min(c2, X2 - 1), a.n_t2 + NG - 1);
         const long long cbase = a.pad0 + (long long)jc * a.st_t1 + (long long)kc * a.st_t2;
         const bool face_ok = (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
         const int je = min(j0 + fj, a.n_t1 - 1), ke = min(k0 + fk, a.n_t2 - 1);
