@@ -61,6 +61,7 @@ struct gks_ctx {
     double* diag_partials;
     int diag_nblk;
     double* umax_part;  // per-workgroup maxima of |U|^2 for the CFL time step
+    int umax_fused;     // formed by the ghost fill (order 5, where they fit), else by a kernel of their own
     // per-axis inverse spacings in the stage precision (face spacings [n + 1], widths [n]) and FP64
     // relative widths; stretched: some axis has its own faces
     void* ihf[3];
@@ -158,6 +159,7 @@ struct Layout {
     void* lo[3];
     double* diag;
     double* umax_part;
+    int umax_cap;
     char* alm;
     char* ibm;
     size_t total;
@@ -221,11 +223,16 @@ bool layout(const gks_config* c, char* base, Layout* L) {
     for (int v = 0; v < 4; ++v) L->qt[v] = cv.ptr<void>(NP * es);
     for (int b = 0; b < 3; ++b) L->lo[b] = c->precision == GKS_FP32 ? cv.ptr<void>(4 * N * es) : nullptr;
     L->diag = cv.ptr<double>(sizeof(double) * 4 * 1024);
-    L->umax_part = cv.ptr<double>(sizeof(double) * UMAX_BLOCKS);
     size_t ab = alm_block_bytes(c->max_act);
     L->alm = ab ? cv.ptr<char>(ab) : nullptr;
     size_t ib = ibm_block_bytes(c->max_ibm);
     L->ibm = ib ? cv.ptr<char>(ib) : nullptr;
+    // a partial maximum per workgroup of the ghost fill; where the workspace could be the static scratch, no more
+    // than that has always held
+    L->umax_cap = UMAX_BLOCKS;
+    if (c->order != 2 && cv.off + sizeof(double) * UMAX_BLOCKS > GKS_STATIC_SCRATCH_BYTES)
+        L->umax_cap = std::max(UMAX_BLOCKS, ghost_parts(n));
+    L->umax_part = cv.ptr<double>(sizeof(double) * L->umax_cap);
     L->total = cv.off;
     return true;
 }
@@ -568,7 +575,8 @@ void face_layout(gks_ctx* c) {
             if (scheme == 0) {
                 t = step * (face_split(dir, 2, slots, sp) + face_split(dir + 2, 1, slots, sp + 2)) + 2 * FACE_LAUNCH;
             } else {
-                t = step * face_split(dir, 3, slots, sp) + FACE_LAUNCH + COMBINE_LAUNCH +
+                // eight slots are left to the workgroup that forms the time step
+                t = step * face_split(dir, 3, slots - 8, sp) + FACE_LAUNCH + COMBINE_LAUNCH +
                     (f64 ? COMBINE_CELL64 : COMBINE_CELL32) * cells;
             }
             if (best < 0.0 || t < best) {
@@ -628,13 +636,24 @@ Face2Args<real> face2_args(gks_ctx* c, int stage, void* const src[4]) {
     return a;
 }
 
-// Ghost cells of a stage input and, for the high-order x pass, its [x][z][y] copy.
+// Ghost cells of a stage input and, for the high-order x pass, its [x][z][y] copy (and, umax, the partial maxima
+// of |U|^2).
 template <typename real>
-hipError_t stage_ghosts(gks_ctx* c, void* const p[4]) {
+hipError_t stage_ghosts(gks_ctx* c, void* const p[4], bool umax) {
     if (c->cfg.order == 2)
         return launch_ghost_shell<real>(field<real>(p), c->g, c->cfg.bc, c->cfg.u_in, c->c, c->cfg.rho_ref, c->stream);
     return launch_ghost_transpose<real>(field<real>(p), field<real>(c->qt), c->g, c->cfg.bc, c->cfg.u_in, c->c,
-                                        c->cfg.rho_ref, c->stream);
+                                        c->cfg.rho_ref, umax && c->umax_fused ? c->umax_part : nullptr, c->stream);
+}
+
+DtArgs dt_args(const gks_ctx* c) {
+    const int parts = c->umax_fused ? ghost_parts(c->g.n) : umax_parts(c->g.n);
+    return DtArgs{c->st, c->umax_part, parts, c->cfg.cfl, c->hmin, c->c, c->cfg.dt_fixed};
+}
+
+// Whether the stage-2 update is the last launch that a step's bookkeeping waits for.
+bool update_ends_step(const gks_ctx* c) {
+    return !c->has_rotor && !c->has_ibm && !(c->hist_buf && c->hist_n < c->hist_cap);
 }
 
 // The face passes and the stage update of one stage.
@@ -642,15 +661,18 @@ template <typename real>
 int stage_faces(gks_ctx* c, int stage, void* const src[4], const int cat[3]) {
     if (c->cfg.order == 2) {
         const int tp = tbeg(c, cat[0], cat[1], cat[2]);
-        HIPCHK(c, launch_stage2<real>(face2_args<real>(c, stage, src), stage, c->stream));
+        Face2Args<real> a = face2_args<real>(c, stage, src);
+        a.finish = stage == 2 && update_ends_step(c) ? c->st : nullptr;
+        HIPCHK(c, launch_stage2<real>(a, stage, c->stream));
         tend(c, tp);
         return GKS_OK;
     }
     FaceArgs<real> a[3];
     for (int d = 0; d < 3; ++d) a[d] = face_args<real>(c, d, stage, src);
+    a[2].finish = stage == 2 && update_ends_step(c) ? c->st : nullptr;
     if (c->side_by_side) {
         const int tp = tbeg(c, cat[0], cat[1], cat[2]);
-        HIPCHK(c, launch_face_xyz<real>(a[0], a[1], a[2], stage, c->stream));
+        HIPCHK(c, launch_face_xyz<real>(a[0], a[1], a[2], dt_args(c), stage, c->stream));
         HIPCHK(c, launch_combine<real>(a[2], c->g, stage, c->stream));
         tend(c, tp);
     } else {
@@ -684,12 +706,13 @@ int steps(gks_ctx* c, int nsteps) {
             c->ckpt_n++;
         }
         tp = tbeg(c, GKS_TIMER_GHOST);
-        HIPCHK(c, stage_ghosts<real>(c, c->q));
+        HIPCHK(c, stage_ghosts<real>(c, c->q, c->cfg.cfl > 0));
         tend(c, tp);
+        // the time step; side by side, the stage-1 face launch forms it
         tp = tbeg(c, GKS_TIMER_DT);
-        if (c->cfg.cfl > 0) HIPCHK(c, launch_umax<real>(field<real>(c->q), c->g, c->cfg.rho_ref, c->umax_part, c->stream));
-        HIPCHK(c, launch_dt(c->st, c->umax_part, umax_blocks(c->g), c->cfg.cfl, c->hmin, c->c, c->cfg.dt_fixed,
-                            c->stream));
+        if (!c->umax_fused && c->cfg.cfl > 0)
+            HIPCHK(c, launch_umax<real>(field<real>(c->q), c->g, c->cfg.rho_ref, c->umax_part, c->stream));
+        if (!c->side_by_side) HIPCHK(c, launch_dt(dt_args(c), c->stream));
         tend(c, tp);
         int rc = stage_faces<real>(c, 1, c->q, cat1);
         if (rc) return rc;
@@ -699,7 +722,7 @@ int steps(gks_ctx* c, int nsteps) {
             tend(c, tp);
         }
         tp = tbeg(c, GKS_TIMER_GHOST);
-        HIPCHK(c, stage_ghosts<real>(c, c->qs));
+        HIPCHK(c, stage_ghosts<real>(c, c->qs, false));
         tend(c, tp);
         rc = stage_faces<real>(c, 2, c->qs, cat2);
         if (rc) return rc;
@@ -721,7 +744,7 @@ int steps(gks_ctx* c, int nsteps) {
         }
         tp = tbeg(c, GKS_TIMER_OTHER);
         double* hist = (c->hist_buf && c->hist_n < c->hist_cap) ? c->hist_buf + 10 * c->hist_n : nullptr;
-        HIPCHK(c, launch_finish(c->st, c->has_rotor, hist, c->stream));
+        if (!update_ends_step(c)) HIPCHK(c, launch_finish(c->st, c->has_rotor, hist, c->stream));
         if (hist) c->hist_n++;
         c->host_step++;
         if (c->stats_buf && c->host_step % c->stats_interval == 0) {
@@ -802,6 +825,8 @@ int gks_init(const gks_config* cfg, gks_field q, gks_field q_stage, gks_field q_
     c->lo_qa = L.lo[2];
     c->diag_partials = L.diag;
     c->umax_part = L.umax_part;
+    const int n_[3] = {cfg->nx, cfg->ny, cfg->nz};
+    c->umax_fused = cfg->order != 2 && ghost_parts(n_) <= L.umax_cap;
     c->alm_mem = reinterpret_cast<double*>(L.alm);
     c->ibm_mem = L.ibm;
     const int n[3] = {cfg->nx, cfg->ny, cfg->nz};
@@ -1235,7 +1260,7 @@ int gks_adjoint(gks_ctx* c, int32_t nsteps, const double w[2], double* grad_s, d
             HIPCHK(c, launch_copy_field(src + (8 + v) * fb, B.qpre[v], (size_t)np * 8, S));
         }
         HIPCHK(c, launch_copy_field(src + slot - 256, &c->st->t, sizeof(double), S));
-        HIPCHK(c, launch_dt(c->st, nullptr, 0, 0.0, c->hmin, c->c, dt, S));
+        HIPCHK(c, launch_dt(DtArgs{c->st, nullptr, 0, 0.0, c->hmin, c->c, dt}, S));
         int rc = ghost_all<double>(c, qwork);
         if (rc) return rc;
         rc = ghost_all<double>(c, c->qs);

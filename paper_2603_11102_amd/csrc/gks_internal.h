@@ -48,6 +48,64 @@ struct LocalOrder<5> : LocalOrder<4> {};  // the z pass that leaves its residual
 
 __host__ __device__ inline int pad8(int n) { return (n + 7) / 8 * 8; }
 
+// Device-resident scalars of a context (lives in the workspace).
+constexpr int UMAX_BLOCKS = 2048;  // workgroups of umax_kernel at most, and the least room for partial maxima
+
+struct DevState {
+    double t, dt, t_next;
+    long long step;
+    double thrust, torque, power, cp, ct;
+    double ibm_force[3];
+    unsigned long long ibm_res_bits;
+    double win_p, win_t;
+    long long win_n;
+    double mass, mom[3];
+    unsigned long long umax_diag_bits;
+    int nonfinite;
+    int ibm_iters_used;
+    int ibm_outside;  // a moving body's point support left the interior (sticky until new points)
+};
+
+// The time step's inputs (cfl <= 0: dt_fixed): partial maxima of |U|^2 and constants.
+struct DtArgs {
+    DevState* st;
+    const double* part;
+    int nparts;
+    double cfl, hmin, c, dt_fixed;
+};
+constexpr int DT_THREADS = 512;
+
+// dt = CFL h_min / (|U|_max + C) from the partial maxima, by one workgroup of N threads (max is order
+// independent, so the result is deterministic); red: N / 64 doubles of LDS.
+template <int N>
+__device__ __forceinline__ void dt_update(const DtArgs& a, double* red) {
+    double mx = 0.0;
+    if (a.cfl > 0.0)
+        for (int i = threadIdx.x; i < a.nparts; i += 8 * N) {  // eight loads in flight
+            double x[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) x[r] = a.part[min(i + r * N, a.nparts - 1)];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) mx = fmax(mx, x[r]);
+        }
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < N / 64; ++w) mx = fmax(mx, red[w]);
+    const double dt = a.cfl > 0.0 ? a.cfl * a.hmin / (sqrt(mx) + a.c) : a.dt_fixed;
+    a.st->dt = dt;
+    a.st->t_next = a.st->t + dt;
+    a.st->ibm_res_bits = 0ULL;
+}
+
+// Bookkeeping at the end of a step, by one thread: where no rotor or body follows the stage update, by that kernel.
+__device__ __forceinline__ void finish_step(DevState* st) {
+    st->t = st->t_next;
+    st->step += 1;
+    st->win_n += 1;
+}
+
 // Arguments of the per-direction face kernel. Arrays are in the face's LOCAL variable order
 // (rho', m_normal, m_t1, m_t2); the caller permutes the global pointers.
 template <typename real>
@@ -91,6 +149,7 @@ struct FaceArgs {
     FluxConst<real> fc;
     real g_global[3];                 // constant body force (x, y, z) for the stage-2 epilogue
     const double* dt_ptr;             // device dt of the current step
+    DevState* finish;                 // not null: this launch ends the step (finish_step)
     int mode;  // 3: x pass (write the blocked x arrays), 0: y pass (write the main arrays),
                // 4: z pass (add both, S2O4 stage update)
 };
@@ -116,6 +175,7 @@ struct Face2Args {
     FluxConst<real> fc;
     real g_global[3];
     const double* dt_ptr;
+    DevState* finish;     // not null: this launch ends the step (finish_step)
 };
 
 // Index of cell (x, y, z) in the blocked layout [z][y/16][x][y%16]: the x pass stores 16 consecutive y
@@ -123,24 +183,6 @@ struct Face2Args {
 __host__ __device__ inline long long rx_block_index(int x, int y, int z, int nx, int nyb) {
     return (((long long)z * nyb + (y >> 4)) * nx + x) * 16 + (y & 15);
 }
-
-// Device-resident scalars of a context (lives in the workspace).
-constexpr int UMAX_BLOCKS = 2048;  // partial maxima of |U|^2 per step (one per umax workgroup)
-
-struct DevState {
-    double t, dt, t_next;
-    long long step;
-    double thrust, torque, power, cp, ct;
-    double ibm_force[3];
-    unsigned long long ibm_res_bits;
-    double win_p, win_t;
-    long long win_n;
-    double mass, mom[3];
-    unsigned long long umax_diag_bits;
-    int nonfinite;
-    int ibm_iters_used;
-    int ibm_outside;  // a moving body's point support left the interior (sticky until new points)
-};
 
 struct GridDesc {
     int n[3];                 // interior cells x, y, z
@@ -163,8 +205,8 @@ hipError_t launch_face_xy(const FaceArgs<real>& ax, const FaceArgs<real>& ay, in
 template <typename real>
 hipError_t launch_face_z(const FaceArgs<real>& a, int stage, hipStream_t s);
 template <typename real>
-hipError_t launch_face_xyz(const FaceArgs<real>& ax, const FaceArgs<real>& ay, const FaceArgs<real>& az, int stage,
-                           hipStream_t s);
+hipError_t launch_face_xyz(const FaceArgs<real>& ax, const FaceArgs<real>& ay, const FaceArgs<real>& az,
+                           const DtArgs& dt, int stage, hipStream_t s);
 // resident workgroups of the order-5 face kernels with tiles of t2 rows
 template <typename real>
 int face_slots(int t2);
@@ -175,7 +217,7 @@ int face_slots(int t2);
     hipError_t launch_face_z<real>(const FaceArgs<real>& a, int stage, hipStream_t s);                          \
     template <>                                                                                                 \
     hipError_t launch_face_xyz<real>(const FaceArgs<real>& ax, const FaceArgs<real>& ay, const FaceArgs<real>& az, \
-                                     int stage, hipStream_t s);                                                 \
+                                     const DtArgs& dt, int stage, hipStream_t s);                               \
     template <>                                                                                                 \
     int face_slots<real>(int t2);
 GKS_FACE_DECL(float)
@@ -208,16 +250,17 @@ template <typename real>
 hipError_t launch_combine(const FaceArgs<real>& az, const GridDesc& g, int stage, hipStream_t s);
 template <typename real>
 hipError_t launch_umax(Field4<real> f, const GridDesc& g, double rho_ref, double* part, hipStream_t s);
-int umax_blocks(const GridDesc& g);
+// workgroups of ghost_transpose_kernel (one partial maximum each) and of umax_kernel
+int ghost_parts(const int n[3]);
+int umax_parts(const int n[3]);
 hipError_t launch_zero_words(void* p, size_t bytes, hipStream_t s);
 template <typename real>
 hipError_t launch_ghost_shell(Field4<real> q, const GridDesc& gd, const int bc[6], const double u_in[3], double c,
                               double rho_ref, hipStream_t s);
 template <typename real>
 hipError_t launch_ghost_transpose(Field4<real> q, Field4<real> qt, const GridDesc& gd, const int bc[6],
-                                  const double u_in[3], double c, double rho_ref, hipStream_t s);
-hipError_t launch_dt(DevState* st, const double* part, int nparts, double cfl, double hmin, double c,
-                     double dt_fixed, hipStream_t s);
+                                  const double u_in[3], double c, double rho_ref, double* part, hipStream_t s);
+hipError_t launch_dt(const DtArgs& a, hipStream_t s);
 hipError_t launch_finish(DevState* st, int has_rotor, double* hist, hipStream_t s);
 hipError_t launch_window_reset(DevState* st, hipStream_t s);
 template <typename real>

@@ -501,15 +501,22 @@ __global__ void __launch_bounds__(FACE_THREADS) face_xy_kernel(const FaceArgs<re
 template <typename real, int STAGE, bool STR>
 __global__ void __launch_bounds__(FACE_THREADS) face_z_kernel(const FaceArgs<real> a) {
     __shared__ FaceLds lds;
+    if (STAGE == 2 && a.finish && blockIdx.x == 0 && threadIdx.x == 0) finish_step(a.finish);
     face_march<real, STAGE, 4, STR>(a, blockIdx.x, pad8(a.n_wg), lds);
 }
 
 // all three directions in one launch, for grids that leave much of the chip idle in each (combine_kernel follows)
 template <typename real, int STAGE, bool STR>
 __global__ void __launch_bounds__(FACE_THREADS) face_xyz_kernel(const FaceArgs<real> ax, const FaceArgs<real> ay,
-                                                                const FaceArgs<real> az) {
+                                                                const FaceArgs<real> az, const DtArgs dt) {
     __shared__ FaceLds lds;
     const int nx = pad8(ax.n_wg), ny = pad8(ay.n_wg), blk = blockIdx.x;
+    if (STAGE == 1 && blk == (int)gridDim.x - 1) {
+        // one more workgroup forms the time step, which the stage update is the first to read
+        static_assert(sizeof(lds.nrm) >= sizeof(double) * (FACE_THREADS / 64), "LDS of dt_update");
+        dt_update<FACE_THREADS>(dt, reinterpret_cast<double*>(&lds.nrm));
+        return;
+    }
     if (blk < nx) face_march<real, STAGE, 3, STR>(ax, blk, nx, lds);
     else if (blk < nx + ny) face_march<real, STAGE, 0, STR>(ay, blk - nx, ny, lds);
     else face_march<real, STAGE, 5, STR>(az, blk - nx - ny, pad8(az.n_wg), lds);
@@ -622,11 +629,11 @@ hipError_t launch_face_z<float>(const FaceArgs<float>& a, int stage, hipStream_t
 
 template <>
 hipError_t launch_face_xyz<float>(const FaceArgs<float>& ax, const FaceArgs<float>& ay, const FaceArgs<float>& az,
-                                  int stage, hipStream_t s) {
+                                  const DtArgs& dt, int stage, hipStream_t s) {
     const bool str = ax.stretched != 0;
     const long long blocks = (long long)pad8(ax.n_wg) + pad8(ay.n_wg) + pad8(az.n_wg);
-    if (stage == 1) GKS_LAUNCH_STR(face_xyz_kernel, 1, blocks, ax, ay, az);
-    else GKS_LAUNCH_STR(face_xyz_kernel, 2, blocks, ax, ay, az);
+    if (stage == 1) GKS_LAUNCH_STR(face_xyz_kernel, 1, blocks + 1, ax, ay, az, dt);
+    else GKS_LAUNCH_STR(face_xyz_kernel, 2, blocks, ax, ay, az, dt);
 }
 
 }  // namespace gks

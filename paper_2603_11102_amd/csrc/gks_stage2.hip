@@ -63,6 +63,7 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
     __shared__ V4 s_fy[NF][O2Y + 1][O2X];
 
     const int tid = threadIdx.x;
+    if (STAGE == 2 && a.finish && blockIdx.x == 0 && tid == 0) finish_step(a.finish);
     // consecutive logical workgroups on the same XCD (grid padded to a multiple of 8)
     int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
     const int nch = (a.n[2] + a.chunk - 1) / a.chunk;

@@ -324,14 +324,19 @@ __global__ void __launch_bounds__(64 * T2) face64_xy_kernel(const FaceArgs<doubl
 template <int T2, int STAGE, bool STR>
 __global__ void __launch_bounds__(64 * T2) face64_z_kernel(const FaceArgs<double> a) {
     __shared__ Face64Lds<T2 + 4> lds;
+    if (STAGE == 2 && a.finish && blockIdx.x == 0 && threadIdx.x == 0) finish_step(a.finish);
     face64_march<T2, STAGE, 4, STR>(a, blockIdx.x, pad8(a.n_wg), lds);
 }
 
 template <int T2, int STAGE, bool STR>
 __global__ void __launch_bounds__(64 * T2) face64_xyz_kernel(const FaceArgs<double> ax, const FaceArgs<double> ay,
-                                                             const FaceArgs<double> az) {
+                                                             const FaceArgs<double> az, const DtArgs dt) {
     __shared__ Face64Lds<T2 + 4> lds;
     const int nx = pad8(ax.n_wg), ny = pad8(ay.n_wg), blk = blockIdx.x;
+    if (STAGE == 1 && blk == (int)gridDim.x - 1) {
+        dt_update<64 * T2>(dt, reinterpret_cast<double*>(&lds.nrm));
+        return;
+    }
     if (blk < nx) face64_march<T2, STAGE, 3, STR>(ax, blk, nx, lds);
     else if (blk < nx + ny) face64_march<T2, STAGE, 0, STR>(ay, blk - nx, ny, lds);
     else face64_march<T2, STAGE, 5, STR>(az, blk - nx - ny, pad8(az.n_wg), lds);
@@ -384,10 +389,10 @@ hipError_t launch_face_z<double>(const FaceArgs<double>& a, int stage, hipStream
 
 template <>
 hipError_t launch_face_xyz<double>(const FaceArgs<double>& ax, const FaceArgs<double>& ay, const FaceArgs<double>& az,
-                                   int stage, hipStream_t s) {
+                                   const DtArgs& dt, int stage, hipStream_t s) {
     const bool str = ax.stretched != 0;
-    const long long blocks = (long long)pad8(ax.n_wg) + pad8(ay.n_wg) + pad8(az.n_wg);
-    GKS_LAUNCH64(face64_xyz_kernel, ax.t2, blocks, ax, ay, az);
+    const long long blocks = (long long)pad8(ax.n_wg) + pad8(ay.n_wg) + pad8(az.n_wg) + (stage == 1 ? 1 : 0);
+    GKS_LAUNCH64(face64_xyz_kernel, ax.t2, blocks, ax, ay, az, dt);
 }
 
 }  // namespace gks

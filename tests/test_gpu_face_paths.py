@@ -68,3 +68,21 @@ def test_order2_stage_vs_oracle(case, grid, precision, bar):
     o, _ = run_oracle(cfg, 2)
     err = rel_errors(s.interior(), oracle_dev(o.Q, cfg.rho_ref))
     assert max(err) < bar, err
+
+
+@pytest.mark.parametrize("grid", [
+    (4, 3, 2100),   # more ghost-fill workgroups than a small workspace holds partial maxima: a pass of its own
+    (40, 33, 30),   # partial maxima from the ghost fill, the step formed beside the face launch
+    (70, 66, 50),   # the same with the step in a launch of its own
+])
+def test_time_step_and_bookkeeping_vs_oracle(grid):
+    cfg = make_case("channel", grid=grid)
+    print_case("time-step", grid=grid)
+    s, outs = run_gpu(cfg, "fp64", 2)
+    _, ref = run_oracle(cfg, 2)
+    for n, (a, b) in enumerate(zip(outs, ref)):
+        assert abs(a["dt"] - b["dt"]) < 1e-14 * b["dt"], (n, a["dt"], b["dt"])
+        assert abs(a["t"] - b["t"]) < 1e-14 * b["t"]
+        assert a["step"] == n + 1 and a["window_steps"] == n + 1
+    s.step(3)
+    assert s.forces()["step"] == 5
