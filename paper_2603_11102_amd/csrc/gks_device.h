@@ -158,6 +158,22 @@ __device__ __forceinline__ void quartic_gauss_deriv(real qm2, real qm1, real q0,
     dp = ev + od;
 }
 
+// The same with the coefficients scaled by the inverse width ih beforehand: three multiplications less, and on a
+// uniform mesh the coefficients stay in scalar registers.
+template <typename real>
+struct QuarticDeriv {
+    real e2, e1, o2, o1, o0;
+    __device__ __forceinline__ explicit QuarticDeriv(real ih)
+        : e2(real(1.0 / 12.0) * ih), e1(real(2.0 / 3.0) * ih), o2(real(-GKS_SQRT3 / 54.0) * ih),
+          o1(real(GKS_SQRT3 * 13.0 / 54.0) * ih), o0(real(-GKS_SQRT3 * 4.0 / 9.0) * ih) {}
+    __device__ __forceinline__ void operator()(real qm2, real qm1, real q0, real qp1, real qp2, real& dm, real& dp) const {
+        const real ev = e2 * (qm2 - qp2) + e1 * (qp1 - qm1);
+        const real od = o2 * (qm2 + qp2) + (o1 * (qm1 + qp1) + o0 * q0);
+        dm = ev - od;
+        dp = ev + od;
+    }
+};
+
 // erf(a) - erf(b) without cancellation when a ~ b in FP32: three-point Gauss-Legendre quadrature of
 // (2/sqrt(pi)) exp(-t^2) over [b, a] (relative error < 2e-8 for |a - b| < 1/4).
 template <typename real>
@@ -272,7 +288,7 @@ struct FluxConst {
 
 // Gas-kinetic flux at one Gauss point, in the face's local frame: variables (rho', m_n, m_t1, m_t2),
 // derivative directions (n, t1, t2). qL, qR: reconstructed left/right states; g[d][v]: dQ_v/dx_d.
-// Adds F0 (if NEED_F0) and F1 to f0, f1 (the caller applies the quadrature weight to the sum).
+// Gives F0 (if NEED_F0) and F1 (the caller sums them and applies the quadrature weight).
 // SHIFT: qL[1], qR[1] hold m_n - cm for a constant cm, and the mass-flux part of f0 receives F0 - cm
 // (the constant cancels in the flux difference of a cell). The half-space weights satisfy
 // hL + hR - 1 = (erf(aL) - erf(aR)) / 2, so the shifted mass flux carries no O(cm) rounding.
@@ -301,10 +317,10 @@ __device__ __forceinline__ void gp_flux(const real qL[4], const real qR[4], cons
         const real s00 = real(2) * (g[0][1] - U[0] * g[0][0]);
         const real s01 = (g[0][2] + g[1][1]) - U[1] * g[0][0] - U[0] * g[1][0];
         const real s02 = (g[0][3] + g[2][1]) - U[2] * g[0][0] - U[0] * g[2][0];
-        f0[0] += mass_flux;
-        f0[1] += (m0[0] * U[0] + k.c2 * rho0p) - mi * s00;
-        f0[2] += m0[0] * U[1] - mi * s01;
-        f0[3] += m0[0] * U[2] - mi * s02;
+        f0[0] = mass_flux;
+        f0[1] = (m0[0] * U[0] + k.c2 * rho0p) - mi * s00;
+        f0[2] = m0[0] * U[1] - mi * s01;
+        f0[3] = m0[0] * U[2] - mi * s02;
     }
     // Euler time derivative of Q0. Its advection term needs no velocity gradient:
     // rho0 (U . grad) U_j = sum_d U_d dm_j/dx_d - U_j sum_d U_d drho/dx_d.
@@ -315,10 +331,10 @@ __device__ __forceinline__ void gp_flux(const real qL[4], const real qR[4], cons
     for (int j = 0; j < 3; ++j)
         qd[j] = U[j] * H - (U[0] * g[0][1 + j] + (U[1] * g[1][1 + j] + (U[2] * g[2][1 + j] + k.c2 * g[j][0])));
     const real tn = qd[0] - U[0] * qd0;  // rho0 dU_n/dt
-    f1[0] += qd[0];
-    f1[1] += U[0] * (qd[0] + tn) + k.c2 * qd0;
-    f1[2] += U[1] * tn + U[0] * qd[1];
-    f1[3] += U[2] * tn + U[0] * qd[2];
+    f1[0] = qd[0];
+    f1[1] = U[0] * (qd[0] + tn) + k.c2 * qd0;
+    f1[2] = U[1] * tn + U[0] * qd[1];
+    f1[3] = U[2] * tn + U[0] * qd[2];
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -93,9 +93,6 @@ __device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int bl
     using real2 = typename Vec2<real>::type;
     constexpr int LOC[4] = {LocalOrder<MODE>::v[0], LocalOrder<MODE>::v[1], LocalOrder<MODE>::v[2],
                             LocalOrder<MODE>::v[3]};
-    // PAIR_PREV: the stage-1 z pass, which sits at the register limit, keeps only its lane's two
-    // variables of the previous face's fluxes (the other passes keep all four: fewer selects per step).
-    constexpr bool PAIR_PREV = (MODE == 4 && STAGE == 1);
     auto& s_nrm = lds.nrm;
     auto& s_t1 = lds.t1;
 
@@ -211,15 +208,15 @@ __device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int bl
         for (int v = 0; v < 4; ++v) nxt[v] = a.q[v][idx];
     }
     const real dt = real(*a.dt_ptr);
-    // the previous face's fluxes: all four variables, or (PAIR_PREV) only this lane's two
-    real fprev0[4] = {0, 0, 0, 0}, fprev1[4] = {0, 0, 0, 0};
+    // the previous face's fluxes of this lane's two variables
     real2 pprev0 = {0, 0}, pprev1 = {0, 0};
 
     const bool hi = m != 0;
     // tangential inverse widths, loaded once (a vector load inside the march would make the wait for
-    // it also wait for the column prefetch): t2 of this thread's face line; t1 of its t1-phase items,
-    // whose t1 position is tid % TILE1 for every item
-    const real ih2 = STR ? a.ih2[min(k0 + fk, a.n_t2 - 1)] : a.inv_h2;
+    // it also wait for the column prefetch): t2 of this thread's face line, as scaled coefficients (in the t1
+    // phase these cost more registers than they save: z pass 4 -> 11 spilled, 0.6 % slower); t1 of its t1-phase
+    // items, whose t1 position is tid % TILE1 for every item
+    const QuarticDeriv<real> qd2(STR ? a.ih2[min(k0 + fk, a.n_t2 - 1)] : a.inv_h2);
     const real ih1 = STR ? a.ih1[min(j0 + tid % TILE1, a.n_t1 - 1)] : a.inv_h1;
     // epilogue operands (z pass) of cell f - 1
     struct Epi {
@@ -346,16 +343,16 @@ __device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int bl
             quartic_gauss_value<real>(y[3][0], y[3][1], y[3][2], y[3][3], y[3][4], vm, vp);
             gp[v][0][3] = vm;
             gp[v][1][3] = vp;
-            quartic_gauss_deriv<real>(y[4][0], y[4][1], y[4][2], y[4][3], y[4][4], vm, vp);
-            gp[v][0][4] = vm * ih2;
-            gp[v][1][4] = vp * ih2;
+            qd2(y[4][0], y[4][1], y[4][2], y[4][3], y[4][4], vm, vp);
+            gp[v][0][4] = vm;
+            gp[v][1][4] = vp;
         }
 
         // ---- flux at this thread's two Gauss points (their quadrature weight 1/4 is part of the divergence)
-        real fa0[4] = {0, 0, 0, 0}, fa1[4] = {0, 0, 0, 0};
+        real fa0[4], fa1[4];
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
-            real qL[4], qR[4], g[3][4];
+            real qL[4], qR[4], g[3][4], f0n[4], f1n[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 qL[v] = gp[v][n][0];
@@ -364,24 +361,26 @@ __device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int bl
                 g[1][v] = gp[v][n][3];
                 g[2][v] = gp[v][n][4];
             }
-            gp_flux<real, NEED_F0, true>(qL, qR, g, a.fc, fa0, fa1, cm);
-        }
+            gp_flux<real, NEED_F0, true>(qL, qR, g, a.fc, f0n, f1n, cm);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            fa1[v] += pair_swap(fa1[v]);
-            if (NEED_F0) fa0[v] += pair_swap(fa0[v]);
+            for (int v = 0; v < 4; ++v) {
+                fa1[v] = n == 0 ? f1n[v] : fa1[v] + f1n[v];
+                if (NEED_F0) fa0[v] = n == 0 ? f0n[v] : fa0[v] + f0n[v];
+            }
         }
-        // this lane's two variables of the face fluxes: global variables 2m and 2m + 1, local indices
-        // LOC[2m], LOC[2m + 1], picked by value with a per-lane select between compile-time indices
-        // (indexing a register array with the lane-dependent index would move it to scratch)
-        auto lane_pair = [&](const real (&x)[4]) -> real2 {
+        // sum with the partner lane, scattered: lane m keeps the global variables 2m and 2m + 1 (local indices
+        // LOC[2m], LOC[2m + 1]) and sends the other two, picked by value with a per-lane select between
+        // compile-time indices (indexing a register array with the lane-dependent index would move it to scratch).
+        // Against all four sums in both lanes, with the selects after them: 12 of 456 instructions and 10 registers
+        // less (192x96x96, with the scaled t2 coefficients: 2.0 % of the step).
+        auto pair_sum = [&](const real (&x)[4]) -> real2 {
             real2 r;
-            r.x = pick(hi, x[LOC[2]], x[LOC[0]]);
-            r.y = pick(hi, x[LOC[3]], x[LOC[1]]);
+            r.x = pick(hi, x[LOC[2]], x[LOC[0]]) + pair_swap(pick(hi, x[LOC[0]], x[LOC[2]]));
+            r.y = pick(hi, x[LOC[3]], x[LOC[1]]) + pair_swap(pick(hi, x[LOC[1]], x[LOC[3]]));
             return r;
         };
-        const real2 fcur1 = lane_pair(fa1);
-        const real2 fcur0 = NEED_F0 ? lane_pair(fa0) : real2{0, 0};
+        const real2 fcur1 = pair_sum(fa1);
+        const real2 fcur0 = NEED_F0 ? pair_sum(fa0) : real2{0, 0};
         if (f > f0 && face_ok) {
             const int cell = f - 1;
             const long long ridx = (long long)cell * a.ist_n + (long long)(j0 + fj) * a.ist_t1 +
@@ -395,13 +394,11 @@ __device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int bl
             // lane-dependent index would fetch pointers from memory and move the arrays to scratch.
             real2 d1, d0;
             const real ihc = real(0.25) * (STR ? a.ihc[cell] : a.inv_hn);  // 1/4: weight of a Gauss point
-            const real2 prev1 = PAIR_PREV ? pprev1 : lane_pair(fprev1);
-            d1.x = -(fcur1.x - prev1.x) * ihc;
-            d1.y = -(fcur1.y - prev1.y) * ihc;
+            d1.x = (pprev1.x - fcur1.x) * ihc;
+            d1.y = (pprev1.y - fcur1.y) * ihc;
             if (NEED_F0) {
-                const real2 prev0 = PAIR_PREV ? pprev0 : lane_pair(fprev0);
-                d0.x = -(fcur0.x - prev0.x) * ihc;
-                d0.y = -(fcur0.y - prev0.y) * ihc;
+                d0.x = (pprev0.x - fcur0.x) * ihc;
+                d0.y = (pprev0.y - fcur0.y) * ihc;
             } else {
                 d0.x = d0.y = real(0);
             }
@@ -452,16 +449,8 @@ __device__ __forceinline__ void face_march(const FaceArgs<real>& a, const int bl
                 if (NEED_F0) st2(a.lo_b, ridx, m, lb);
             }
         }
-        if constexpr (PAIR_PREV) {
-            pprev1 = fcur1;
-            if (NEED_F0) pprev0 = fcur0;
-        } else {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                fprev1[v] = fa1[v];
-                if (NEED_F0) fprev0[v] = fa0[v];
-            }
-        }
+        pprev1 = fcur1;
+        if (NEED_F0) pprev0 = fcur0;
     };
     // software pipeline over two LDS buffers with one barrier per face: the face step of f reads
     // s_t1[buf], the t1 phase of f + 1 reads s_nrm[buf ^ 1] and writes s_t1[buf ^ 1], the column

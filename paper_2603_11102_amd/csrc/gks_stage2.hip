@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
         const V4 p1a = at(-1, 1, 0), p1b = at(0, 1, 0), m1a = at(-1, -1, 0), m1b = at(0, -1, 0);
         const V4 p2a = at(-1, 0, 1), p2b = at(0, 0, 1), m2a = at(-1, 0, -1), m2b = at(0, 0, -1);
         auto get = [](const V4& x, int v) { return v == 0 ? x.x : v == 1 ? x.y : v == 2 ? x.z : x.w; };
-        real qL[4], qR[4], g[3][4], f0[4] = {0, 0, 0, 0}, f1[4] = {0, 0, 0, 0};
+        real qL[4], qR[4], g[3][4], f0[4], f1[4];
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
             const int v = kLocal[D][l];

@@ -258,7 +258,7 @@ __device__ __forceinline__ void face64_march(const FaceArgs<double>& a, const in
                     w[v][q] = dpp<ROW_SHR4, BANK_H1>(gp[v][0][q], gp[v][1][q]);
                     w[2 + v][q] = dpp<ROW_SHL4, BANK_H0>(gp[v][1][q], gp[v][0][q]);
                 }
-            double fa0[4] = {0, 0, 0, 0}, fa1[4] = {0, 0, 0, 0};
+            double fa0[4], fa1[4];
             {
                 double qL[4], qR[4], g[3][4];
 #pragma unroll
