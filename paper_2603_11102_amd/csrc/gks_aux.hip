@@ -159,26 +159,39 @@ __device__ __forceinline__ void ghost_transform(real v[4], int axis, int side, i
 
 // part (when not null): each workgroup's maximum of |U|^2 over its interior cells, for the CFL time step (a
 // pass of its own over the field took 8.5 us on the 192 x 96 x 96 channel, 66 us on 384 x 192 x 192).
+//
+// Tiles of 32 x 32 cells, two cells a thread: on small grids a tile's chain of loads, boundary transforms and
+// stores is what the launch takes (32^3 boxes: 256 threads of four cells each made the FP32 step 3.1 us and the
+// FP64 step 2.7 us longer, 48.1 and 78.0 us; 1024 threads gain 0.4 us there and lose 0.9 % on 192 x 96 x 96). On
+// large grids it is bound by memory, 32 B (FP32) or 64 B a cell, and by the lines that rows of X and Y cells share
+// at their ends: x runs fastest and neighbouring workgroups go to one XCD, so that both parts of such a line
+// meet in its L2 (z fastest: 384 x 192 x 192 FP32 0.7 %, 192 x 96 x 96 1.1 % of the step). Tiles of 64 x 64 are no
+// faster there (0.3 %, and 4 % slower on 32^3), tiles of 16 rows 2 % slower.
+constexpr int GHOST_TILE = 32, GHOST_THREADS = 512;
+
 template <typename real>
-__global__ void __launch_bounds__(256) ghost_transpose_kernel(Field4<real> q, Field4<real> qt, GhostAll G, double* part) {
-    __shared__ real t[4][32][33];
-    __shared__ double s_max[4];
+__global__ void __launch_bounds__(GHOST_THREADS) ghost_transpose_kernel(Field4<real> q, Field4<real> qt, GhostAll G,
+                                                                        double* part, int n_wg) {
+    constexpr int T = GHOST_TILE, RS = GHOST_THREADS / T, NR = T / RS;
+    __shared__ real t[4][T][T + 1];
+    __shared__ double s_max[GHOST_THREADS / 64];
     double mx = 0.0;
     const int X = G.n[0] + 6, Y = G.n[1] + 6, Z = G.n[2] + 6;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    // z is the fastest grid index: consecutive workgroups write neighbouring z rows of the [x][z][y]
-    // copy (10 % faster than x-fastest tiles on the 192 x 96 x 96 channel)
-    const int x0 = blockIdx.y * 32, y0 = blockIdx.z * 32, z = blockIdx.x;
+    const int tx = threadIdx.x % T, ty = threadIdx.x / T;
+    const int blk = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (blk >= n_wg) return;
+    const int nx = (X + T - 1) / T;
+    const int x0 = blk % nx * T, z = blk / nx % Z, y0 = blk / nx / Z * T;
     // every lane finds the cell its value comes from (itself inside the domain, the interior source of
-    // a ghost cell) and all 16 loads are issued before any is used; cells outside the padded block read
+    // a ghost cell) and all its loads are issued before any is used; cells outside the padded block read
     // cell 0 and are not used
-    int sd[4][3];
-    long long src[4], dst[4];
-    bool in[4], gh[4];
+    int sd[NR][3];
+    long long src[NR], dst[NR];
+    bool in[NR], gh[NR];
     const int sk = ghost_source(z - 3, G.n[2], G.bc_lo[2], G.bc_hi[2], sd[0][2]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int x = x0 + tx, y = y0 + ty + 8 * i;
+    for (int i = 0; i < NR; ++i) {
+        const int x = x0 + tx, y = y0 + ty + RS * i;
         in[i] = x < X && y < Y;
         sd[i][2] = sd[0][2];
         const int si = ghost_source(x - 3, G.n[0], G.bc_lo[0], G.bc_hi[0], sd[i][0]);
@@ -187,13 +200,13 @@ __global__ void __launch_bounds__(256) ghost_transpose_kernel(Field4<real> q, Fi
         dst[i] = ((long long)z * Y + y) * X + x;
         src[i] = in[i] ? ((long long)(sk + 3) * Y + (sj + 3)) * X + (si + 3) : 0;
     }
-    real v[4][4];
+    real v[NR][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
         for (int w = 0; w < 4; ++w) v[i][w] = q.v[w][src[i]];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NR; ++i) {
         if (gh[i]) {
             for (int a = 0; a < 3; ++a)
                 if (sd[i][a] >= 0) ghost_transform(v[i], a, sd[i][a], sd[i][a] == 0 ? G.bc_lo[a] : G.bc_hi[a], G);
@@ -201,7 +214,7 @@ __global__ void __launch_bounds__(256) ghost_transpose_kernel(Field4<real> q, Fi
             for (int w = 0; w < 4; ++w) q.v[w][dst[i]] = v[i][w];
         }
 #pragma unroll
-        for (int w = 0; w < 4; ++w) t[w][ty + 8 * i][tx] = v[i][w];
+        for (int w = 0; w < 4; ++w) t[w][ty + RS * i][tx] = v[i][w];
         if (part && in[i] && !gh[i]) {
             const double rho = G.rho_ref + (double)v[i][0];
             const double mx_ = (double)v[i][1], my_ = (double)v[i][2], mz_ = (double)v[i][3];
@@ -214,13 +227,14 @@ __global__ void __launch_bounds__(256) ghost_transpose_kernel(Field4<real> q, Fi
         if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = mx;
     }
     __syncthreads();
-    if (part && threadIdx.x == 0)
-        part[((long long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] =
-            fmax(fmax(s_max[0], s_max[1]), fmax(s_max[2], s_max[3]));
+    if (part && threadIdx.x == 0) {
+        for (int w = 1; w < GHOST_THREADS / 64; ++w) mx = fmax(mx, s_max[w]);
+        part[blk] = mx;
+    }
 #pragma unroll
     for (int w = 0; w < 4; ++w)
 #pragma unroll
-        for (int r = ty; r < 32; r += 8) {
+        for (int r = ty; r < T; r += RS) {
             const int y = y0 + tx, x = x0 + r;
             if (x < X && y < Y) qt.v[w][((long long)x * Z + z) * Y + y] = t[w][tx][r];
         }
@@ -292,9 +306,8 @@ template <typename real>
 hipError_t launch_ghost_transpose(Field4<real> q, Field4<real> qt, const GridDesc& gd, const int bc[6],
                                   const double u_in[3], double c, double rho_ref, double* part, hipStream_t s) {
     const GhostAll G = ghost_args(gd, bc, u_in, c, rho_ref);
-    const int X = gd.n[0] + 6, Y = gd.n[1] + 6, Z = gd.n[2] + 6;
-    hipLaunchKernelGGL((ghost_transpose_kernel<real>), dim3(Z, (X + 31) / 32, (Y + 31) / 32), dim3(256), 0, s, q,
-                       qt, G, part);
+    const int n_wg = ghost_parts(gd.n);
+    hipLaunchKernelGGL((ghost_transpose_kernel<real>), dim3(pad8(n_wg)), dim3(GHOST_THREADS), 0, s, q, qt, G, part, n_wg);
     return hipGetLastError();
 }
 
@@ -392,7 +405,11 @@ hipError_t launch_combine(const FaceArgs<real>& az, const GridDesc& g, int stage
 }
 
 int umax_parts(const int n[3]) { return (int)std::min(((long long)n[0] * n[1] * n[2] + 255) / 256, (long long)UMAX_BLOCKS); }
-int ghost_parts(const int n[3]) { return (n[2] + 6) * ((n[0] + 6 + 31) / 32) * ((n[1] + 6 + 31) / 32); }
+// workgroups of the ghost fill
+int ghost_parts(const int n[3]) {
+    constexpr int T = GHOST_TILE;
+    return (n[2] + 6) * ((n[0] + 6 + T - 1) / T) * ((n[1] + 6 + T - 1) / T);
+}
 
 template <typename real>
 hipError_t launch_umax(Field4<real> f, const GridDesc& g, double rho_ref, double* part, hipStream_t s) {
