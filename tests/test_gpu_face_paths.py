@@ -86,3 +86,18 @@ def test_time_step_and_bookkeeping_vs_oracle(grid):
         assert a["step"] == n + 1 and a["window_steps"] == n + 1
     s.step(3)
     assert s.forces()["step"] == 5
+
+
+@pytest.mark.parametrize("precision,bar", [("fp64", 1e-12), ("fp32", 1e-5)])
+@pytest.mark.parametrize("case,grid", [
+    ("tgv", (26, 27, 4)),      # padded rows of one ghost-fill tile and of one tile and a cell; idle workgroups
+    ("channel", (27, 26, 9)),  # the other way round
+    ("alm", (54, 27, 27)),     # a row of one tile and a cell, every kind of open side
+])
+def test_ghost_fill_tiles_vs_oracle(case, grid, precision, bar):
+    cfg = make_case(case, grid=grid).with_(rotor=None)
+    print_case("ghost-tiles", case=case, grid=grid, precision=precision)
+    s, _ = run_gpu(cfg, precision, 2)
+    o, _ = run_oracle(cfg, 2)
+    err = rel_errors(s.interior(), oracle_dev(o.Q, cfg.rho_ref))
+    assert max(err) < bar, err
