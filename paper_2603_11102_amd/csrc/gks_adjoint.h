@@ -30,17 +30,20 @@ struct AdjSplit {
 };
 AdjSplit adj_split(int n_n, int n_t1, int n_t2);
 
+enum { ADJ_SUM_ACC, ADJ_SUM_ZERO, ADJ_SUM_LAM_STAR };
+
 struct AdjFaceArgs {
     const double* q[4];     // field in LOCAL variable order (padded)
-    const double* mu0[4];   // seed of L (interior, local order), stage 1 only
-    const double* mu1[4];   // seed of L_t
+    const double* lam[4];   // the flux seeds are l[0] lam + l[1] star (of L, stage 1 only) and
+    const double* star[4];  // lt[0] lam + lt[1] star (of L_t): padded, local order; star in stage 1 only
+    double l[2], lt[2];
     double* slab;           // [tile][march][cell, chunk + 5][variable][12 t2 rows][20 t1 columns]: cell adjoints
-    double* acc[4];         // padded cell adjoint accumulator (LOCAL order)
+    double* acc[4];         // padded cell adjoint (LOCAL order), ghost cells zero beforehand
+    int sum;                // what adj_sum_kernel adds the direction's cell adjoints to
     int n_n, n_t1, n_t2;
     int tiles_t1, tiles_t2;
     int chunk, nch, n_wg;  // marches of chunk of the n_n + 1 faces, nch per tile, one per workgroup
     long long st_n, st_t1, st_t2;
-    long long ist_n, ist_t1, ist_t2;
     long long pad0;
     // inverse spacings (device, the forward's arrays; 1/h on a uniform axis): normal face spacings
     // [n_n + 1], normal widths [n_n], t1 widths [n_t1], t2 widths [n_t2]
@@ -56,14 +59,10 @@ struct AdjFaceArgs {
 size_t adjoint_workspace_bytes(int nx, int ny, int nz, int n_act);
 
 struct AdjBuffers {
-    double* lam[4];      // padded: adjoint of Q^{n+1} (then of Q^n)
-    double* lam_pre[4];  // padded: adjoint of Q^{n+1,pre}
+    double* lam[4];      // padded: adjoint of Q^{n+1}, after the actuator line of Q^{n+1,pre}
     double* lam_star[4]; // padded: adjoint of Q*
-    double* acc[4];      // padded: transpose results
-    double* qwork[4];    // padded: Q^n recomputed
-    double* qpre[4];     // padded: Q^{n+1,pre}
-    double* mu0[4];      // interior seeds
-    double* mu1[4];
+    double* lam_new[4];  // padded: adjoint of Q^n, the next step's lam
+    double* qwork[4];    // padded: Q^n
     double* slab;
     double* pt;          // per-point scratch of the ALM adjoint: [16][n_act]
 };
@@ -75,11 +74,8 @@ hipError_t launch_adj_direction(const AdjFaceArgs& a, int stage, hipStream_t s);
 // (global variable order) the fill was applied to
 hipError_t launch_adj_fold(double* f[4], const GridDesc& g, const int bc[6], const double* const q[4],
                            const double u_in[3], double c, double rho_ref, hipStream_t s);
-// y = a x + b z over n elements (z may be null)
-hipError_t launch_axpby(double* y, const double* x, double a, const double* z, double b, long long n, hipStream_t s);
-// interior extraction / scatter between padded and interior layouts: dst_int = a * src_pad (+ b * src2_pad)
-hipError_t launch_pad_to_int(double* dst, const double* src, double a, const double* src2, double b,
-                             const GridDesc& g, hipStream_t s);
+// interior cells of a padded field, four variables back to back
+hipError_t launch_interior(double* dst, const double* const src[4], const GridDesc& g, hipStream_t s);
 hipError_t launch_zero(double* y, long long n, hipStream_t s);
 
 // immersed-body adjoint (a body at rest): lam (padded, adjoint of the field after the forcing) becomes
@@ -89,8 +85,7 @@ hipError_t launch_ibm_adjoint(double* lam[4], const IbmArgs& a, hipStream_t s);
 // actuator-line adjoint
 struct AlmAdjArgs {
     AlmArgs fwd;             // forward arguments (positions and per-point data of this step)
-    const double* lam_m[3];  // padded momentum adjoint (of the field after the projection)
-    double* lam_pre[4];      // padded adjoint being formed (of the field before the projection)
+    double* lam[4];          // padded adjoint of the field after the projection, then of the one before it
     const double* qpre[4];   // padded field before the projection (FP64)
     double* grad_s;          // n_act, accumulated
     double* pt;              // scratch [16][n_act]

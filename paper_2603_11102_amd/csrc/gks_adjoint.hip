@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "gks.h"
 #include "gks_adjoint.h"
 
 namespace gks {
@@ -81,7 +82,7 @@ __device__ __forceinline__ double dpp_shr(double x) {
 // partial sums in the two-cell halo and at the ends of a march, which adj_sum_kernel adds in a fixed order.
 // With separate kernels the Gauss-point adjoints (640 B a face) and the inputs of the tangential WENO evaluations
 // (192 B) went through memory, at 2.6 to 3.7 TB/s and one wave per SIMD: 1.95 ms per direction and stage of the
-// 128^3 rotor box, against 0.98 ms and 0.10 ms of adj_sum_kernel. This one writes 60 B a face and is bound by FP64
+// 128^3 rotor box, against 0.94 ms and 0.07 ms of adj_sum_kernel. This one writes 60 B a face and is bound by FP64
 // issue and its barriers.
 //
 // t2 transpose: each lane forms, for its two variables, the WENO terms of its face for the five rows it reaches
@@ -130,8 +131,18 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
     auto lane_field = [&](const double* const(&p)[4]) {
         return hi ? (m ? p[3] : p[2]) : (m ? p[1] : p[0]);
     };
-    const double* const mu1 = lane_field(a.mu1);
-    const double* const mu0 = lane_field(a.mu0);
+    const double* const lam = lane_field(a.lam);
+    const double* const star = lane_field(a.star);
+    // the two seeds of a cell over its width
+    auto seed = [&](long long idx, double w, double& m0, double& m1) {
+        const double x = lam[idx] * w;
+        m1 = a.lt[0] * x;
+        if (NEED_F0) {
+            const double y = star[idx] * w;
+            m0 = a.l[0] * x + a.l[1] * y;
+            m1 += a.lt[1] * y;
+        }
+    };
     // t1 role: position tj of variable tv
     const int tj = tid & 15, tv = (tid >> 4) & 3;
 
@@ -143,7 +154,7 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
         const long long cbase = a.pad0 + (long long)jc * a.st_t1 + (long long)kc * a.st_t2;
         const bool face_ok = (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
         const int je = min(j0 + fj, a.n_t1 - 1), ke = min(k0 + fk, a.n_t2 - 1);
-        const long long mbase = (long long)je * a.ist_t1 + (long long)ke * a.ist_t2;
+        const long long mbase = a.pad0 + (long long)je * a.st_t1 + (long long)ke * a.st_t2;
         const double ih2 = a.ih2[ke], ih1 = a.ih1[min(j0 + tj, a.n_t1 - 1)];
         // cells f0-3 .. f0+1 and the next; of the evaluation on cell f0-1 its right value (q^L of face f0) and
         // that value's coefficients; the adjoints of cells f-3 .. f+2 that the faces so far reach
@@ -164,18 +175,12 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
         // seeds Fbar(f) = mu(f) / w_f - mu(f-1) / w_{f-1} (cell widths w; no cell beyond the ends) of this
         // lane's variable; the lower cell's term is kept from face to face
         double lo0 = 0.0, lo1 = 0.0;
-        if (f0 >= 1) {
-            const double w = a.ihc[f0 - 1];
-            lo1 = mu1[mbase + (long long)(f0 - 1) * a.ist_n] * w;
-            if (NEED_F0) lo0 = mu0[mbase + (long long)(f0 - 1) * a.ist_n] * w;
-        }
+        if (f0 >= 1) seed(mbase + (long long)(f0 - 1) * a.st_n, a.ihc[f0 - 1], lo0, lo1);
         for (int f = f0; f < f1; ++f) {
             double up0 = 0.0, up1;
             {
                 const int c = min(f, a.n_n - 1);
-                const double w = f < a.n_n ? a.ihc[c] : 0.0;
-                up1 = mu1[mbase + (long long)c * a.ist_n] * w;
-                if (NEED_F0) up0 = mu0[mbase + (long long)c * a.ist_n] * w;
+                seed(mbase + (long long)c * a.st_n, f < a.n_n ? a.ihc[c] : 0.0, up0, up1);
             }
             // ---- column phase
             {
@@ -446,57 +451,86 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
 }
 
 // ------------------------------------------------------------------------------------------------
-// Sum of the tiles' and marches' shares into the padded cell adjoint (accumulated). A workgroup takes 32 t1
-// positions x 32 cells of the normal for one t2 position and variable: read along t1 (the slabs' fastest index),
-// written along the axis of unit stride (the normal in the x direction) through LDS.
+// Sum of the tiles' and marches' shares into the padded cell adjoint: added to it, or (the first direction) stored
+// over it, in the interior on top of lam + star where the directions complete lam^n. A workgroup takes 32 t1
+// positions x 16 cells of the normal for one t2 position and variable: read along t1 (the slabs' fastest index),
+// written along the axis of unit stride (the normal in the x direction) through LDS. The up to four tiles' shares
+// of a cell are in flight together and the marches that reach a cell are found once per workgroup: with a loop over
+// tiles and marches that divided for each cell, four cells a thread, it took 24 us a direction on 48^3 and 99 us on
+// 128^3, now 9.5 and 69 us (128^3: 270 MB, 3.9 TB/s). 32 cells: 11.4 and 66 us; one cell a thread: 10.6 and 87 us.
 // ------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) adj_sum_kernel(const AdjFaceArgs a) {
-    constexpr int X2 = AdjTile::T2 + 4;
-    __shared__ double s_t[32][33];
-    const int nt1 = (a.n_t1 + 4 + 31) / 32, nn = (a.n_n + 6 + 31) / 32;
-    int b = blockIdx.x;
+constexpr int ADJ_SUM_THREADS = 256, ADJ_SUM_CELLS = 16;
+
+__global__ void __launch_bounds__(ADJ_SUM_THREADS) adj_sum_kernel(const AdjFaceArgs a, int n_wg) {
+    constexpr int X2 = AdjTile::T2 + 4, NI = ADJ_SUM_CELLS, RS = ADJ_SUM_THREADS / 32, NR = NI / RS;
+    __shared__ double s_t[NI][33];
+    const int nt1 = (a.n_t1 + 4 + 31) / 32, nn = (a.n_n + 6 + NI - 1) / NI;
+    int b = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+    if (b >= n_wg) return;
     const int jx0 = (b % nt1) * 32 - 2;
     b /= nt1;
-    const int i0 = (b % nn) * 32 - 3;
+    const int i0 = (b % nn) * NI - 3;
     b /= nn;
     const int v = b % 4, kx = b / 4 - 2;
     const int lane = threadIdx.x & 31, row = threadIdx.x >> 5;
     const int nf = a.n_n + 1;
+    // marches whose faces reach cell i: faces i - 2 .. i + 3
+    __shared__ int s_m[NI][2];
+    if (threadIdx.x < NI) {
+        const int i = i0 + (int)threadIdx.x;
+        s_m[threadIdx.x][0] = max(i - 2, 0) / a.chunk;
+        s_m[threadIdx.x][1] = min(i + 3, a.n_n) / a.chunk;
+    }
+    __syncthreads();
     {
         const int jx = jx0 + lane;
-        // the tiles whose columns hold (jx, kx), ascending
+        // the tiles whose columns hold (jx, kx): in t1 and t2 the one before (its last four columns), then the own
         const int T1 = (jx + 2) / TILE1, c1 = (jx + 2) % TILE1, T2 = (kx + 2) / AdjTile::T2, c2 = (kx + 2) % AdjTile::T2;
+        const long long tile_len = (long long)a.nch * (a.chunk + 5) * ADJ_CELL;
+        const double* p[4];
+        bool ok[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int i = i0 + row + 8 * s;
+        for (int e = 0; e < 4; ++e) {
+            const int d1 = 1 - (e & 1), d2 = 1 - (e >> 1);
+            const int t1 = T1 - d1, t2 = T2 - d2;
+            ok[e] = jx < a.n_t1 + 2 && t1 >= 0 && t1 < a.tiles_t1 && (d1 == 0 || c1 < EXT1 - TILE1) && t2 >= 0 &&
+                    t2 < a.tiles_t2 && (d2 == 0 || c2 < X2 - AdjTile::T2);
+            p[e] = a.slab + ((long long)t2 * a.tiles_t1 + t1) * tile_len + v * (X2 * EXT1) +
+                   (c2 + AdjTile::T2 * d2) * EXT1 + c1 + TILE1 * d1;
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int i = i0 + row + RS * r;
             double sum = 0.0;
-            if (jx < a.n_t1 + 2 && i < a.n_n + 3) {
-                // marches whose faces reach cell i: faces i - 2 .. i + 3
-                const int m0 = max(i - 2, 0) / a.chunk, m1 = min(i + 3, a.n_n) / a.chunk;
-                for (int e = 0; e < 4; ++e) {
-                    const int d1 = 1 - (e & 1), d2 = 1 - (e >> 1);
-                    const int t1 = T1 - d1, t2 = T2 - d2, x1 = c1 + TILE1 * d1, x2 = c2 + AdjTile::T2 * d2;
-                    if (t1 < 0 || t1 >= a.tiles_t1 || x1 >= EXT1 || t2 < 0 || t2 >= a.tiles_t2 || x2 >= X2) continue;
-                    const long long tile = (long long)t2 * a.tiles_t1 + t1;
-                    for (int m = m0; m <= m1; ++m) {
-                        const int f0 = m * a.chunk, len = min(a.chunk, nf - f0), slot = i - (f0 - 3);
-                        if (slot < 0 || slot >= len + 5) continue;
-                        sum += a.slab[((tile * a.nch + m) * (a.chunk + 5) + slot) * ADJ_CELL + v * (X2 * EXT1) + x2 * EXT1 + x1];
-                    }
+            if (i < a.n_n + 3) {
+                for (int m = s_m[row + RS * r][0]; m <= s_m[row + RS * r][1]; ++m) {
+                    const int f0 = m * a.chunk, len = min(a.chunk, nf - f0), slot = i - (f0 - 3);
+                    if (slot < 0 || slot >= len + 5) continue;
+                    const long long o = ((long long)m * (a.chunk + 5) + slot) * ADJ_CELL;
+                    double x[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (ok[e]) x[e] = p[e][o];
+                    sum += (x[0] + x[1]) + (x[2] + x[3]);
                 }
             }
-            s_t[row + 8 * s][lane] = sum;
+            s_t[row + RS * r][lane] = sum;
         }
     }
     __syncthreads();
     const bool along_n = a.st_n == 1;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int r = row + 8 * s;
-        const int i = i0 + (along_n ? lane : r), jx = jx0 + (along_n ? r : lane);
-        if (jx < a.n_t1 + 2 && i < a.n_n + 3)
-            a.acc[v][a.pad0 + (long long)i * a.st_n + (long long)jx * a.st_t1 + (long long)kx * a.st_t2] +=
-                s_t[i - i0][jx - jx0];
+    for (int r = 0; r < NR; ++r) {
+        const int t = threadIdx.x + ADJ_SUM_THREADS * r;
+        const int i = i0 + (along_n ? t % NI : t / 32), jx = jx0 + (along_n ? t / NI : t % 32);
+        if (jx < a.n_t1 + 2 && i < a.n_n + 3) {
+            const long long p = a.pad0 + (long long)i * a.st_n + (long long)jx * a.st_t1 + (long long)kx * a.st_t2;
+            double base = 0.0;
+            if (a.sum == ADJ_SUM_ACC) base = a.acc[v][p];
+            else if (a.sum == ADJ_SUM_LAM_STAR && i >= 0 && i < a.n_n && jx >= 0 && jx < a.n_t1 && kx >= 0 && kx < a.n_t2)
+                base = a.lam[v][p] + a.star[v][p];
+            a.acc[v][p] = base + s_t[i - i0][jx - jx0];
+        }
     }
 }
 
@@ -506,9 +540,9 @@ hipError_t launch_adj_passes(const AdjFaceArgs& a, int stage, hipStream_t s) {
     const dim3 fgrid((unsigned)pad8(a.n_wg)), fblock(AdjTile::THREADS);
     if (stage == 1) hipLaunchKernelGGL((adj_face_kernel<1, EXACT>), fgrid, fblock, 0, s, a);
     else hipLaunchKernelGGL((adj_face_kernel<2, EXACT>), fgrid, fblock, 0, s, a);
-    const long long blocks = (long long)((a.n_t1 + 4 + 31) / 32) * ((a.n_n + 6 + 31) / 32) * 4 * (a.n_t2 + 4);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(adj_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    const long long blocks = (long long)((a.n_t1 + 4 + 31) / 32) * ((a.n_n + 6 + ADJ_SUM_CELLS - 1) / ADJ_SUM_CELLS) * 4 * (a.n_t2 + 4);
+    if (blocks > 0x7fffffffLL - 7) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(adj_sum_kernel, dim3(pad8((int)blocks)), dim3(ADJ_SUM_THREADS), 0, s, a, (int)blocks);
     return hipGetLastError();
 }
 
@@ -518,7 +552,8 @@ hipError_t launch_adj_direction(const AdjFaceArgs& a, int stage, hipStream_t s) 
 
 // ------------------------------------------------------------------------------------------------
 // transpose of the ghost fill: axes in reverse order (z, y, x); each thread folds the six ghost cells
-// of one line in a fixed order
+// of one line and variable in a fixed order (a wave per variable: the ghost values of a side are in flight
+// together, and inflow sides read all four variables before any is cleared)
 // ------------------------------------------------------------------------------------------------
 struct FoldArgs {
     int axis, n, np1, np2;
@@ -530,42 +565,57 @@ struct FoldArgs {
     Field4<const double> q;
 };
 
-__global__ void adj_fold_kernel(Field4<double> f, FoldArgs g) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (long long)g.np1 * g.np2) return;
-    const int p1 = (int)(t % g.np1), p2 = (int)(t / g.np1);
-    const long long base = (long long)p1 * g.st_1 + (long long)p2 * g.st_2;
+__global__ void __launch_bounds__(256) adj_fold_kernel(Field4<double> f, FoldArgs g) {
+    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long t = (long long)blockIdx.x * 64 + (threadIdx.x & 63);
+    const bool ok = t < (long long)g.np1 * g.np2;
+    const long long base = (t % g.np1) * g.st_1 + (t / g.np1) * g.st_2;
+    double* const fv = f.v[v];
+    auto at = [&](int i) { return base + (long long)(i + 3) * g.st_a; };  // cell i, 0 .. n - 1 inside
+    auto ghost = [&](int side, int layer) { return at(side == 0 ? -1 - layer : g.n + layer); };
+    double d[2][3];
+    if (ok)
+#pragma unroll
+        for (int side = 0; side < 2; ++side)
+#pragma unroll
+            for (int layer = 0; layer < 3; ++layer) {
+                const long long p = ghost(side, layer);
+                d[side][layer] = (side == 0 ? g.bc_lo : g.bc_hi) != GKS_BC_INFLOW
+                                     ? fv[p]
+                                     : f.v[0][p] + g.u_in[0] * f.v[1][p] + g.u_in[1] * f.v[2][p] + g.u_in[2] * f.v[3][p];
+            }
+    __syncthreads();
+    if (!ok) return;
     for (int side = 0; side < 2; ++side) {
         const int kind = side == 0 ? g.bc_lo : g.bc_hi;
-        for (int layer = 0; layer < 3; ++layer) {
-            const int gi = side == 0 ? (2 - layer) : (g.n + 3 + layer);
-            int src_i;
-            if (kind == 0) src_i = side == 0 ? (g.n - 1 - layer) : layer;
-            else if (kind == 1 || kind == 2) src_i = side == 0 ? layer : (g.n - 1 - layer);
-            else src_i = side == 0 ? 0 : g.n - 1;
-            const long long dst = base + (long long)gi * g.st_a;
-            const long long src = base + (long long)(src_i + 3) * g.st_a;
-            if (kind == 3) {  // inflow
+#pragma unroll
+        for (int layer = 0; layer < 3; ++layer) fv[ghost(side, layer)] = 0.0;
+        if (kind == GKS_BC_INFLOW || kind == GKS_BC_OUTFLOW) {
+            const long long src = at(side == 0 ? 0 : g.n - 1);
+            double w = 1.0;
+            if (kind == GKS_BC_INFLOW) {
                 // ghost = (rho_g - rho_ref, rho_g u_in) with rho_g = rho_i e^x, x = s (u_in,n - m_n / rho_i) / C
                 // (s = +1 on the low side, -1 on the high side): only rho' and m_n of the source enter,
                 // d rho_g / d rho' = e^x (1 + s u_n / C), d rho_g / d m_n = -s e^x / C
+                if (v != 0 && v != 1 + g.axis) continue;
                 const double sgn = side == 0 ? 1.0 : -1.0;
-                const double rho_i = g.rho_ref + g.q.v[0][src];
-                const double un = g.q.v[1 + g.axis][src] / rho_i;
+                const double un = g.q.v[1 + g.axis][src] / (g.rho_ref + g.q.v[0][src]);
                 const double ex = exp(sgn * (g.u_in[g.axis] - un) / g.c);
-                const double br = f.v[0][dst] + g.u_in[0] * f.v[1][dst] + g.u_in[1] * f.v[2][dst] + g.u_in[2] * f.v[3][dst];
-                f.v[0][src] += ex * (1.0 + sgn * un / g.c) * br;
-                f.v[1 + g.axis][src] += -sgn * ex / g.c * br;
-                for (int v = 0; v < 4; ++v) f.v[v][dst] = 0.0;
-                continue;
+                w = v == 0 ? ex * (1.0 + sgn * un / g.c) : -sgn * ex / g.c;
             }
-            for (int v = 0; v < 4; ++v) {
-                double sg = 1.0;
-                if (kind == 1 && v > 0) sg = -1.0;
-                if (kind == 2 && v == 1 + g.axis) sg = -1.0;
-                f.v[v][src] += sg * f.v[v][dst];
-                f.v[v][dst] = 0.0;
-            }
+            double x = fv[src];
+#pragma unroll
+            for (int layer = 0; layer < 3; ++layer) x += w * d[side][layer];
+            fv[src] = x;
+        } else {
+            const bool odd = (kind == GKS_BC_NOSLIP_WALL && v > 0) || (kind == GKS_BC_SLIP_WALL && v == 1 + g.axis);
+            const bool low = (side == 0) != (kind == GKS_BC_PERIODIC);  // periodic: from the other end
+            double x[3];
+#pragma unroll
+            for (int layer = 0; layer < 3; ++layer) x[layer] = fv[at(low ? layer : g.n - 1 - layer)];
+#pragma unroll
+            for (int layer = 0; layer < 3; ++layer)
+                fv[at(low ? layer : g.n - 1 - layer)] = x[layer] + (odd ? -d[side][layer] : d[side][layer]);
         }
     }
 }
@@ -591,7 +641,7 @@ hipError_t launch_adj_fold(double* fp[4], const GridDesc& gd, const int bc[6], c
         g.rho_ref = rho_ref;
         for (int v = 0; v < 4; ++v) g.q.v[v] = q[v];
         const long long total = (long long)g.np1 * g.np2;
-        hipLaunchKernelGGL(adj_fold_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, f, g);
+        hipLaunchKernelGGL(adj_fold_kernel, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, s, f, g);
     }
     return hipGetLastError();
 }
@@ -599,18 +649,7 @@ hipError_t launch_adj_fold(double* fp[4], const GridDesc& gd, const int bc[6], c
 // ------------------------------------------------------------------------------------------------
 // elementwise helpers
 // ------------------------------------------------------------------------------------------------
-__global__ void axpby_kernel(double* y, const double* x, double a, const double* z, double b, long long n) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    y[i] = a * x[i] + (z ? b * z[i] : 0.0);
-}
-
-hipError_t launch_axpby(double* y, const double* x, double a, const double* z, double b, long long n, hipStream_t s) {
-    hipLaunchKernelGGL(axpby_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, x, a, z, b, n);
-    return hipGetLastError();
-}
-
-__global__ void pad_to_int_kernel(double* dst, const double* src, double a, const double* src2, double b, GridDesc g) {
+__global__ void __launch_bounds__(256) interior_kernel(double* dst, Field4<const double> src, GridDesc g) {
     const long long n = (long long)g.n[0] * g.n[1] * g.n[2];
     const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n) return;
@@ -619,13 +658,15 @@ __global__ void pad_to_int_kernel(double* dst, const double* src, double a, cons
     const int j = (int)(r % g.n[1]);
     const int k = (int)(r / g.n[1]);
     const long long p = g.pad0 + i * g.st[0] + j * g.st[1] + (long long)k * g.st[2];
-    dst[c] = a * src[p] + (src2 ? b * src2[p] : 0.0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) dst[v * n + c] = src.v[v][p];
 }
 
-hipError_t launch_pad_to_int(double* dst, const double* src, double a, const double* src2, double b,
-                             const GridDesc& g, hipStream_t s) {
+hipError_t launch_interior(double* dst, const double* const src[4], const GridDesc& g, hipStream_t s) {
     const long long n = (long long)g.n[0] * g.n[1] * g.n[2];
-    hipLaunchKernelGGL(pad_to_int_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst, src, a, src2, b, g);
+    Field4<const double> f;
+    for (int v = 0; v < 4; ++v) f.v[v] = src[v];
+    hipLaunchKernelGGL(interior_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst, f, g);
     return hipGetLastError();
 }
 
@@ -712,7 +753,7 @@ __global__ void __launch_bounds__(256) alm_adj_gather_kernel(AlmAdjArgs A) {
         if (r2 <= cut) {
             const double gw = norm * exp(-r2 * ie2);
             const long long q = pidx_g(a.g, i, j, k);
-            for (int d = 0; d < 3; ++d) acc[d] += gw * A.lam_m[d][q];
+            for (int d = 0; d < 3; ++d) acc[d] += gw * A.lam[1 + d][q];
         }
     }
     __shared__ double red[3][256];
@@ -810,54 +851,65 @@ __global__ void alm_adj_points_kernel(AlmAdjArgs A) {
 // adjoint of the velocity sampling (trilinear, or the mean of trilinear samples along the direction of
 // motion) in gather form: one thread per cell of the sampling box adds, for the points in ascending
 // order and their samples in ascending order, the terms of every sample whose eight trilinear cells
-// hold it (the order of a serial sweep over points, samples and corners)
+// hold it (the order of a serial sweep over points, samples and corners). Bound by the test of every sample in
+// every cell: the workgroup places 256 samples at a time in LDS (each thread placing all of them, with two
+// trigonometric functions and three divisions a sample, took 39 us for 48 points on 48^3 cells and 78 us for 96 on 128^3,
+// against 14 and 18 us)
 __global__ void __launch_bounds__(256) alm_adj_scatter_kernel(AlmAdjArgs A) {
     const AlmArgs& a = A.fwd;
+    __shared__ int s_i[3][256];
+    __shared__ double s_w[3][256], s_u[3][256];
     const long long ncell = (long long)a.samp_n[0] * a.samp_n[1] * a.samp_n[2];
     const long long tcell = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tcell >= ncell) return;
+    const bool ok = tcell < ncell;
     const int ci = a.samp_lo[0] + (int)(tcell % a.samp_n[0]);
     const int cj = a.samp_lo[1] + (int)((tcell / a.samp_n[0]) % a.samp_n[1]);
     const int ck = a.samp_lo[2] + (int)(tcell / ((long long)a.samp_n[0] * a.samp_n[1]));
     const long long q = pidx_g(a.g, ci, cj, ck);
-    const double rho = a.rho_ref + A.qpre[0][q];
-    const double Uc[3] = {A.qpre[1][q] / rho, A.qpre[2][q] / rho, A.qpre[3][q] / rho};
-    double lam[4] = {A.lam_pre[0][q], A.lam_pre[1][q], A.lam_pre[2][q], A.lam_pre[3][q]};
+    double rho = 0.0, Uc[3] = {0.0, 0.0, 0.0}, lam[4] = {0.0, 0.0, 0.0, 0.0};
+    if (ok) {
+        rho = a.rho_ref + A.qpre[0][q];
+        for (int c = 0; c < 3; ++c) Uc[c] = A.qpre[1 + c][q] / rho;
+        for (int v = 0; v < 4; ++v) lam[v] = A.lam[v][q];
+    }
     bool touched = false;
     const int ns = a.line_n > 1 ? a.line_n : 1;
-    const double t = a.st->t_next;
-    for (int p = 0; p < a.n_act; ++p) {
-        double Ub[3] = {A.pt[3 * a.n_act + p], A.pt[4 * a.n_act + p], A.pt[5 * a.n_act + p]};
-        if (ns > 1)
-            for (int c = 0; c < 3; ++c) Ub[c] /= (double)ns;
-        const int bl = p / a.npb;
-        const double th = a.theta0 + a.omega * t + 2.0 * M_PI * (double)bl / (double)a.nb;
-        const double et1 = -sin(th), et2 = cos(th);
-        for (int k = 0; k < ns; ++k) {
+    const long long nsamp = (long long)a.n_act * ns;
+    for (long long s0 = 0; s0 < nsamp; s0 += 256) {
+        const int cnt = (int)min(256LL, nsamp - s0);
+        __syncthreads();
+        if ((int)threadIdx.x < cnt) {
+            const int p = (int)((s0 + threadIdx.x) / ns), k = (int)((s0 + threadIdx.x) % ns), bl = p / a.npb;
+            const double th = a.theta0 + a.omega * a.st->t_next + 2.0 * M_PI * (double)bl / (double)a.nb;
             const double sk = ns > 1 ? line_offset(a, k) : 0.0;
-            const double Xs[3] = {a.X[3 * p], a.X[3 * p + 1] + sk * et1, a.X[3 * p + 2] + sk * et2};
-            int i0[3];
-            double w1[3];
+            const double Xs[3] = {a.X[3 * p], a.X[3 * p + 1] + sk * -sin(th), a.X[3 * p + 2] + sk * cos(th)};
             for (int d = 0; d < 3; ++d) {
                 const double fc = (Xs[d] - a.g.x0[d]) / a.g.h[d] - 0.5;
                 const double fl = floor(fc);
-                i0[d] = (int)fl;
-                w1[d] = fc - fl;
+                s_i[d][threadIdx.x] = (int)fl;
+                s_w[d][threadIdx.x] = fc - fl;
+                const double Ub = A.pt[(3 + d) * a.n_act + p];
+                s_u[d][threadIdx.x] = ns > 1 ? Ub / (double)ns : Ub;
             }
-            const int dx = ci - i0[0], dy = cj - i0[1], dz = ck - i0[2];
+        }
+        __syncthreads();
+        for (int s = 0; s < cnt; ++s) {
+            const int dx = ci - s_i[0][s], dy = cj - s_i[1][s], dz = ck - s_i[2][s];
             if (dx < 0 || dx > 1 || dy < 0 || dy > 1 || dz < 0 || dz > 1) continue;
+            const double w1[3] = {s_w[0][s], s_w[1][s], s_w[2][s]};
             const double w = (dx ? w1[0] : 1.0 - w1[0]) * (dy ? w1[1] : 1.0 - w1[1]) * (dz ? w1[2] : 1.0 - w1[2]);
             double dot = 0.0;
             for (int c = 0; c < 3; ++c) {
-                lam[1 + c] += w * Ub[c] / rho;
-                dot += Ub[c] * Uc[c];
+                const double Ub = s_u[c][s];
+                lam[1 + c] += w * Ub / rho;
+                dot += Ub * Uc[c];
             }
             lam[0] += -w * dot / rho;
             touched = true;
         }
     }
-    if (touched)
-        for (int v = 0; v < 4; ++v) A.lam_pre[v][q] = lam[v];
+    if (ok && touched)
+        for (int v = 0; v < 4; ++v) A.lam[v][q] = lam[v];
 }
 
 hipError_t launch_alm_adjoint(const AlmAdjArgs& A, hipStream_t s) {
@@ -890,12 +942,9 @@ void adjoint_carve(char* base, int nx, int ny, int nz, int n_act, AdjBuffers* b,
         return p;
     };
     const size_t np = (size_t)(nx + 6) * (ny + 6) * (nz + 6);
-    const size_t N = (size_t)nx * ny * nz;
-    double** pads[6] = {b->lam, b->lam_pre, b->lam_star, b->acc, b->qwork, b->qpre};
-    for (int a = 0; a < 6; ++a)
+    double** pads[4] = {b->lam, b->lam_star, b->lam_new, b->qwork};
+    for (int a = 0; a < 4; ++a)
         for (int v = 0; v < 4; ++v) pads[a][v] = reinterpret_cast<double*>(take(np * 8));
-    for (int v = 0; v < 4; ++v) b->mu0[v] = reinterpret_cast<double*>(take(N * 8));
-    for (int v = 0; v < 4; ++v) b->mu1[v] = reinterpret_cast<double*>(take(N * 8));
     const int n[3] = {nx, ny, nz};
     const int ax[3][3] = {{0, 1, 2}, {1, 0, 2}, {2, 0, 1}};
     size_t cells = 0;  // (tile, march, cell) of the tile kernel's output

@@ -463,19 +463,29 @@ FaceArgs<real> face_args(gks_ctx* c, int d, int stage, void* const src[4]) {
     return face_args_buf<real>(c, d, 2, src, c->q, c->qa, nullptr, c->qt, c->lo_qa, c->lo_q, nullptr);
 }
 
-AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, void* const src[4], int exact) {
+AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, int stage, void* const src[4], double dt, int exact) {
     AdjFaceArgs a;
     std::memset(&a, 0, sizeof(a));
     const int* pm = kPerm[d];
     const int* ax = kAxes[d];
-    const long long ist[3] = {1, c->cfg.nx, (long long)c->cfg.nx * c->cfg.ny};
     for (int v = 0; v < 4; ++v) {
         const int gv = pm[v];
         a.q[v] = static_cast<const double*>(src[gv]);
-        a.mu0[v] = B.mu0[gv];
-        a.mu1[v] = B.mu1[gv];
-        a.acc[v] = B.acc[gv];
+        a.lam[v] = B.lam[gv];
+        a.star[v] = B.lam_star[gv];
+        a.acc[v] = stage == 1 ? B.lam_new[gv] : B.lam_star[gv];
     }
+    // stage 2: lam* = (dt^2/3) J_Lt(Q*)^T lam; stage 1: seeds dt lam + dt/2 lam* (of L) and dt^2/6 lam + dt^2/8 lam*
+    // (of L_t) at Q^n, onto lam + lam*
+    if (stage == 1) {
+        a.l[0] = dt;
+        a.l[1] = 0.5 * dt;
+        a.lt[0] = dt * dt / 6.0;
+        a.lt[1] = dt * dt / 8.0;
+    } else {
+        a.lt[0] = dt * dt / 3.0;
+    }
+    a.sum = d > 0 ? ADJ_SUM_ACC : stage == 1 ? ADJ_SUM_LAM_STAR : ADJ_SUM_ZERO;
     a.slab = B.slab;
     a.n_n = c->g.n[ax[0]];
     a.n_t1 = c->g.n[ax[1]];
@@ -489,9 +499,6 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, void* const src[4],
     a.st_n = c->g.st[ax[0]];
     a.st_t1 = c->g.st[ax[1]];
     a.st_t2 = c->g.st[ax[2]];
-    a.ist_n = ist[ax[0]];
-    a.ist_t1 = ist[ax[1]];
-    a.ist_t2 = ist[ax[2]];
     a.pad0 = c->g.pad0;
     a.ihf = static_cast<const double*>(c->ihf[ax[0]]);
     a.ihc = static_cast<const double*>(c->ihc[ax[0]]);
@@ -1240,43 +1247,33 @@ int gks_adjoint(gks_ctx* c, int32_t nsteps, const double w[2], double* grad_s, d
     const long long np = c->g.n_padded;
     const double dt = c->cfg.dt_fixed;
     hipStream_t S = c->stream;
-    for (int v = 0; v < 4; ++v) HIPCHK(c, launch_zero(B.lam[v], np, S));
+    // the three adjoint fields lie back to back; their ghost cells stay zero between the direction passes
+    HIPCHK(c, launch_zero(B.lam[0], B.lam_new[3] + np - B.lam[0], S));
     HIPCHK(c, launch_zero(grad_s, c->alm.n_act, S));
     const size_t slot = gks_checkpoint_slot_bytes(&c->cfg);
     const size_t fb = ((size_t)np * 8 + 255) & ~size_t(255);
-    void* qwork[4];
-    void* qpre[4];
-    for (int v = 0; v < 4; ++v) {
-        qwork[v] = B.qwork[v];
-        qpre[v] = B.qpre[v];
-    }
+    void* const qwork[4] = {B.qwork[0], B.qwork[1], B.qwork[2], B.qwork[3]};
     for (int n = nsteps - 1; n >= 0; --n) {
         // step n from its checkpoint: Q^n, Q* and the field before the body forces (stored by the
-        // forward, bitwise what a recompute gives), and t
+        // forward, bitwise what a recompute gives; the last is read in place), and t
         const char* src = c->ckpt + (size_t)n * slot;
-        for (int v = 0; v < 4; ++v) {
-            HIPCHK(c, launch_copy_field(src + v * fb, B.qwork[v], (size_t)np * 8, S));
-            HIPCHK(c, launch_copy_field(src + (4 + v) * fb, c->qs[v], (size_t)np * 8, S));
-            HIPCHK(c, launch_copy_field(src + (8 + v) * fb, B.qpre[v], (size_t)np * 8, S));
-        }
-        HIPCHK(c, launch_copy_field(src + slot - 256, &c->st->t, sizeof(double), S));
-        HIPCHK(c, launch_dt(DtArgs{c->st, nullptr, 0, 0.0, c->hmin, c->c, dt}, S));
-        int rc = ghost_all<double>(c, qwork);
-        if (rc) return rc;
-        rc = ghost_all<double>(c, c->qs);
-        if (rc) return rc;
-        HIPCHK(c, launch_alm_points_only(field<double>(qpre), c->alm, S));
+        const double* ck[12];
+        for (int v = 0; v < 12; ++v) ck[v] = reinterpret_cast<const double*>(src + v * fb);
+        HIPCHK(c, launch_restore(ck, ck + 4, field<double>(qwork), field<double>(c->qs), c->g, c->cfg.bc, c->cfg.u_in,
+                                 c->c, c->cfg.rho_ref, reinterpret_cast<const double*>(src + slot - 256),
+                                 DtArgs{c->st, nullptr, 0, 0.0, c->hmin, c->c, dt}, S));
+        Field4<double> qpre;
+        for (int v = 0; v < 4; ++v) qpre.v[v] = const_cast<double*>(ck[8 + v]);  // sampled only
+        HIPCHK(c, launch_alm_points_only(qpre, c->alm, S));
         // immersed body (at rest): lam becomes the adjoint of the field before the forcing
         if (c->has_ibm) HIPCHK(c, launch_ibm_adjoint(B.lam, c->ibm, S));
-        // actuator line: lam_pre = lam + (sampling path); gradient in s
-        for (int v = 0; v < 4; ++v) HIPCHK(c, launch_axpby(B.lam_pre[v], B.lam[v], 1.0, nullptr, 0.0, np, S));
+        // actuator line: lam becomes the adjoint of the field before it (sampling path); gradient in s
         AlmAdjArgs A;
         std::memset(&A, 0, sizeof(A));
         A.fwd = c->alm;
-        for (int v = 0; v < 3; ++v) A.lam_m[v] = B.lam[1 + v];
         for (int v = 0; v < 4; ++v) {
-            A.lam_pre[v] = B.lam_pre[v];
-            A.qpre[v] = B.qpre[v];
+            A.lam[v] = B.lam[v];
+            A.qpre[v] = ck[8 + v];
         }
         A.grad_s = grad_s;
         A.pt = B.pt;
@@ -1284,35 +1281,17 @@ int gks_adjoint(gks_ctx* c, int32_t nsteps, const double w[2], double* grad_s, d
         A.w1 = w[1];
         A.inv_n = 1.0 / nsteps;
         HIPCHK(c, launch_alm_adjoint(A, S));
-        // stage 2: lam* = (dt^2/3) J_Lt(Q*)^T lam_pre
-        for (int v = 0; v < 4; ++v) {
-            HIPCHK(c, launch_pad_to_int(B.mu1[v], B.lam_pre[v], dt * dt / 3.0, nullptr, 0.0, c->g, S));
-            HIPCHK(c, launch_zero(B.acc[v], np, S));
+        for (int stage = 2; stage >= 1; --stage) {
+            void* const* const q = stage == 2 ? c->qs : qwork;
+            for (int d = 0; d < 3; ++d) HIPCHK(c, launch_adj_direction(adj_args(c, B, d, stage, q, dt, exact), stage, S));
+            const double* const qd[4] = {static_cast<const double*>(q[0]), static_cast<const double*>(q[1]),
+                                         static_cast<const double*>(q[2]), static_cast<const double*>(q[3])};
+            HIPCHK(c, launch_adj_fold(stage == 2 ? B.lam_star : B.lam_new, c->g, c->cfg.bc, qd, c->cfg.u_in, c->c,
+                                      c->cfg.rho_ref, S));
         }
-        for (int d = 0; d < 3; ++d) HIPCHK(c, launch_adj_direction(adj_args(c, B, d, c->qs, exact), 2, S));
-        const double* qs_d[4] = {static_cast<const double*>(c->qs[0]), static_cast<const double*>(c->qs[1]),
-                                 static_cast<const double*>(c->qs[2]), static_cast<const double*>(c->qs[3])};
-        HIPCHK(c, launch_adj_fold(B.acc, c->g, c->cfg.bc, qs_d, c->cfg.u_in, c->c, c->cfg.rho_ref, S));
-        for (int v = 0; v < 4; ++v) HIPCHK(c, launch_axpby(B.lam_star[v], B.acc[v], 1.0, nullptr, 0.0, np, S));
-        // stage 1: seeds dt lam_pre + dt/2 lam* (of L) and dt^2/6 lam_pre + dt^2/8 lam* (of L_t) at Q^n
-        for (int v = 0; v < 4; ++v) {
-            HIPCHK(c, launch_pad_to_int(B.mu0[v], B.lam_pre[v], dt, B.lam_star[v], 0.5 * dt, c->g, S));
-            HIPCHK(c, launch_pad_to_int(B.mu1[v], B.lam_pre[v], dt * dt / 6.0, B.lam_star[v], dt * dt / 8.0, c->g, S));
-            HIPCHK(c, launch_zero(B.acc[v], np, S));
-        }
-        for (int d = 0; d < 3; ++d) HIPCHK(c, launch_adj_direction(adj_args(c, B, d, qwork, exact), 1, S));
-        const double* qw_d[4] = {B.qwork[0], B.qwork[1], B.qwork[2], B.qwork[3]};
-        HIPCHK(c, launch_adj_fold(B.acc, c->g, c->cfg.bc, qw_d, c->cfg.u_in, c->c, c->cfg.rho_ref, S));
-        // lam^n = lam_pre + lam* + J^T(...)
-        for (int v = 0; v < 4; ++v) {
-            HIPCHK(c, launch_axpby(B.lam[v], B.lam_pre[v], 1.0, B.lam_star[v], 1.0, np, S));
-            HIPCHK(c, launch_axpby(B.lam[v], B.lam[v], 1.0, B.acc[v], 1.0, np, S));
-        }
+        for (int v = 0; v < 4; ++v) std::swap(B.lam[v], B.lam_new[v]);
     }
-    if (grad_q0) {
-        const long long N = (long long)c->cfg.nx * c->cfg.ny * c->cfg.nz;
-        for (int v = 0; v < 4; ++v) HIPCHK(c, launch_pad_to_int(grad_q0 + v * N, B.lam[v], 1.0, nullptr, 0.0, c->g, S));
-    }
+    if (grad_q0) HIPCHK(c, launch_interior(grad_q0, B.lam, c->g, S));
     HIPCHK(c, hipStreamSynchronize(S));
     return GKS_OK;
 }
