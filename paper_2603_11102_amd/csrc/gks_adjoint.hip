@@ -70,6 +70,17 @@ __device__ __forceinline__ double dpp_shr(double x) {
     return dpp_move<0x110 + K, 0xF, true>(0.0, x);
 }
 
+// Kernel arguments as they stand in the argument block, by a reference the compiler cannot see through: it then
+// loads a field with a scalar load where it is used. With copies of them all, which spill into vector registers,
+// adj_face_kernel keeps 7 dwords more in scratch: the 128^3 window of 20 steps took 174 ms, now 167. (The
+// forward's FP64 kernels lose their 99 spilled scalars too, but wait for the loads: 32^3 2 % slower.)
+template <typename T>
+__device__ __forceinline__ const T& args_in_place(const T& a) {
+    int zero = 0;
+    asm("" : "+s"(zero));
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(&a) + zero);
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
@@ -93,7 +104,8 @@ __device__ __forceinline__ double dpp_shr(double x) {
 // landing in lanes 14, 15, 0 and 1.
 // ------------------------------------------------------------------------------------------------
 template <int STAGE, bool EXACT>
-__global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFaceArgs a) {
+__global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFaceArgs args) {
+    const AdjFaceArgs& a = args_in_place(args);
     constexpr bool NEED_F0 = (STAGE == 1);
     constexpr int T2 = AdjTile::T2, X2 = T2 + 4, NTH = AdjTile::THREADS, NW = EXACT ? 5 : 2;
     static_assert(T2 == 8 && NTH == 64 * T2 && 2 * EXT1 * X2 <= NTH, "thread roles");
