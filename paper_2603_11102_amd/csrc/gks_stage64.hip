@@ -20,7 +20,7 @@
 //   * a reduce-scatter over the four lanes leaves lane (h, m) the face flux of global variable 2h + m, whose
 //     divergence, accumulation or stage update it does.
 // Measured, 192 x 96 x 96 channel: 1.85 ms a step with two lanes per face, 1.56 ms with four (12-row tiles, three
-// waves per SIMD); the tile height is chosen per direction (FACE64_ROWS).
+// waves per SIMD), 1.45 ms with the directions sharing launches; the tile height is chosen per direction (FACE64_ROWS).
 #include "gks_internal.h"
 
 namespace gks {
@@ -50,9 +50,11 @@ __device__ __forceinline__ T sel(bool c, T x, T y) {
 }  // namespace
 
 // LDS, per variable: column values [q^L, q^R, D, C][t2 row][t1 column] and t1-phase results
-// [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. Blocks are padded so that a
-// half wave's 64-bit reads meet no bank twice: the t1 phase reads 16 positions of two consecutive
-// variables (32 words apart modulo 64), the t2 phase 16 values of variables v and v + 2 (2 x 16 words).
+// [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. A 64-bit read
+// takes 16 lanes at a time over 32 banks: in the t1 phase 16 positions of one variable; in the t2 phase 8 values
+// (four faces, two Gauss lines) of each of the variables v and v + 2, whose blocks are padded to start 16 words
+// apart modulo 32 (32 words apart, every such read took two turns: 55 M conflict cycles a stage-1 x and y launch
+// of the 192 x 96 x 96 channel against 13 M; 32^3 75.1 -> 72.4 us a step, the channel 0.6 %).
 template <int X2>
 struct Face64Lds {
     struct {
@@ -61,7 +63,7 @@ struct Face64Lds {
     } nrm[4];
     struct {
         double a[5][X2][TILE1][2];
-        double pad[(8 - (5 * X2 * TILE1 * 2) % 32 + 32) % 32];
+        double pad[(4 - (5 * X2 * TILE1 * 2) % 32 + 32) % 32];
     } t1[4];
 };
 
