@@ -50,11 +50,11 @@ __device__ __forceinline__ T sel(bool c, T x, T y) {
 }  // namespace
 
 // LDS, per variable: column values [q^L, q^R, D, C][t2 row][t1 column] and t1-phase results
-// [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. A 64-bit read
-// takes 16 lanes at a time over 32 banks: in the t1 phase 16 positions of one variable; in the t2 phase 8 values
-// (four faces, two Gauss lines) of each of the variables v and v + 2, whose blocks are padded to start 16 words
-// apart modulo 32 (32 words apart, every such read took two turns: 55 M conflict cycles a stage-1 x and y launch
-// of the 192 x 96 x 96 channel against 13 M; 32^3 75.1 -> 72.4 us a step, the channel 0.6 %).
+// [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][Gauss line m][t1 position]. A 64-bit access takes 16 lanes at a time
+// over 32 banks: the t1 phase reads and stores 16 positions of one variable and line; the t2 phase reads four
+// faces of both lines of the variables v and v + 2, so lines start 8 words apart modulo 32 and those variables'
+// blocks 16. (With the lines interleaved, 128-bit stores, and the blocks 32 words apart: 55 M conflict cycles in a
+// stage-1 x and y launch of the 192 x 96 x 96 channel, now 4.5 M; 1.43 ms a step, now 1.39; 32^3 75.1 us, now 71.4.)
 template <int X2>
 struct Face64Lds {
     struct {
@@ -62,8 +62,8 @@ struct Face64Lds {
         double pad[(16 - (4 * X2 * EXT1) % 32 + 32) % 32];
     } nrm[4];
     struct {
-        double a[5][X2][TILE1][2];
-        double pad[(4 - (5 * X2 * TILE1 * 2) % 32 + 32) % 32];
+        double a[5][X2][2][TILE1 + 4];
+        double pad[(4 - (5 * X2 * 2 * (TILE1 + 4)) % 32 + 32) % 32];
     } t1[4];
 };
 
@@ -219,10 +219,12 @@ __device__ __forceinline__ void face64_march(const FaceArgs<double>& a, const in
                             for (int r = 0; r < 5; ++r) x[r] = s_nrm[v].a[q][tk][tj + r];
                             if (q < 2) weno_gauss<double>(x[0], x[1], x[2], x[3], x[4], eps, vm, vp);
                             else quartic_gauss_value<double>(x[0], x[1], x[2], x[3], x[4], vm, vp);
-                            *reinterpret_cast<double2*>(s_t1[v].a[q == 3 ? 4 : q][tk][tj]) = double2{vm, vp};
+                            s_t1[v].a[q == 3 ? 4 : q][tk][0][tj] = vm;
+                            s_t1[v].a[q == 3 ? 4 : q][tk][1][tj] = vp;
                             if (q == 3) {
                                 quartic_gauss_deriv<double>(x[0], x[1], x[2], x[3], x[4], vm, vp);
-                                *reinterpret_cast<double2*>(s_t1[v].a[3][tk][tj]) = double2{vm * ih1, vp * ih1};
+                                s_t1[v].a[3][tk][0][tj] = vm * ih1;
+                                s_t1[v].a[3][tk][1][tj] = vp * ih1;
                             }
                         }
                     }
@@ -238,7 +240,7 @@ __device__ __forceinline__ void face64_march(const FaceArgs<double>& a, const in
                 for (int q = 0; q < 5; ++q) {
                     double y[5];
 #pragma unroll
-                    for (int r = 0; r < 5; ++r) y[r] = t.a[q][fk + r][fj][m];
+                    for (int r = 0; r < 5; ++r) y[r] = t.a[q][fk + r][m][fj];
                     double vm, vp;
                     if (q < 2) weno_gauss<double>(y[0], y[1], y[2], y[3], y[4], eps, vm, vp);
                     else if (q < 4) quartic_gauss_value<double>(y[0], y[1], y[2], y[3], y[4], vm, vp);
