@@ -33,19 +33,20 @@ FLOP_PER_CELL_STEP = 3 * (FLOP_STAGE1_PER_CELL_DIR + FLOP_STAGE2_PER_CELL_DIR) +
 PEAK_TFLOPS = {"fp32": 157.3, "fp64": 78.6}   # MI355X published vector peaks
 PEAK_HBM_GBS = 8000.0
 
-# HBM bytes per stage-1 face-pass launch (mean over the x, y, z launches) of the FP32 channel workload,
-# from two rocprofv3 --pmc runs (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) of
+# HBM bytes of the FP32 channel workload per stage-1 direction (order 5: the x and y directions' launch and the z
+# direction's, over three) or per stage-1 launch (order 2: one launch does the stage), from two
+# rocprofv3 --pmc runs (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) of
 # "bench.py [--order 2] --steps 4 --warmup 2 --repeats 1 --no-fp64 --no-cpu-baseline --no-adjoint --no-bodies",
 # each scaled by what the same counter reads for a plain 1 GiB device copy ("bench.py --calibrate-copy 1024":
 # FETCH_SIZE x 2.0, WRITE_SIZE x 1.0). A figure belongs to the kernel sources it was measured on; bench
 # reports null once they differ.
 TRAFFIC = {
     5: {"sources": ("gks_stage.hip", "gks_device.h", "gks_internal.h"),
-         "sources_sha256": "231c17131be534ff89f16fca6c5dd7cd445b185a47cac350e12eab1dbd2df8be",
-         "fetch_bytes": 197_497_908, "write_bytes": 84_954_526},
+         "sources_sha256": "74a0e054672a89b95dc40c1c18878549ed5c441882effcac096cbb264d987483",
+         "fetch_bytes": 212_077_722, "write_bytes": 85_683_520},
     2: {"sources": ("gks_stage2.hip", "gks_device.h", "gks_internal.h"),
-         "sources_sha256": "8d5906e99bf19247d8bea11a23e4b01fef46cdf6bf5fbb341931ecfb6df876bf",
-         "fetch_bytes": 102_163_699, "write_bytes": 77_066_262},
+         "sources_sha256": "92459f4e1fa4f798bca3a8f98c19eb4a3c88585477dc9a1582c18b6a9e9721bf",
+         "fetch_bytes": 289_071_270, "write_bytes": 141_285_597},
 }
 
 
@@ -95,9 +96,17 @@ def _time_graph(s, steps, side):
 
 
 def stage1_launch_ms(timing):
-    """Mean duration of one stage-1 face launch (x, y and z passes) from the per-launch event timing."""
+    """Mean duration of a stage-1 direction (x, y, z) from the per-launch event timing, which splits a launch that
+    does several directions evenly over them."""
     s1_ms = sum(timing[k][0] for k in ("s1x", "s1y", "s1z"))
     return s1_ms / max(1, sum(timing[k][1] for k in ("s1x", "s1y", "s1z")))
+
+
+def face_kernels(precision, stretched):
+    """Name of the stage-1 kernels a roofline entry stands for (small grids: all directions in one launch)."""
+    base, args = ("face", "float, 1") if precision == "fp32" else ("face64", "12 | 8, 1")
+    return (f"{base}_xy_kernel, {base}_z_kernel or {base}_xyz_kernel<{args}, {str(stretched).lower()}> (stage 1: mean "
+            "over the x, y, z directions)")
 
 
 def run_gpu(cfg, precision, steps, warmup, graph=False, repeats=5):
@@ -287,9 +296,7 @@ def main():
                    "cells": n, "bc": list(cfg.bc), "ma": cfg.ma,
                    "launch": "one HIP graph replay of the timed steps" if args.graph else "eager",
                    **({"ibm_yaw_rad_per_time": args.ibm_yaw} if args.ibm_yaw else {})},
-        "roofline": {"bound": "alu", "kernel": f"face_kernel<{'float' if args.precision == 'fp32' else 'double'}, 1, "
-                                                f"3 | 0 | 4, {str(stretched).lower()}> (stage 1: mean over the x, y, z "
-                                                "launches)",
+        "roofline": {"bound": "alu", "kernel": face_kernels(args.precision, stretched),
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                      "traffic": measured_traffic(args.case, args.precision, 5), "avg_launch_ms": avg_launch_ms,
                      "algorithmic_flop_per_launch": flops_launch},
@@ -297,18 +304,15 @@ def main():
         "flop_per_cell_step": FLOP_PER_CELL_STEP,
     }
     if args.order == 2:
-        # second-order variant: a few hundred flops per cell and direction against the same memory
-        # traffic as the high-order pass, so the HBM roofline is the reference. Algorithmic bytes per
-        # cell of a stage-1 launch (FP32): x and y read the field (16) and write L, L_t (32); z reads
-        # the field, both residuals (64), Q^n and its low-order part (32) and writes Q*, S and their
-        # low-order parts (64); FP64 has no low-order parts.
-        per_cell = ((48 + 48 + 176) / 3.0) if args.precision == "fp32" else ((96 + 96 + 288) / 3.0)
-        bytes_launch = per_cell * n
+        # second-order variant: a few hundred flops per cell and direction, so the HBM roofline is the reference.
+        # One launch does a stage: stage 1 reads the field and its low-order part and writes Q*, S and their
+        # low-order parts (FP32: 32 + 64 bytes per cell; FP64 has no low-order parts: 32 + 64).
+        bytes_launch = 96.0 * n
+        avg_launch_ms *= 3.0
         result["metric"] = "cell-updates/s per S2O4 step (second-order variant)"
         result["config"]["workload"] += ", second-order GKS"
-        result["roofline"] = {"bound": "hbm", "kernel": f"face2_kernel<{'float' if es == 4 else 'double'}, 1, "
-                                                        f"3 | 0 | 4, {str(stretched).lower()}> (stage 1: mean over "
-                                                        "the x, y, z launches)",
+        result["roofline"] = {"bound": "hbm", "kernel": f"stage2_kernel<{'float' if es == 4 else 'double'}, 1, "
+                                                        f"{str(stretched).lower()}> (the stage-1 launch)",
                               "achieved": bytes_launch / (avg_launch_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
                               "unit": "GB/s", "frac": bytes_launch / (avg_launch_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
                               "traffic": measured_traffic(args.case, args.precision, 2),
@@ -331,11 +335,15 @@ def main():
         rl2 = [float(torch.linalg.vector_norm(q32[v] - q64[v]) / torch.linalg.vector_norm(q64[v])) for v in range(4)]
         result["fp64"] = {"value": n * args.steps / (ms64 * 1e-3), "ms_per_step": ms64 / args.steps,
                           "window_ms_per_step": [w / args.steps for w in win64],
-                          "roofline": {"bound": "alu", "kernel": f"face_kernel<double, 1, 3 | 0 | 4, "
-                                                                 f"{str(stretched).lower()}> (stage 1: mean over "
-                                                                 "the x, y, z launches)",
+                          "roofline": {"bound": "alu", "kernel": face_kernels("fp64", stretched),
                                        "achieved": a64_tf, "peak": PEAK_TFLOPS["fp64"], "unit": "TFLOP/s",
                                        "frac": a64_tf / PEAK_TFLOPS["fp64"], "avg_launch_ms": l64}}
+        if args.order == 2:
+            gbs = bytes_launch / (3.0 * l64 * 1e-3) / 1e9
+            result["fp64"]["roofline"] = {"bound": "hbm", "kernel": f"stage2_kernel<double, 1, {str(stretched).lower()}> "
+                                                                    "(the stage-1 launch)",
+                                          "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                                          "frac": gbs / PEAK_HBM_GBS, "avg_launch_ms": 3.0 * l64}
         result["fp32_vs_fp64_rel_l2"] = {"after_steps": done, "per_variable": rl2}
         print(f"[bench] fp64: {ms64 / args.steps:.3f} ms/step; fp32 vs fp64 rel L2 {rl2}", flush=True)
     s.close()
