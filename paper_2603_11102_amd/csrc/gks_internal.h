@@ -15,16 +15,16 @@ constexpr int FACE_THREADS = 512;        // 8 wave64 per workgroup
 
 // Tiles of the order-5 face kernels, TILE1 x T2 faces. FP32: 16 x 16 faces, 512 threads (two waves per
 // SIMD, up to 256 registers each), two lanes per face. FP64: four lanes per face, 16 x 12 faces on 768
-// threads or 16 x 8 on 512. A step of the 12-row tile takes 1.30 times a step of the 8-row one for 1.5 times
+// threads or 16 x 8 on 512. A step of the 12-row tile takes about 1.3 times a step of the 8-row one for 1.5 times
 // the faces, so it wins where both fill the chip and loses on small or badly divided planes (us a step,
-// 12 rows / 8 rows: 192 x 96 x 96 channel 1452 / 1655, periodic cubes 128^3 1748 / 1883, 56^3 214 / 245,
-// 64^3 295 / 277, 24^3 63 / 56). 16 rows do not fit: 128 registers a thread spill (192 x 96 x 96: 1690 to 1960).
+// 12 rows / 8 rows: 192 x 96 x 96 channel 1387 / 1508, periodic cubes 128^3 1674 / 1720, 56^3 204 / 226,
+// 64^3 281 / 258, 24^3 61 / 54). 16 rows do not fit: 128 registers a thread spill (192 x 96 x 96: 1690 to 1960).
 constexpr int FACE64_ROWS[2] = {12, 8};
 constexpr double FACE64_STEP[2] = {6000.0, 4600.0};  // ns a face step
 constexpr double FACE32_STEP = 4300.0;
 // ns: what a face launch costs beyond its face steps, a combine launch, and the latter's time per cell.
 // Measured on periodic cubes, us a step, two launches a stage against one and the combine: FP32 16^3 65 / 44,
-// 40^3 96 / 84, 56^3 149 / 147, 128^3 906 / 1078; FP64 16^3 65 / 45, 40^3 127 / 118, 128^3 1752 / 2001.
+// 40^3 96 / 84, 56^3 148 / 147, 128^3 906 / 1083; FP64 16^3 62 / 44, 40^3 119 / 110, 128^3 1671 / 1917.
 constexpr double FACE_LAUNCH = 1000.0, COMBINE_LAUNCH = 3000.0, COMBINE_CELL32 = 0.039, COMBINE_CELL64 = 0.052;
 
 // Local index (the pass's variable order: density, normal momentum, t1, t2 momenta) of each global

@@ -1,5 +1,6 @@
 // gks_stage.hip -- the FP32 S2O4 stage kernels (the FP64 ones are in gks_stage64.hip): reconstruction,
-// gas-kinetic flux, flux divergence and the stage combination, one launch per face direction (Section 2,
+// gas-kinetic flux, flux divergence and the stage combination, the x and y directions in one launch and z in one,
+// or all three together on small grids (Section 2,
 // Eqs. (semi), (finite), (x_example), (flux); the two-stage fourth-order combinations). Also the work split
 // of both precisions.
 //
