@@ -42,10 +42,10 @@ PEAK_HBM_GBS = 8000.0
 # reports null once they differ.
 TRAFFIC = {
     5: {"sources": ("gks_stage.hip", "gks_device.h", "gks_internal.h"),
-         "sources_sha256": "74a0e054672a89b95dc40c1c18878549ed5c441882effcac096cbb264d987483",
+         "sources_sha256": "33fed9e10ad47e19f7248895b82d67a2af8a05dfbc8f3950aa500e1a0e0ad6bb",
          "fetch_bytes": 212_077_722, "write_bytes": 85_683_520},
     2: {"sources": ("gks_stage2.hip", "gks_device.h", "gks_internal.h"),
-         "sources_sha256": "92459f4e1fa4f798bca3a8f98c19eb4a3c88585477dc9a1582c18b6a9e9721bf",
+         "sources_sha256": "3eab90dc2d2524c7189990b89333d2738d0c68de31bce4d7af7b3e225f1a0e26",
          "fetch_bytes": 289_071_270, "write_bytes": 141_285_597},
 }
 

@@ -34,8 +34,12 @@ enum { ADJ_SUM_ACC, ADJ_SUM_ZERO, ADJ_SUM_LAM_STAR };
 
 struct AdjFaceArgs {
     const double* q[4];     // field in LOCAL variable order (padded)
-    const double* lam[4];   // the flux seeds are l[0] lam + l[1] star (of L, stage 1 only) and
-    const double* star[4];  // lt[0] lam + lt[1] star (of L_t): padded, local order; star in stage 1 only
+    // the flux seeds are l[0] lam + l[1] star (of L, stage 1 only) and lt[0] lam + lt[1] star (of L_t); star in
+    // stage 1 only. lam, star: padded, local order; seed_lam, seed_star: the same in q's layout
+    const double* lam[4];
+    const double* star[4];
+    const double* seed_lam[4];
+    const double* seed_star[4];
     double l[2], lt[2];
     double* slab;           // [tile][march][cell, chunk + 5][variable][12 t2 rows][20 t1 columns]: cell adjoints
     double* acc[4];         // padded cell adjoint (LOCAL order), ghost cells zero beforehand
@@ -45,6 +49,7 @@ struct AdjFaceArgs {
     int chunk, nch, n_wg;  // marches of chunk of the n_n + 1 faces, nch per tile, one per workgroup
     long long st_n, st_t1, st_t2;
     long long pad0;
+    long long qst_n, qst_t1, qst_t2, qpad0;  // of q and the seeds (the x direction reads [x][z][y] copies)
     // inverse spacings (device, the forward's arrays; 1/h on a uniform axis): normal face spacings
     // [n_n + 1], normal widths [n_n], t1 widths [n_t1], t2 widths [n_t2]
     const double* ihf;
@@ -63,6 +68,9 @@ struct AdjBuffers {
     double* lam_star[4]; // padded: adjoint of Q*
     double* lam_new[4];  // padded: adjoint of Q^n, the next step's lam
     double* qwork[4];    // padded: Q^n
+    double* qwork_t[4];  // [x][z][y] copies, read by the x direction: Q^n, lam, lam_star
+    double* lam_t[4];
+    double* star_t[4];
     double* slab;
     double* pt;          // per-point scratch of the ALM adjoint: [16][n_act]
 };
@@ -76,6 +84,8 @@ hipError_t launch_adj_fold(double* f[4], const GridDesc& g, const int bc[6], con
                            const double u_in[3], double c, double rho_ref, hipStream_t s);
 // interior cells of a padded field, four variables back to back
 hipError_t launch_interior(double* dst, const double* const src[4], const GridDesc& g, hipStream_t s);
+// the [x][z][y] copy of a padded field
+hipError_t launch_adj_transpose(double* const dst[4], const double* const src[4], const GridDesc& g, hipStream_t s);
 hipError_t launch_zero(double* y, long long n, hipStream_t s);
 
 // immersed-body adjoint (a body at rest): lam (padded, adjoint of the field after the forcing) becomes

@@ -145,8 +145,8 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
     auto lane_field = [&](const double* const(&p)[4]) {
         return hi ? (m ? p[3] : p[2]) : (m ? p[1] : p[0]);
     };
-    const double* const lam = lane_field(a.lam);
-    const double* const star = lane_field(a.star);
+    const double* const lam = lane_field(a.seed_lam);
+    const double* const star = lane_field(a.seed_star);
     // the two seeds of a cell over its width
     auto seed = [&](long long idx, double w, double& m0, double& m1) {
         const double x = lam[idx] * w;
@@ -165,10 +165,10 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
         const int j0 = (tile % a.tiles_t1) * TILE1, k0 = (tile / a.tiles_t1) * T2;
         // columns outside the padded domain read a clamped column; their faces have zero seeds
         const int jc = min(j0 - 2 + c1, a.n_t1 + NG - 1), kc = min(k0 - 2 + min(c2, X2 - 1), a.n_t2 + NG - 1);
-        const long long cbase = a.pad0 + (long long)jc * a.st_t1 + (long long)kc * a.st_t2;
+        const long long cbase = a.qpad0 + (long long)jc * a.qst_t1 + (long long)kc * a.qst_t2;
         const bool face_ok = (j0 + fj < a.n_t1) && (k0 + fk < a.n_t2);
         const int je = min(j0 + fj, a.n_t1 - 1), ke = min(k0 + fk, a.n_t2 - 1);
-        const long long mbase = a.pad0 + (long long)je * a.st_t1 + (long long)ke * a.st_t2;
+        const long long mbase = a.qpad0 + (long long)je * a.qst_t1 + (long long)ke * a.qst_t2;
         const double ih2 = a.ih2[ke], ih1 = a.ih1[min(j0 + tj, a.n_t1 - 1)];
         // cells f0-3 .. f0+1 and the next; of the evaluation on cell f0-1 its right value (q^L of face f0) and
         // that value's coefficients; the adjoints of cells f-3 .. f+2 that the faces so far reach
@@ -176,8 +176,8 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
 #pragma unroll
-            for (int r = 0; r < 5; ++r) ring[v][r] = qcol[v][cbase + (long long)(f0 - 3 + r) * a.st_n];
-            nxt[v] = qcol[v][cbase + (long long)min(f0 + 2, a.n_n + 2) * a.st_n];
+            for (int r = 0; r < 5; ++r) ring[v][r] = qcol[v][cbase + (long long)(f0 - 3 + r) * a.qst_n];
+            nxt[v] = qcol[v][cbase + (long long)min(f0 + 2, a.n_n + 2) * a.qst_n];
             double left, wr[3], wl[3];
             weno_faces_w<double>(ring[v][0], ring[v][1], ring[v][2], ring[v][3], ring[v][4], eps, carry[v], left, wr, wl);
             weno_coefs<EXACT>(0, ring[v], eps, wr, carry[v], coefL[v]);
@@ -189,17 +189,17 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
         // seeds Fbar(f) = mu(f) / w_f - mu(f-1) / w_{f-1} (cell widths w; no cell beyond the ends) of this
         // lane's variable; the lower cell's term is kept from face to face
         double lo0 = 0.0, lo1 = 0.0;
-        if (f0 >= 1) seed(mbase + (long long)(f0 - 1) * a.st_n, a.ihc[f0 - 1], lo0, lo1);
+        if (f0 >= 1) seed(mbase + (long long)(f0 - 1) * a.qst_n, a.ihc[f0 - 1], lo0, lo1);
         for (int f = f0; f < f1; ++f) {
             double up0 = 0.0, up1;
             {
                 const int c = min(f, a.n_n - 1);
-                seed(mbase + (long long)c * a.st_n, f < a.n_n ? a.ihc[c] : 0.0, up0, up1);
+                seed(mbase + (long long)c * a.qst_n, f < a.n_n ? a.ihc[c] : 0.0, up0, up1);
             }
             // ---- column phase
             {
                 const double ihf = a.ihf[f];
-                const long long idx = cbase + (long long)min(f + 3, a.n_n + 2) * a.st_n;
+                const long long idx = cbase + (long long)min(f + 3, a.n_n + 2) * a.qst_n;
 #pragma unroll
                 for (int v = 0; v < 2; ++v) {
 #pragma unroll
@@ -684,6 +684,48 @@ hipError_t launch_interior(double* dst, const double* const src[4], const GridDe
     return hipGetLastError();
 }
 
+// The [x][z][y] copies that the tile kernel's x direction reads: along x in the fields themselves each column and
+// face keeps a line of its own in use, more than the L2s hold (128^3, stage 1: 1135 us against 825 of the other
+// directions, with the copies 830; 48^3 113 and 91). A copy is bound by memory: 30 to 52 us on 128^3,
+// 5.8 us on 48^3.
+__global__ void __launch_bounds__(512) adj_transpose_kernel(Field4<double> dst, Field4<const double> src, int X, int Y, int Z,
+                                                            int n_wg) {
+    __shared__ double t[4][32][33];
+    const int blk = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+    if (blk >= n_wg) return;
+    const int nbx = (X + 31) / 32, x0 = blk % nbx * 32, z = blk / nbx % Z, y0 = blk / nbx / Z * 32;
+    const int lane = threadIdx.x & 31, row = threadIdx.x >> 5;
+    double v[4][2];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int x = min(x0 + lane, X - 1), y = min(y0 + row + 16 * i, Y - 1);
+            v[w][i] = src.v[w][((long long)z * Y + y) * X + x];
+        }
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) t[w][row + 16 * i][lane] = v[w][i];
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int i = row; i < 32; i += 16)
+            if (x0 + i < X && y0 + lane < Y) dst.v[w][((long long)(x0 + i) * Z + z) * Y + y0 + lane] = t[w][lane][i];
+}
+
+hipError_t launch_adj_transpose(double* const dst[4], const double* const src[4], const GridDesc& g, hipStream_t s) {
+    Field4<double> d;
+    Field4<const double> f;
+    for (int v = 0; v < 4; ++v) d.v[v] = dst[v], f.v[v] = src[v];
+    const int X = g.n[0] + 6, Y = g.n[1] + 6, Z = g.n[2] + 6;
+    const long long blocks = (long long)((X + 31) / 32) * ((Y + 31) / 32) * Z;
+    if (blocks > 0x7fffffffLL - 7) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(adj_transpose_kernel, dim3(pad8((int)blocks)), dim3(512), 0, s, d, f, X, Y, Z, (int)blocks);
+    return hipGetLastError();
+}
+
 __global__ void zero_kernel(double* y, long long n) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) y[i] = 0.0;
@@ -956,8 +998,8 @@ void adjoint_carve(char* base, int nx, int ny, int nz, int n_act, AdjBuffers* b,
         return p;
     };
     const size_t np = (size_t)(nx + 6) * (ny + 6) * (nz + 6);
-    double** pads[4] = {b->lam, b->lam_star, b->lam_new, b->qwork};
-    for (int a = 0; a < 4; ++a)
+    double** pads[7] = {b->lam, b->lam_star, b->lam_new, b->qwork, b->qwork_t, b->lam_t, b->star_t};
+    for (int a = 0; a < 7; ++a)
         for (int v = 0; v < 4; ++v) pads[a][v] = reinterpret_cast<double*>(take(np * 8));
     const int n[3] = {nx, ny, nz};
     const int ax[3][3] = {{0, 1, 2}, {1, 0, 2}, {2, 0, 1}};

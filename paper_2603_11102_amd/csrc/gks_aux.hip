@@ -169,9 +169,14 @@ __device__ __forceinline__ void ghost_transform(real v[4], int axis, int side, i
 // faster there (0.3 %, and 4 % slower on 32^3), tiles of 16 rows 2 % slower.
 constexpr int GHOST_TILE = 32, GHOST_THREADS = 512;
 
-template <typename real>
-__global__ void __launch_bounds__(GHOST_THREADS) ghost_transpose_kernel(Field4<real> q, Field4<real> qt, GhostAll G,
-                                                                        double* part, int n_wg) {
+//
+// RESTORE: a step's state for its adjoint. The interior is read from a checkpoint (`from`) and every cell written to
+// q; the first of a step's two launches sets its time (t). The adjoint's x direction reads the copy. Bound by
+// memory: 59 us on 128^3, 7.2 us on 48^3 for 64 B a cell read once and written twice.
+template <typename real, bool RESTORE>
+__global__ void __launch_bounds__(GHOST_THREADS) ghost_transpose_kernel(Field4<const real> from, Field4<real> q,
+                                                                        Field4<real> qt, GhostAll G, double* part,
+                                                                        int n_wg, const double* t_n, const DtArgs dt) {
     constexpr int T = GHOST_TILE, RS = GHOST_THREADS / T, NR = T / RS;
     __shared__ real t[4][T][T + 1];
     __shared__ double s_max[GHOST_THREADS / 64];
@@ -204,15 +209,16 @@ __global__ void __launch_bounds__(GHOST_THREADS) ghost_transpose_kernel(Field4<r
 #pragma unroll
     for (int i = 0; i < NR; ++i)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) v[i][w] = q.v[w][src[i]];
+        for (int w = 0; w < 4; ++w) v[i][w] = from.v[w][src[i]];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         if (gh[i]) {
             for (int a = 0; a < 3; ++a)
                 if (sd[i][a] >= 0) ghost_transform(v[i], a, sd[i][a], sd[i][a] == 0 ? G.bc_lo[a] : G.bc_hi[a], G);
+        }
+        if (RESTORE ? in[i] : gh[i])
 #pragma unroll
             for (int w = 0; w < 4; ++w) q.v[w][dst[i]] = v[i][w];
-        }
 #pragma unroll
         for (int w = 0; w < 4; ++w) t[w][ty + RS * i][tx] = v[i][w];
         if (part && in[i] && !gh[i]) {
@@ -238,6 +244,10 @@ __global__ void __launch_bounds__(GHOST_THREADS) ghost_transpose_kernel(Field4<r
             const int y = y0 + tx, x = x0 + r;
             if (x < X && y < Y) qt.v[w][((long long)x * Z + z) * Y + y] = t[w][tx][r];
         }
+    if (RESTORE && t_n && blk == 0) {
+        if (threadIdx.x == 0) dt.st->t = *t_n;
+        dt_update<GHOST_THREADS>(dt, s_max);
+    }
 }
 
 GhostAll ghost_args(const GridDesc& gd, const int bc[6], const double u_in[3], double c, double rho_ref) {
@@ -298,37 +308,6 @@ __global__ void __launch_bounds__(256) ghost_shell_kernel(Field4<real> q, GhostA
     for (int w = 0; w < 4; ++w) q.v[w][dst] = v[w];
 }
 
-// A step's state for its adjoint, in one launch: Q^n and Q* from the checkpoint with their ghost cells, and the
-// step's time. Bound by memory, 128 B a cell: 5.9 us on 48^3, 53 us on 128^3 (5.5 TB/s, in part from the caches);
-// as copies of single fields and a fill per axis it took 20 launches and 80 and 145 us.
-__global__ void __launch_bounds__(256) restore_kernel(Field4<const double> cn, Field4<const double> cs, Field4<double> qn,
-                                                      Field4<double> qs, GhostAll G, const double* t, const DtArgs d) {
-    __shared__ double red[4];
-    const int X = G.n[0] + 6, Y = G.n[1] + 6;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
-        if (threadIdx.x == 0) d.st->t = *t;
-        dt_update<256>(d, red);
-    }
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= X * Y) return;
-    const bool second = blockIdx.z != 0;
-    double v[4];
-    ghost_value(second ? cs : cn, p % X - 3, p / X - 3, (int)blockIdx.y - 3, G, v);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) (second ? qs.v[w] : qn.v[w])[(long long)blockIdx.y * X * Y + p] = v[w];
-}
-
-hipError_t launch_restore(const double* const cn[4], const double* const cs[4], Field4<double> qn, Field4<double> qs,
-                          const GridDesc& gd, const int bc[6], const double u_in[3], double c, double rho_ref,
-                          const double* t, const DtArgs& d, hipStream_t s) {
-    Field4<const double> fn, fs;
-    for (int v = 0; v < 4; ++v) fn.v[v] = cn[v], fs.v[v] = cs[v];
-    const int plane = (gd.n[0] + 6) * (gd.n[1] + 6);
-    hipLaunchKernelGGL(restore_kernel, dim3((plane + 255) / 256, gd.n[2] + 6, 2), dim3(256), 0, s, fn, fs, qn, qs,
-                       ghost_args(gd, bc, u_in, c, rho_ref), t, d);
-    return hipGetLastError();
-}
-
 template <typename real>
 hipError_t launch_ghost_shell(Field4<real> q, const GridDesc& gd, const int bc[6], const double u_in[3], double c,
                               double rho_ref, hipStream_t s) {
@@ -344,7 +323,21 @@ hipError_t launch_ghost_transpose(Field4<real> q, Field4<real> qt, const GridDes
                                   const double u_in[3], double c, double rho_ref, double* part, hipStream_t s) {
     const GhostAll G = ghost_args(gd, bc, u_in, c, rho_ref);
     const int n_wg = ghost_parts(gd.n);
-    hipLaunchKernelGGL((ghost_transpose_kernel<real>), dim3(pad8(n_wg)), dim3(GHOST_THREADS), 0, s, q, qt, G, part, n_wg);
+    Field4<const real> from;
+    for (int v = 0; v < 4; ++v) from.v[v] = q.v[v];
+    hipLaunchKernelGGL((ghost_transpose_kernel<real, false>), dim3(pad8(n_wg)), dim3(GHOST_THREADS), 0, s, from, q, qt, G,
+                       part, n_wg, nullptr, DtArgs{});
+    return hipGetLastError();
+}
+
+hipError_t launch_restore(const double* const from[4], Field4<double> q, Field4<double> qt, const GridDesc& gd,
+                          const int bc[6], const double u_in[3], double c, double rho_ref, const double* t,
+                          const DtArgs& dt, hipStream_t s) {
+    Field4<const double> f;
+    for (int v = 0; v < 4; ++v) f.v[v] = from[v];
+    const int n_wg = ghost_parts(gd.n);
+    hipLaunchKernelGGL((ghost_transpose_kernel<double, true>), dim3(pad8(n_wg)), dim3(GHOST_THREADS), 0, s, f, q, qt,
+                       ghost_args(gd, bc, u_in, c, rho_ref), nullptr, n_wg, t, dt);
     return hipGetLastError();
 }
 

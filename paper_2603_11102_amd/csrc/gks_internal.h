@@ -268,9 +268,10 @@ hipError_t launch_diag(Field4<real> f, const real* lo, const GridDesc& g, double
                        DevState* st,
                        hipStream_t s);
 int diag_blocks(const GridDesc& g);
-hipError_t launch_restore(const double* const cn[4], const double* const cs[4], Field4<double> qn, Field4<double> qs,
-                          const GridDesc& gd, const int bc[6], const double u_in[3], double c, double rho_ref,
-                          const double* t, const DtArgs& d, hipStream_t s);
+// checkpointed interior to q with its ghost cells and to the [x][z][y] copy; t (or null): the step's time
+hipError_t launch_restore(const double* const from[4], Field4<double> q, Field4<double> qt, const GridDesc& gd,
+                          const int bc[6], const double u_in[3], double c, double rho_ref, const double* t,
+                          const DtArgs& dt, hipStream_t s);
 hipError_t launch_copy_field(const void* src, void* dst, size_t bytes, hipStream_t s);
 
 }  // namespace gks
