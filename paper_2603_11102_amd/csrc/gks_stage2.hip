@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
     using V4 = typename Vec4<real>::type;
     constexpr bool NEED_F0 = (STAGE == 1);
     constexpr bool COMP = sizeof(real) == 4;   // FP32: compensated state in the stage update
-    constexpr bool SHIFT = sizeof(real) == 4;  // FP32: momenta carried as deviations from workgroup constants
+    constexpr bool SHIFT = sizeof(real) == 4;  // FP32: normal momenta of a face as deviations from a workgroup constant
     constexpr int NF = NEED_F0 ? 2 : 1;
     __shared__ V4 s_q[4][O2H2][O2H1];       // planes, plane k in slot k mod 4
     __shared__ V4 s_fx[NF][O2Y][O2X + 1];   // fluxes of the lower x faces (F1, then F0)
@@ -92,15 +92,14 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
 #pragma unroll
             for (int v = 0; v < 4; ++v) x[s][v] = a.q[v][src[s] + off];
     };
-    real cm[3] = {0, 0, 0};
     auto store_plane = [&](int k, const real (&x)[2][4]) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             V4 y;
             y.x = x[s][0];
-            y.y = SHIFT ? x[s][1] - cm[0] : x[s][1];
-            y.z = SHIFT ? x[s][2] - cm[1] : x[s][2];
-            y.w = SHIFT ? x[s][3] - cm[2] : x[s][3];
+            y.y = x[s][1];
+            y.z = x[s][2];
+            y.w = x[s][3];
             (&s_q[k & 3][0][0])[pos[s]] = y;
         }
     };
@@ -109,9 +108,12 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
 #pragma unroll
     for (int r = 0; r < 4; ++r) load_plane(k0 - 2 + r, pre[r]);
     load_plane(k0 + 2, nxt);
+    real cm[3] = {0, 0, 0};
     if constexpr (SHIFT) {
         // the midrange of each momentum over the chunk's first plane of the tile: the constant part of a mass
-        // flux then cancels exactly between the two faces of a cell and FP32 rounding acts on the deviation only
+        // flux then cancels exactly between the two faces of a cell and FP32 rounding acts on the deviation only. The
+        // planes in LDS keep the momenta whole: a tangential momentum much smaller than the midrange (at a no-slip
+        // wall) would lose its low bits to the shift, and with them its derivatives
         __shared__ float s_range[6][O2_THREADS / 64];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -153,12 +155,9 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
             const int v = kLocal[D][l];
             const real qm2 = get(cm2, v), qm1 = get(cm1, v), q0 = get(c0, v), qp1 = get(cp1, v);
             const real dm = q0 - qm1;
-            qL[l] = qm1 + real(0.5) * van_leer(qm1 - qm2, dm);
-            qR[l] = q0 - real(0.5) * van_leer(dm, qp1 - q0);
-            if (SHIFT && l > 1) {  // tangential momenta enter the flux whole
-                qL[l] += cm[v - 1];
-                qR[l] += cm[v - 1];
-            }
+            const real sh = SHIFT && l == 1 ? cm[D] : real(0);  // the normal momentum's deviation enters the flux
+            qL[l] = (SHIFT && l == 1 ? qm1 - sh : qm1) + real(0.5) * van_leer(qm1 - qm2, dm);
+            qR[l] = (SHIFT && l == 1 ? q0 - sh : q0) - real(0.5) * van_leer(dm, qp1 - q0);
             g[0][l] = dm * ihf;
             g[1][l] = ((get(p1a, v) + get(p1b, v)) - (get(m1a, v) + get(m1b, v))) * (real(0.25) * ih1);
             g[2][l] = ((get(p2a, v) + get(p2b, v)) - (get(m2a, v) + get(m2b, v))) * (real(0.25) * ih2);
