@@ -61,7 +61,7 @@ struct gks_ctx {
     double* diag_partials;
     int diag_nblk;
     double* umax_part;  // per-workgroup maxima of |U|^2 for the CFL time step
-    int umax_fused;     // formed by the ghost fill (order 5, where they fit), else by a kernel of their own
+    int umax_fused;     // formed by the ghost fill (order 5), else by a kernel of their own
     // per-axis inverse spacings in the stage precision (face spacings [n + 1], widths [n]) and FP64
     // relative widths; stretched: some axis has its own faces
     void* ihf[3];
@@ -159,7 +159,6 @@ struct Layout {
     void* lo[3];
     double* diag;
     double* umax_part;
-    int umax_cap;
     char* alm;
     char* ibm;
     size_t total;
@@ -223,16 +222,11 @@ bool layout(const gks_config* c, char* base, Layout* L) {
     for (int v = 0; v < 4; ++v) L->qt[v] = cv.ptr<void>(NP * es);
     for (int b = 0; b < 3; ++b) L->lo[b] = c->precision == GKS_FP32 ? cv.ptr<void>(4 * N * es) : nullptr;
     L->diag = cv.ptr<double>(sizeof(double) * 4 * 1024);
+    L->umax_part = cv.ptr<double>(sizeof(double) * UMAX_BLOCKS);
     size_t ab = alm_block_bytes(c->max_act);
     L->alm = ab ? cv.ptr<char>(ab) : nullptr;
     size_t ib = ibm_block_bytes(c->max_ibm);
     L->ibm = ib ? cv.ptr<char>(ib) : nullptr;
-    // a partial maximum per workgroup of the ghost fill; where the workspace could be the static scratch, no more
-    // than that has always held
-    L->umax_cap = UMAX_BLOCKS;
-    if (c->order != 2 && cv.off + sizeof(double) * UMAX_BLOCKS > GKS_STATIC_SCRATCH_BYTES)
-        L->umax_cap = std::max(UMAX_BLOCKS, ghost_parts(n));
-    L->umax_part = cv.ptr<double>(sizeof(double) * L->umax_cap);
     L->total = cv.off;
     return true;
 }
@@ -846,8 +840,6 @@ int gks_init(const gks_config* cfg, gks_field q, gks_field q_stage, gks_field q_
     c->lo_qa = L.lo[2];
     c->diag_partials = L.diag;
     c->umax_part = L.umax_part;
-    const int n_[3] = {cfg->nx, cfg->ny, cfg->nz};
-    c->umax_fused = cfg->order != 2 && ghost_parts(n_) <= L.umax_cap;
     c->alm_mem = reinterpret_cast<double*>(L.alm);
     c->ibm_mem = L.ibm;
     const int n[3] = {cfg->nx, cfg->ny, cfg->nz};
@@ -884,6 +876,12 @@ int gks_init(const gks_config* cfg, gks_field q, gks_field q_stage, gks_field q_
     c->diag_nblk = diag_blocks(c->g);
     c->flags = cfg->ma > 0.3 ? GKS_WARN_MACH : 0;
     face_layout(c);
+    // The ghost fill leaves a partial maximum of |U|^2 per workgroup. More of them than have a place of their own stand
+    // in the y pass's residual array, which nothing holds values in until the stage-1 face launches: the time step is
+    // formed before those, except side by side, where the ghost fill then leaves the maxima to umax_kernel.
+    const bool own = ghost_parts(n) <= UMAX_BLOCKS;
+    c->umax_fused = cfg->order != 2 && (own || !c->side_by_side);
+    if (c->umax_fused && !own) c->umax_part = static_cast<double*>(c->r0);
     hipError_t e = cfg->precision == GKS_FP32 ? upload_metrics<float>(c, cfg) : upload_metrics<double>(c, cfg);
     if (e == hipSuccess) e = hipMemsetAsync(c->st, 0, sizeof(DevState), c->stream);
     if (e == hipSuccess) e = clear_low_parts(c);

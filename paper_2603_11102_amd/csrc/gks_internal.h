@@ -49,7 +49,7 @@ struct LocalOrder<5> : LocalOrder<4> {};  // the z pass that leaves its residual
 __host__ __device__ inline int pad8(int n) { return (n + 7) / 8 * 8; }
 
 // Device-resident scalars of a context (lives in the workspace).
-constexpr int UMAX_BLOCKS = 2048;  // workgroups of umax_kernel at most, and the least room for partial maxima
+constexpr int UMAX_BLOCKS = 2048;  // workgroups of umax_kernel at most, and the room for partial maxima
 
 struct DevState {
     double t, dt, t_next;
