@@ -21,12 +21,12 @@ namespace gks {
 struct AdjTile {
     static constexpr int T2 = 8, THREADS = 64 * T2;
 };
-constexpr int ADJ_CELL = 4 * (AdjTile::T2 + 4) * EXT1;  // doubles per cell layer of a tile's columns
 constexpr int ADJ_SLOTS = 256;  // workgroups at once (256 CUs); fixed, since the workspace's size depends on the split
 
-// Work split of one direction: marches of `chunk` faces, nch per tile.
+// Work split of one direction: marches of `chunk` faces, nch per tile. x1, x2: columns of a tile that the slab
+// keeps, 20 x 12, or of a single narrow tile only those the domain's cells reach.
 struct AdjSplit {
-    int tiles_t1, tiles_t2, chunk, nch;
+    int tiles_t1, tiles_t2, chunk, nch, x1, x2;
 };
 AdjSplit adj_split(int n_n, int n_t1, int n_t2);
 
@@ -41,12 +41,13 @@ struct AdjFaceArgs {
     const double* seed_lam[4];
     const double* seed_star[4];
     double l[2], lt[2];
-    double* slab;           // [tile][march][cell, chunk + 5][variable][12 t2 rows][20 t1 columns]: cell adjoints
+    double* slab;           // [tile][march][cell, chunk + 5][variable][x2 t2 rows][x1 t1 columns]: cell adjoints
     double* acc[4];         // padded cell adjoint (LOCAL order), ghost cells zero beforehand
     int sum;                // what adj_sum_kernel adds the direction's cell adjoints to
     int n_n, n_t1, n_t2;
     int tiles_t1, tiles_t2;
     int chunk, nch, n_wg;  // marches of chunk of the n_n + 1 faces, nch per tile, one per workgroup
+    int x1, x2;
     long long st_n, st_t1, st_t2;
     long long pad0;
     long long qst_n, qst_t1, qst_t2, qpad0;  // of q and the seeds (the x direction reads [x][z][y] copies)
@@ -67,10 +68,7 @@ struct AdjBuffers {
     double* lam[4];      // padded: adjoint of Q^{n+1}, after the actuator line of Q^{n+1,pre}
     double* lam_star[4]; // padded: adjoint of Q*
     double* lam_new[4];  // padded: adjoint of Q^n, the next step's lam
-    double* qwork[4];    // padded: Q^n
-    double* qwork_t[4];  // [x][z][y] copies, read by the x direction: Q^n, lam, lam_star
-    double* lam_t[4];
-    double* star_t[4];
+    double* star_t[4];   // [x][z][y] copy of lam_star, read by the x direction
     double* slab;
     double* pt;          // per-point scratch of the ALM adjoint: [16][n_act]
 };

@@ -121,7 +121,7 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
     constexpr int T1S = 5 * X2 * 32 + 4;
     // adjoints of the normal face values [variable][q^L, q^R, D][t2 row][t1 column], beside the t1-line adjoints
     double* const s_fb = s_w + 4 * T1S;
-    static_assert(4 * T1S + 12 * X2 * EXT1 <= 32 * NTH && X2 * EXT1 * 4 == ADJ_CELL, "LDS regions");
+    static_assert(4 * T1S + 12 * X2 * EXT1 <= 32 * NTH, "LDS regions");
     auto t1_at = [&](int v, int q, int row, int c) -> double& { return s_w[v * T1S + (q * X2 + row) * 32 + c]; };
 
     const int tid = threadIdx.x;
@@ -185,7 +185,10 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
             for (int r = 0; r < 6; ++r) cell[v][r] = 0.0;
         }
         // this march's cells f0-3 .. f1+1 of its columns, [cell][variable][column]
-        double* const slab = a.slab + ((long long)tile * a.nch + f0 / a.chunk) * (a.chunk + 5) * ADJ_CELL;
+        const int var_len = a.x1 * a.x2;
+        const bool keep = col && c1 < a.x1 && c2 < a.x2;
+        double* slab = a.slab + ((long long)tile * a.nch + f0 / a.chunk) * (a.chunk + 5) * (4 * var_len) + cv * var_len +
+                       c2 * a.x1 + c1;
         // seeds Fbar(f) = mu(f) / w_f - mu(f-1) / w_{f-1} (cell widths w; no cell beyond the ends) of this
         // lane's variable; the lower cell's term is kept from face to face
         double lo0 = 0.0, lo1 = 0.0;
@@ -447,20 +450,20 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
                     cell[v][3] += 15.0 * bD;
                     cell[v][4] -= bD;
                     weno_coefs<EXACT>(0, ring[v], eps, wr, right, coefL[v]);
-                    slab[(long long)(f - f0) * ADJ_CELL + (cv + v) * (X2 * EXT1) + ct] = cell[v][0];
+                    if (keep) slab[v * var_len] = cell[v][0];
 #pragma unroll
                     for (int r = 0; r < 5; ++r) cell[v][r] = cell[v][r + 1];
                     cell[v][5] = 0.0;
                 }
+                slab += 4 * var_len;
             }
             // the next face rewrites s_nrm at once (last read before the barrier) and s_fb after two barriers
         }
-        if (col)
+        if (keep)
 #pragma unroll
             for (int v = 0; v < 2; ++v)
 #pragma unroll
-                for (int r = 0; r < 5; ++r)
-                    slab[(long long)(f1 - f0 + r) * ADJ_CELL + (cv + v) * (X2 * EXT1) + ct] = cell[v][r];
+                for (int r = 0; r < 5; ++r) slab[(4 * r + v) * var_len] = cell[v][r];
     }
 }
 
@@ -500,7 +503,8 @@ __global__ void __launch_bounds__(ADJ_SUM_THREADS) adj_sum_kernel(const AdjFaceA
         const int jx = jx0 + lane;
         // the tiles whose columns hold (jx, kx): in t1 and t2 the one before (its last four columns), then the own
         const int T1 = (jx + 2) / TILE1, c1 = (jx + 2) % TILE1, T2 = (kx + 2) / AdjTile::T2, c2 = (kx + 2) % AdjTile::T2;
-        const long long tile_len = (long long)a.nch * (a.chunk + 5) * ADJ_CELL;
+        const int var_len = a.x1 * a.x2;
+        const long long tile_len = (long long)a.nch * (a.chunk + 5) * (4 * var_len);
         const double* p[4];
         bool ok[4];
 #pragma unroll
@@ -509,8 +513,8 @@ __global__ void __launch_bounds__(ADJ_SUM_THREADS) adj_sum_kernel(const AdjFaceA
             const int t1 = T1 - d1, t2 = T2 - d2;
             ok[e] = jx < a.n_t1 + 2 && t1 >= 0 && t1 < a.tiles_t1 && (d1 == 0 || c1 < EXT1 - TILE1) && t2 >= 0 &&
                     t2 < a.tiles_t2 && (d2 == 0 || c2 < X2 - AdjTile::T2);
-            p[e] = a.slab + ((long long)t2 * a.tiles_t1 + t1) * tile_len + v * (X2 * EXT1) +
-                   (c2 + AdjTile::T2 * d2) * EXT1 + c1 + TILE1 * d1;
+            p[e] = a.slab + ((long long)t2 * a.tiles_t1 + t1) * tile_len + v * var_len + (c2 + AdjTile::T2 * d2) * a.x1 + c1 +
+                   TILE1 * d1;
         }
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -520,7 +524,7 @@ __global__ void __launch_bounds__(ADJ_SUM_THREADS) adj_sum_kernel(const AdjFaceA
                 for (int m = s_m[row + RS * r][0]; m <= s_m[row + RS * r][1]; ++m) {
                     const int f0 = m * a.chunk, len = min(a.chunk, nf - f0), slot = i - (f0 - 3);
                     if (slot < 0 || slot >= len + 5) continue;
-                    const long long o = ((long long)m * (a.chunk + 5) + slot) * ADJ_CELL;
+                    const long long o = ((long long)m * (a.chunk + 5) + slot) * (4 * var_len);
                     double x[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -987,6 +991,8 @@ AdjSplit adj_split(int n_n, int n_t1, int n_t2) {
     s.tiles_t2 = (n_t2 + AdjTile::T2 - 1) / AdjTile::T2;
     s.chunk = face_chunk(n_n + 1, s.tiles_t1 * s.tiles_t2, ADJ_SLOTS);
     s.nch = (n_n + 1 + s.chunk - 1) / s.chunk;
+    s.x1 = std::min(EXT1, n_t1 + 4);
+    s.x2 = std::min(AdjTile::T2 + 4, n_t2 + 4);
     return s;
 }
 
@@ -998,17 +1004,17 @@ void adjoint_carve(char* base, int nx, int ny, int nz, int n_act, AdjBuffers* b,
         return p;
     };
     const size_t np = (size_t)(nx + 6) * (ny + 6) * (nz + 6);
-    double** pads[7] = {b->lam, b->lam_star, b->lam_new, b->qwork, b->qwork_t, b->lam_t, b->star_t};
-    for (int a = 0; a < 7; ++a)
+    double** pads[4] = {b->lam, b->lam_star, b->lam_new, b->star_t};
+    for (int a = 0; a < 4; ++a)
         for (int v = 0; v < 4; ++v) pads[a][v] = reinterpret_cast<double*>(take(np * 8));
     const int n[3] = {nx, ny, nz};
     const int ax[3][3] = {{0, 1, 2}, {1, 0, 2}, {2, 0, 1}};
-    size_t cells = 0;  // (tile, march, cell) of the tile kernel's output
+    size_t cells = 0;  // doubles of the tile kernel's output
     for (int d = 0; d < 3; ++d) {
         const AdjSplit sp = adj_split(n[ax[d][0]], n[ax[d][1]], n[ax[d][2]]);
-        cells = std::max(cells, (size_t)sp.tiles_t1 * sp.tiles_t2 * sp.nch * (sp.chunk + 5));
+        cells = std::max(cells, (size_t)sp.tiles_t1 * sp.tiles_t2 * sp.nch * (sp.chunk + 5) * 4 * sp.x1 * sp.x2);
     }
-    b->slab = reinterpret_cast<double*>(take(cells * ADJ_CELL * 8));
+    b->slab = reinterpret_cast<double*>(take(cells * 8));
     b->pt = reinterpret_cast<double*>(take(16 * (size_t)std::max(n_act, 1) * 8));
     *total = off;
 }

@@ -457,18 +457,19 @@ FaceArgs<real> face_args(gks_ctx* c, int d, int stage, void* const src[4]) {
     return face_args_buf<real>(c, d, 2, src, c->q, c->qa, nullptr, c->qt, c->lo_qa, c->lo_q, nullptr);
 }
 
-AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, int stage, void* const src[4], void* const xt[4],
-                     double dt, int exact) {
+// Of a direction and stage: the stage's field stands in q_stage and, copied for the x direction, in the [x][z][y]
+// copy of the step, the copy of lam in q_acc.
+AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, int stage, double dt, int exact) {
     AdjFaceArgs a;
     std::memset(&a, 0, sizeof(a));
     const int* pm = kPerm[d];
     const int* ax = kAxes[d];
     for (int v = 0; v < 4; ++v) {
         const int gv = pm[v];
-        a.q[v] = static_cast<const double*>(src[gv]);
+        a.q[v] = static_cast<const double*>(d == 0 ? c->qt[gv] : c->qs[gv]);
         a.lam[v] = B.lam[gv];
         a.star[v] = B.lam_star[gv];
-        a.seed_lam[v] = d == 0 ? B.lam_t[gv] : B.lam[gv];
+        a.seed_lam[v] = d == 0 ? static_cast<const double*>(c->qa[gv]) : B.lam[gv];
         a.seed_star[v] = d == 0 ? B.star_t[gv] : B.lam_star[gv];
         a.acc[v] = stage == 1 ? B.lam_new[gv] : B.lam_star[gv];
     }
@@ -492,6 +493,8 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, int stage, void* co
     a.tiles_t2 = sp.tiles_t2;
     a.chunk = sp.chunk;
     a.nch = sp.nch;
+    a.x1 = sp.x1;
+    a.x2 = sp.x2;
     a.n_wg = sp.tiles_t1 * sp.tiles_t2 * sp.nch;
     a.st_n = c->g.st[ax[0]];
     a.st_t1 = c->g.st[ax[1]];
@@ -502,7 +505,6 @@ AdjFaceArgs adj_args(gks_ctx* c, const AdjBuffers& B, int d, int stage, void* co
     a.qst_t2 = a.st_t2;
     if (d == 0) {
         const long long Y = c->cfg.ny + 6, Z = c->cfg.nz + 6;
-        for (int v = 0; v < 4; ++v) a.q[v] = static_cast<const double*>(xt[pm[v]]);
         a.qst_n = Y * Z;
         a.qst_t1 = 1;
         a.qst_t2 = Y;
@@ -1264,8 +1266,6 @@ int gks_adjoint(gks_ctx* c, int32_t nsteps, const double w[2], double* grad_s, d
     HIPCHK(c, launch_zero(grad_s, c->alm.n_act, S));
     const size_t slot = gks_checkpoint_slot_bytes(&c->cfg);
     const size_t fb = ((size_t)np * 8 + 255) & ~size_t(255);
-    void* const qwork[4] = {B.qwork[0], B.qwork[1], B.qwork[2], B.qwork[3]};
-    void* const qwork_t[4] = {B.qwork_t[0], B.qwork_t[1], B.qwork_t[2], B.qwork_t[3]};
     for (int n = nsteps - 1; n >= 0; --n) {
         // step n from its checkpoint: Q^n, Q* and the field before the body forces (stored by the
         // forward, bitwise what a recompute gives; the last is read in place), and t
@@ -1273,10 +1273,12 @@ int gks_adjoint(gks_ctx* c, int32_t nsteps, const double w[2], double* grad_s, d
         const double* ck[12];
         for (int v = 0; v < 12; ++v) ck[v] = reinterpret_cast<const double*>(src + v * fb);
         const DtArgs fixed{c->st, nullptr, 0, 0.0, c->hmin, c->c, dt};
-        HIPCHK(c, launch_restore(ck, field<double>(qwork), field<double>(qwork_t), c->g, c->cfg.bc, c->cfg.u_in, c->c,
-                                 c->cfg.rho_ref, reinterpret_cast<const double*>(src + slot - 256), fixed, S));
-        HIPCHK(c, launch_restore(ck + 4, field<double>(c->qs), field<double>(c->qt), c->g, c->cfg.bc, c->cfg.u_in, c->c,
-                                 c->cfg.rho_ref, nullptr, fixed, S));
+        // Q* for stage 2, with the step's time; Q^n takes its place for stage 1
+        auto restore = [&](const double* const from[4], const double* t) {
+            return launch_restore(from, field<double>(c->qs), field<double>(c->qt), c->g, c->cfg.bc, c->cfg.u_in, c->c,
+                                  c->cfg.rho_ref, t, fixed, S);
+        };
+        HIPCHK(c, restore(ck + 4, reinterpret_cast<const double*>(src + slot - 256)));
         Field4<double> qpre;
         for (int v = 0; v < 4; ++v) qpre.v[v] = const_cast<double*>(ck[8 + v]);  // sampled only
         HIPCHK(c, launch_alm_points_only(qpre, c->alm, S));
@@ -1296,13 +1298,14 @@ int gks_adjoint(gks_ctx* c, int32_t nsteps, const double w[2], double* grad_s, d
         A.w1 = w[1];
         A.inv_n = 1.0 / nsteps;
         HIPCHK(c, launch_alm_adjoint(A, S));
-        HIPCHK(c, launch_adj_transpose(B.lam_t, B.lam, c->g, S));
+        double* const lam_t[4] = {static_cast<double*>(c->qa[0]), static_cast<double*>(c->qa[1]),
+                                  static_cast<double*>(c->qa[2]), static_cast<double*>(c->qa[3])};
+        HIPCHK(c, launch_adj_transpose(lam_t, B.lam, c->g, S));
         for (int stage = 2; stage >= 1; --stage) {
-            void* const* const q = stage == 2 ? c->qs : qwork;
-            void* const* const qt = stage == 2 ? c->qt : qwork_t;
-            for (int d = 0; d < 3; ++d) HIPCHK(c, launch_adj_direction(adj_args(c, B, d, stage, q, qt, dt, exact), stage, S));
-            const double* const qd[4] = {static_cast<const double*>(q[0]), static_cast<const double*>(q[1]),
-                                         static_cast<const double*>(q[2]), static_cast<const double*>(q[3])};
+            if (stage == 1) HIPCHK(c, restore(ck, nullptr));
+            for (int d = 0; d < 3; ++d) HIPCHK(c, launch_adj_direction(adj_args(c, B, d, stage, dt, exact), stage, S));
+            const double* const qd[4] = {static_cast<const double*>(c->qs[0]), static_cast<const double*>(c->qs[1]),
+                                         static_cast<const double*>(c->qs[2]), static_cast<const double*>(c->qs[3])};
             HIPCHK(c, launch_adj_fold(stage == 2 ? B.lam_star : B.lam_new, c->g, c->cfg.bc, qd, c->cfg.u_in, c->c,
                                       c->cfg.rho_ref, S));
             if (stage == 2) HIPCHK(c, launch_adj_transpose(B.star_t, B.lam_star, c->g, S));

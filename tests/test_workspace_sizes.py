@@ -32,3 +32,18 @@ def config(grid, precision, order=5, max_act=0, max_ibm=0):
 def test_context_workspace_fits_a_stored_size(grid, precision, order, max_act, max_ibm, stored):
     need = L.load().gks_workspace_bytes(C.byref(config(grid, precision, order, max_act, max_ibm)))
     assert 0 < need <= stored
+
+
+@pytest.mark.parametrize("grid,n_act,stored", [
+    ((128, 128, 128), 96, 2587484672),
+    ((48, 48, 48), 48, 146426368),
+    ((20, 120, 20), 96, 70588416),
+    ((17, 9, 9), 6, 2835200),       # one cell past a tile, nine of two tiles' sixteen rows
+    ((16, 8, 9), 6, 2465024),
+    ((3, 24, 3), 0, 948224),        # narrower than a tile
+    ((9, 3, 3), 6, 420352),
+    ((3, 3, 187), 3, 6529024),
+])
+def test_adjoint_workspace_fits_a_stored_size(grid, n_act, stored):
+    need = L.load().gks_adjoint_workspace_bytes(C.byref(config(grid, L.GKS_FP64, 5, 96)), n_act)
+    assert 0 < need <= stored
