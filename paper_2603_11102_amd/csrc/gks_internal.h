@@ -237,7 +237,7 @@ struct FaceSplit {
 int face_split(const FaceDir* dirs, int ndirs, int slots, FaceSplit* out);
 // second-order variant (gks_stage2.hip): one launch per stage; stage2_chunk: planes per workgroup
 template <typename real>
-hipError_t launch_stage2(Face2Args<real> a, int stage, hipStream_t s);
+hipError_t launch_stage2(const Face2Args<real>& a, int stage, hipStream_t s);
 int stage2_chunk(const int n[3], int f64);
 
 // host launchers (gks_aux.hip)

@@ -3,9 +3,9 @@
 // stages of the high-order scheme, with van Leer-limited linear face states, central-difference gradients
 // of the equilibrium state and one flux evaluation at the face centre.
 //
-// One launch does a whole stage: a workgroup of 512 threads owns 32 x 16 cells of the (x, y) plane and
-// marches along z; each thread evaluates the three lower (x, y) and upper (z) faces of its cell. The scheme
-// reads 13 cells per face and does a few hundred operations on them, so it is bound by the passes over memory:
+// One launch does a whole stage: a workgroup of 512 threads owns 32 x 16 cells of the (x, y) plane (16 x 32 on
+// grids of few cells in x) and marches along z; each thread evaluates the three lower (x, y) and upper (z) faces of
+// its cell. The scheme reads 13 cells per face and does a few hundred operations on them, so it is bound by the passes over memory:
 // one pass per direction (with residual arrays between them and a transposed copy of the field for the x
 // pass) moved 590 MB per stage 1 of the 192 x 96 x 96 channel in FP32, where reading the state and writing
 // the stage's results is 200 MB. Four planes of the tile and its two-cell halo live in LDS (46 KB FP32, two
@@ -20,8 +20,13 @@ namespace gks {
 
 namespace {
 
-constexpr int O2X = 32, O2Y = 16, O2_THREADS = O2X * O2Y;
-constexpr int O2H1 = O2X + 4, O2H2 = O2Y + 4;  // tile plus two cells per side
+constexpr int O2_THREADS = 512;
+
+// Cells of a tile along x; along y it has O2_THREADS / this many. 16 on grids of up to 16 cells in x, which leave at
+// least half of a 32-cell row idle (FP32, us a step with 32 / 16, and with a launch per direction on 16 x 16 tiles:
+// 3 x 512 x 512 513 / 296, 424; 8 x 512 x 512 557 / 333, 571; 12 x 512 x 512 601 / 379, 676); 32 else, whose rows fill whole
+// cache lines. The halo is as large either way (720 cells).
+int stage2_tile_x(int nx) { return nx <= 16 ? 16 : 32; }
 
 template <typename real>
 __device__ __forceinline__ real van_leer(real dm, real dp) {
@@ -51,9 +56,11 @@ constexpr int kLocal[3][4] = {{0, 1, 2, 3}, {0, 2, 1, 3}, {0, 3, 1, 2}};
 
 }  // namespace
 
-template <typename real, int STAGE, bool STR>
+template <typename real, int STAGE, bool STR, int O2X>
 __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_kernel(const Face2Args<real> a) {
     using V4 = typename Vec4<real>::type;
+    constexpr int O2Y = O2_THREADS / O2X, O2H1 = O2X + 4, O2H2 = O2Y + 4;  // tile, and with two cells per side
+    static_assert(O2X <= 64 && O2Y <= 64 && O2H1 * O2H2 <= 2 * O2_THREADS, "a wave per upper end, two cells a thread");
     constexpr bool NEED_F0 = (STAGE == 1);
     constexpr bool COMP = sizeof(real) == 4;   // FP32: compensated state in the stage update
     constexpr bool SHIFT = sizeof(real) == 4;  // FP32: normal momenta of a face as deviations from a workgroup constant
@@ -77,7 +84,7 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
     const int ti = tid % O2X, tj = tid / O2X;
     const int i = i0 + ti, j = j0 + tj;
     const bool in = i < a.n[0] && j < a.n[1];
-    // cells of a plane that this thread stages: positions tid and tid + 512 of the 36 x 20 ones, clamped to the
+    // cells of a plane that this thread stages: positions tid and tid + 512 of the 720 ones, clamped to the
     // padded domain (what lies beyond reaches no cell of it)
     const int pos[2] = {tid, min(tid + O2_THREADS, O2H1 * O2H2 - 1)};
     long long src[2];
@@ -306,31 +313,38 @@ int stage2_chunk(const int n[3], int f64) {
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) {
         const hipError_t e =
-            f64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage2_kernel<double, 1, false>, O2_THREADS, 0)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage2_kernel<float, 1, false>, O2_THREADS, 0);
+            f64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage2_kernel<double, 1, false, 32>, O2_THREADS, 0)
+                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage2_kernel<float, 1, false, 32>, O2_THREADS, 0);
         if (e == hipSuccess) slots = cus * per_cu;
     }
-    return face_chunk(n[2], ((n[0] + O2X - 1) / O2X) * ((n[1] + O2Y - 1) / O2Y), slots);
+    const int tx = stage2_tile_x(n[0]), ty = O2_THREADS / tx;
+    return face_chunk(n[2], ((n[0] + tx - 1) / tx) * ((n[1] + ty - 1) / ty), slots);
 }
 
-template <typename real>
-hipError_t launch_stage2(Face2Args<real> a, int stage, hipStream_t s) {
+template <typename real, int O2X>
+hipError_t launch_stage2_tiles(Face2Args<real> a, int stage, hipStream_t s) {
+    constexpr int O2Y = O2_THREADS / O2X;
     a.tiles_x = (a.n[0] + O2X - 1) / O2X;
     a.tiles_y = (a.n[1] + O2Y - 1) / O2Y;
     const long long blocks = ((long long)a.tiles_x * a.tiles_y * ((a.n[2] + a.chunk - 1) / a.chunk) + 7) / 8 * 8;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(O2_THREADS);
     if (stage == 1) {
-        if (a.stretched) hipLaunchKernelGGL((stage2_kernel<real, 1, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((stage2_kernel<real, 1, false>), grid, block, 0, s, a);
+        if (a.stretched) hipLaunchKernelGGL((stage2_kernel<real, 1, true, O2X>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((stage2_kernel<real, 1, false, O2X>), grid, block, 0, s, a);
     } else {
-        if (a.stretched) hipLaunchKernelGGL((stage2_kernel<real, 2, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((stage2_kernel<real, 2, false>), grid, block, 0, s, a);
+        if (a.stretched) hipLaunchKernelGGL((stage2_kernel<real, 2, true, O2X>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((stage2_kernel<real, 2, false, O2X>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }
 
-template hipError_t launch_stage2<float>(Face2Args<float>, int, hipStream_t);
-template hipError_t launch_stage2<double>(Face2Args<double>, int, hipStream_t);
+template <typename real>
+hipError_t launch_stage2(const Face2Args<real>& a, int stage, hipStream_t s) {
+    return stage2_tile_x(a.n[0]) == 16 ? launch_stage2_tiles<real, 16>(a, stage, s) : launch_stage2_tiles<real, 32>(a, stage, s);
+}
+
+template hipError_t launch_stage2<float>(const Face2Args<float>&, int, hipStream_t);
+template hipError_t launch_stage2<double>(const Face2Args<double>&, int, hipStream_t);
 
 }  // namespace gks
