@@ -70,10 +70,7 @@ struct gks_ctx {
     int stretched;
     std::vector<double> faces[3];  // host copy of the faces of each stretched axis (empty when uniform)
     double lam, c, hmin, eps;
-    int t2[3];         // t2 rows of a face tile, per direction
-    int chunk[3];      // faces per workgroup of the face kernels, per direction
-    int seg_len[3], n_wg[3];  // work split of the order-5 face launches (FaceArgs)
-    int side_by_side;  // order 5: the three directions of a stage run in one launch (face_layout)
+    FacePlan plan;     // order 2: chunk[2] alone, planes per workgroup
     int flags;
     // actuator line model
     int has_rotor;
@@ -407,13 +404,13 @@ FaceArgs<real> face_args_buf(gks_ctx* c, int d, int stage, void* const src[4], v
     a.n_n = c->g.n[ax[0]];
     a.n_t1 = c->g.n[ax[1]];
     a.n_t2 = c->g.n[ax[2]];
-    const int t2 = c->t2[d];
+    const int t2 = c->plan.rows;
     a.t2 = t2;
     a.tiles_t1 = (a.n_t1 + TILE1 - 1) / TILE1;
     a.tiles_t2 = (a.n_t2 + t2 - 1) / t2;
-    a.chunk = c->chunk[d];
-    a.seg_len = c->seg_len[d];
-    a.n_wg = c->n_wg[d];
+    a.chunk = c->plan.chunk[d];
+    a.seg_len = c->plan.seg_len[d];
+    a.n_wg = c->plan.n_wg[d];
     a.st_n = c->g.st[ax[0]];
     a.st_t1 = c->g.st[ax[1]];
     a.st_t2 = c->g.st[ax[2]];
@@ -561,53 +558,16 @@ void tend(gks_ctx* c, int pair) {
     if (pair >= 0) (void)hipEventRecord(c->ev_pool[2 * pair + 1], c->stream);
 }
 
-// Tiles, work split and launches of the face passes.
 void face_layout(gks_ctx* c) {
-    const gks_config* cfg = &c->cfg;
-    const bool f64 = cfg->precision == GKS_FP64;
-    const int n[3] = {cfg->nx, cfg->ny, cfg->nz};
-    auto tiles = [&](int d, int rows) {
-        const int* ax = kAxes[d];
-        return ((n[ax[1]] + TILE1 - 1) / TILE1) * ((n[ax[2]] + rows - 1) / rows);
-    };
-    c->side_by_side = 0;
-    if (cfg->order == 2) {
-        for (int d = 0; d < 3; ++d) c->t2[d] = c->chunk[d] = c->seg_len[d] = c->n_wg[d] = 0;
-        c->chunk[2] = stage2_chunk(n, f64);
+    const bool f64 = c->cfg.precision == GKS_FP64;
+    c->plan = FacePlan{};
+    if (c->cfg.order == 2) {
+        c->plan.chunk[2] = stage2_chunk(c->g.n, f64);
         return;
     }
-    // Each tile height (FP64: two, see FACE64_ROWS) in both launch schemes, by estimated time in ns: face steps
-    // of the longest workgroup times the step, and per launch its start and end.
-    const double cells = (double)n[0] * n[1] * n[2];
-    double best = -1.0;
-    for (int o = 0; o < (f64 ? 2 : 1); ++o) {
-        const int rows = f64 ? FACE64_ROWS[o] : TILE2;
-        const int slots = f64 ? face_slots<double>(rows) : face_slots<float>(rows);
-        const double step = f64 ? FACE64_STEP[o] : FACE32_STEP;
-        FaceDir dir[3];
-        for (int d = 0; d < 3; ++d) dir[d] = FaceDir{n[kAxes[d][0]], tiles(d, rows)};
-        for (int scheme = 0; scheme < 2; ++scheme) {
-            FaceSplit sp[3];
-            double t;
-            if (scheme == 0) {
-                t = step * (face_split(dir, 2, slots, sp) + face_split(dir + 2, 1, slots, sp + 2)) + 2 * FACE_LAUNCH;
-            } else {
-                // eight slots are left to the workgroup that forms the time step
-                t = step * face_split(dir, 3, slots - 8, sp) + FACE_LAUNCH + COMBINE_LAUNCH +
-                    (f64 ? COMBINE_CELL64 : COMBINE_CELL32) * cells;
-            }
-            if (best < 0.0 || t < best) {
-                best = t;
-                c->side_by_side = scheme;
-                for (int d = 0; d < 3; ++d) {
-                    c->t2[d] = rows;
-                    c->chunk[d] = sp[d].chunk;
-                    c->seg_len[d] = sp[d].seg_len;
-                    c->n_wg[d] = (int)sp[d].n_wg;
-                }
-            }
-        }
-    }
+    const int slots[2] = {f64 ? face_slots<double>(FACE64_ROWS[0]) : face_slots<float>(TILE2),
+                          f64 ? face_slots<double>(FACE64_ROWS[1]) : 0};
+    c->plan = face_plan(c->g.n, f64, slots);
 }
 
 // FP32: zero the low-order parts of the compensated state (the state is then the field itself).
@@ -646,7 +606,7 @@ Face2Args<real> face2_args(gks_ctx* c, int stage, void* const src[4]) {
         a.g_global[d] = real(c->cfg.body_force[d]);
     }
     a.pad0 = c->g.pad0;
-    a.chunk = c->chunk[2];
+    a.chunk = c->plan.chunk[2];
     a.stretched = c->stretched;
     a.fc = flux_const<real>(c);
     a.dt_ptr = &c->st->dt;
@@ -687,7 +647,7 @@ int stage_faces(gks_ctx* c, int stage, void* const src[4], const int cat[3]) {
     FaceArgs<real> a[3];
     for (int d = 0; d < 3; ++d) a[d] = face_args<real>(c, d, stage, src);
     a[2].finish = stage == 2 && update_ends_step(c) ? c->st : nullptr;
-    if (c->side_by_side) {
+    if (c->plan.side_by_side) {
         const int tp = tbeg(c, cat[0], cat[1], cat[2]);
         HIPCHK(c, launch_face_xyz<real>(a[0], a[1], a[2], dt_args(c), stage, c->stream));
         HIPCHK(c, launch_combine<real>(a[2], c->g, stage, c->stream));
@@ -729,7 +689,7 @@ int steps(gks_ctx* c, int nsteps) {
         tp = tbeg(c, GKS_TIMER_DT);
         if (!c->umax_fused && c->cfg.cfl > 0)
             HIPCHK(c, launch_umax<real>(field<real>(c->q), c->g, c->cfg.rho_ref, c->umax_part, c->stream));
-        if (!c->side_by_side) HIPCHK(c, launch_dt(dt_args(c), c->stream));
+        if (!c->plan.side_by_side) HIPCHK(c, launch_dt(dt_args(c), c->stream));
         tend(c, tp);
         int rc = stage_faces<real>(c, 1, c->q, cat1);
         if (rc) return rc;
@@ -882,7 +842,7 @@ int gks_init(const gks_config* cfg, gks_field q, gks_field q_stage, gks_field q_
     // in the y pass's residual array, which nothing holds values in until the stage-1 face launches: the time step is
     // formed before those, except side by side, where the ghost fill then leaves the maxima to umax_kernel.
     const bool own = ghost_parts(n) <= UMAX_BLOCKS;
-    c->umax_fused = cfg->order != 2 && (own || !c->side_by_side);
+    c->umax_fused = cfg->order != 2 && (own || !c->plan.side_by_side);
     if (c->umax_fused && !own) c->umax_part = static_cast<double*>(c->r0);
     hipError_t e = cfg->precision == GKS_FP32 ? upload_metrics<float>(c, cfg) : upload_metrics<double>(c, cfg);
     if (e == hipSuccess) e = hipMemsetAsync(c->st, 0, sizeof(DevState), c->stream);
@@ -1441,5 +1401,27 @@ void gks_destroy(gks_ctx* c) {
 }
 
 const char* gks_last_error(const gks_ctx* c) { return c ? c->err.c_str() : g_init_error.c_str(); }
+
+// Not part of the ABI, for tests: the plan of a context, or (ctx null) the one a configuration gets where slots[0] and
+// slots[1] workgroups of the taller and the lower tile run at once. out: side_by_side, rows, then chunk, seg_len and
+// n_wg of the x, y and z passes.
+int gks_face_plan(const gks_ctx* c, const gks_config* cfg, const int slots[2], int out[11]) {
+    if (!out || (!c && (!slots || !validate(cfg).empty()))) return GKS_E_INVALID_ARG;
+    FacePlan p{};
+    if (c) {
+        p = c->plan;
+    } else if (cfg->order != 2) {
+        const int n[3] = {cfg->nx, cfg->ny, cfg->nz};
+        p = face_plan(n, cfg->precision == GKS_FP64, slots);
+    }
+    out[0] = p.side_by_side;
+    out[1] = p.rows;
+    for (int d = 0; d < 3; ++d) {
+        out[2 + 3 * d] = p.chunk[d];
+        out[3 + 3 * d] = p.seg_len[d];
+        out[4 + 3 * d] = p.n_wg[d];
+    }
+    return GKS_OK;
+}
 
 }  // extern "C"

@@ -235,6 +235,14 @@ struct FaceSplit {
     long long n_wg;
 };
 int face_split(const FaceDir* dirs, int ndirs, int slots, FaceSplit* out);
+// Tiles, work split and launches of a grid's order-5 face passes.
+struct FacePlan {
+    int side_by_side;  // the three directions of a stage run in one launch
+    int rows;          // t2 rows of a tile (FP64: see FACE64_ROWS)
+    int chunk[3], seg_len[3], n_wg[3];  // FaceArgs, per direction
+};
+// slots: workgroups that run at once with tiles of each height (FP32: the first)
+FacePlan face_plan(const int n[3], bool f64, const int slots[2]);
 // second-order variant (gks_stage2.hip): one launch per stage; stage2_chunk: planes per workgroup
 template <typename real>
 hipError_t launch_stage2(const Face2Args<real>& a, int stage, hipStream_t s);

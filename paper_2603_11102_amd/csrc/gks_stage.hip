@@ -558,19 +558,31 @@ int face_split(const FaceDir* dirs, int ndirs, int slots, FaceSplit* out) {
         long long best = (long long)d.tiles * ((d.n + chunk - 1) / chunk);
         o->seg_len = 0;
         o->chunk = chunk;
-        for (int segs = 1; segs <= (T - 2) / d.n + 2; ++segs) {
+        // A run of len cells at offset off in its tile takes len + 2 (tiles it meets) steps. Fewer than `first` tiles are
+        // fewer than any run of T - 2 segs cells meets (unless one run is everything), and runs only get shorter and
+        // more with segs: the first length that fits is the one sought, at most two steps on.
+        const int first = total <= T - 2 ? 1 : (T - 1) / (d.n + 2) + 1;
+        for (int segs = first; segs <= (T - 2) / d.n + 2; ++segs) {
             const long long len = std::min((long long)T - 2 * segs, total);
             if (len < 1) break;
             const long long wgs = (total + len - 1) / len;
-            if (wgs >= best || wgs > slots) continue;
-            long long worst = 0;
-            for (long long w = 0; w < wgs; ++w) {
-                const long long c0 = w * len, c1 = std::min(c0 + len, total);
-                worst = std::max(worst, (c1 - c0) + 2 * ((c1 - 1) / d.n - c0 / d.n + 1));
+            if (wgs >= best || wgs > slots) break;
+            const long long met = (len - 1) / d.n + 1, rem = (len - 1) % d.n;  // tiles met from off = 0; met + 1 if off + rem >= n
+            if (len + 2 * met > T) continue;
+            bool fits = true;
+            if (len + 2 * (met + 1) > T) {
+                long long off = 0;
+                for (long long w = 0; fits && w < wgs; ++w) {
+                    const long long l = std::min(len, total - w * len);
+                    fits = l == len ? off + rem < d.n : l + 2 * ((off + l - 1) / d.n + 1) <= T;
+                    off += rem + 1;
+                    if (off >= d.n) off -= d.n;
+                }
             }
-            if (worst > T) continue;
+            if (!fits) continue;
             best = wgs;
             o->seg_len = (int)len;
+            break;
         }
         o->n_wg = best;
         return best;
@@ -592,6 +604,44 @@ int face_split(const FaceDir* dirs, int ndirs, int slots, FaceSplit* out) {
     }
     total_wgs(hi, out);
     return hi;
+}
+
+FacePlan face_plan(const int n[3], bool f64, const int slots[2]) {
+    // Each tile height (FP64: two, see FACE64_ROWS) in both launch schemes, by estimated time in ns: face steps
+    // of the longest workgroup times the step, and per launch its start and end.
+    constexpr int ax[3][3] = {{0, 1, 2}, {1, 0, 2}, {2, 0, 1}};  // (normal, t1, t2)
+    const double cells = (double)n[0] * n[1] * n[2];
+    double best = -1.0;
+    FacePlan plan{};
+    for (int o = 0; o < (f64 ? 2 : 1); ++o) {
+        const int rows = f64 ? FACE64_ROWS[o] : TILE2;
+        const double step = f64 ? FACE64_STEP[o] : FACE32_STEP;
+        FaceDir dir[3];
+        for (int d = 0; d < 3; ++d)
+            dir[d] = FaceDir{n[ax[d][0]], ((n[ax[d][1]] + TILE1 - 1) / TILE1) * ((n[ax[d][2]] + rows - 1) / rows)};
+        for (int scheme = 0; scheme < 2; ++scheme) {
+            FaceSplit sp[3];
+            double t;
+            if (scheme == 0) {
+                t = step * (face_split(dir, 2, slots[o], sp) + face_split(dir + 2, 1, slots[o], sp + 2)) + 2 * FACE_LAUNCH;
+            } else {
+                // eight slots are left to the workgroup that forms the time step
+                t = step * face_split(dir, 3, slots[o] - 8, sp) + FACE_LAUNCH + COMBINE_LAUNCH +
+                    (f64 ? COMBINE_CELL64 : COMBINE_CELL32) * cells;
+            }
+            if (best < 0.0 || t < best) {
+                best = t;
+                plan.side_by_side = scheme;
+                plan.rows = rows;
+                for (int d = 0; d < 3; ++d) {
+                    plan.chunk[d] = sp[d].chunk;
+                    plan.seg_len[d] = sp[d].seg_len;
+                    plan.n_wg[d] = (int)sp[d].n_wg;
+                }
+            }
+        }
+    }
+    return plan;
 }
 
 #define GKS_LAUNCH_STR(KERNEL, ST, BLOCKS, ...)                                                               \
