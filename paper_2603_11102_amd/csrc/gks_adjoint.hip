@@ -42,25 +42,7 @@ __device__ __forceinline__ double wcoef(int side, const double* c, int r) {
     }
 }
 
-// DPP moves inside a row of 16 lanes. dpp_sel: lanes of the four-lane banks in BANK take the value of lane + 4
-// (ROW_SHL4), lane - 4 (ROW_SHR4) or lane ^ 8 (ROW_ROR8), the others keep `old`. dpp_shift: the value of lane +
-// k (shl) or lane - k (shr), zero where that lies outside the row.
-constexpr int ROW_SHL4 = 0x104, ROW_SHR4 = 0x114, ROW_ROR8 = 0x128;
-constexpr int BANK_H0 = 0x5, BANK_H1 = 0xA, BANK_M0 = 0x3, BANK_M1 = 0xC;
-
-template <int CTRL, int BANK, bool ZERO>
-__device__ __forceinline__ double dpp_move(double old, double x) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const unsigned long long o = (unsigned long long)__double_as_longlong(old);
-    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)(o & 0xffffffffu), (int)(unsigned)(b & 0xffffffffu), CTRL,
-                                               0xF, BANK, ZERO);
-    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(o >> 32), (int)(unsigned)(b >> 32), CTRL, 0xF, BANK, ZERO);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-template <int CTRL, int BANK>
-__device__ __forceinline__ double dpp_sel(double old, double x) {
-    return dpp_move<CTRL, BANK, false>(old, x);
-}
+// The value of lane + K (shl) or lane - K (shr) of a row, zero where that lies outside it.
 template <int K>
 __device__ __forceinline__ double dpp_shl(double x) {
     return dpp_move<0x100 + K, 0xF, true>(0.0, x);
@@ -275,19 +257,19 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
                 for (int v = 0; v < 2; ++v)
 #pragma unroll
                     for (int q = 0; q < 5; ++q) {
-                        w[v][q] = dpp_sel<ROW_SHR4, BANK_H1>(gp[v][0][q], gp[v][1][q]);
-                        w[2 + v][q] = dpp_sel<ROW_SHL4, BANK_H0>(gp[v][1][q], gp[v][0][q]);
+                        w[v][q] = dpp_move<ROW_SHR4, BANK_H1>(gp[v][0][q], gp[v][1][q]);
+                        w[2 + v][q] = dpp_move<ROW_SHL4, BANK_H0>(gp[v][1][q], gp[v][0][q]);
                     }
             }
             // ---- reverse of the flux at this lane's Gauss point
             {
                 // the four lanes of a face hold one seed each: all four to every lane
                 auto all_lanes = [&](double x, double (&y)[4]) {
-                    const double e = dpp_sel<ROW_ROR8, BANK_M1>(x, x), o = dpp_sel<ROW_ROR8, BANK_M0>(x, x);
-                    y[0] = dpp_sel<ROW_SHR4, BANK_H1>(e, e);
-                    y[1] = dpp_sel<ROW_SHR4, BANK_H1>(o, o);
-                    y[2] = dpp_sel<ROW_SHL4, BANK_H0>(e, e);
-                    y[3] = dpp_sel<ROW_SHL4, BANK_H0>(o, o);
+                    const double e = dpp_move<ROW_ROR8, BANK_M1>(x, x), o = dpp_move<ROW_ROR8, BANK_M0>(x, x);
+                    y[0] = dpp_move<ROW_SHR4, BANK_H1>(e, e);
+                    y[1] = dpp_move<ROW_SHR4, BANK_H1>(o, o);
+                    y[2] = dpp_move<ROW_SHL4, BANK_H0>(e, e);
+                    y[3] = dpp_move<ROW_SHL4, BANK_H0>(o, o);
                 };
                 double b0[4] = {0, 0, 0, 0}, b1[4];
                 all_lanes(face_ok ? up1 - lo1 : 0.0, b1);
@@ -321,8 +303,8 @@ __global__ void __launch_bounds__(AdjTile::THREADS) adj_face_kernel(const AdjFac
                 double gn[2][5];  // the exchange undone: both Gauss points of variable 2h + v
 #pragma unroll
                 for (int q = 0; q < 5; ++q) {
-                    gn[0][q] = dpp_sel<ROW_SHR4, BANK_H1>(w[v][q], w[2 + v][q]);
-                    gn[1][q] = dpp_sel<ROW_SHL4, BANK_H0>(w[2 + v][q], w[v][q]);
+                    gn[0][q] = dpp_move<ROW_SHR4, BANK_H1>(w[v][q], w[2 + v][q]);
+                    gn[1][q] = dpp_move<ROW_SHL4, BANK_H0>(w[2 + v][q], w[v][q]);
                 }
 #pragma unroll
                 for (int side = 0; side < 2; ++side) {

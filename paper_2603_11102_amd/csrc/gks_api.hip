@@ -444,7 +444,6 @@ FaceArgs<real> face_args_buf(gks_ctx* c, int d, int stage, void* const src[4], v
     // applies the S2O4 combination
     a.rx_nx = c->cfg.nx;
     a.rx_nyb = (c->cfg.ny + 15) / 16;
-    a.mode = d == 0 ? 3 : (d == 1 ? 0 : 4);
     return a;
 }
 

@@ -365,12 +365,6 @@ __device__ __forceinline__ void store4(real* p, long long i, const real v[4]) {
     x.x = v[0], x.y = v[1], x.z = v[2], x.w = v[3];
     *reinterpret_cast<typename Vec4T<real>::type*>(p + 4 * i) = x;
 }
-// error-free sum (Knuth): s + e == a + b exactly
-__device__ __forceinline__ void exact_sum(float a, float b, float& s, float& e) {
-    s = a + b;
-    const float bb = s - a;
-    e = (a - (s - bb)) + (b - bb);
-}
 
 template <typename real, int STAGE>
 __global__ void __launch_bounds__(256) combine_kernel(const FaceArgs<real> a, GridDesc g) {
@@ -406,11 +400,11 @@ __global__ void __launch_bounds__(256) combine_kernel(const FaceArgs<real> a, Gr
         const real add2 = F0 ? dt * L0 + (dt * dt * real(1.0 / 6.0)) * L1 : real(0);
         if constexpr (COMP) {
             float sh, sl;
-            exact_sum(q, lo[v] + add, sh, sl);
+            two_sum(q, lo[v] + add, sh, sl);
             oa[p] = sh;
             la[v] = sl;
             if (F0) {
-                exact_sum(q, lo[v] + add2, sh, sl);
+                two_sum(q, lo[v] + add2, sh, sl);
                 ob[p] = sh;
                 lb[v] = sl;
             }

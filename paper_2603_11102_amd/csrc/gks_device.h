@@ -55,6 +55,29 @@ __device__ __forceinline__ double fma_uniform(double a, double b, double c) {
     return r;
 }
 
+// Error-free sum (Knuth): s + e == a + b exactly, s = fl(a + b).
+__device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
+    s = a + b;
+    const float bb = s - a;
+    e = (a - (s - bb)) + (b - bb);
+}
+
+// DPP moves inside a row of 16 lanes. In the FP64 face kernels lane bit 2 is h, bit 3 is m; a bank mask picks the four-lane
+// banks that take the moved value (the others keep `old`), so a move with a per-lane choice is one instruction per
+// word. ZERO: lanes whose source lies outside the row take zero, else they keep `old`.
+constexpr int ROW_SHL4 = 0x104, ROW_SHR4 = 0x114, ROW_ROR8 = 0x128;  // from lane + 4, lane - 4, lane ^ 8
+constexpr int BANK_H0 = 0x5, BANK_H1 = 0xA, BANK_M0 = 0x3, BANK_M1 = 0xC;
+
+template <int CTRL, int BANK, bool ZERO = false>
+__device__ __forceinline__ double dpp_move(double old, double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned long long o = (unsigned long long)__double_as_longlong(old);
+    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)(o & 0xffffffffu), (int)(unsigned)(b & 0xffffffffu), CTRL,
+                                               0xF, BANK, ZERO);
+    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(o >> 32), (int)(unsigned)(b >> 32), CTRL, 0xF, BANK, ZERO);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
 // ---------------------------------------------------------------------------------------------
 // WENO-JS on five cells q[-2..2], written in the stencil's first differences
 // d1 = q[-1] - q[-2], d2 = q[0] - q[-1], d3 = q[1] - q[0], d4 = q[2] - q[1]. Sub-stencil k's quadratic

@@ -150,8 +150,6 @@ struct FaceArgs {
     real g_global[3];                 // constant body force (x, y, z) for the stage-2 epilogue
     const double* dt_ptr;             // device dt of the current step
     DevState* finish;                 // not null: this launch ends the step (finish_step)
-    int mode;  // 3: x pass (write the blocked x arrays), 0: y pass (write the main arrays),
-               // 4: z pass (add both, S2O4 stage update)
 };
 
 // Arguments of the second-order stage kernel; arrays in the global variable order.

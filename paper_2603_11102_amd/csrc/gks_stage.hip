@@ -53,13 +53,6 @@ __device__ __forceinline__ void st2(real* p, long long i, int m, typename Vec2<r
 // crossbar (ds_bpermute), off the VALU that bounds the kernel.
 __device__ __forceinline__ float pair_swap(float x) { return __shfl_xor(x, 1); }
 
-// Error-free sum (Knuth): s + e == a + b exactly, s = fl(a + b).
-__device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
-    s = a + b;
-    const float bb = s - a;
-    e = (a - (s - bb)) + (b - bb);
-}
-
 // LDS: two buffers, so that the phases of consecutive faces overlap; per variable the column values
 // [q^L, q^R, D, C][t2 row][t1 column] and the t1-phase results
 // [q^L_m, q^R_m, D_m, (dC/dt1)_m, C_m][t2 row][t1 position][Gauss line m]. A wave of the t1 phase takes

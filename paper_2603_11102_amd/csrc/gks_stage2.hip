@@ -45,12 +45,6 @@ struct Vec4<double> {
     using type = double4;
 };
 
-__device__ __forceinline__ void two_sum2(float a, float b, float& s, float& e) {
-    s = a + b;
-    const float bb = s - a;
-    e = (a - (s - bb)) + (b - bb);
-}
-
 // global variable of each local one (density, normal, t1, t2 momenta) of the x, y, z faces
 constexpr int kLocal[3][4] = {{0, 1, 2, 3}, {0, 2, 1, 3}, {0, 3, 1, 2}};
 
@@ -282,11 +276,11 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
                 const real add2 = NEED_F0 ? dt * L0[v] + (dt * dt * real(1.0 / 6.0)) * L1[v] : real(0);
                 if constexpr (COMP) {
                     float sh, sl_;
-                    two_sum2(qe[v], lov[v] + add, sh, sl_);
+                    two_sum(qe[v], lov[v] + add, sh, sl_);
                     a.out_a[v][p] = sh;
                     la[v] = sl_;
                     if (NEED_F0) {
-                        two_sum2(qe[v], lov[v] + add2, sh, sl_);
+                        two_sum(qe[v], lov[v] + add2, sh, sl_);
                         a.out_b[v][p] = sh;
                         lb[v] = sl_;
                     }

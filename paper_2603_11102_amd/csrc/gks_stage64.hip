@@ -29,21 +29,6 @@ namespace gks {
 
 namespace {
 
-// DPP moves inside a row of 16 lanes. Lane bit 2 is h, bit 3 is m; a bank mask picks the four-lane banks that
-// take the moved value (the others keep `old`), so a move with a per-lane choice is one instruction per word.
-constexpr int ROW_SHL4 = 0x104, ROW_SHR4 = 0x114, ROW_ROR8 = 0x128;  // from lane + 4, lane - 4, lane ^ 8
-constexpr int BANK_H0 = 0x5, BANK_H1 = 0xA, BANK_M0 = 0x3, BANK_M1 = 0xC;
-
-template <int CTRL, int BANK>
-__device__ __forceinline__ double dpp(double old, double x) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const unsigned long long o = (unsigned long long)__double_as_longlong(old);
-    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)(o & 0xffffffffu), (int)(unsigned)(b & 0xffffffffu), CTRL,
-                                               0xF, BANK, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(o >> 32), (int)(unsigned)(b >> 32), CTRL, 0xF, BANK, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 template <typename T>
 __device__ __forceinline__ T sel(bool c, T x, T y) {
     return c ? x : y;
@@ -261,8 +246,8 @@ __device__ __forceinline__ void face64_march(const FaceArgs<double>& a, const in
             for (int v = 0; v < 2; ++v)
 #pragma unroll
                 for (int q = 0; q < 5; ++q) {
-                    w[v][q] = dpp<ROW_SHR4, BANK_H1>(gp[v][0][q], gp[v][1][q]);
-                    w[2 + v][q] = dpp<ROW_SHL4, BANK_H0>(gp[v][1][q], gp[v][0][q]);
+                    w[v][q] = dpp_move<ROW_SHR4, BANK_H1>(gp[v][0][q], gp[v][1][q]);
+                    w[2 + v][q] = dpp_move<ROW_SHL4, BANK_H0>(gp[v][1][q], gp[v][0][q]);
                 }
             double fa0[4], fa1[4];
             {
@@ -282,8 +267,8 @@ __device__ __forceinline__ void face64_march(const FaceArgs<double>& a, const in
                 double y[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    y[i] = dpp<ROW_SHL4, BANK_H0>(x[LOC[2 + i]], x[LOC[i]]) + dpp<ROW_SHR4, BANK_H1>(x[LOC[i]], x[LOC[2 + i]]);
-                return dpp<ROW_ROR8, BANK_M0>(y[1], y[0]) + dpp<ROW_ROR8, BANK_M1>(y[0], y[1]);
+                    y[i] = dpp_move<ROW_SHL4, BANK_H0>(x[LOC[2 + i]], x[LOC[i]]) + dpp_move<ROW_SHR4, BANK_H1>(x[LOC[i]], x[LOC[2 + i]]);
+                return dpp_move<ROW_ROR8, BANK_M0>(y[1], y[0]) + dpp_move<ROW_ROR8, BANK_M1>(y[0], y[1]);
             };
             const double cur1 = scatter_sum(fa1);
             const double cur0 = NEED_F0 ? scatter_sum(fa0) : 0.0;
