@@ -3,10 +3,10 @@
 //
 // Forward operator per face direction (Section 2): normal WENO/derivative reconstruction ->
 // t1 Gauss-point sweep -> t2 Gauss-point sweep -> gas-kinetic flux at the 2x2 Gauss points ->
-// face quadrature and divergence. Its transpose is applied pass by pass in gather form (each output
+// face quadrature and divergence. Its transpose is applied tile by tile in gather form (each output
 // is one thread summing a fixed list of terms), with the WENO nonlinear weights frozen at their
-// forward values; every other operation is linearised exactly. No atomics are used, so gradients are
-// bitwise reproducible.
+// forward values or differentiated too; every other operator is linearised exactly. No atomics are
+// used, so gradients are bitwise reproducible.
 #include <algorithm>
 #include <type_traits>
 

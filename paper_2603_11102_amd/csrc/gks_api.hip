@@ -210,6 +210,8 @@ bool layout(const gks_config* c, char* base, Layout* L) {
         L->ihc[a] = cv.ptr<void>(n[a] * es);
         L->wrel[a] = cv.ptr<double>(sizeof(double) * n[a]);
     }
+    // the second-order variant has no use for the residual arrays and the copy; a workspace and what fits the static
+    // scratch are the same for both orders
     L->r0 = cv.ptr<void>(4 * N * es);
     L->r1 = cv.ptr<void>(4 * N * es);
     const size_t NB = (size_t)c->nx * ((c->ny + 15) / 16) * 16 * c->nz;
@@ -557,6 +559,7 @@ void tend(gks_ctx* c, int pair) {
     if (pair >= 0) (void)hipEventRecord(c->ev_pool[2 * pair + 1], c->stream);
 }
 
+// Plan of the face passes (order 2: planes per workgroup of its one launch a stage).
 void face_layout(gks_ctx* c) {
     const bool f64 = c->cfg.precision == GKS_FP64;
     c->plan = FacePlan{};

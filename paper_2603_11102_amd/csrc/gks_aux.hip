@@ -171,8 +171,8 @@ constexpr int GHOST_TILE = 32, GHOST_THREADS = 512;
 
 //
 // RESTORE: a step's state for its adjoint. The interior is read from a checkpoint (`from`) and every cell written to
-// q; the first of a step's two launches sets its time (t). The adjoint's x direction reads the copy. Bound by
-// memory: 59 us on 128^3, 7.2 us on 48^3 for 64 B a cell read once and written twice.
+// q; the launch before stage 2 sets the step's time (t). The adjoint's x direction reads the copy. Bound by
+// memory: 59 us on 128^3, 7.2 us on 48^3 for 32 B a cell read and 64 B written.
 template <typename real, bool RESTORE>
 __global__ void __launch_bounds__(GHOST_THREADS) ghost_transpose_kernel(Field4<const real> from, Field4<real> q,
                                                                         Field4<real> qt, GhostAll G, double* part,
@@ -343,7 +343,7 @@ hipError_t launch_restore(const double* const from[4], Field4<double> q, Field4<
 
 // Stage update from the three directions' residuals, for launches in which they run side by side: one thread
 // per cell. The z pass's residual stands in the output fields; it and the sums are formed as in the z pass.
-// Bound by memory: FP32 224 B a cell in stage 1 and 144 B in stage 2.
+// Bound by memory: FP32 192 B a cell in stage 1 and 112 B in stage 2.
 template <typename real>
 struct Vec4T;
 template <>

@@ -5,13 +5,13 @@
 //
 // One launch does a whole stage: a workgroup of 512 threads owns 32 x 16 cells of the (x, y) plane (16 x 32 on
 // grids of few cells in x) and marches along z; each thread evaluates the three lower (x, y) and upper (z) faces of
-// its cell. The scheme reads 13 cells per face and does a few hundred operations on them, so it is bound by the passes over memory:
-// one pass per direction (with residual arrays between them and a transposed copy of the field for the x
-// pass) moved 590 MB per stage 1 of the 192 x 96 x 96 channel in FP32, where reading the state and writing
-// the stage's results is 200 MB. Four planes of the tile and its two-cell halo live in LDS (46 KB FP32, two
-// workgroups per CU), the next plane is loaded a step ahead, the x and y fluxes of a plane are exchanged through
-// LDS and the z flux is kept from one plane to the next. The faces at the tile's upper x and y ends are extra
-// evaluations of two waves.
+// its cell. The scheme reads 13 cells per face and does a few hundred operations on them, so it is bound by the passes
+// over memory: one pass per direction (with residual arrays between them and a transposed copy of the field for the x
+// pass) moved 590 MB per stage 1 of the 192 x 96 x 96 channel in FP32, this one 408 MB, where reading the state and
+// writing the stage's results is 170 MB (the rest are halos and 10 to 27 spilled registers a lane). Four planes of the
+// tile and its two-cell halo live in LDS (46 KB FP32, two workgroups per CU), the next plane is loaded a step ahead, the
+// x and y fluxes of a plane are exchanged through LDS and the z flux is kept from one plane to the next. The faces at the
+// tile's upper x and y ends are extra evaluations of two waves.
 #include <type_traits>
 
 #include "gks_internal.h"

@@ -1,7 +1,7 @@
 // gks_stage64.hip -- the FP64 S2O4 stage kernels (the FP32 ones are in gks_stage.hip): reconstruction,
 // gas-kinetic flux, flux divergence and the stage combination, the x and y directions in one launch and z in one,
-// or all three together on small grids
-// (Section 2, Eqs. (semi), (finite), (x_example), (flux); the two-stage fourth-order combinations).
+// or all three together on small grids (Section 2, Eqs. (semi), (finite), (x_example), (flux); the two-stage
+// fourth-order combinations).
 //
 // One workgroup owns a tile of 16 x T2 faces in the tangential plane and marches along the normal over its
 // share of the tile-major (tile, cell) order (face_split). FOUR lanes work on a face: lane bits 2 (h) and 3
@@ -21,8 +21,8 @@
 //   * a reduce-scatter over the four lanes leaves lane (h, m) the face flux of global variable 2h + m, whose
 //     divergence, accumulation or stage update it does.
 // Measured, 192 x 96 x 96 channel: 1.85 ms a step with two lanes per face, 1.56 ms with four (12-row tiles, three
-// waves per SIMD), 1.45 ms with the directions sharing launches, 1.39 ms
-// with the LDS layout below; the tile height is chosen per direction (FACE64_ROWS).
+// waves per SIMD), 1.45 ms with the directions sharing launches, 1.39 ms with the LDS layout below; the tile height is
+// chosen per grid, one for all directions (FACE64_ROWS, face_plan).
 #include "gks_internal.h"
 
 namespace gks {

@@ -86,9 +86,10 @@ def face_plan(n_n, tiles, chunk, slots=256):
 
 def seams(cfg, precision):
     """Per axis, a (nz, ny, nx) mask of the cells on either side of a seam of the face kernels along that
-    axis, for launches of one direction each (with passes that share launches the marches end elsewhere and FP64
-    tiles may have 12 rows: test_gpu_face_seams samples the seams of the library's own plan): the first and last cell of each march of the pass normal to it (aligned chunks, or the runs of
-    the tile-major split, which start and end at different cells in different tiles), and the tile edges
+    axis, for launches of one direction each (with passes that share launches the marches end elsewhere
+    and FP64 tiles may have 12 rows: test_gpu_face_seams samples the seams of the library's own plan): the
+    first and last cell of each march of the pass normal to it (aligned chunks, or the runs of the
+    tile-major split, which start and end at different cells in different tiles), and the tile edges
     across the faces of the other passes (16 x 16 faces in FP32, 16 x 8 in FP64)."""
     n = (cfg.nx, cfg.ny, cfg.nz)
     t2 = 16 if precision == "fp32" else 8
