@@ -42,11 +42,11 @@ PEAK_HBM_GBS = 8000.0
 # reports null once they differ.
 TRAFFIC = {
     5: {"sources": ("gks_stage.hip", "gks_device.h", "gks_internal.h"),
-         "sources_sha256": "33fed9e10ad47e19f7248895b82d67a2af8a05dfbc8f3950aa500e1a0e0ad6bb",
-         "fetch_bytes": 212_077_722, "write_bytes": 85_683_520},
+         "sources_sha256": "95ddcffab1ffa999652e4bc3546ff8f113efd539c59e6922a425032c3b0e60e1",
+         "fetch_bytes": 212_104_448, "write_bytes": 85_683_926},
     2: {"sources": ("gks_stage2.hip", "gks_device.h", "gks_internal.h"),
-         "sources_sha256": "3eab90dc2d2524c7189990b89333d2738d0c68de31bce4d7af7b3e225f1a0e26",
-         "fetch_bytes": 289_071_270, "write_bytes": 141_285_597},
+         "sources_sha256": "a72e1544e96eaa6cdd889fdacca7b5264794226bbed0d877a2aff4e8f6116bae",
+         "fetch_bytes": 268_833_587, "write_bytes": 139_084_640},
 }
 
 
@@ -312,7 +312,7 @@ def main():
         result["metric"] = "cell-updates/s per S2O4 step (second-order variant)"
         result["config"]["workload"] += ", second-order GKS"
         result["roofline"] = {"bound": "hbm", "kernel": f"stage2_kernel<{'float' if es == 4 else 'double'}, 1, "
-                                                        f"{str(stretched).lower()}> (the stage-1 launch)",
+                                                        f"{str(stretched).lower()}, 32 | 16> (the stage-1 launch)",
                               "achieved": bytes_launch / (avg_launch_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
                               "unit": "GB/s", "frac": bytes_launch / (avg_launch_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
                               "traffic": measured_traffic(args.case, args.precision, 2),
@@ -340,7 +340,7 @@ def main():
                                        "frac": a64_tf / PEAK_TFLOPS["fp64"], "avg_launch_ms": l64}}
         if args.order == 2:
             gbs = bytes_launch / (3.0 * l64 * 1e-3) / 1e9
-            result["fp64"]["roofline"] = {"bound": "hbm", "kernel": f"stage2_kernel<double, 1, {str(stretched).lower()}> "
+            result["fp64"]["roofline"] = {"bound": "hbm", "kernel": f"stage2_kernel<double, 1, {str(stretched).lower()}, 32 | 16> "
                                                                     "(the stage-1 launch)",
                                           "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                           "frac": gbs / PEAK_HBM_GBS, "avg_launch_ms": 3.0 * l64}
