@@ -75,7 +75,7 @@ __device__ __forceinline__ const T& args_in_place(const T& a) {
 // partial sums in the two-cell halo and at the ends of a march, which adj_sum_kernel adds in a fixed order.
 // With separate kernels the Gauss-point adjoints (640 B a face) and the inputs of the tangential WENO evaluations
 // (192 B) went through memory, at 2.6 to 3.7 TB/s and one wave per SIMD: 1.95 ms per direction and stage of the
-// 128^3 rotor box, against 0.94 ms and 0.07 ms of adj_sum_kernel. This one writes 60 B a face and is bound by FP64
+// 128^3 rotor box, against 0.79 ms and 0.07 ms of adj_sum_kernel. This one writes 60 B a face and is bound by FP64
 // issue and its barriers.
 //
 // t2 transpose: each lane forms, for its two variables, the WENO terms of its face for the five rows it reaches

@@ -172,7 +172,7 @@ constexpr int GHOST_TILE = 32, GHOST_THREADS = 512;
 //
 // RESTORE: a step's state for its adjoint. The interior is read from a checkpoint (`from`) and every cell written to
 // q; the launch before stage 2 sets the step's time (t). The adjoint's x direction reads the copy. Bound by
-// memory: 59 us on 128^3, 7.2 us on 48^3 for 32 B a cell read and 64 B written.
+// memory: 56 us on 128^3, 7.2 us on 48^3 for 32 B a cell read and 64 B written.
 template <typename real, bool RESTORE>
 __global__ void __launch_bounds__(GHOST_THREADS) ghost_transpose_kernel(Field4<const real> from, Field4<real> q,
                                                                         Field4<real> qt, GhostAll G, double* part,
