@@ -111,14 +111,22 @@ __global__ void __launch_bounds__(O2_THREADS, sizeof(real) == 4 ? 4 : 2) stage2_
     load_plane(k0 + 2, nxt);
     real cm[3] = {0, 0, 0};
     if constexpr (SHIFT) {
-        // the midrange of each momentum over the chunk's first plane of the tile: the constant part of a mass
+        // the midrange of each momentum over the domain's cells in the chunk's first plane of the tile (ghost cells
+        // mirror a momentum at a wall, and the midrange would be zero in a stream towards it): the constant part of a mass
         // flux then cancels exactly between the two faces of a cell and FP32 rounding acts on the deviation only. The
         // planes in LDS keep the momenta whole: a tangential momentum much smaller than the midrange (at a no-slip
         // wall) would lose its low bits to the shift, and with them its derivatives
         __shared__ float s_range[6][O2_THREADS / 64];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            float lo = fminf(pre[2][0][1 + d], pre[2][1][1 + d]), up = fmaxf(pre[2][0][1 + d], pre[2][1][1 + d]);
+            float lo = 3.0e38f, up = -3.0e38f;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int ci = i0 - 2 + pos[s] % O2H1, cj = j0 - 2 + pos[s] / O2H1;
+                if (ci < 0 || ci >= a.n[0] || cj < 0 || cj >= a.n[1]) continue;
+                lo = fminf(lo, pre[2][s][1 + d]);
+                up = fmaxf(up, pre[2][s][1 + d]);
+            }
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) {
                 lo = fminf(lo, __shfl_xor(lo, o));

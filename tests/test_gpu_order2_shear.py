@@ -1,4 +1,4 @@
-"""FP32 second-order variant: the momentum of a shear layer at a wall, relative to its own size.
+"""FP32 second-order variant: what is small beside a workgroup's momenta keeps its own digits.
 
 A momentum that doubles from cell to cell away from two no-slip walls, 2^-15 at the walls and 1 in the core, at
 uniform density: the exact scheme reduces to the diffusion of that momentum, every other term cancels bit for bit
@@ -61,3 +61,34 @@ def test_wall_momentum_keeps_its_own_digits(axis, stretched):
     err = ((f["fp32"][1 + along] - ref) / ref).abs().max()
     print(f"[order2-shear] axis {axis} stretched {stretched}: worst relative error {float(err) / U:.1f} u")
     assert float(err) < 24 * U
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_density_of_a_stream_between_walls_keeps_its_own_digits(axis):
+    # A stream of 0.27 with disturbances of 1e-3 towards slip walls, whose ghost cells mirror it to -0.27: away from
+    # the walls the density changes by the disturbances' divergence only, and FP32 must round at their size, not at the
+    # stream's. A mass flux taken as its deviation from a constant near 0.27 carries 4 roundings of 1e-3 in its products
+    # and, with a = sqrt(lambda) U = 0.019, u a on the difference of aL and aR: (0.27 * 0.56 a + 2 a^2 / (2 sqrt(pi
+    # lambda))) u = 0.006 u; a step's density takes two faces times dt / h = 0.03: 6e-4 u. The bar is four times that;
+    # whole mass fluxes round at 0.27 / 4 and more, 1e-2 u here.
+    from paper_2603_11102_amd import GksSolver
+    n, h = [20, 18, 6], 0.1
+    n[axis] = 24
+    q = np.zeros((4, n[2], n[1], n[0]))
+    q[0] = 1.0
+    # both precisions start from the same field
+    q[1 + axis] = (0.27 + 1e-3 * np.random.default_rng(6).uniform(-1, 1, size=q[1].shape)).astype(np.float32)
+    cfg = make_case("channel", grid=(8, 8, 8)).with_(
+        nx=n[0], ny=n[1], nz=n[2], x0=0.0, y0=0.0, z0=0.0, lx=h * n[0], ly=h * n[1], lz=h * n[2], order=2, ma=0.1, mu=1e-3,
+        bc=tuple("slip" if a // 2 == axis else "periodic" for a in range(6)), cfl=0.0, dt_fixed=0.03 * h,
+        body_force=(0.0, 0.0, 0.0), q0=q)
+    print_case("order2-stream", axis=axis)
+    f = {}
+    for p in ("fp32", "fp64"):
+        s = GksSolver(cfg, precision=p)
+        s.step(1)
+        f[p] = s.interior()[0].narrow(2 - axis, 6, 12)  # a step reaches four cells
+        s.close()
+    err = float((f["fp32"] - f["fp64"]).abs().max())
+    print(f"[order2-stream] worst density error {err / U:.2e} u, density deviation up to {float(f['fp64'].abs().max()):.1e}")
+    assert err < 2.5e-3 * U
