@@ -45,8 +45,8 @@ TRAFFIC = {
          "sources_sha256": "95ddcffab1ffa999652e4bc3546ff8f113efd539c59e6922a425032c3b0e60e1",
          "fetch_bytes": 212_066_572, "write_bytes": 85_685_278},
     2: {"sources": ("gks_stage2.hip", "gks_device.h", "gks_internal.h"),
-         "sources_sha256": "a72e1544e96eaa6cdd889fdacca7b5264794226bbed0d877a2aff4e8f6116bae",
-         "fetch_bytes": 268_082_649, "write_bytes": 139_222_224},
+         "sources_sha256": "647ae6aeff21101ab03438cece0c36a21a3ae1ea3010ed1b65c40b57278d1277",
+         "fetch_bytes": 268_767_552, "write_bytes": 139_175_817},
 }
 
 
